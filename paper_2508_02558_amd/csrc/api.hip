@@ -89,7 +89,7 @@ constexpr float kLog2e = 1.4426950408889634f;
 
 // ---------------------------------------------------------------- attention planning
 struct AttnPlan {
-  bool mfma;
+  bool mfma;  // one of the kernels for bf16, head_dim 128, 32 query rows; otherwise the general one
   bool gqa;   // grouped-query kernel: one workgroup per (batch, KV head), wave = query head
   int n_split, tiles_per_split, waves;
   size_t part_o_bytes, part_ml_bytes;
@@ -100,6 +100,46 @@ bool seg_fits_u32(int64_t row_stride, int32_t n, int esize) {
   return n <= 0 || ((int64_t)(n - 1) * row_stride + 128) * esize < (int64_t)1 << 31;
 }
 
+int row_blocks(const sdllm_shape_t& s, int32_t rows) { return (rows + block_rows(s.dtype) - 1) / block_rows(s.dtype); }
+
+// The general kernel: one workgroup per (head, block of query rows) and key split.
+void plan_general(AttnPlan& pl, const sdllm_shape_t& s, int32_t nq, int tiles, bool may_split) {
+  const int64_t vheads = (int64_t)s.batch * s.n_q_heads * row_blocks(s, nq);
+  const int most_waves = kGeneralMaxWaves;
+  int n_split = 1;
+  if (may_split && vheads <= kNumCUs / 2) {
+    // Within one workgroup per CU (also what keeps the partials of every plan below SDLLM_STATIC_SCRATCH_BYTES:
+    // 256 x 16.25 KB).  bf16: the thresholds of the 32-row kernel.  fp32: a tile is 1 us (head_dim 64) or
+    // 2 us (128) of a SIMD's matrix work and a second launch 4 us, so split from 24 or 12 tiles on, down to 8 or 4 per
+    // workgroup (8 heads of 128, 32 rows, 22 tiles, with row statistics: 25.8 -> 12.8 + 4.0 us).
+    n_split = (int)(kNumCUs / vheads);
+    if (n_split > 8) n_split = 8;
+    const int least = s.dtype == SDLLM_F32 ? (s.head_dim == 64 ? 8 : 4) : vheads <= 32 ? 7 : 11;
+    const int max_split = s.dtype == SDLLM_F32 && tiles < 3 * least ? 1 : tiles / least;
+    if (n_split > max_split) n_split = max_split;
+    if (n_split < 1) n_split = 1;
+  }
+  pl.tiles_per_split = (tiles + n_split - 1) / n_split;
+  pl.n_split = pl.tiles_per_split > 0 ? (tiles + pl.tiles_per_split - 1) / pl.tiles_per_split : 1;
+  // Waves per workgroup: a CU holds `cu_waves` of them (registers), as one workgroup or several, so `w` waves take
+  // ceil(workgroups / (CUs x cu_waves / w)) rounds of ceil(tiles / w) tiles each; the fewest win (560 workgroups x 35
+  // tiles of head_dim 64, bf16, all rows of a sequence: 28 us with two waves, 23 us with four), the smaller merge
+  // among equals.
+  const int cu_waves = s.head_dim == 64 ? 12 : 8;
+  int64_t least = INT64_MAX;
+  for (int w = 2; w <= most_waves; w *= 2) {
+    const int64_t slots = (int64_t)kNumCUs * (cu_waves / w);
+    const int64_t cost = ((vheads * pl.n_split + slots - 1) / slots) * ((pl.tiles_per_split + w - 1) / w);
+    if (cost < least) { least = cost; pl.waves = w; }
+  }
+  if (pl.waves > pl.tiles_per_split) pl.waves = pl.tiles_per_split;
+  if (pl.waves < 1) pl.waves = 1;
+  if (pl.n_split > 1) {
+    pl.part_o_bytes = align_up((size_t)vheads * pl.n_split * block_rows(s.dtype) * s.head_dim * sizeof(float));
+    pl.part_ml_bytes = align_up((size_t)vheads * pl.n_split * 2 * block_rows(s.dtype) * sizeof(float));
+  }
+}
+
 AttnPlan plan_attn(const sdllm_shape_t& s, int32_t n0, int64_t sr0, int32_t n1, int64_t sr1) {
   AttnPlan pl{};
   pl.mfma = s.dtype == SDLLM_BF16 && s.head_dim == 128 && s.block_len == 32 && seg_fits_u32(sr0, n0, 2) &&
@@ -107,6 +147,10 @@ AttnPlan plan_attn(const sdllm_shape_t& s, int32_t n0, int64_t sr0, int32_t n1, 
   pl.n_split = 1;
   pl.tiles_per_split = 0;
   pl.waves = 1;
+  if (!pl.mfma) {
+    plan_general(pl, s, s.block_len, (n0 + kTileKeys - 1) / kTileKeys + (n1 + kTileKeys - 1) / kTileKeys, true);
+    return pl;
+  }
   // Grouped-query heads: either one workgroup per query head (K/V then come G times out of L2, but the
   // eight waves of a head split its keys and merge in LDS) or the shared-tile kernel (K/V read once,
   // one wave per head, key splits merged through fp32 partials and a second launch).  Measured on
@@ -213,8 +257,12 @@ bool fuses_columns(const AttnPlan& pl, const sdllm_shape_t& s) {
 int32_t run_attn(const sdllm_shape_t& s, const void* q, const KvSegment& a, const KvSegment& b, void* out, void* ws,
                  size_t ws_bytes, hipStream_t stream, float* cand_ml = nullptr, int cand0_end = 0, int cand1_begin = 0,
                  AttnParams* deferred = nullptr, float* score_out = nullptr, int score_stride = 0) {
-  const AttnPlan pl = plan_attn(s, a.n, a.sr, b.n, b.sr);
-  if (pl.ws_bytes() > 0 && (!ws || ws_bytes < pl.ws_bytes())) return SDLLM_ERR_WORKSPACE;
+  AttnPlan pl = plan_attn(s, a.n, a.sr, b.n, b.sr);
+  if (pl.ws_bytes() > 0 && (!ws || ws_bytes < pl.ws_bytes())) {
+    if (pl.mfma) return SDLLM_ERR_WORKSPACE;
+    // the general kernel works without a workspace too: one workgroup per 32 rows walks all keys
+    plan_general(pl, s, s.block_len, (a.n + kTileKeys - 1) / kTileKeys + (b.n + kTileKeys - 1) / kTileKeys, false);
+  }
   AttnParams p{};
   p.q = q;
   p.out = out;
@@ -228,7 +276,7 @@ int32_t run_attn(const sdllm_shape_t& s, const void* q, const KvSegment& a, cons
   p.n_split = pl.n_split; p.tiles_per_split = pl.tiles_per_split; p.waves = pl.waves;
   p.part_o = (float*)ws;
   p.part_ml = (float*)((char*)ws + pl.part_o_bytes);
-  p.cand_ml = pl.mfma ? cand_ml : nullptr;
+  p.cand_ml = cand_ml;
   p.cand0_end = cand0_end;
   p.cand1_begin = cand1_begin;
   // the column sweep rides on the statistics launch of the one-workgroup-per-head kernel (fuses_columns below)
@@ -241,8 +289,9 @@ int32_t run_attn(const sdllm_shape_t& s, const void* q, const KvSegment& a, cons
     if (deferred) *deferred = p;
     if (e == hipSuccess && pl.n_split > 1 && !deferred) e = launch_attn_combine(p, s.dtype, stream);
   } else {
-    e = launch_attn_simple(p, s.dtype, stream);
+    e = launch_attn_general(p, s.dtype, false, stream);
     if (deferred) deferred->n_split = 1;
+    if (e == hipSuccess && pl.n_split > 1) e = launch_attn_combine(p, s.dtype, stream);
   }
   return e == hipSuccess ? SDLLM_OK : SDLLM_ERR_HIP;
 }
@@ -315,9 +364,19 @@ ScorePlan plan_score(const sdllm_shape_t& s) {
     if (rows < (size_t)kNumCUs && n_part > kNumCUs / (int)rows) n_part = kNumCUs / (int)rows;
     pl.tiles_per_part = (tiles + n_part - 1) / n_part;
     pl.n_part = (tiles + pl.tiles_per_part - 1) / pl.tiles_per_part;   // no empty part
+  } else {
+    // row statistics: a statistics-only run of the general attention kernel over the whole sequence
+    AttnPlan st{};
+    plan_general(st, s, s.block_len, (s.seq_len + kTileKeys - 1) / kTileKeys, true);
+    pl.n_part = st.n_split; pl.tiles_per_part = st.tiles_per_split; pl.waves = st.waves;
   }
-  pl.ml_bytes = align_up((size_t)s.batch * s.n_q_heads * pl.n_part * 2 * s.block_len * sizeof(float));
+  pl.ml_bytes = align_up((size_t)s.batch * s.n_q_heads * row_blocks(s, s.block_len) * pl.n_part * 2 * block_rows(s.dtype) * sizeof(float));
   return pl;
+}
+
+// The position from which keys are scored again after the prefix: past the block, or never (prefix-only eviction).
+int candidates_resume(const sdllm_shape_t& s) {
+  return s.evict_scope == SDLLM_EVICT_PREFIX_ONLY ? s.seq_len : s.block_off + s.block_len;
 }
 
 int32_t check_q(const sdllm_shape_t& s, const void* q) {
@@ -371,7 +430,25 @@ int32_t score_select_impl(const sdllm_shape_t& s, const void* q_blk, const void*
   sp.n_stat_part = ext_ml ? ext_parts : pl.n_part;
   sp.skip_stats = ext_ml != nullptr;
   // scores_ready: the dense attention of this step already left the scores in the workspace's score buffer
-  hipError_t e = scores_ready ? hipSuccess : pl.mfma ? launch_score_mfma_bf16(sp, hs) : launch_score_simple(sp, s.dtype, hs);
+  hipError_t e = hipSuccess;
+  if (!scores_ready && pl.mfma) {
+    e = launch_score_mfma_bf16(sp, hs);
+  } else if (!scores_ready) {
+    if (sp.softmax && !ext_ml && sp.n_cand > 0) {
+      AttnParams p{};
+      p.q = q_blk;
+      p.q_sb = sp.q_sb; p.q_sh = sp.q_sh; p.q_sr = sp.q_sr;
+      p.seg[0] = KvSegment{k_full, nullptr, sp.k_sb, sp.k_sh, sp.k_sr, s.seq_len};
+      p.batch = sp.batch; p.hq = sp.hq; p.hkv = sp.hkv; p.group = sp.group; p.nq = sp.nq; p.d = sp.d;
+      p.scale_log2 = sp.scale_log2;
+      p.n_split = pl.n_part; p.tiles_per_split = pl.tiles_per_part; p.waves = pl.waves;
+      p.cand_ml = ml;
+      p.cand0_end = s.block_off;
+      p.cand1_begin = candidates_resume(s);
+      e = launch_attn_general(p, s.dtype, true, hs);
+    }
+    if (e == hipSuccess) e = launch_score_cols_general(sp, s.dtype, hs);
+  }
   if (e != hipSuccess) return SDLLM_ERR_HIP;
 
   SelectParams q{};
@@ -417,10 +494,10 @@ BlockStepWs plan_block_step(const sdllm_shape_t& s) {
   if (sparse.ws_bytes() > w.base) w.base = sparse.ws_bytes();
   if (w.score_off + sc.ws_bytes() > w.base) w.base = w.score_off + sc.ws_bytes();
   w.base = align_up(w.base);
-  w.fuse = dense.mfma && sc.mfma && s.score_mode == SDLLM_SOFTMAX_MEAN && c.n_cand > 0;
+  w.fuse = s.score_mode == SDLLM_SOFTMAX_MEAN && c.n_cand > 0;
   w.stats_parts = dense.n_split;
   w.fuse_cols = w.fuse && fuses_columns(dense, s);
-  w.stats_bytes = w.fuse ? align_up((size_t)s.batch * s.n_q_heads * dense.n_split * 64 * sizeof(float)) : 0;
+  w.stats_bytes = w.fuse ? align_up((size_t)s.batch * s.n_q_heads * row_blocks(s, s.block_len) * dense.n_split * 2 * block_rows(s.dtype) * sizeof(float)) : 0;
   return w;
 }
 
@@ -605,9 +682,8 @@ int32_t sdllm_block_step(const sdllm_shape_t* shape, int32_t step_in_block, int3
     st = run_attn(s, q_blk, a, b, out, ws, ws_bytes, (hipStream_t)stream, nullptr, 0, 0, defer);
   else {
     // cache-update step: the dense attention also leaves the scoring softmax's row statistics
-    const int cand1 = s.evict_scope == SDLLM_EVICT_PREFIX_ONLY ? s.seq_len : s.block_off + s.block_len;
     // ... and, where one workgroup owns a head, the saliency scores themselves (first buffer of the scoring workspace)
-    st = run_attn(s, q_blk, a, b, out, ws, w.base, (hipStream_t)stream, (float*)((char*)ws + w.base), s.block_off, cand1,
+    st = run_attn(s, q_blk, a, b, out, ws, w.base, (hipStream_t)stream, (float*)((char*)ws + w.base), s.block_off, candidates_resume(s),
                   defer, w.fuse_cols ? (float*)((char*)ws + w.score_off) : nullptr, c.n_cand);
   }
   if (st != SDLLM_OK || state == SDLLM_STATE_FULL) return st;
@@ -652,7 +728,8 @@ int32_t sdllm_dense_attn(const sdllm_shape_t* shape, const void* q_full, const i
     p.scale_log2 = scale_log2;
     e = launch_dense_full_mfma_bf16(p, (hipStream_t)stream);
   } else {
-    // generic path: one wave per query row over a single key segment
+    AttnPlan pl{};
+    plan_general(pl, s, s.seq_len, (s.seq_len + kTileKeys - 1) / kTileKeys, false);
     AttnParams p{};
     p.q = q_full; p.out = out_full;
     p.seg[0] = KvSegment{k_full, v_full, s.kv_stride[0], s.kv_stride[1], s.kv_stride[2], s.seq_len};
@@ -662,8 +739,8 @@ int32_t sdllm_dense_attn(const sdllm_shape_t* shape, const void* q_full, const i
     p.batch = s.batch; p.hq = s.n_q_heads; p.hkv = s.n_kv_heads; p.group = s.n_q_heads / s.n_kv_heads;
     p.nq = s.seq_len; p.d = s.head_dim;
     p.scale_log2 = scale_log2;
-    p.n_split = 1; p.waves = 1;
-    e = launch_attn_simple(p, s.dtype, (hipStream_t)stream);
+    p.n_split = 1; p.tiles_per_split = pl.tiles_per_split; p.waves = pl.waves;
+    e = launch_attn_general(p, s.dtype, false, (hipStream_t)stream);
   }
   return e == hipSuccess ? SDLLM_OK : SDLLM_ERR_HIP;
 }

@@ -28,14 +28,14 @@ __device__ __forceinline__ void merge_pieces(RowPiece& a, const RowPiece& b) {
 }
 
 // One thread folds the splits first, first + step, ... of one query row's four output columns.  ml
-// points at the row's max of split 0 (split stride ml_ss floats, the sum nq floats further on), po at the
+// points at the row's max of split 0 (split stride 2 R floats, the sum R floats further on), po at the
 // row's four numerators of split 0 (split stride po_ss floats).  One sweep in batches of eight (then
 // four) splits: all loads of a batch (max, sum, numerators) are requested before any is used, then folded
 // into the running piece.  The partials were written a moment ago and mostly sit in L2; what a merge
 // pays for is dependent round trips, and a separate pass for the overall max plus batches of four cost
 // five or six of them.
-__device__ __forceinline__ RowPiece fold_splits(const float* ml, int ml_ss, int nq, const float* po, size_t po_ss, int n_split,
-                                                int first, int step) {
+template <int R>
+__device__ __forceinline__ RowPiece fold_splits(const float* ml, const float* po, size_t po_ss, int n_split, int first, int step) {
   RowPiece r;
   const int n_mine = first < n_split ? (n_split - first + step - 1) / step : 0;
   auto fold = [&](auto batch, int j0) {
@@ -45,8 +45,8 @@ __device__ __forceinline__ RowPiece fold_splits(const float* ml, int ml_ss, int 
 #pragma unroll
     for (int u = 0; u < NB; ++u) {
       const int s = first + min(j0 + u, n_mine - 1) * step;   // past the end (last batch only): re-read the last one, weight 0 below
-      m_s[u] = ml[s * ml_ss];
-      l_s[u] = ml[s * ml_ss + nq];
+      m_s[u] = ml[s * 2 * R];
+      l_s[u] = ml[s * 2 * R + R];
       o_s[u] = *reinterpret_cast<const mf32x4*>(po + s * po_ss);
     }
     float m_new = r.m;
@@ -115,9 +115,11 @@ __device__ __forceinline__ void combine_block(const AttnParams& p, int block_id)
   const int row = growc - head * p.nq;
   const int b = head / p.hq;
   const int h = head - b * p.hq;
-  const float* ml = p.part_ml + (size_t)head * p.n_split * 2 * p.nq + row;        // split stride 2*nq
-  const float* po = p.part_o + ((size_t)head * p.n_split * p.nq + row) * p.d + c4;   // split stride nq*d
-  RowPiece r = fold_splits(ml, 2 * p.nq, p.nq, po, (size_t)p.nq * p.d, p.n_split, sub, TPI);
+  constexpr int R = sizeof(T) == 2 ? kGeneralRowsBf16 : kGeneralRowsF32;   // partials come in blocks of R rows
+  const size_t slot0 = ((size_t)head * ((p.nq + R - 1) / R) + row / R) * p.n_split;
+  const float* ml = p.part_ml + slot0 * 2 * R + row % R;
+  const float* po = p.part_o + (slot0 * R + row % R) * p.d + c4;
+  RowPiece r = fold_splits<R>(ml, po, (size_t)R * p.d, p.n_split, sub, TPI);
 #pragma unroll
   for (int o = 1; o < TPI; o <<= 1) {
     RowPiece other;

@@ -15,6 +15,10 @@ constexpr int kTileKeys = 32;        // keys per MFMA tile (one 32x32 block of l
 constexpr int kMaxWavesPerWg = 8;    // attention / scoring workgroups hold up to 8 waves
 constexpr int kNumCUs = 256;         // MI355X
 constexpr int kNumXCDs = 8;
+// query rows per workgroup of the general kernels (general_tile.h), also of the 32-row bf16 kernels
+constexpr int kGeneralRowsBf16 = 32, kGeneralRowsF32 = 16;
+constexpr int kGeneralMaxWaves = 8;
+inline int block_rows(int dtype) { return dtype == 0 ? kGeneralRowsBf16 : kGeneralRowsF32; }
 
 // Workgroup ids are dealt round-robin over the 8 XCDs, each with its own L2.  This renumbering gives
 // every XCD one contiguous range of the result instead (XCD x gets the ids it was dealt, in order,
@@ -68,11 +72,12 @@ struct AttnParams {
   int32_t n_split;          // workgroups per head
   int32_t tiles_per_split;  // 32-key tiles each workgroup owns
   int32_t waves;            // waves per workgroup
-  float* part_o;            // [B*Hq, n_split, nq, d] fp32 partial numerators (n_split > 1)
-  float* part_ml;           // [B*Hq, n_split, 2, nq] running max (log2 domain) and denominator
+  // per block of R query rows (R = block_rows(dtype), N = ceil(nq / R) blocks per head, one for the 32-row kernels):
+  float* part_o;            // [B*Hq, N, n_split, R, d] fp32 partial numerators (n_split > 1)
+  float* part_ml;           // [B*Hq, N, n_split, 2, R] running max (log2 domain) and denominator
   // Optional by-product of a dense (single-segment) launch: the softmax row statistics of the
   // scoring pass, i.e. (max, sum) per query row over the CANDIDATE keys only, which are the keys
-  // outside [cand0_end, cand1_begin).  Layout [B*Hq, n_split, 2, nq], the layout the scoring
+  // outside [cand0_end, cand1_begin).  Layout [B*Hq, N, n_split, 2, R], the layout the scoring
   // kernels read their partial statistics in.  Null: not produced.
   float* cand_ml;
   int32_t cand0_end, cand1_begin;
@@ -102,7 +107,7 @@ struct ScoreParams {
   // row statistics of the softmax (pass 1 -> pass 2)
   int32_t n_part;       // workgroups per (batch, KV head) row of the scoring kernels
   int32_t tiles_per_part;
-  float* part_ml;       // [B*Hq, n_stat_part, 2, nq]
+  float* part_ml;       // [B*Hq, N, n_stat_part, 2, R]
   int32_t n_stat_part;  // partial (max, sum) pairs per query row in part_ml
   int32_t skip_stats;   // 1: part_ml was already filled (by the dense attention of the same step)
   int32_t cols_follow;  // set by the launcher: the statistics kernel runs the column pass itself (n_part == 1)
@@ -163,11 +168,12 @@ hipError_t launch_attn_mfma_bf16(const AttnParams& p, hipStream_t s);
 hipError_t launch_attn_gqa_mfma_bf16(const AttnParams& p, hipStream_t s);
 bool attn_gqa_supports_group(int group);
 int attn_gqa_waves_per_wg(int group);
-hipError_t launch_attn_simple(const AttnParams& p, int dtype, hipStream_t s);
+// any type, head_dim and row count; stats_only: nothing but cand_ml
+hipError_t launch_attn_general(const AttnParams& p, int dtype, bool stats_only, hipStream_t s);
 hipError_t launch_attn_combine(const AttnParams& p, int dtype, hipStream_t s);
 hipError_t launch_score_mfma_bf16(const ScoreParams& p, hipStream_t s);
 bool score_mfma_supports_group(int group);
-hipError_t launch_score_simple(const ScoreParams& p, int dtype, hipStream_t s);
+hipError_t launch_score_cols_general(const ScoreParams& p, int dtype, hipStream_t s);   // part_ml filled before (softmax)
 hipError_t launch_select(const SelectParams& p, hipStream_t s);
 SelectWorkspace select_workspace(const SelectParams& p);
 int select_max_segment();

@@ -1,0 +1,87 @@
+"""The general kernels (fp32, head_dim 64, block lengths other than 32, large groups, far-apart rows) against the oracle,
+at the sizes where their tiling can go wrong: 32-row blocks with 1 to 32 valid rows, one and two row blocks, tiles with a
+ragged end on either side of the block, keys split over workgroups, more query blocks than one LDS stage of the scoring
+holds.  Tolerances are those of tests/parity_util.py."""
+import pytest
+import torch
+
+from paper_2508_02558_amd import binding as B
+from paper_2508_02558_amd import workloads as wl
+from tests import parity_util as U
+from tests.test_gpu_parity import _run_block
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+@pytest.mark.parametrize("dtype,d,block,q_heads,kv_heads,batch,prompt,modes", [
+    ("bf16", 128, 1, 2, 2, 1, 33, {}),                     # one valid row of 32
+    ("bf16", 128, 33, 4, 2, 1, 200, {}),                   # second row block with one row
+    ("bf16", 128, 64, 9, 1, 1, 161, {}),                   # 18 query blocks: several LDS stages of queries
+    ("bf16", 128, 64, 4, 4, 2, 1500, dict(select_mode=B.SDLLM_JOINT, k_rounding=B.SDLLM_FLOOR)),   # keys split
+    ("bf16", 128, 32, 9, 1, 2, 100, {}),                   # 32-row dense kernel, general scoring (group > 8)
+    ("bf16", 64, 32, 8, 2, 3, 500, dict(score_mode=B.SDLLM_LOGIT_MEAN)),
+    ("bf16", 64, 24, 14, 2, 1, 1000, {}),                  # keys split, padding rows in every query block
+    ("bf16", 64, 48, 2, 2, 1, 0, {}),                      # no prefix
+    ("f32", 64, 32, 2, 2, 1, 2300, {}),                    # keys split
+    ("f32", 64, 64, 14, 2, 1, 77, dict(evict_scope=B.SDLLM_EVICT_PREFIX_ONLY)),
+    ("f32", 128, 40, 6, 2, 2, 130, {}),                    # six heads x two row blocks, more than one LDS stage
+    ("f32", 128, 8, 4, 1, 1, 700, dict(score_mode=B.SDLLM_LOGIT_MEAN)),
+])
+def test_general_block(dtype, d, block, q_heads, kv_heads, batch, prompt, modes):
+    w = wl.WORKLOADS["llada8b_layer"].scaled(dtype=dtype, head_dim=d, block=block, n_q_heads=q_heads, n_kv_heads=kv_heads,
+                                             batch=batch, prompt=prompt, gen=3 * block)
+    _run_block(w, block_index=1, n_steps=3, **modes)
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("f32", 64), ("f32", 128)])
+@pytest.mark.parametrize("L", [1, 31, 33, 64, 97, 300])
+def test_general_dense_attn_row_and_tile_edges(dtype, d, L):
+    print(f"[case] general dense_attn {dtype} d={d} L={L}", flush=True)
+    torch.manual_seed(L)
+    t = torch.float32 if dtype == "f32" else torch.bfloat16
+    q, k, v = (torch.randn(2, h, L, d, device=DEV).to(t) for h in (6, 2, 2))
+    out = torch.zeros_like(q)
+    shape = B.make_shape(batch=2, n_q_heads=6, n_kv_heads=2, head_dim=d, seq_len=L, block_off=0, block_len=min(32, L), dtype=U.DT[dtype])
+    B.sdllm_dense_attn(shape, q, k, v, out)
+    torch.cuda.synchronize()
+    U.assert_close(out, U.oracle_attention_batch(q, k, v), dtype, f"L={L}")
+
+
+@pytest.mark.parametrize("dtype,d,block,n_cached", [("bf16", 64, 16, 900), ("f32", 64, 32, 1000), ("f32", 128, 50, 700)])
+def test_general_sparse_attn_without_a_workspace(dtype, d, block, n_cached):
+    # shapes whose keys are split over workgroups when there is room for the partials run unsplit when there is none
+    print(f"[case] general sparse_attn, no workspace: {dtype} d={d} b={block} n={n_cached}", flush=True)
+    torch.manual_seed(n_cached)
+    t = torch.float32 if dtype == "f32" else torch.bfloat16
+    shape = B.make_shape(batch=1, n_q_heads=2, n_kv_heads=1, head_dim=d, seq_len=4096, block_off=2048, block_len=block,
+                         dtype=U.DT[dtype], cache_rows=n_cached)
+    need = B.sdllm_workspace_bytes(shape, B.SDLLM_OP_SPARSE_ATTN, n_cached)
+    assert need > 256
+    q = torch.randn(1, 2, block, d, device=DEV).to(t)
+    kc, vc = (torch.randn(1, 1, n_cached, d, device=DEV).to(t) for _ in range(2))
+    kb, vb = (torch.randn(1, 1, block, d, device=DEV).to(t) for _ in range(2))
+    ref = U.oracle_attention_batch(q, torch.cat([kc, kb], 2), torch.cat([vc, vb], 2))
+    for ws in (None, torch.empty(need, dtype=torch.uint8, device=DEV)):
+        out = torch.full_like(q, float("nan"))
+        B.sdllm_sparse_attn(shape, q, kc, vc, n_cached, kb, vb, out, ws)
+        torch.cuda.synchronize()
+        U.assert_close(out, ref, dtype, "no workspace" if ws is None else "workspace")
+
+
+def test_rows_too_far_apart_for_32_bit_offsets():
+    print("[case] cache rows 32 MiB apart", flush=True)
+    torch.manual_seed(5)
+    n, d, step = 70, 128, 1 << 24
+    store = torch.empty(n * step, dtype=torch.bfloat16, device=DEV)
+    kc = store.as_strided((1, 1, n, d), (0, 0, step, 1), 0)
+    vc = store.as_strided((1, 1, n, d), (0, 0, step, 1), d)
+    kc.copy_(torch.randn(1, 1, n, d, device=DEV))
+    vc.copy_(torch.randn(1, 1, n, d, device=DEV))
+    q, kb, vb = (torch.randn(1, 1, 32, d, device=DEV).bfloat16() for _ in range(3))
+    shape = B.make_shape(batch=1, n_q_heads=1, n_kv_heads=1, head_dim=d, seq_len=4096, block_off=2048, block_len=32,
+                         dtype=B.SDLLM_BF16, cache_stride=(0, 0, step))
+    out = torch.zeros_like(q)
+    B.sdllm_sparse_attn(shape, q, kc, vc, n, kb, vb, out, None)
+    torch.cuda.synchronize()
+    U.assert_close(out, U.oracle_attention_batch(q, torch.cat([kc, kb], 2), torch.cat([vc, vb], 2)), "bf16", "far rows")
