@@ -107,10 +107,22 @@ def _ptr(t) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
+_torch = None
+
+
+def _current_raw_stream() -> int:
+    """Handle of torch's current stream on its current device.  torch.cuda.current_stream() builds a Stream object
+    around the same number on every call: 3.0 us, a third of what a small step costs the host, against 0.3 us."""
+    global _torch
+    if _torch is None:
+        import torch
+        _torch = torch
+    return _torch._C._cuda_getCurrentRawStream(_torch.cuda.current_device())
+
+
 def _stream(stream) -> Optional[int]:
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream or None
+        return _current_raw_stream() or None
     if isinstance(stream, int):
         return stream or None
     return stream.cuda_stream or None
