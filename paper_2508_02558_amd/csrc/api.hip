@@ -91,6 +91,7 @@ constexpr float kLog2e = 1.4426950408889634f;
 struct AttnPlan {
   bool mfma;  // one of the kernels for bf16, head_dim 128, 32 query rows; otherwise the general one
   bool gqa;   // grouped-query kernel: one workgroup per (batch, KV head), wave = query head
+  bool stream;   // one workgroup per head with tiles fetched straight into LDS
   int n_split, tiles_per_split, waves;
   size_t part_o_bytes, part_ml_bytes;
   size_t ws_bytes() const { return part_o_bytes + part_ml_bytes; }
@@ -151,28 +152,45 @@ AttnPlan plan_attn(const sdllm_shape_t& s, int32_t n0, int64_t sr0, int32_t n1, 
     plan_general(pl, s, s.block_len, (n0 + kTileKeys - 1) / kTileKeys + (n1 + kTileKeys - 1) / kTileKeys, true);
     return pl;
   }
-  // Grouped-query heads: either one workgroup per query head (K/V then come G times out of L2, but the
-  // eight waves of a head split its keys and merge in LDS) or the shared-tile kernel (K/V read once,
-  // one wave per head, key splits merged through fp32 partials and a second launch).  Measured on
-  // MI355X (G = 2, 3, 4, 5, 7, 8; batch 1-64; 2k-49k keys; sparse and dense steps), in wave-tiles of
-  // work (heads x 32-key tiles): with four waves per workgroup (G = 7, 8) the shared-tile kernel wins
-  // from about 30 000, from about 22 000 when each head has 512 tiles or more (long prompts: the
-  // dense step of the batch-1 32k-prompt Dream shape 48.6 -> 44.4 us, of the 48k one 65 -> 56 us),
-  // and from about 18 000 with 128 heads or more, whose rows need few key splits (140 heads x 136
-  // tiles: 37.9 -> 33.4 us; 84 heads x 264 tiles lose, 34.2 against 39.1 us);
-  // with two waves per workgroup (G = 2, 4) what decides is the number of heads, sparse and dense
-  // step alike: 256 heads lose (G = 4: 28/51 us per head against 34/50 us shared), 384 heads win
-  // (G = 4: 46/82 against 42/68 us; G = 2: 54/97 against 50/80 us), 512 heads tie, 640 win.
-  const int all_tiles = (n0 + kTileKeys - 1) / kTileKeys + (n1 + kTileKeys - 1) / kTileKeys;
-  const int64_t wave_tiles = (int64_t)s.batch * s.n_q_heads * all_tiles;
+  const int tiles = (n0 + kTileKeys - 1) / kTileKeys + (n1 + kTileKeys - 1) / kTileKeys;
+  const int64_t wave_tiles = (int64_t)s.batch * s.n_q_heads * tiles;
   const int group = s.n_q_heads / s.n_kv_heads;
-  const int heads_all = s.batch * s.n_q_heads;
-  pl.gqa = pl.mfma && attn_gqa_supports_group(group) &&
-           (attn_gqa_waves_per_wg(group) >= 4
-                ? wave_tiles >= 30000 || (all_tiles >= 512 && wave_tiles >= 22000) || (heads_all >= 128 && wave_tiles >= 18000)
-                : heads_all >= 320 && wave_tiles >= 26000);
+  const int heads = s.batch * s.n_q_heads;
+  // Key splits of the kernels with one workgroup per head, only while the grid is small: as many as keep
+  // it within one workgroup per CU (an eight-wave workgroup fills a CU's LDS, so workgroup
+  // number 257 waits for a whole round: 56 heads x 4 splits 15.1 us, x 5 splits 22.3 us), at most 8
+  // (28 heads, replayed as a HIP graph so that only GPU time counts: 69 tiles 12.6 us with 6 splits and
+  // 12.15 us with 8, 137 tiles 16.85 -> 15.2 us, 261 tiles 20.3 -> 18.5 us), and a minimum of tiles per
+  // workgroup.  Batch-1 shapes are pure latency and a wave with
+  // one or two tiles beats a longer chain (28/4 heads x 4352 keys: 17.2 -> 15.0 us with 6 or 7 splits
+  // instead of 4).  From 129 heads on there is one workgroup per head.
+  // A split costs fp32 partials and a second launch of about 4 us: with up to 32 heads (where three or
+  // more splits fit) seven tiles per workgroup repay it, one tile per wave or two (32 heads x 21 tiles,
+  // sparse step 12.1 -> 11.6 us, dense step over 41 tiles 14.0 -> 12.9 us with 3 splits); from 64 heads
+  // on it takes eleven (128 heads x 21 tiles: 14.5 us unsplit, 15.9 us with 2 splits).
+  int n_split = kNumCUs / heads;
+  const int most = 8;
+  if (n_split > most) n_split = most;
+  const int max_split = tiles / (heads <= 32 ? 7 : 11);
+  if (n_split > max_split) n_split = max_split;
+  if (n_split < 1) n_split = 1;
+  // Grouped-query heads with much work: the shared-tile kernel (K/V read once per group, one wave per head, key
+  // splits merged through fp32 partials and a second launch) against one workgroup per query head.
+  // Two waves per workgroup (G = 2, 4), measured for sparse and dense steps: 256 heads lose (G = 4: 28/51 us per
+  // head against 34/50 us shared), 384 heads win (G = 4: 46/82 against 42/68 us; G = 2: 54/97 against 50/80 us),
+  // 512 heads tie, 640 win.
+  // Four waves (G = 7, 8): with more heads than CUs from 42 000 wave-tiles (heads x tiles) on (448 heads:
+  // 70 tiles 30.1 us per head against 37.7 us, 136 tiles 70.9 against 58.2; 512 heads: 70 tiles 31.5 against
+  // 39.7, 136 tiles 71.2 against 62.0).  With fewer, one workgroup per head (and split) takes 6 us, 4 more if
+  // split, and 0.155 us per tile whatever number of CUs it occupies, the shared-tile kernel 13.4 us and 0.72 us
+  // per thousand wave-tiles (224 heads x 144 tiles: 29.0 against 37.1 us): the latter wins where CUs stay idle
+  // over many tiles.
+  const int used = heads * n_split;
+  pl.gqa = attn_gqa_supports_group(group) &&
+           (attn_gqa_waves_per_wg(group) < 4 ? heads >= 320 && wave_tiles >= 26000
+            : heads > kNumCUs                ? wave_tiles >= 42000
+                                             : (int64_t)tiles * (215 - used) > n_split * (n_split == 1 ? 10000 : 4700));
   if (pl.gqa) {
-    const int tiles = (n0 + kTileKeys - 1) / kTileKeys + (n1 + kTileKeys - 1) / kTileKeys;
     const int rows = s.batch * s.n_kv_heads;
     // As many key splits as keep the grid within what the CUs hold at once (a few workgroups more
     // would wait for a whole round), but never fewer than 4 tiles (two LDS stages) each.  Four-wave
@@ -181,10 +199,10 @@ AttnPlan plan_attn(const sdllm_shape_t& s, int32_t n0, int64_t sr0, int32_t n1, 
     const int wg_waves = attn_gqa_waves_per_wg(group);
     const int wgs_per_row = (group + wg_waves - 1) / wg_waves;   // head splits
     const int room = (wg_waves >= 4 ? 2 : 3) * kNumCUs;
-    int n_split = room / (rows * wgs_per_row);
+    n_split = room / (rows * wgs_per_row);
     if (n_split < 1) n_split = 1;
-    const int max_split = tiles / 4 > 1 ? tiles / 4 : 1;
-    if (n_split > max_split) n_split = max_split;
+    const int most_split = tiles / 4 > 1 ? tiles / 4 : 1;
+    if (n_split > most_split) n_split = most_split;
     pl.tiles_per_split = (tiles + n_split - 1) / n_split;
     pl.n_split = (tiles + pl.tiles_per_split - 1) / pl.tiles_per_split;
     pl.waves = s.n_q_heads / s.n_kv_heads;
@@ -193,27 +211,28 @@ AttnPlan plan_attn(const sdllm_shape_t& s, int32_t n0, int64_t sr0, int32_t n1, 
       pl.part_o_bytes = align_up(slots * s.block_len * s.head_dim * sizeof(float));
       pl.part_ml_bytes = align_up(slots * 2 * s.block_len * sizeof(float));
     }
-  } else if (pl.mfma) {
-    const int tiles = (n0 + kTileKeys - 1) / kTileKeys + (n1 + kTileKeys - 1) / kTileKeys;
-    const int heads = s.batch * s.n_q_heads;
-    // Split the keys of a head over workgroups only while the grid is small: as many splits as keep
-    // the grid within one workgroup per CU (an eight-wave workgroup fills a CU's LDS, so workgroup
-    // number 257 waits for a whole round: 56 heads x 4 splits 15.1 us, x 5 splits 22.3 us), at most 8
-    // (28 heads, replayed as a HIP graph so that only GPU time counts: 69 tiles 12.6 us with 6 splits and
-    // 12.15 us with 8, 137 tiles 16.85 -> 15.2 us, 261 tiles 20.3 -> 18.5 us), and a minimum of tiles per
-    // workgroup (below).  Batch-1 shapes are pure latency and a wave with
-    // one or two tiles beats a longer chain (28/4 heads x 4352 keys: 17.2 -> 15.0 us with 6 or 7 splits
-    // instead of 4).  From 129 heads on there is one workgroup per head.
-    int n_split = kNumCUs / heads;
-    const int most = 8;
-    if (n_split > most) n_split = most;
-    // A split costs fp32 partials and a second launch of about 4 us: with up to 32 heads (where three or
-    // more splits fit) seven tiles per workgroup repay it, one tile per wave or two (32 heads x 21 tiles,
-    // sparse step 12.1 -> 11.6 us, dense step over 41 tiles 14.0 -> 12.9 us with 3 splits); from 64 heads
-    // on it takes eleven (128 heads x 21 tiles: 14.5 us unsplit, 15.9 us with 2 splits).
-    const int max_split = tiles / (heads <= 32 ? 7 : 11);
-    if (n_split > max_split) n_split = max_split;
-    if (n_split < 1) n_split = 1;
+  } else {
+    // The kernel that fetches tiles straight into LDS (attn_stream_mfma.hip) takes
+    // * grouped-query heads with one workgroup per head: always with 129 to 256 heads (8 x 28/4 heads: 28 tiles
+    //   11.8 -> 11.3 us, 75 tiles 20.9 -> 19.5 us, 144 tiles 37.1 -> 29.0 us), with more where four of its
+    //   waves beat the shared-tile kernel (above);
+    // * fewer grouped-query heads instead of key splits, up to the tile count at which two or more workgroups per head
+    //   repay the combine launch: 8 heads 21 tiles 9.6 -> 9.1 us, 28 tiles 9.6 against 10.2; 28 heads 21 tiles 10.6 -> 9.3 us, 28 tiles 10.7 against 10.4, 36 tiles 10.9 against
+    //   12.0 us; 56 heads 36 tiles 12.3 -> 12.1 us, 45 tiles 12.4 against 13.4; 112 heads 45 tiles 14.6 -> 13.9 us,
+    //   60 tiles 15.9 against 16.0;
+    // * split grouped-query heads whose waves get three tiles or more (28 heads x 1040 tiles in 8 splits 39.3 -> 33.2
+    //   us, 112 heads x 136 in 2 22.2 -> 21.0 us; two tiles: 24 heads x 71 tiles 11.0 against 12.0 us);
+    // * multi-head calls instead of splits up to 16 MB of keys and values, sixteen of which (layers) fit the memory-side
+    //   cache: 32 heads x 21 tiles 10.7 -> 9.6 us, 64 heads x 14 10.3 -> 9.0 us with the cache holding them, no
+    //   difference or up to 5 % loss from HBM.  Beyond that the non-temporal streams of attn_mfma.hip win, as they
+    //   do for the dense rows of calls that they leave unsplit (they then sweep the scores as well).
+    const bool unsplit_pays = heads <= 8 ? tiles <= 22 : heads <= 32 ? tiles <= 26 : heads <= 64 ? tiles <= 38 : heads <= 128 ? tiles <= 48 : true;
+    if (group > 1)
+      pl.stream = heads > kNumCUs ? attn_gqa_supports_group(group) && attn_gqa_waves_per_wg(group) >= 4 && tiles >= 36
+                                  : unsplit_pays || tiles >= 24 * n_split;
+    else
+      pl.stream = heads <= 128 && wave_tiles <= 1024 && unsplit_pays && (n1 > 0 || n_split > 1);
+    if (pl.stream && unsplit_pays) n_split = 1;
     pl.tiles_per_split = (tiles + n_split - 1) / n_split;
     pl.waves = pl.tiles_per_split < kMaxWavesPerWg ? pl.tiles_per_split : kMaxWavesPerWg;
     // split workgroups: two tiles per wave when there are fewer than sixteen (28 heads x 69 tiles in 6
@@ -229,9 +248,15 @@ AttnPlan plan_attn(const sdllm_shape_t& s, int32_t n0, int64_t sr0, int32_t n1, 
     // Up to one head per CU the grouped-query heads keep eight waves: there they are short of
     // arithmetic throughput, not of bandwidth (B=8 Dream shape: 22 -> 26 us with fewer).
     if (n_split == 1) {
-      const bool mha = s.n_q_heads == s.n_kv_heads;
-      const int cap = heads > 2 * kNumCUs ? 2 : heads > kNumCUs ? 4 : (mha ? 5 : kMaxWavesPerWg);
+      const int cap = heads > 2 * kNumCUs ? 2 : heads > kNumCUs ? 4 : (group == 1 ? 5 : kMaxWavesPerWg);
       if (pl.waves > cap) pl.waves = cap;
+    }
+    // Fetching into LDS: few tiles are done soonest by waves that take three or four each (28 heads: 8 tiles 6.7 us with
+    // four waves and 7.8 with eight, 14 tiles 8.0 with five and 9.0, 21 tiles 9.3 with six and 10.2, 45 tiles 13.5
+    // and 13.9, 60 tiles 16.4 and 15.6).
+    if (pl.stream) {
+      const int w = heads > kNumCUs ? 4 : n_split > 1 || tiles > 50 ? kMaxWavesPerWg : tiles > 16 ? 6 : tiles > 9 ? 5 : 4;
+      pl.waves = w < pl.tiles_per_split ? w : pl.tiles_per_split;
     }
     pl.n_split = (tiles + pl.tiles_per_split - 1) / pl.tiles_per_split;   // no empty split
     if (pl.n_split > 1) {
@@ -246,7 +271,7 @@ AttnPlan plan_attn(const sdllm_shape_t& s, int32_t n0, int64_t sr0, int32_t n1, 
 // Whether the dense launch of a cache-update step can also leave the saliency scores: multi-head attention
 // (one query head per KV head) on the one-workgroup-per-head kernel, no key splits, at least two waves.
 bool fuses_columns(const AttnPlan& pl, const sdllm_shape_t& s) {
-  return pl.mfma && !pl.gqa && pl.n_split == 1 && pl.waves >= 2 && s.n_q_heads == s.n_kv_heads;
+  return pl.mfma && !pl.gqa && !pl.stream && pl.n_split == 1 && pl.waves >= 2 && s.n_q_heads == s.n_kv_heads;
 }
 
 // cand_ml != null (dense MFMA launches only): also emit the scoring pass's row statistics over the
@@ -285,7 +310,7 @@ int32_t run_attn(const sdllm_shape_t& s, const void* q, const KvSegment& a, cons
   p.score_inv_count = 1.f / (float)(s.block_len * (s.n_q_heads / s.n_kv_heads));
   hipError_t e;
   if (pl.mfma) {
-    e = pl.gqa ? launch_attn_gqa_mfma_bf16(p, stream) : launch_attn_mfma_bf16(p, stream);
+    e = pl.stream ? launch_attn_stream_mfma_bf16(p, stream) : pl.gqa ? launch_attn_gqa_mfma_bf16(p, stream) : launch_attn_mfma_bf16(p, stream);
     if (deferred) *deferred = p;
     if (e == hipSuccess && pl.n_split > 1 && !deferred) e = launch_attn_combine(p, s.dtype, stream);
   } else {

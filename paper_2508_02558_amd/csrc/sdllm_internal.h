@@ -166,6 +166,7 @@ struct DenseFullParams {
 // kernel launchers (each returns hipGetLastError() after its launches)
 hipError_t launch_attn_mfma_bf16(const AttnParams& p, hipStream_t s);
 hipError_t launch_attn_gqa_mfma_bf16(const AttnParams& p, hipStream_t s);
+hipError_t launch_attn_stream_mfma_bf16(const AttnParams& p, hipStream_t s);
 bool attn_gqa_supports_group(int group);
 int attn_gqa_waves_per_wg(int group);
 // any type, head_dim and row count; stats_only: nothing but cand_ml

@@ -1,0 +1,49 @@
+"""The attention kernel that fetches tiles straight into LDS, at the sizes where its pipeline and its launch rule can go
+wrong: waves with no, one, two and many tiles, a ragged last tile of either key segment, key splits, more heads than CUs,
+and the scoring statistics when the block's own keys share tiles with candidates.  Tolerances: tests/parity_util.py."""
+import pytest
+import torch
+
+from paper_2508_02558_amd import binding as B
+from paper_2508_02558_amd import workloads as wl
+from tests import parity_util as U
+from tests.test_gpu_parity import _run_block
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+@pytest.mark.parametrize("batch,q_heads,kv_heads,n_cached", [
+    (1, 7, 1, 0), (1, 7, 1, 1), (1, 7, 1, 96), (1, 7, 1, 97), (2, 8, 2, 255), (1, 14, 2, 512), (3, 6, 2, 671),
+    (1, 32, 32, 77), (4, 8, 8, 400),                        # multi-head calls small enough to go unsplit
+    (8, 28, 4, 1633), (5, 28, 4, 2111),                     # one workgroup per head, eight waves
+    (1, 28, 4, 6211), (4, 28, 4, 1721),                     # split keys, three tiles per wave or more
+    (10, 28, 4, 1185),                                      # more heads than CUs: four waves
+])
+def test_stream_sparse_attn(batch, q_heads, kv_heads, n_cached):
+    print(f"[case] stream sparse_attn B={batch} {q_heads}/{kv_heads} n_cached={n_cached}", flush=True)
+    torch.manual_seed(n_cached + batch)
+    b, d, rows = 32, 128, max(1, n_cached)
+    shape = B.make_shape(batch=batch, n_q_heads=q_heads, n_kv_heads=kv_heads, head_dim=d, seq_len=16384, block_off=8192,
+                         block_len=b, dtype=B.SDLLM_BF16, cache_rows=rows)
+    q = (2.0 * torch.randn(batch, q_heads, b, d, device=DEV)).bfloat16()
+    kc, vc = (torch.randn(batch, kv_heads, rows, d, device=DEV).bfloat16() for _ in range(2))
+    kb, vb = (torch.randn(batch, kv_heads, b, d, device=DEV).bfloat16() for _ in range(2))
+    out = torch.full_like(q, float("nan"))
+    ws = torch.empty(B.sdllm_workspace_bytes(shape, B.SDLLM_OP_SPARSE_ATTN, n_cached), dtype=torch.uint8, device=DEV)
+    B.sdllm_sparse_attn(shape, q, kc, vc, n_cached, kb, vb, out, ws)
+    torch.cuda.synchronize()
+    k_all = torch.cat([kc[:, :, :n_cached], kb], 2)
+    v_all = torch.cat([vc[:, :, :n_cached], vb], 2)
+    U.assert_close(out, U.oracle_attention_batch(q, k_all, v_all), "bf16", f"n_cached={n_cached}")
+
+
+@pytest.mark.parametrize("q_heads,kv_heads,batch,prompt,modes", [
+    (14, 2, 1, 333, {}),                                                   # block off the tile grid on both sides
+    (7, 1, 2, 64, dict(evict_scope=B.SDLLM_EVICT_PREFIX_ONLY)),            # few candidate tiles, long mixed tail
+    (28, 4, 2, 3111, {}),                                                  # statistics from key splits
+    (14, 2, 1, 0, {}),                                                     # no prefix
+])
+def test_stream_statistics_at_the_cache_update_step(q_heads, kv_heads, batch, prompt, modes):
+    w = wl.WORKLOADS["dream7b_gqa"].scaled(batch=batch, n_q_heads=q_heads, n_kv_heads=kv_heads, prompt=prompt, gen=160)
+    _run_block(w, block_index=2, n_steps=3, **modes)
