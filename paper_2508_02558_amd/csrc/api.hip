@@ -141,7 +141,8 @@ void plan_general(AttnPlan& pl, const sdllm_shape_t& s, int32_t nq, int tiles, b
   }
 }
 
-AttnPlan plan_attn(const sdllm_shape_t& s, int32_t n0, int64_t sr0, int32_t n1, int64_t sr1) {
+// stats: the launch also leaves the scoring's row statistics (which kernel runs may depend on it, the splits do not).
+AttnPlan plan_attn(const sdllm_shape_t& s, int32_t n0, int64_t sr0, int32_t n1, int64_t sr1, bool stats = false) {
   AttnPlan pl{};
   pl.mfma = s.dtype == SDLLM_BF16 && s.head_dim == 128 && s.block_len == 32 && seg_fits_u32(sr0, n0, 2) &&
             seg_fits_u32(sr1, n1, 2);
@@ -179,17 +180,17 @@ AttnPlan plan_attn(const sdllm_shape_t& s, int32_t n0, int64_t sr0, int32_t n1, 
   // Two waves per workgroup (G = 2, 4), measured for sparse and dense steps: 256 heads lose (G = 4: 28/51 us per
   // head against 34/50 us shared), 384 heads win (G = 4: 46/82 against 42/68 us; G = 2: 54/97 against 50/80 us),
   // 512 heads tie, 640 win.
-  // Four waves (G = 7, 8): with more heads than CUs from 42 000 wave-tiles (heads x tiles) on (448 heads:
-  // 70 tiles 30.1 us per head against 37.7 us, 136 tiles 70.9 against 58.2; 512 heads: 70 tiles 31.5 against
-  // 39.7, 136 tiles 71.2 against 62.0).  With fewer, one workgroup per head (and split) takes 6 us, 4 more if
-  // split, and 0.155 us per tile whatever number of CUs it occupies, the shared-tile kernel 13.4 us and 0.72 us
-  // per thousand wave-tiles (224 heads x 144 tiles: 29.0 against 37.1 us): the latter wins where CUs stay idle
-  // over many tiles.
+  // Four waves (G = 7, 8): from 5000 tiles over all KV heads on, 80 MB of keys and values (dense rows, G = 7: 32 KV heads
+  // x 144 tiles 40.1 us shared against 32.5 us per head, x 269 tiles 58.8 against 64.1; 4 x 1040 tiles 39.0 against 35.0,
+  // x 1421 45.3 against 51.9; 448 query heads: 4480 tiles 37.7 against 30.1, 8704 58.2 against 70.9; G = 8: 16 x 269
+  // tiles 41.7 against 35.6), and before that where one workgroup per head (and split) leaves CUs idle over many tiles
+  // (140 heads x 144 tiles 31.1 against 32.5 us; 16 heads in 8 splits: 455 tiles 22.6 against 20.7 us, 652 tiles 26.0
+  // against 25.1 or, from HBM, 26.6 against 28.6, 1040 tiles 30.4 against 33.3).
   const int used = heads * n_split;
+  const int64_t all_tiles = (int64_t)s.batch * s.n_kv_heads * tiles;
   pl.gqa = attn_gqa_supports_group(group) &&
            (attn_gqa_waves_per_wg(group) < 4 ? heads >= 320 && wave_tiles >= 26000
-            : heads > kNumCUs                ? wave_tiles >= 42000
-                                             : (int64_t)tiles * (215 - used) > n_split * (n_split == 1 ? 10000 : 4700));
+                                             : all_tiles > 5000 || (heads <= kNumCUs && (int64_t)tiles * (215 - used) > n_split * (n_split == 1 ? 10000 : 6500)));
   if (pl.gqa) {
     const int rows = s.batch * s.n_kv_heads;
     // As many key splits as keep the grid within what the CUs hold at once (a few workgroups more
@@ -220,8 +221,9 @@ AttnPlan plan_attn(const sdllm_shape_t& s, int32_t n0, int64_t sr0, int32_t n1, 
     //   repay the combine launch: 8 heads 21 tiles 9.6 -> 9.1 us, 28 tiles 9.6 against 10.2; 28 heads 21 tiles 10.6 -> 9.3 us, 28 tiles 10.7 against 10.4, 36 tiles 10.9 against
     //   12.0 us; 56 heads 36 tiles 12.3 -> 12.1 us, 45 tiles 12.4 against 13.4; 112 heads 45 tiles 14.6 -> 13.9 us,
     //   60 tiles 15.9 against 16.0;
-    // * split grouped-query heads whose waves get three tiles or more (28 heads x 1040 tiles in 8 splits 39.3 -> 33.2
-    //   us, 112 heads x 136 in 2 22.2 -> 21.0 us; two tiles: 24 heads x 71 tiles 11.0 against 12.0 us);
+    // * split grouped-query heads at the cache-update step, where the other kernel masks every tile for the scoring's
+    //   statistics, if its waves get three tiles or more (28 heads x 1040 tiles, whole step 88.4 -> 85.8 us); without
+    //   statistics that one is as fast or faster (28 heads x 652 tiles 25.1 against 26.9 us);
     // * multi-head calls instead of splits up to 16 MB of keys and values, sixteen of which (layers) fit the memory-side
     //   cache: 32 heads x 21 tiles 10.7 -> 9.6 us, 64 heads x 14 10.3 -> 9.0 us with the cache holding them, no
     //   difference or up to 5 % loss from HBM.  Beyond that the non-temporal streams of attn_mfma.hip win, as they
@@ -229,7 +231,7 @@ AttnPlan plan_attn(const sdllm_shape_t& s, int32_t n0, int64_t sr0, int32_t n1, 
     const bool unsplit_pays = heads <= 8 ? tiles <= 22 : heads <= 32 ? tiles <= 26 : heads <= 64 ? tiles <= 38 : heads <= 128 ? tiles <= 48 : true;
     if (group > 1)
       pl.stream = heads > kNumCUs ? attn_gqa_supports_group(group) && attn_gqa_waves_per_wg(group) >= 4 && tiles >= 36
-                                  : unsplit_pays || tiles >= 24 * n_split;
+                                  : unsplit_pays || (stats && tiles >= 24 * n_split);
     else
       pl.stream = heads <= 128 && wave_tiles <= 1024 && unsplit_pays && (n1 > 0 || n_split > 1);
     if (pl.stream && unsplit_pays) n_split = 1;
@@ -282,7 +284,7 @@ bool fuses_columns(const AttnPlan& pl, const sdllm_shape_t& s) {
 int32_t run_attn(const sdllm_shape_t& s, const void* q, const KvSegment& a, const KvSegment& b, void* out, void* ws,
                  size_t ws_bytes, hipStream_t stream, float* cand_ml = nullptr, int cand0_end = 0, int cand1_begin = 0,
                  AttnParams* deferred = nullptr, float* score_out = nullptr, int score_stride = 0) {
-  AttnPlan pl = plan_attn(s, a.n, a.sr, b.n, b.sr);
+  AttnPlan pl = plan_attn(s, a.n, a.sr, b.n, b.sr, cand_ml != nullptr);
   if (pl.ws_bytes() > 0 && (!ws || ws_bytes < pl.ws_bytes())) {
     if (pl.mfma) return SDLLM_ERR_WORKSPACE;
     // the general kernel works without a workspace too: one workgroup per 32 rows walks all keys

@@ -12,8 +12,7 @@
 // What bounds it now: 8 waves x 16 KB per 1.3 us and CU (12.6 KB/us per wave), a chain of LDS reads, eight
 // dependent logits products, softmax and eight independent products per tile at two waves per SIMD.
 // Measured against the kernels it took over from (8 x 28/4 heads): 4608 keys, dense rows 40.2 -> 32.9 us
-// (shared-tile kernel, key splits and combine launch before); 2336 keys 20.9 -> 19.5 us; 28/4 heads x 33 280
-// keys in 9 splits 39.6 -> 33.2 us.  Small calls, where eight or fewer waves of one workgroup now do what
+// (shared-tile kernel, key splits and combine launch before); 2336 keys 20.9 -> 19.5 us.  Small calls, where eight or fewer waves of one workgroup now do what
 // key splits and a combine launch did: 56 heads x 28 tiles 12.9 -> 10.5 us, 32 heads x 21 tiles 10.7 -> 9.6 us.
 #include <type_traits>
 
@@ -108,7 +107,7 @@ __device__ __forceinline__ void tile_candidate_stats(const f32x16& sn, int pos0,
   }
 }
 
-template <int NSEG, bool STATS>
+template <int NSEG, bool STATS, bool TOUCH>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attn_stream_mfma_bf16_kernel(const AttnParams p) {
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
@@ -156,8 +155,35 @@ void attn_stream_mfma_bf16_kernel(const AttnParams p) {
     const int t = tile_of(pos_of(j));
     return t < sp.tiles0 ? min(kTileKeys, sp.n0 - t * kTileKeys) : min(kTileKeys, sp.n1 - (t - sp.tiles0) * kTileKeys);
   };
-  auto landed = [&](bool all) {   // every fetch of this wave is in LDS, or all but the eight requested last
+  // Each of the group's heads brings every group-th tile into L2 four tiles ahead of the others and itself, one request
+  // per 128-byte line (its first word, to LDS that nobody reads): the siblings run in step, so without it all of
+  // them wait for the same line from memory (8 x 28/4 heads x 4608 keys 42.5 -> 39.0 us with the keys in HBM, 36.0
+  // -> 34.3 us with them in the memory-side cache; three or five tiles ahead are the same, seven lose half of it).
+  constexpr int kAhead = 4;
+  auto touch = [&](int j) {
+    typedef __attribute__((address_space(1))) const void gvoid;
+    typedef __attribute__((address_space(3))) void lvoid;
+    uint32_t stride;
+    const TileSrc ts = tile_src(sp, tile_of(pos_of(j)), stride);
+    const uint32_t off = (uint32_t)min(lane >> 1, ts.rows - 1) * stride + ((lane & 1) << 7);
+    uint8_t* unread = smem + nw * kParkBytes + wave * 512;   // the statistics' place in the merge
+    __builtin_amdgcn_global_load_lds((gvoid*)(ts.k + off), (lvoid*)unread, 4, 0, 0);
+    __builtin_amdgcn_global_load_lds((gvoid*)(ts.v + off), (lvoid*)(unread + 256), 4, 0, 0);
+  };
+  int touch_next = 0;                                        // this head's next tile j: (wave + j) % group == h % group
+  if (TOUCH) {
+    touch_next = (h + 8 * p.group - wave) % p.group;
+    while (touch_next < 2) touch_next += p.group;
+  }
+  bool touched = false;                                      // two requests more after the last K tile's
+  auto touch_up_to = [&](int j) {
+    if (!TOUCH) return;
+    touched = touch_next <= j && touch_next < n_mine;
+    if (touched) { touch(touch_next); touch_next += p.group; }
+  };
+  auto landed = [&](bool all) {   // every fetch of this wave is in LDS, or all but the eight (and the touch) requested last
     if (all) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    else if (TOUCH && touched) asm volatile("s_waitcnt vmcnt(10)" ::: "memory");
     else asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
     wave_lds_sync();
   };
@@ -193,6 +219,7 @@ void attn_stream_mfma_bf16_kernel(const AttnParams p) {
     read_k_frags(k_lds, half, col, a);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     if (j + 1 < n_mine) fetch_k(j + 1);
+    touch_up_to(j + kAhead);
     __builtin_amdgcn_sched_barrier(0);
     tile_logits_mma(a, qf, sn);
     __builtin_amdgcn_sched_barrier(0);
@@ -203,7 +230,9 @@ void attn_stream_mfma_bf16_kernel(const AttnParams p) {
     logits(0);
     softmax(0);
     for (int j = 0; j + 1 < n_mine; ++j) {
-      landed(j == 0);                       // K(j+1); V(j) may still fly, except that V(0) was requested before K(1)
+      // K(j+1); V(j) may still fly, except that V(0) was requested before K(1)
+      if (TOUCH && j == 0 && touched) { asm volatile("s_waitcnt vmcnt(2)" ::: "memory"); wave_lds_sync(); }
+      else landed(j == 0);
       logits(j + 1);
       landed(j + 2 >= n_mine);              // V(j); K(j+2), if there is one, may still fly
       read_v_frags(v_lds, lane, f);
@@ -323,15 +352,21 @@ void attn_stream_mfma_bf16_kernel(const AttnParams p) {
   }
 }
 
-template <int NSEG, bool STATS>
-static hipError_t launch_variant(const AttnParams& p, hipStream_t s) {
+template <int NSEG, bool STATS, bool TOUCH>
+static hipError_t launch_touch(const AttnParams& p, hipStream_t s) {
   static LdsOptIn lds;
-  const auto kernel = attn_stream_mfma_bf16_kernel<NSEG, STATS>;
+  const auto kernel = attn_stream_mfma_bf16_kernel<NSEG, STATS, TOUCH>;
   const hipError_t e = lds.ensure(reinterpret_cast<const void*>(kernel), kMaxWavesPerWg * kStreamWaveLds);
   if (e != hipSuccess) return e;
   if (p.waves < 1 || p.waves > kMaxWavesPerWg) return hipErrorInvalidValue;
   hipLaunchKernelGGL(kernel, dim3(p.n_split * p.batch * p.hq), dim3(p.waves * kWave), p.waves * kStreamWaveLds, s, p);
   return hipGetLastError();
+}
+
+// Touching ahead pays from about a dozen tiles per wave on (8 x 28/4 heads: 144 tiles above, 74 tiles 19.8 -> 20.8 us).
+template <int NSEG, bool STATS>
+static hipError_t launch_variant(const AttnParams& p, hipStream_t s) {
+  return p.group > 1 && p.tiles_per_split >= 12 * p.waves ? launch_touch<NSEG, STATS, true>(p, s) : launch_touch<NSEG, STATS, false>(p, s);
 }
 
 hipError_t launch_attn_stream_mfma_bf16(const AttnParams& p, hipStream_t s) {
