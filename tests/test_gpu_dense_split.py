@@ -1,0 +1,28 @@
+"""Full-sequence attention with the keys of a head shared out between two or four groups of a workgroup's waves: sequence
+lengths around the stage (two or four tiles) and row-block edges, groups without a tile, and a grid that takes each
+variant.  Tolerances: tests/parity_util.py."""
+import pytest
+import torch
+
+from paper_2508_02558_amd import binding as B
+from tests import parity_util as U
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+@pytest.mark.parametrize("batch,q_heads,kv_heads,L", [
+    (1, 2, 1, 97), (1, 2, 1, 128), (1, 2, 1, 129), (1, 3, 1, 161), (2, 4, 2, 255), (1, 2, 2, 385), (1, 4, 4, 1025),   # four groups
+    (1, 28, 4, 513), (2, 12, 4, 705), (1, 28, 4, 735), (2, 12, 4, 1057),                                            # two groups
+    (8, 28, 4, 200),                                                                                                # whole rows
+])
+def test_dense_attn_key_groups(batch, q_heads, kv_heads, L):
+    print(f"[case] dense_attn key groups B={batch} {q_heads}/{kv_heads} L={L}", flush=True)
+    torch.manual_seed(L + q_heads)
+    q, k, v = ((g * torch.randn(batch, h, L, 128, device=DEV)).bfloat16() for g, h in ((2.0, q_heads), (1.0, kv_heads), (1.0, kv_heads)))
+    out = torch.full_like(q, float("nan"))
+    shape = B.make_shape(batch=batch, n_q_heads=q_heads, n_kv_heads=kv_heads, head_dim=128, seq_len=L, block_off=0, block_len=32,
+                         dtype=B.SDLLM_BF16)
+    B.sdllm_dense_attn(shape, q, k, v, out)
+    torch.cuda.synchronize()
+    U.assert_close(out, U.oracle_attention_batch(q, k, v), "bf16", f"L={L}")
