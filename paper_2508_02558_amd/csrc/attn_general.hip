@@ -39,11 +39,15 @@ __global__ __launch_bounds__(kGeneralMaxWaves * kWave) void attn_general_kernel(
   const int nw = blockDim.x >> 6;
   const int part = lane / R, col = lane % R;
 
+  // workgroups that read the same keys (the query heads of a KV group, their row blocks) sit on one XCD
   const int wg = xcd_contiguous_id(blockIdx.x, gridDim.x);
-  const int split = wg % p.n_split;
-  const int vhead = wg / p.n_split;                  // (batch, query head, block of R rows)
-  const int head = vhead / rblocks;
-  const int b = head / p.hq, h = head - b * p.hq, g = h / p.group;
+  const int per_key = p.group * rblocks;
+  const int pair = wg / per_key;
+  const int split = pair % p.n_split;
+  const int bg = pair / p.n_split;
+  const int b = bg / p.hkv, g = bg - b * p.hkv;
+  const int vhead = bg * per_key + wg - pair * per_key;   // (batch, query head, block of R rows)
+  const int head = vhead / rblocks, h = head - b * p.hq;
   const int row = (vhead - head * rblocks) * R + col;
   const bool row_valid = row < p.nq;
 

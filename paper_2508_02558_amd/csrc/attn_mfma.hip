@@ -49,13 +49,15 @@ __global__ __launch_bounds__(512) void attn_mfma_bf16_kernel(const AttnParams p)
   const int col = lane & 31;
 
   // Consecutive workgroup ids go round-robin over the 8 XCDs; renumber so that the workgroups of
-  // one KV group (its query heads and key splits) sit on one XCD and share that XCD's L2.
+  // one KV group and key split (its query heads: they read the same keys) sit on one XCD and share that XCD's L2.
   const int wg = xcd_contiguous_id(blockIdx.x, gridDim.x);
-  const int split = wg % p.n_split;
-  const int head = wg / p.n_split;
-  const int b = head / p.hq;
-  const int h = head - b * p.hq;
-  const int g = h / p.group;
+  const int pair = wg / p.group;
+  const int split = pair % p.n_split;
+  const int bg = pair / p.n_split;
+  const int b = bg / p.hkv;
+  const int g = bg - b * p.hkv;
+  const int h = g * p.group + wg - pair * p.group;
+  const int head = b * p.hq + h;
 
   const SegPtrs sp = seg_ptrs(p, b, g, NSEG == 2);
   const int ntiles = sp.tiles0 + (sp.n1 + kTileKeys - 1) / kTileKeys;

@@ -116,11 +116,13 @@ void attn_stream_mfma_bf16_kernel(const AttnParams p) {
   const int nw = blockDim.x >> 6;
   const int half = lane >> 5, col = lane & 31;
 
-  // workgroups of one KV group (its query heads and key splits) sit on one XCD and share its L2
+  // workgroups of one KV group and key split sit on one XCD and share its L2
   const int wg = xcd_contiguous_id(blockIdx.x, gridDim.x);
-  const int split = wg % p.n_split;
-  const int head = wg / p.n_split;
-  const int b = head / p.hq, h = head - b * p.hq, g = h / p.group;
+  const int pair = wg / p.group;
+  const int split = pair % p.n_split;
+  const int bg = pair / p.n_split;
+  const int b = bg / p.hkv, g = bg - b * p.hkv;
+  const int h = g * p.group + wg - pair * p.group, head = b * p.hq + h;
 
   const SegPtrs sp = seg_ptrs(p, b, g, NSEG == 2);
   const int ntiles = sp.tiles0 + (sp.n1 + kTileKeys - 1) / kTileKeys;
