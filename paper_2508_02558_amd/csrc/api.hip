@@ -107,17 +107,22 @@ int row_blocks(const sdllm_shape_t& s, int32_t rows) { return (rows + block_rows
 void plan_general(AttnPlan& pl, const sdllm_shape_t& s, int32_t nq, int tiles, bool may_split) {
   const int64_t vheads = (int64_t)s.batch * s.n_q_heads * row_blocks(s, nq);
   const int most_waves = kGeneralMaxWaves;
+  // Tiles from which splitting a head's keys repays the second launch, and the fewest a split is left with.  Sparse steps,
+  // split against unsplit: bf16, head_dim 128, 8 or 28 row blocks x 14 tiles 10.4 / 9.2 us, x 24 10.4 / 11.2; 64 x 24
+  // 12.0 / 11.5, x 36 12.2 / 14.3; 128 x 36 16.7 / 17.1 (two blocks of a head) and 19.5 / 17.4 (one); head_dim 64,
+  // whose tiles are half as long, 8 or 28 x 24 9.7 / 8.3, x 48 9.7 / 11.8, 128 x 48 15.0 / 13.6, x 75 19.0 / 18.8.  fp32, where
+  // a tile is 0.5 or 1 us of a SIMD's matrix work, head_dim 64, 16 x 14 10.2 / 10.2, x 24 10.6 / 13.4; head_dim 128,
+  // 16 x 14 13.1 / 16.3.
+  const bool f32 = s.dtype == SDLLM_F32, d64 = s.head_dim == 64;
+  const int from = f32 ? (d64 ? 16 : 12) : d64 ? (vheads <= 64 ? 36 : 76) : vheads <= 32 ? 20 : vheads <= 64 ? 28 : 40;
+  const int least = f32 ? (d64 ? 8 : 4) : vheads <= 32 ? 7 : 11;
   int n_split = 1;
-  if (may_split && vheads <= kNumCUs / 2) {
-    // Within one workgroup per CU (also what keeps the partials of every plan below SDLLM_STATIC_SCRATCH_BYTES:
-    // 256 x 16.25 KB).  bf16: the thresholds of the 32-row kernel.  fp32: a tile is 1 us (head_dim 64) or
-    // 2 us (128) of a SIMD's matrix work and a second launch 4 us, so split from 24 or 12 tiles on, down to 8 or 4 per
-    // workgroup (8 heads of 128, 32 rows, 22 tiles, with row statistics: 25.8 -> 12.8 + 4.0 us).
+  if (may_split && vheads <= kNumCUs / 2 && tiles >= from) {
+    // within one workgroup per CU, which also keeps the partials of every plan below SDLLM_STATIC_SCRATCH_BYTES
+    // (256 x 16.25 KB)
     n_split = (int)(kNumCUs / vheads);
     if (n_split > 8) n_split = 8;
-    const int least = s.dtype == SDLLM_F32 ? (s.head_dim == 64 ? 8 : 4) : vheads <= 32 ? 7 : 11;
-    const int max_split = s.dtype == SDLLM_F32 && tiles < 3 * least ? 1 : tiles / least;
-    if (n_split > max_split) n_split = max_split;
+    if (n_split > tiles / least) n_split = tiles / least;
     if (n_split < 1) n_split = 1;
   }
   pl.tiles_per_split = (tiles + n_split - 1) / n_split;
@@ -127,11 +132,11 @@ void plan_general(AttnPlan& pl, const sdllm_shape_t& s, int32_t nq, int tiles, b
   // tiles of head_dim 64, bf16, all rows of a sequence: 28 us with two waves, 23 us with four), the smaller merge
   // among equals.
   const int cu_waves = s.head_dim == 64 ? 12 : 8;
-  int64_t least = INT64_MAX;
+  int64_t fewest = INT64_MAX;
   for (int w = 2; w <= most_waves; w *= 2) {
     const int64_t slots = (int64_t)kNumCUs * (cu_waves / w);
     const int64_t cost = ((vheads * pl.n_split + slots - 1) / slots) * ((pl.tiles_per_split + w - 1) / w);
-    if (cost < least) { least = cost; pl.waves = w; }
+    if (cost < fewest) { fewest = cost; pl.waves = w; }
   }
   if (pl.waves > pl.tiles_per_split) pl.waves = pl.tiles_per_split;
   if (pl.waves < 1) pl.waves = 1;
@@ -185,12 +190,15 @@ AttnPlan plan_attn(const sdllm_shape_t& s, int32_t n0, int64_t sr0, int32_t n1, 
   // x 1421 45.3 against 51.9; 448 query heads: 4480 tiles 37.7 against 30.1, 8704 58.2 against 70.9; G = 8: 16 x 269
   // tiles 41.7 against 35.6), and before that where one workgroup per head (and split) leaves CUs idle over many tiles
   // (140 heads x 144 tiles 31.1 against 32.5 us; 16 heads in 8 splits: 455 tiles 22.6 against 20.7 us, 652 tiles 26.0
-  // against 25.1 or, from HBM, 26.6 against 28.6, 1040 tiles 30.4 against 33.3).
+  // against 25.1 or, from HBM, 26.6 against 28.6, 1040 tiles 30.4 against 33.3; but its partials take up to 34 MB, so
+  // not below 22 000 wave-tiles, where sdllm_sparse_attn_noalloc would have to refuse the call).
   const int used = heads * n_split;
   const int64_t all_tiles = (int64_t)s.batch * s.n_kv_heads * tiles;
   pl.gqa = attn_gqa_supports_group(group) &&
            (attn_gqa_waves_per_wg(group) < 4 ? heads >= 320 && wave_tiles >= 26000
-                                             : all_tiles > 5000 || (heads <= kNumCUs && (int64_t)tiles * (215 - used) > n_split * (n_split == 1 ? 10000 : 6500)));
+            : all_tiles > 5000               ? true
+            : n_split == 1                   ? heads <= kNumCUs && wave_tiles >= 18000 && (int64_t)tiles * (215 - used) > 10000
+                                             : wave_tiles >= 22000 && tiles >= 512 && (int64_t)tiles * (215 - used) > n_split * 6500);
   if (pl.gqa) {
     const int rows = s.batch * s.n_kv_heads;
     // As many key splits as keep the grid within what the CUs hold at once (a few workgroups more
@@ -218,9 +226,9 @@ AttnPlan plan_attn(const sdllm_shape_t& s, int32_t n0, int64_t sr0, int32_t n1, 
     //   11.8 -> 11.3 us, 75 tiles 20.9 -> 19.5 us, 144 tiles 37.1 -> 29.0 us), with more where four of its
     //   waves beat the shared-tile kernel (above);
     // * fewer grouped-query heads instead of key splits, up to the tile count at which two or more workgroups per head
-    //   repay the combine launch: 8 heads 21 tiles 9.6 -> 9.1 us, 28 tiles 9.6 against 10.2; 28 heads 21 tiles 10.6 -> 9.3 us, 28 tiles 10.7 against 10.4, 36 tiles 10.9 against
-    //   12.0 us; 56 heads 36 tiles 12.3 -> 12.1 us, 45 tiles 12.4 against 13.4; 112 heads 45 tiles 14.6 -> 13.9 us,
-    //   60 tiles 15.9 against 16.0;
+    //   repay the combine launch: 8 heads 21 tiles 9.6 -> 9.1 us, 28 tiles 9.6 against 10.2; 28 heads 21 tiles 10.6 -> 9.3 us, 28 tiles
+    //   10.7 against 10.4, 36 tiles 10.9 against 12.0 us; 56 heads 28 tiles 12.9 -> 10.5 us, 45 tiles 12.4 against 13.4;
+    //   72 heads (three splits) 37 tiles 11.8 against 12.6; 112 heads 45 tiles 14.6 -> 13.9 us, 60 tiles 15.9 against 16.0;
     // * split grouped-query heads at the cache-update step, where the other kernel masks every tile for the scoring's
     //   statistics, if its waves get three tiles or more (28 heads x 1040 tiles, whole step 88.4 -> 85.8 us); without
     //   statistics that one is as fast or faster (28 heads x 652 tiles 25.1 against 26.9 us);
@@ -228,7 +236,11 @@ AttnPlan plan_attn(const sdllm_shape_t& s, int32_t n0, int64_t sr0, int32_t n1, 
     //   cache: 32 heads x 21 tiles 10.7 -> 9.6 us, 64 heads x 14 10.3 -> 9.0 us with the cache holding them, no
     //   difference or up to 5 % loss from HBM.  Beyond that the non-temporal streams of attn_mfma.hip win, as they
     //   do for the dense rows of calls that they leave unsplit (they then sweep the scores as well).
-    const bool unsplit_pays = heads <= 8 ? tiles <= 22 : heads <= 32 ? tiles <= 26 : heads <= 64 ? tiles <= 38 : heads <= 128 ? tiles <= 48 : true;
+    const bool unsplit_pays = heads <= 8     ? tiles <= 22
+                              : heads <= 32  ? tiles <= 26
+                              : heads <= 85  ? tiles <= 33
+                              : heads <= 128 ? tiles <= 48
+                                             : true;
     if (group > 1)
       pl.stream = heads > kNumCUs ? attn_gqa_supports_group(group) && attn_gqa_waves_per_wg(group) >= 4 && tiles >= 36
                                   : unsplit_pays || (stats && tiles >= 24 * n_split);
