@@ -51,12 +51,13 @@ __global__ __launch_bounds__(512) void attn_mfma_bf16_kernel(const AttnParams p)
   // Consecutive workgroup ids go round-robin over the 8 XCDs; renumber so that the workgroups of
   // one KV group and key split (its query heads: they read the same keys) sit on one XCD and share that XCD's L2.
   const int wg = xcd_contiguous_id(blockIdx.x, gridDim.x);
-  const int pair = wg / p.group;
+  const int group = SHARED_KV ? p.group : 1;
+  const int pair = wg / group;
   const int split = pair % p.n_split;
   const int bg = pair / p.n_split;
   const int b = bg / p.hkv;
   const int g = bg - b * p.hkv;
-  const int h = g * p.group + wg - pair * p.group;
+  const int h = g * group + wg - pair * group;
   const int head = b * p.hq + h;
 
   const SegPtrs sp = seg_ptrs(p, b, g, NSEG == 2);
