@@ -232,10 +232,12 @@ AttnPlan plan_attn(const sdllm_shape_t& s, int32_t n0, int64_t sr0, int32_t n1, 
     // * split grouped-query heads at the cache-update step, where the other kernel masks every tile for the scoring's
     //   statistics, if its waves get three tiles or more (28 heads x 1040 tiles, whole step 88.4 -> 85.8 us); without
     //   statistics that one is as fast or faster (28 heads x 652 tiles 25.1 against 26.9 us);
-    // * multi-head calls instead of splits up to 16 MB of keys and values, sixteen of which (layers) fit the memory-side
-    //   cache: 32 heads x 21 tiles 10.7 -> 9.6 us, 64 heads x 14 10.3 -> 9.0 us with the cache holding them, no
-    //   difference or up to 5 % loss from HBM.  Beyond that the non-temporal streams of attn_mfma.hip win, as they
-    //   do for the dense rows of calls that they leave unsplit (they then sweep the scores as well).
+    // * multi-head calls instead of splits up to 8 MB of keys and values, thirty-two of which (layers) fit the memory-side
+    //   cache: 16 heads x 21 tiles 10.4 -> 9.3 us, 32 heads x 14 10.4 -> 8.0 us, 64 x 8 7.7 -> 6.8 us.  Beyond that a decoder's
+    //   layers evict each other and the keys come from HBM, where 32 heads x 21 tiles take 11.2 us split and
+    //   11.7 us unsplit (replayed as a graph 10.7 against 11.8; 10.7 against 9.6 if the cache holds them); the
+    //   non-temporal streams of attn_mfma.hip also keep the dense rows of calls that they leave unsplit (they then
+    //   sweep the scores as well).
     const bool unsplit_pays = heads <= 8     ? tiles <= 22
                               : heads <= 32  ? tiles <= 26
                               : heads <= 85  ? tiles <= 33
@@ -245,7 +247,7 @@ AttnPlan plan_attn(const sdllm_shape_t& s, int32_t n0, int64_t sr0, int32_t n1, 
       pl.stream = heads > kNumCUs ? attn_gqa_supports_group(group) && attn_gqa_waves_per_wg(group) >= 4 && tiles >= 36
                                   : unsplit_pays || (stats && tiles >= 24 * n_split);
     else
-      pl.stream = heads <= 128 && wave_tiles <= 1024 && unsplit_pays && (n1 > 0 || n_split > 1);
+      pl.stream = heads <= 128 && wave_tiles <= 512 && unsplit_pays && (n1 > 0 || n_split > 1);
     if (pl.stream && unsplit_pays) n_split = 1;
     pl.tiles_per_split = (tiles + n_split - 1) / n_split;
     pl.waves = pl.tiles_per_split < kMaxWavesPerWg ? pl.tiles_per_split : kMaxWavesPerWg;

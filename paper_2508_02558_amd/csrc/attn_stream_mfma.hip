@@ -11,9 +11,10 @@
 // 16 KB a wave needs for its two tiles let eight waves sit on a CU, which is why the buffers are single.
 // What bounds it now: 8 waves x 16 KB per 1.3 us and CU (12.6 KB/us per wave), a chain of LDS reads, eight
 // dependent logits products, softmax and eight independent products per tile at two waves per SIMD.
-// Measured against the kernels it took over from (8 x 28/4 heads): 4608 keys, dense rows 40.2 -> 32.9 us
-// (shared-tile kernel, key splits and combine launch before); 2336 keys 20.9 -> 19.5 us.  Small calls, where eight or fewer waves of one workgroup now do what
-// key splits and a combine launch did: 56 heads x 28 tiles 12.9 -> 10.5 us, 32 heads x 21 tiles 10.7 -> 9.6 us.
+// Measured against the kernels it took over from: 8 x 28/4 heads, 4608 keys, dense rows 39.9 -> 33.9 us (shared-tile
+// kernel, key splits and combine launch before), 2336 keys 20.6 -> 19.4 us.  Small calls, where eight or fewer waves
+// of one workgroup now do what key splits and a combine launch did: 56/8 heads x 28 tiles 12.9 -> 10.5 us, 32 heads x 14
+// tiles 10.4 -> 8.0 us.
 #include <type_traits>
 
 #include "attn_tile_math.h"
