@@ -10,8 +10,9 @@
 // leave two waves per SIMD.
 //   logits^T = K_tile Q^T: register i of a lane is key Ops::key(i, part) for query row `col`.
 //   O^T += V_tile^T P^T: results 4u .. 4u+3 of a lane are four output columns from Ops::unit_col(u, part) on.
-// fp32 probabilities throughout: with bf16 tensors they go into the second product as the sum of two bf16
-// parts (16 significand bits; their rounding is 250 times finer than that of the bf16 result).
+// fp32 probabilities throughout: with bf16 tensors they enter the second product as the sum of three bf16 parts, which
+// together hold all 24 significand bits (two parts, 16 bits, would take 0 to 5 % less time in sparse steps and 2 to 7 %
+// less over all rows of a sequence: 2 x 8 heads of 64 x 1092 rows 21.8 us against 22.9).
 #pragma once
 
 #include "mfma_tile.h"
@@ -209,6 +210,24 @@ __device__ __forceinline__ void g_v_publish(uint8_t* tile, int lane, const typen
 template <int D>
 __device__ __forceinline__ void g_v_publish(uint8_t*, int, const typename Ops<float, D>::V&) {}
 
+// Eight probabilities as the sum of three bf16 operands: each part is what the one before left, cut off after eight bits.
+__device__ __forceinline__ void g_bf16_parts(const float* p, bf16x8 (&part)[3]) {
+  u32x4 out[3];
+  const auto cut = [](float x) { return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, x) & 0xffff0000u); };
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    float x[2] = {p[2 * j], p[2 * j + 1]};
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      out[k][j] = __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, x[1]), __builtin_bit_cast(uint32_t, x[0]), 0x07060302u);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) x[i] -= cut(x[i]);
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < 3; ++k) part[k] = __builtin_bit_cast(bf16x8, out[k]);
+}
+
 // bf16: V^T operands through the transposing LDS read (lane s of a 16-lane group points at key row s/4 and
 // column piece s%4 and receives four consecutive keys of one column)
 template <int D>
@@ -218,15 +237,6 @@ __device__ __forceinline__ void g_pv(const uint8_t* tile, const typename Ops<__b
   typedef __attribute__((address_space(3))) gi16x4 lds_i16x4;
   const int part = lane >> 5, grp = (lane >> 4) & 1, s16 = lane & 15;
   const uint8_t* base = tile + (part * 4 + (s16 >> 2)) * O::kVRow + (grp * 16 + (s16 & 3) * 4) * 2;
-  bf16x8 hi[2], lo[2];
-#pragma unroll
-  for (int st = 0; st < 2; ++st)
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const float x = p[st * 8 + j];
-      hi[st][j] = (__bf16)x;
-      lo[st][j] = (__bf16)(x - (float)hi[st][j]);
-    }
   bf16x8 av[2][O::NE];
 #pragma unroll
   for (int st = 0; st < 2; ++st)
@@ -238,10 +248,12 @@ __device__ __forceinline__ void g_pv(const uint8_t* tile, const typename Ops<__b
     }
 #pragma unroll
   for (int st = 0; st < 2; ++st) {
+    bf16x8 parts[3];
+    g_bf16_parts(p + st * 8, parts);
 #pragma unroll
-    for (int e = 0; e < O::NE; ++e) acc[e] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[st][e], hi[st], acc[e], 0, 0, 0);
+    for (int k = 0; k < 3; ++k)
 #pragma unroll
-    for (int e = 0; e < O::NE; ++e) acc[e] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[st][e], lo[st], acc[e], 0, 0, 0);
+      for (int e = 0; e < O::NE; ++e) acc[e] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[st][e], parts[k], acc[e], 0, 0, 0);
   }
 }
 // fp32: step i contracts the four keys that the parts of a row hold in register i

@@ -85,3 +85,30 @@ def test_rows_too_far_apart_for_32_bit_offsets():
     B.sdllm_sparse_attn(shape, q, kc, vc, n, kb, vb, out, None)
     torch.cuda.synchronize()
     U.assert_close(out, U.oracle_attention_batch(q, torch.cat([kc, kb], 2), torch.cat([vc, vb], 2)), "bf16", "far rows")
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_probabilities_keep_24_bits_with_bf16_tensors(d):
+    # Row i: key 1 has probability x_i / (2 + x_i), keys 0 and 2 have 1 / (2 + x_i), the others none.  Column i of V is
+    # 1 for key 1, minus the first 16 bits of x_i for keys 0 and 2, so out[i, i] is what x_i has below them.  Bound, in units
+    # of 2^-24 relative to x_i: 2 for the exponential, 1 for its argument, 8 for the sums of terms near 1, 16 in all; then
+    # the rounding of the result to bf16.  Sixteen-bit probabilities are off by up to 64.
+    print(f"[case] 24-bit probabilities d={d}", flush=True)
+    b = 31
+    i = torch.arange(b)
+    q, k, v = (torch.zeros(1, 1, b, d, dtype=torch.float64) for _ in range(3))
+    q[..., 0], q[..., 1] = (i + 1) / 8, 64
+    k[0, 0, 1, 0] = -1
+    k[0, 0, 3:, 1] = -256
+    x = torch.exp(-(i + 1).double() / 64)
+    hi = x.bfloat16().double()
+    lo = (x - hi).bfloat16().double()
+    v[0, 0, 0, :b], v[0, 0, 1, :b], v[0, 0, 2, :b] = -hi, 1, -lo
+    shape = B.make_shape(batch=1, n_q_heads=1, n_kv_heads=1, head_dim=d, seq_len=64, block_off=0, block_len=b, dtype=B.SDLLM_BF16,
+                         softmax_scale=0.125)
+    qb, kb, vb = (t.bfloat16().to(DEV) for t in (q, k, v))
+    out = torch.zeros_like(qb)
+    B.sdllm_sparse_attn(shape, qb, None, None, 0, kb, vb, out, None)
+    torch.cuda.synchronize()
+    got, want = out[0, 0, i, i].double().cpu(), (x - hi - lo) / (2 + x)
+    assert ((got - want).abs() <= 16 * 2.0 ** -24 * x / (2 + x) + 2.0 ** -9 * want.abs()).all()
