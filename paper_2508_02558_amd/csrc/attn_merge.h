@@ -48,6 +48,7 @@ __device__ __forceinline__ RowPiece fold_splits(const float* ml, const float* po
       m_s[u] = ml[s * 2 * R];
       l_s[u] = ml[s * 2 * R + R];
       o_s[u] = *reinterpret_cast<const mf32x4*>(po + s * po_ss);
+      if (j0 + u >= n_mine) o_s[u] = mf32x4{0.f, 0.f, 0.f, 0.f};   // a weight of 0 alone would make NaN of an infinity
     }
     float m_new = r.m;
 #pragma unroll

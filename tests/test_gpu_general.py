@@ -112,3 +112,29 @@ def test_probabilities_keep_24_bits_with_bf16_tensors(d):
     torch.cuda.synchronize()
     got, want = out[0, 0, i, i].double().cpu(), (x - hi - lo) / (2 + x)
     assert ((got - want).abs() <= 16 * 2.0 ** -24 * x / (2 + x) + 2.0 ** -9 * want.abs()).all()
+
+
+@pytest.mark.parametrize("dtype,d,block,n_cached", [
+    ("f32", 64, 1, 0), ("f32", 128, 33, 70), ("f32", 128, 33, 1300),                              # the last with key splits
+])
+def test_infinite_values_stay_infinite(dtype, d, block, n_cached):
+    # a key of positive weight with an infinity in V: that column is infinite, the others are not touched
+    print(f"[case] infinities in V: {dtype} d={d} b={block} n={n_cached}", flush=True)
+    torch.manual_seed(d + n_cached)
+    t = torch.float32 if dtype == "f32" else torch.bfloat16
+    shape = B.make_shape(batch=1, n_q_heads=2, n_kv_heads=1, head_dim=d, seq_len=4096, block_off=2048, block_len=block,
+                         dtype=U.DT[dtype], cache_rows=max(1, n_cached))
+    q = torch.randn(1, 2, block, d, device=DEV).to(t)
+    kc, vc = (torch.randn(1, 1, max(1, n_cached), d, device=DEV).to(t) for _ in range(2))
+    kb, vb = (torch.randn(1, 1, block, d, device=DEV).to(t) for _ in range(2))
+    vb[0, 0, -1, 3], vb[0, 0, 0, d - 1] = float("inf"), float("-inf")
+    if n_cached:
+        vc[0, 0, n_cached // 2, 17], vc[0, 0, n_cached - 1, 40] = float("-inf"), float("inf")
+    ws = torch.empty(B.sdllm_workspace_bytes(shape, B.SDLLM_OP_SPARSE_ATTN, n_cached), dtype=torch.uint8, device=DEV)
+    out = torch.zeros_like(q)
+    B.sdllm_sparse_attn(shape, q, kc, vc, n_cached, kb, vb, out, ws)
+    torch.cuda.synchronize()
+    ref = U.oracle_attention_batch(q, torch.cat([kc[:, :, :n_cached], kb], 2), torch.cat([vc[:, :, :n_cached], vb], 2))
+    inf = torch.from_numpy(ref).isinf()
+    assert inf.any() and torch.equal(out.cpu().double()[inf], torch.from_numpy(ref)[inf])
+    U.assert_close(torch.where(inf.to(DEV), torch.zeros_like(out), out), torch.where(inf, 0.0, torch.from_numpy(ref)).numpy(), dtype, "finite columns")
