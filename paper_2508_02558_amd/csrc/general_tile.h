@@ -12,7 +12,7 @@
 //   O^T += V_tile^T P^T: results 4u .. 4u+3 of a lane are four output columns from Ops::unit_col(u, part) on.
 // fp32 probabilities throughout: with bf16 tensors they enter the second product as the sum of three bf16 parts, which
 // together hold all 24 significand bits (two parts, 16 bits, would take 0 to 5 % less time in sparse steps and 2 to 7 %
-// less over all rows of a sequence: 2 x 8 heads of 64 x 1092 rows 21.8 us against 22.9).
+// less over all rows of a sequence: 2 x 8 heads of 64 x 1092 rows 21.8 us against 23.6 with the step below).
 #pragma once
 
 #include "mfma_tile.h"
@@ -221,7 +221,7 @@ __device__ __forceinline__ void g_bf16_parts(const float* p, bf16x8 (&part)[3]) 
     for (int k = 0; k < 3; ++k) {
       out[k][j] = __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, x[1]), __builtin_bit_cast(uint32_t, x[0]), 0x07060302u);
 #pragma unroll
-      for (int i = 0; i < 2; ++i) x[i] -= cut(x[i]);
+      for (int i = 0; i < 2; ++i) x[i] = __builtin_amdgcn_fmed3f(x[i] - cut(x[i]), x[i], 0x1p-126f);   // zero stays zero
     }
   }
 #pragma unroll

@@ -116,6 +116,7 @@ def test_probabilities_keep_24_bits_with_bf16_tensors(d):
 
 @pytest.mark.parametrize("dtype,d,block,n_cached", [
     ("f32", 64, 1, 0), ("f32", 128, 33, 70), ("f32", 128, 33, 1300),                              # the last with key splits
+    ("bf16", 64, 1, 0), ("bf16", 128, 1, 0), ("bf16", 64, 33, 70), ("bf16", 128, 48, 1300),
 ])
 def test_infinite_values_stay_infinite(dtype, d, block, n_cached):
     # a key of positive weight with an infinity in V: that column is infinite, the others are not touched
