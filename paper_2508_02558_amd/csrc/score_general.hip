@@ -86,9 +86,16 @@ __global__ __launch_bounds__(kColWaves * kWave) void score_cols_general_kernel(c
       float total[O::kKeysPerLane];
 #pragma unroll
       for (int n = 0; n < O::kKeysPerLane; ++n) total[n] = 0.f;
+      int row0 = blk0 % rblocks * R;   // of block k, in its head
       for (int k = 0; k < here; ++k) {
         float s[O::NS], sum[O::kKeysPerLane];
         O::score(lds_q + k * kQBytes, keys, col, part, s);
+        if (p.nq - row0 < R) {   // zero rows meeting an infinite key are NaN
+          asm volatile("");      // a real branch (wave-uniform)
+#pragma unroll
+          for (int i = 0; i < O::NS; ++i) s[i] = row0 + O::query(i, part) < p.nq ? s[i] : 0.f;
+        }
+        row0 = row0 + R < p.nq ? row0 + R : 0;
 #pragma unroll
         for (int n = 0; n < O::kKeysPerLane; ++n) sum[n] = 0.f;
         if (p.softmax) {

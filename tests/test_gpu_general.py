@@ -139,3 +139,31 @@ def test_infinite_values_stay_infinite(dtype, d, block, n_cached):
     inf = torch.from_numpy(ref).isinf()
     assert inf.any() and torch.equal(out.cpu().double()[inf], torch.from_numpy(ref)[inf])
     U.assert_close(torch.where(inf.to(DEV), torch.zeros_like(out), out), torch.where(inf, 0.0, torch.from_numpy(ref)).numpy(), dtype, "finite columns")
+
+
+@pytest.mark.parametrize("dtype,d,block,q_heads", [("bf16", 64, 24, 4), ("bf16", 128, 40, 9), ("f32", 64, 8, 2), ("f32", 128, 50, 6)])
+@pytest.mark.parametrize("mode", [B.SDLLM_SOFTMAX_MEAN, B.SDLLM_LOGIT_MEAN])
+def test_scores_of_infinitely_low_keys(dtype, d, block, q_heads, mode):
+    # query blocks with padding rows: a key whose logits are all -inf weighs nothing (softmax) or -inf (logits), and the
+    # other candidates keep their scores
+    print(f"[case] -inf keys in the scoring: {dtype} d={d} b={block} mode={mode}", flush=True)
+    torch.manual_seed(block)
+    t = torch.float32 if dtype == "f32" else torch.bfloat16
+    L, off = 300, 131
+    shape = B.make_shape(batch=1, n_q_heads=q_heads, n_kv_heads=1, head_dim=d, seq_len=L, block_off=off, block_len=block,
+                         dtype=U.DT[dtype], score_mode=mode)
+    q = torch.randn(1, q_heads, block, d, device=DEV).to(t)
+    q[..., 0] = q[..., 0].abs() + 0.25
+    k = torch.randn(1, 1, L, d, device=DEV).to(t)
+    k[0, 0, 100, 0] = k[0, 0, L - 1, 0] = float("-inf")
+    low = [100, L - 1 - block]                                  # as candidates
+    gl = U.GpuLayer(shape, DEV)
+    _, _, score = gl.score_select(q, k)
+    got = score[0, 0].double().cpu()
+    kept = torch.ones(L - block, dtype=torch.bool)
+    kept[low] = False
+    cand = torch.cat([k[0, 0, :off], k[0, 0, off + block:]])
+    a = torch.stack([q[0, h].double().cpu() @ cand[kept.to(DEV)].double().cpu().T / d ** 0.5 for h in range(q_heads)])
+    want = (torch.softmax(a, -1) if mode == B.SDLLM_SOFTMAX_MEAN else a).mean((0, 1))
+    assert (got[low] == (0.0 if mode == B.SDLLM_SOFTMAX_MEAN else float("-inf"))).all()
+    torch.testing.assert_close(got[kept], want, rtol=2e-5, atol=1e-12 if mode == B.SDLLM_SOFTMAX_MEAN else 2e-5)
