@@ -88,7 +88,7 @@ __global__ __launch_bounds__(kGeneralMaxWaves * kWave) void attn_general_kernel(
   for (int e = 0; e < O::NE; ++e)
 #pragma unroll
     for (int i = 0; i < kAccRegs; ++i) acc[e][i] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;      // softmax reference of the row; sum over the keys this lane has seen
+  float m_run = kNoMax, l_run = 0.f;      // softmax reference of the row; sum over the keys this lane has seen
   float mc_run = -INFINITY, lc_run = 0.f;    // over candidate keys only
 
   for (; t < t_end; t += nw) {
@@ -188,7 +188,7 @@ __global__ __launch_bounds__(kGeneralMaxWaves * kWave) void attn_general_kernel(
     p.cand_ml[slot * 2 * R + R + lane] = lc;
   }
   if (MODE == kStatsOnly) return;
-  // a wave that saw no tile parked (-inf, 0, 0), one that is not there counts for nothing
+  // a wave that saw no tile parked (kNoMax, 0, 0), one that is not there counts for nothing
   float f_w[kGeneralMaxWaves], l_w[kGeneralMaxWaves], m_tot = -INFINITY, l_all = 0.f;
 #pragma unroll
   for (int w = 0; w < kGeneralMaxWaves; ++w) {

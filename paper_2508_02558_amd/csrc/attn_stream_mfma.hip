@@ -200,7 +200,7 @@ void attn_stream_mfma_bf16_kernel(const AttnParams p) {
   for (int e = 0; e < 4; ++e)
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[e][i] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;
+  float m_run = kNoMax, l_run = 0.f;
   float mc_run = -INFINITY, lc_run = 0.f;   // the same over candidate keys only (STATS)
 
   bf16x8 a[8], pb[2];
@@ -317,7 +317,7 @@ void attn_stream_mfma_bf16_kernel(const AttnParams p) {
     for (int s = 0; s < KS; ++s) m_tot = fmaxf(m_tot, m_s[s]);
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
-      f_s[s] = m_s[s] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_s[s] - m_tot);   // a wave that saw no tile: 0
+      f_s[s] = __builtin_amdgcn_exp2f(m_s[s] - m_tot);   // a wave that saw no tile: 0
       l_all += f_s[s] * l_s[s];
     }
     const float inv = 1.f / l_all;

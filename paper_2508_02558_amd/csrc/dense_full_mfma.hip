@@ -188,7 +188,7 @@ __global__ __launch_bounds__(512) void dense_split_mfma_bf16_kernel(const DenseF
   for (int e = 0; e < 4; ++e)
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[e][i] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;
+  float m_run = kNoMax, l_run = 0.f;
 
   u32x4 kreg[NT], vreg[NT];
   full_load_stage<NT>(k_base, v_base, stride, 0, n_keys, tid, kreg, vreg);
@@ -258,7 +258,7 @@ __global__ __launch_bounds__(512) void dense_split_mfma_bf16_kernel(const DenseF
   }
 #pragma unroll
   for (int k = 0; k < KS; ++k) {
-    f_w[k] = f_w[k] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(f_w[k] - m_tot);   // a group without tiles: 0
+    f_w[k] = __builtin_amdgcn_exp2f(f_w[k] - m_tot);   // a group without tiles: 0
     l_all += f_w[k] * reinterpret_cast<const float*>(parked(k) + kWave * kRowBytes)[32 + col];
   }
   const float inv = 1.f / l_all;

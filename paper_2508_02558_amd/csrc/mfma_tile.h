@@ -72,6 +72,10 @@ __device__ __forceinline__ void store_rows_v(uint8_t* lds_tile, int lane, const 
     *reinterpret_cast<u32x4*>(lds_tile + vtile_off(j * 4 + (lane >> 4), lane & 15)) = reg[j];
 }
 
+// Softmax reference of a row before its first key of finite logit.  Finite itself: against -inf the numerators of a tile
+// whose logits are all -inf would be exp2(-inf + inf).  Everything scaled by exp2(kNoMax - m) is zero, as with -inf.
+constexpr float kNoMax = -3.0e38f;
+
 // make this wave's LDS writes visible to its own later reads (wave-private tiles need no s_barrier)
 __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");

@@ -6,6 +6,7 @@ import torch
 
 from paper_2508_02558_amd import binding as B
 from tests import parity_util as U
+from tests.test_gpu_general import _hide
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -26,3 +27,18 @@ def test_dense_attn_key_groups(batch, q_heads, kv_heads, L):
     B.sdllm_dense_attn(shape, q, k, v, out)
     torch.cuda.synchronize()
     U.assert_close(out, U.oracle_attention_batch(q, k, v), "bf16", f"L={L}")
+
+
+@pytest.mark.parametrize("batch,q_heads,kv_heads,L", [(1, 2, 1, 300), (1, 28, 4, 735)])
+def test_tiles_of_infinitely_low_keys(batch, q_heads, kv_heads, L):
+    # whole tiles without weight, among them the first of a key group
+    print(f"[case] dense_attn key groups, -inf tiles L={L}", flush=True)
+    torch.manual_seed(L)
+    q, k, v = (torch.randn(batch, h, L, 128, device=DEV).bfloat16() for h in (q_heads, kv_heads, kv_heads))
+    kept = _hide(k, q, [*range(32, 64), *range(96, 128)])
+    out = torch.zeros_like(q)
+    shape = B.make_shape(batch=batch, n_q_heads=q_heads, n_kv_heads=kv_heads, head_dim=128, seq_len=L, block_off=0, block_len=32,
+                         dtype=B.SDLLM_BF16)
+    B.sdllm_dense_attn(shape, q, k, v, out)
+    torch.cuda.synchronize()
+    U.assert_close(out, U.oracle_attention_batch(q, k[:, :, kept], v[:, :, kept]), "bf16", f"L={L}")

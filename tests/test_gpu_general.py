@@ -167,3 +167,29 @@ def test_scores_of_infinitely_low_keys(dtype, d, block, q_heads, mode):
     want = (torch.softmax(a, -1) if mode == B.SDLLM_SOFTMAX_MEAN else a).mean((0, 1))
     assert (got[low] == (0.0 if mode == B.SDLLM_SOFTMAX_MEAN else float("-inf"))).all()
     torch.testing.assert_close(got[kept], want, rtol=2e-5, atol=1e-12 if mode == B.SDLLM_SOFTMAX_MEAN else 2e-5)
+
+
+def _hide(k, q, keys):
+    """Makes the logits of `keys` -inf for every query; returns the others."""
+    q[..., 0] = q[..., 0].abs() + 0.25
+    k[:, :, keys, 0] = float("-inf")
+    return [i for i in range(k.shape[2]) if i not in set(keys)]
+
+
+@pytest.mark.parametrize("dtype,d,block,n_cached", [("bf16", 64, 32, 500), ("bf16", 128, 48, 1300), ("f32", 64, 16, 500), ("f32", 128, 32, 300)])
+def test_tiles_of_infinitely_low_keys(dtype, d, block, n_cached):
+    # whole tiles without weight, among them the first of a wave
+    print(f"[case] -inf tiles: {dtype} d={d} b={block} n={n_cached}", flush=True)
+    torch.manual_seed(block + d)
+    t = torch.float32 if dtype == "f32" else torch.bfloat16
+    shape = B.make_shape(batch=1, n_q_heads=2, n_kv_heads=1, head_dim=d, seq_len=4096, block_off=2048, block_len=block,
+                         dtype=U.DT[dtype], cache_rows=n_cached)
+    q = torch.randn(1, 2, block, d, device=DEV).to(t)
+    kc, vc = (torch.randn(1, 1, n_cached, d, device=DEV).to(t) for _ in range(2))
+    kb, vb = (torch.randn(1, 1, block, d, device=DEV).to(t) for _ in range(2))
+    kept = _hide(kc, q, [*range(64, 130), *range(224, 256)])
+    ws = torch.empty(B.sdllm_workspace_bytes(shape, B.SDLLM_OP_SPARSE_ATTN, n_cached), dtype=torch.uint8, device=DEV)
+    out = torch.zeros_like(q)
+    B.sdllm_sparse_attn(shape, q, kc, vc, n_cached, kb, vb, out, ws)
+    torch.cuda.synchronize()
+    U.assert_close(out, U.oracle_attention_batch(q, torch.cat([kc[:, :, kept], kb], 2), torch.cat([vc[:, :, kept], vb], 2)), dtype, "kept keys")

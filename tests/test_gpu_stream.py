@@ -7,6 +7,7 @@ import torch
 from paper_2508_02558_amd import binding as B
 from paper_2508_02558_amd import workloads as wl
 from tests import parity_util as U
+from tests.test_gpu_general import _hide
 from tests.test_gpu_parity import _run_block
 
 pytestmark = pytest.mark.gpu
@@ -47,3 +48,20 @@ def test_stream_sparse_attn(batch, q_heads, kv_heads, n_cached):
 def test_stream_statistics_at_the_cache_update_step(q_heads, kv_heads, batch, prompt, modes):
     w = wl.WORKLOADS["dream7b_gqa"].scaled(batch=batch, n_q_heads=q_heads, n_kv_heads=kv_heads, prompt=prompt, gen=160)
     _run_block(w, block_index=2, n_steps=3, **modes)
+
+
+@pytest.mark.parametrize("n_cached", [128, 600])
+def test_tiles_of_infinitely_low_keys(n_cached):
+    # whole tiles without weight, among them the first of a wave
+    print(f"[case] stream, -inf tiles n_cached={n_cached}", flush=True)
+    torch.manual_seed(n_cached)
+    q = torch.randn(1, 7, 32, 128, device=DEV).bfloat16()
+    kc, vc, kb, vb = (torch.randn(1, 1, n, 128, device=DEV).bfloat16() for n in (n_cached, n_cached, 32, 32))
+    kept = _hide(kc, q, [*range(32, 64), *range(96, 128)])
+    shape = B.make_shape(batch=1, n_q_heads=7, n_kv_heads=1, head_dim=128, seq_len=4096, block_off=2048, block_len=32,
+                         dtype=B.SDLLM_BF16, cache_rows=n_cached)
+    out = torch.zeros_like(q)
+    ws = torch.empty(B.sdllm_workspace_bytes(shape, B.SDLLM_OP_SPARSE_ATTN, n_cached), dtype=torch.uint8, device=DEV)
+    B.sdllm_sparse_attn(shape, q, kc, vc, n_cached, kb, vb, out, ws)
+    torch.cuda.synchronize()
+    U.assert_close(out, U.oracle_attention_batch(q, torch.cat([kc[:, :, kept], kb], 2), torch.cat([vc[:, :, kept], vb], 2)), "bf16", "kept keys")
