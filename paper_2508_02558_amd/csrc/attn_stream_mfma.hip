@@ -184,6 +184,13 @@ void attn_stream_mfma_bf16_kernel(const AttnParams p) {
     touched = touch_next <= j && touch_next < n_mine;
     if (touched) { touch(touch_next); touch_next += p.group; }
   };
+  // The waits below count requests, so they hang on the order of issue: K(0), V(0), K(1), touch, and from then on for each
+  // tile K(j+2), touch, V(j+1), every one of them whole before the next begins.  Memory and scheduling barriers between
+  // them keep the compiler from interleaving requests whose LDS destinations it can tell apart.
+  auto in_order = [] {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
   auto landed = [&](bool all) {   // every fetch of this wave is in LDS, or all but the eight (and the touch) requested last
     if (all) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     else if (TOUCH && touched) asm volatile("s_waitcnt vmcnt(10)" ::: "memory");
@@ -193,7 +200,13 @@ void attn_stream_mfma_bf16_kernel(const AttnParams p) {
 
   bf16x8 qf[8];
   load_q_frags((const char*)p.q + 2 * (b * p.q_sb + h * p.q_sh + col * p.q_sr), half, qf);
-  if (n_mine > 0) { fetch_k(0); fetch_v(0); }
+  if (n_mine > 0) {
+    in_order();
+    fetch_k(0);
+    in_order();
+    fetch_v(0);
+    in_order();
+  }
 
   f32x16 acc[4];
 #pragma unroll
@@ -222,8 +235,9 @@ void attn_stream_mfma_bf16_kernel(const AttnParams p) {
     read_k_frags(k_lds, half, col, a);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     if (j + 1 < n_mine) fetch_k(j + 1);
+    in_order();
     touch_up_to(j + kAhead);
-    __builtin_amdgcn_sched_barrier(0);
+    in_order();
     tile_logits_mma(a, qf, sn);
     __builtin_amdgcn_sched_barrier(0);
   };
@@ -240,7 +254,7 @@ void attn_stream_mfma_bf16_kernel(const AttnParams p) {
       landed(j + 2 >= n_mine);              // V(j); K(j+2), if there is one, may still fly
       read_v_frags(v_lds, lane, f);
       fetch_v(j + 1);
-      __builtin_amdgcn_sched_barrier(0);
+      in_order();
       pv_block(f, pb, acc);
       __builtin_amdgcn_sched_barrier(0);
       softmax(j + 1);
