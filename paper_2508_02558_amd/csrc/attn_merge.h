@@ -48,7 +48,6 @@ __device__ __forceinline__ RowPiece fold_splits(const float* ml, const float* po
       m_s[u] = ml[s * 2 * R];
       l_s[u] = ml[s * 2 * R + R];
       o_s[u] = *reinterpret_cast<const mf32x4*>(po + s * po_ss);
-      if (j0 + u >= n_mine) o_s[u] = mf32x4{0.f, 0.f, 0.f, 0.f};   // a weight of 0 alone would make NaN of an infinity
     }
     float m_new = r.m;
 #pragma unroll
@@ -61,7 +60,9 @@ __device__ __forceinline__ RowPiece fold_splits(const float* ml, const float* po
     for (int u = 0; u < NB; ++u) {
       const float f = (j0 + u < n_mine && m_s[u] != -INFINITY) ? __builtin_amdgcn_exp2f(m_s[u] - m_new) : 0.f;
       r.l += f * l_s[u];
-      r.o += f * o_s[u];
+      // not f * o alone: with an infinity in o the weight of 0 would make it NaN
+#pragma unroll
+      for (int c = 0; c < 4; ++c) r.o[c] = j0 + u < n_mine ? __builtin_fmaf(f, o_s[u][c], r.o[c]) : r.o[c];
     }
     r.m = m_new;
   };
