@@ -39,7 +39,7 @@ size_t attn_mfma_lds_bytes(int waves) { return (size_t)waves * kWaveLds; }
 // with plain loads by the statistics launches: the scoring that follows (the column sweep at the end of
 // this kernel, or the scoring kernel) reads the same rows again and finds part of them in L2 and the
 // memory-side cache (B=8 LLaDA shape, cache-update step: 234 -> 226 us).
-template <int NSEG, bool STATS, bool DEEP, bool SHARED_KV>
+template <int NSEG, bool STATS, bool DEEP, bool SHARED_KV, bool BY_SPLIT>
 __global__ __launch_bounds__(512) void attn_mfma_bf16_kernel(const AttnParams p) {
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
   const int lane = threadIdx.x & 63;
@@ -48,16 +48,17 @@ __global__ __launch_bounds__(512) void attn_mfma_bf16_kernel(const AttnParams p)
   const int half = lane >> 5;
   const int col = lane & 31;
 
-  // Consecutive workgroup ids go round-robin over the 8 XCDs; renumber so that the workgroups of
-  // one KV group and key split (its query heads: they read the same keys) sit on one XCD and share that XCD's L2.
+  // Consecutive workgroup ids go round-robin over the 8 XCDs; renumber so that neighbours sit on one XCD and share its L2:
+  // the query heads of one KV group and key split, which read the same keys, or (BY_SPLIT) the splits of one head.
   const int wg = xcd_contiguous_id(blockIdx.x, gridDim.x);
-  const int group = SHARED_KV ? p.group : 1;
+  const int group = SHARED_KV && !BY_SPLIT ? p.group : 1;
   const int pair = wg / group;
   const int split = pair % p.n_split;
   const int bg = pair / p.n_split;
-  const int b = bg / p.hkv;
-  const int g = bg - b * p.hkv;
-  const int h = g * group + wg - pair * group;
+  const int b = bg / (BY_SPLIT ? p.hq : p.hkv);
+  const int g_or_h = bg - b * (BY_SPLIT ? p.hq : p.hkv);
+  const int h = BY_SPLIT ? g_or_h : g_or_h * group + wg - pair * group;
+  const int g = BY_SPLIT ? h / p.group : g_or_h;
   const int head = b * p.hq + h;
 
   const SegPtrs sp = seg_ptrs(p, b, g, NSEG == 2);
@@ -323,14 +324,14 @@ __global__ __launch_bounds__(512) void attn_mfma_bf16_kernel(const AttnParams p)
   }
 }
 
-template <int NSEG, bool STATS, bool DEEP, bool SHARED_KV>
+template <int NSEG, bool STATS, bool DEEP, bool SHARED_KV, bool BY_SPLIT = false>
 static hipError_t launch_variant(const AttnParams& p, hipStream_t s) {
   const int nwg = p.batch * p.hq * p.n_split;
   static LdsOptIn lds;
-  const hipError_t e = lds.ensure(reinterpret_cast<const void*>(attn_mfma_bf16_kernel<NSEG, STATS, DEEP, SHARED_KV>),
+  const hipError_t e = lds.ensure(reinterpret_cast<const void*>(attn_mfma_bf16_kernel<NSEG, STATS, DEEP, SHARED_KV, BY_SPLIT>),
                                   (int)attn_mfma_lds_bytes(kMaxWavesPerWg));
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((attn_mfma_bf16_kernel<NSEG, STATS, DEEP, SHARED_KV>), dim3(nwg), dim3(p.waves * kWave),
+  hipLaunchKernelGGL((attn_mfma_bf16_kernel<NSEG, STATS, DEEP, SHARED_KV, BY_SPLIT>), dim3(nwg), dim3(p.waves * kWave),
                      attn_mfma_lds_bytes(p.waves), s, p);
   return hipGetLastError();
 }
@@ -339,6 +340,13 @@ template <int NSEG, bool STATS>
 static hipError_t launch_nseg(const AttnParams& p, hipStream_t s) {
   // at most half the CUs busy: latency-bound, take the deep prefetch
   const bool deep = p.batch * p.hq * p.n_split <= kNumCUs / 2;
+  // Splits of a head side by side: key splits of 24 tiles or more on more than half the chip, over one segment up to 40 (28
+  // heads, sparse, 300 tiles 19.6 -> 19.0 us; 56 x 260 26.6 -> 25.7; 32 heads, dense rows, 242 tiles 17.5 -> 17.0).  Shorter ones
+  // gain 0 to 8 % from heads side by side (16 heads x 34 tiles 10.1 -> 9.4 us), fewer workgroups 1 to 4 % (16 x 1000 tiles 38.1
+  // -> 36.5), longer dense rows 1 to 4 % (28 x 700 tiles 31.2 -> 30.2).
+  if constexpr (!STATS)
+    if (p.group > 1 && !deep && p.n_split > 1 && p.tiles_per_split >= 24 && (NSEG == 2 || p.tiles_per_split < 40))
+      return launch_variant<NSEG, false, false, true, true>(p, s);
   if (p.group > 1) return deep ? launch_variant<NSEG, STATS, true, true>(p, s) : launch_variant<NSEG, STATS, false, true>(p, s);
   return deep ? launch_variant<NSEG, STATS, true, false>(p, s) : launch_variant<NSEG, STATS, false, false>(p, s);
 }
