@@ -1,12 +1,15 @@
 /*
- * sdllm_bench.h - measurement aids exported by libsdllm.so next to the product API of sdllm.h.
- * Nothing here is part of the method; benchmarks use it to find what the memory system delivers.
+ * sdllm_bench.h - measurement and test aids exported by libsdllm.so next to the product API of sdllm.h.
+ * Nothing here is part of the method; benchmarks use it to find what the memory system delivers, tests to see
+ * which kernel a call runs.
  */
 #ifndef SDLLM_BENCH_H
 #define SDLLM_BENCH_H
 
 #include <stddef.h>
 #include <stdint.h>
+
+#include "sdllm.h"
 
 #ifdef __cplusplus
 extern "C" {
@@ -21,6 +24,30 @@ extern "C" {
  * Returns SDLLM_OK (0), SDLLM_ERR_INVALID_ARG (-1) or SDLLM_ERR_HIP (-4) as in sdllm.h.
  */
 int32_t sdllm_stream_read_probe(const void* src, size_t bytes, void* sink, void* stream);
+
+/* Attention calls, by what is attended */
+#define SDLLM_CALL_SPARSE 0 /* sdllm_sparse_attn with n_cached keys, or sdllm_block_step, state 2 */
+#define SDLLM_CALL_FULL 1   /* sdllm_block_step, state 0 */
+#define SDLLM_CALL_UPDATE 2 /* sdllm_block_step, state 1: its dense rows */
+#define SDLLM_CALL_DENSE 3  /* sdllm_dense_attn */
+
+#define SDLLM_KERNEL_GENERAL 0     /* any type, head_dim and row count */
+#define SDLLM_KERNEL_PER_HEAD 1    /* bf16, head_dim 128, 32 rows: one workgroup per query head and key split */
+#define SDLLM_KERNEL_SHARED_TILE 2 /* the same rows, K/V tiles shared by the query heads of a KV head */
+#define SDLLM_KERNEL_STREAM 3      /* as PER_HEAD, tiles fetched straight into LDS */
+#define SDLLM_KERNEL_DENSE 4       /* bf16, head_dim 128, all rows of a sequence */
+
+typedef struct sdllm_launch_plan {
+  int32_t kernel;        /* SDLLM_KERNEL_* */
+  int32_t key_splits;    /* workgroups that share a head's keys; merged by a second launch if more than one */
+  int32_t waves;         /* per workgroup (SHARED_TILE: query heads per KV head) */
+  int32_t touches_ahead; /* STREAM: 1 if the heads of a group bring tiles into L2 for each other */
+  int32_t key_groups;    /* DENSE: groups of waves that share a row block's keys */
+} sdllm_launch_plan_t;
+
+/* How an attention call of this shape is launched (n_cached: SDLLM_CALL_SPARSE only), given all the workspace it asks
+ * for.  Host only; the pointers are host pointers. */
+int32_t sdllm_launch_plan(const sdllm_shape_t* shape, int32_t call, int32_t n_cached, sdllm_launch_plan_t* plan);
 
 #ifdef __cplusplus
 }

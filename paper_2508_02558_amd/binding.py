@@ -29,7 +29,12 @@ SDLLM_OP_SCORE_SELECT, SDLLM_OP_COMPACT_KV, SDLLM_OP_SPARSE_ATTN, SDLLM_OP_BLOCK
 
 EXPORTED = ("sdllm_error_string", "sdllm_version", "sdllm_retained_count", "sdllm_workspace_bytes",
             "sdllm_cache_state", "sdllm_score_select", "sdllm_compact_kv", "sdllm_sparse_attn",
-            "sdllm_sparse_attn_noalloc", "sdllm_block_step", "sdllm_dense_attn", "sdllm_stream_read_probe")
+            "sdllm_sparse_attn_noalloc", "sdllm_block_step", "sdllm_dense_attn", "sdllm_stream_read_probe",
+            "sdllm_launch_plan")
+
+# constants of include/sdllm_bench.h
+SDLLM_CALL_SPARSE, SDLLM_CALL_FULL, SDLLM_CALL_UPDATE, SDLLM_CALL_DENSE = 0, 1, 2, 3
+SDLLM_KERNEL_GENERAL, SDLLM_KERNEL_PER_HEAD, SDLLM_KERNEL_SHARED_TILE, SDLLM_KERNEL_STREAM, SDLLM_KERNEL_DENSE = 0, 1, 2, 3, 4
 
 
 class sdllm_shape_t(ctypes.Structure):
@@ -43,6 +48,11 @@ class sdllm_shape_t(ctypes.Structure):
         ("q_stride", ctypes.c_int64 * 3), ("kv_stride", ctypes.c_int64 * 3), ("blk_stride", ctypes.c_int64 * 3),
         ("cache_stride", ctypes.c_int64 * 3), ("out_stride", ctypes.c_int64 * 3),
     ]
+
+
+class sdllm_launch_plan_t(ctypes.Structure):
+    _fields_ = [("kernel", ctypes.c_int32), ("key_splits", ctypes.c_int32), ("waves", ctypes.c_int32),
+                ("touches_ahead", ctypes.c_int32), ("key_groups", ctypes.c_int32)]
 
 
 class SdllmError(RuntimeError):
@@ -90,6 +100,8 @@ def load() -> ctypes.CDLL:
     lib.sdllm_dense_attn.argtypes = [shp, vp, ctypes.POINTER(ctypes.c_int64), vp, vp, vp, ctypes.POINTER(ctypes.c_int64), vp]
     lib.sdllm_stream_read_probe.restype = i32
     lib.sdllm_stream_read_probe.argtypes = [vp, sz, vp, vp]
+    lib.sdllm_launch_plan.restype = i32
+    lib.sdllm_launch_plan.argtypes = [shp, i32, i32, ctypes.POINTER(sdllm_launch_plan_t)]
     _lib = lib
     return lib
 
@@ -233,3 +245,9 @@ def sdllm_dense_attn(shape, q_full, k_full, v_full, out_full, stream=None) -> No
 def sdllm_stream_read_probe(src, sink=None, stream=None) -> None:
     _check(load().sdllm_stream_read_probe(_ptr(src), src.numel() * src.element_size(), _ptr(sink), _stream(stream)),
            "sdllm_stream_read_probe")
+
+
+def sdllm_launch_plan(shape: sdllm_shape_t, call: int, n_cached: int = 0) -> sdllm_launch_plan_t:
+    plan = sdllm_launch_plan_t()
+    _check(load().sdllm_launch_plan(ctypes.byref(shape), call, n_cached, ctypes.byref(plan)), "sdllm_launch_plan")
+    return plan

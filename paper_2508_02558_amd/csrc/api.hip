@@ -101,6 +101,11 @@ bool seg_fits_u32(int64_t row_stride, int32_t n, int esize) {
   return n <= 0 || ((int64_t)(n - 1) * row_stride + 128) * esize < (int64_t)1 << 31;
 }
 
+// Whether sdllm_dense_attn runs the bf16 kernel for whole sequences; otherwise the general one.
+bool dense_full_takes(const sdllm_shape_t& s) {
+  return s.dtype == SDLLM_BF16 && s.head_dim == 128 && seg_fits_u32(s.kv_stride[2], s.seq_len, 2);
+}
+
 int row_blocks(const sdllm_shape_t& s, int32_t rows) { return (rows + block_rows(s.dtype) - 1) / block_rows(s.dtype); }
 
 // The general kernel: one workgroup per (head, block of query rows) and key split.
@@ -758,7 +763,7 @@ int32_t sdllm_dense_attn(const sdllm_shape_t* shape, const void* q_full, const i
     return SDLLM_ERR_INVALID_ARG;
   const float scale_log2 = scale_of(s) * kLog2e;
   hipError_t e;
-  if (s.dtype == SDLLM_BF16 && s.head_dim == 128 && seg_fits_u32(s.kv_stride[2], s.seq_len, 2)) {
+  if (dense_full_takes(s)) {
     DenseFullParams p{};
     p.q = q_full; p.k = k_full; p.v = v_full; p.out = out_full;
     p.q_sb = q_full_stride[0]; p.q_sh = q_full_stride[1]; p.q_sr = q_full_stride[2];
@@ -784,6 +789,30 @@ int32_t sdllm_dense_attn(const sdllm_shape_t* shape, const void* q_full, const i
     e = launch_attn_general(p, s.dtype, false, (hipStream_t)stream);
   }
   return e == hipSuccess ? SDLLM_OK : SDLLM_ERR_HIP;
+}
+
+int32_t sdllm_launch_plan(const sdllm_shape_t* shape, int32_t call, int32_t n_cached, sdllm_launch_plan_t* plan) {
+  const int32_t st = check_shape(shape);
+  if (st != SDLLM_OK) return st;
+  const sdllm_shape_t& s = *shape;
+  if (!plan || call < SDLLM_CALL_SPARSE || call > SDLLM_CALL_DENSE || n_cached < 0) return SDLLM_ERR_INVALID_ARG;
+  *plan = sdllm_launch_plan_t{};
+  if (call == SDLLM_CALL_DENSE && dense_full_takes(s)) {
+    plan->kernel = SDLLM_KERNEL_DENSE;
+    plan->key_splits = 1;
+    plan->waves = kMaxWavesPerWg;
+    plan->key_groups = dense_full_key_groups(s.batch * s.n_q_heads, s.seq_len);
+    return SDLLM_OK;
+  }
+  AttnPlan pl{};
+  if (call == SDLLM_CALL_SPARSE) pl = plan_attn(s, n_cached, s.cache_stride[2], s.block_len, s.blk_stride[2]);
+  else if (call == SDLLM_CALL_DENSE) plan_general(pl, s, s.seq_len, (s.seq_len + kTileKeys - 1) / kTileKeys, false);
+  else pl = plan_attn(s, s.seq_len, s.kv_stride[2], 0, 0, call == SDLLM_CALL_UPDATE && true);
+  plan->kernel = !pl.mfma ? SDLLM_KERNEL_GENERAL : pl.gqa ? SDLLM_KERNEL_SHARED_TILE : pl.stream ? SDLLM_KERNEL_STREAM : SDLLM_KERNEL_PER_HEAD;
+  plan->key_splits = pl.n_split;
+  plan->waves = pl.waves;
+  plan->touches_ahead = pl.stream && stream_touches_ahead(s.n_q_heads / s.n_kv_heads, pl.tiles_per_split, pl.waves);
+  return SDLLM_OK;
 }
 
 int32_t sdllm_stream_read_probe(const void* src, size_t bytes, void* sink, void* stream) {

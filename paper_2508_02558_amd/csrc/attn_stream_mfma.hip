@@ -380,11 +380,9 @@ static hipError_t launch_touch(const AttnParams& p, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Touching ahead pays from about a dozen tiles per wave on (8 x 28/4 heads: 144 tiles above, 74 tiles 19.8 -> 20.8 us) and
-// for groups that share the requests out thinly (6 x 32/8 heads x 243 tiles, every fourth tile each: 70.1 -> 71.6 us).
 template <int NSEG, bool STATS>
 static hipError_t launch_variant(const AttnParams& p, hipStream_t s) {
-  return p.group >= 7 && p.tiles_per_split >= 12 * p.waves ? launch_touch<NSEG, STATS, true>(p, s) : launch_touch<NSEG, STATS, false>(p, s);
+  return stream_touches_ahead(p.group, p.tiles_per_split, p.waves) ? launch_touch<NSEG, STATS, true>(p, s) : launch_touch<NSEG, STATS, false>(p, s);
 }
 
 hipError_t launch_attn_stream_mfma_bf16(const AttnParams& p, hipStream_t s) {

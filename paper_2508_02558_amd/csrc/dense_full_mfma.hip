@@ -294,12 +294,12 @@ static hipError_t launch_full(const DenseFullParams& p, hipStream_t s) {
 // positions), times the rounds in which the CUs, one workgroup each, go through the grid.  28 heads: 200 positions
 // 12.2 -> 8.5 us (4 groups), 400 18.1 -> 11.0 (4), 735 26.1 -> 19.2 (2); 24 heads x 1277 39.6 -> 28.6 (2); 8 heads x 1277
 // 38.8 -> 18.9 (4).  28 heads x 1277 stay whole: 280 half workgroups need a second round (53.8 against 39.8 us).
-static int full_key_groups(const DenseFullParams& p) {
-  const int tiles = (p.seq_len + kTileKeys - 1) / kTileKeys;
+int dense_full_key_groups(int heads, int seq_len) {
+  const int tiles = (seq_len + kTileKeys - 1) / kTileKeys;
   int best = 1;
   double least = 0;
   for (int ks = 1; ks <= 4; ks *= 2) {
-    const int64_t wgs = (int64_t)((p.seq_len + full_rows_per_wg(ks) - 1) / full_rows_per_wg(ks)) * p.batch * p.hq;
+    const int64_t wgs = (int64_t)((seq_len + full_rows_per_wg(ks) - 1) / full_rows_per_wg(ks)) * heads;
     const int64_t rounds = (wgs + kNumCUs - 1) / kNumCUs;
     const int mine = (tiles + ks - 1) / ks;
     const double us = (double)rounds * (ks == 1 ? 4.3 + 0.9 * mine : ks == 2 ? 6.2 + 1.08 * mine : 5.8 + 1.3 * mine);
@@ -309,7 +309,7 @@ static int full_key_groups(const DenseFullParams& p) {
 }
 
 hipError_t launch_dense_full_mfma_bf16(const DenseFullParams& p, hipStream_t s) {
-  switch (full_key_groups(p)) {
+  switch (dense_full_key_groups(p.batch * p.hq, p.seq_len)) {
     case 2: return launch_full<2>(p, s);
     case 4: return launch_full<4>(p, s);
     default: return launch_full<1>(p, s);

@@ -167,6 +167,10 @@ struct DenseFullParams {
 hipError_t launch_attn_mfma_bf16(const AttnParams& p, hipStream_t s);
 hipError_t launch_attn_gqa_mfma_bf16(const AttnParams& p, hipStream_t s);
 hipError_t launch_attn_stream_mfma_bf16(const AttnParams& p, hipStream_t s);
+// Touching tiles ahead (attn_stream_mfma.hip) pays from about a dozen tiles per wave on (8 x 28/4 heads: 144 tiles 36.0 -> 34.3 us,
+// 74 tiles 19.8 -> 20.8) and for groups that share the requests out thinly (6 x 32/8 heads x 243 tiles, every fourth tile
+// each: 70.1 -> 71.6 us).
+inline bool stream_touches_ahead(int group, int tiles_per_split, int waves) { return group >= 7 && tiles_per_split >= 12 * waves; }
 bool attn_gqa_supports_group(int group);
 int attn_gqa_waves_per_wg(int group);
 // any type, head_dim and row count; stats_only: nothing but cand_ml
@@ -182,6 +186,7 @@ hipError_t launch_compact(const CompactParams& p, hipStream_t s);
 // the gather plus the split-KV merge of a bf16 attention launch whose partials are still in the workspace
 hipError_t launch_compact_combine(const CompactParams& p, const AttnParams& a, hipStream_t s);
 hipError_t launch_dense_full_mfma_bf16(const DenseFullParams& p, hipStream_t s);
+int dense_full_key_groups(int heads, int seq_len);   // key groups its workgroups are divided into
 hipError_t launch_stream_read(const void* src, size_t bytes, uint32_t* sink, hipStream_t s);
 
 }  // namespace sdllm
