@@ -151,8 +151,9 @@ void plan_general(AttnPlan& pl, const sdllm_shape_t& s, int32_t nq, int tiles, b
   }
 }
 
-// stats: the launch also leaves the scoring's row statistics (which kernel runs may depend on it, the splits do not).
-AttnPlan plan_attn(const sdllm_shape_t& s, int32_t n0, int64_t sr0, int32_t n1, int64_t sr1, bool stats = false) {
+// update: the dense rows of a cache-update step, where the merge of key splits costs no launch of its own (it runs in the
+// compaction's) and the kernel mostly leaves the scoring's row statistics as well.
+AttnPlan plan_attn(const sdllm_shape_t& s, int32_t n0, int64_t sr0, int32_t n1, int64_t sr1, bool update = false) {
   AttnPlan pl{};
   pl.mfma = s.dtype == SDLLM_BF16 && s.head_dim == 128 && s.block_len == 32 && seg_fits_u32(sr0, n0, 2) &&
             seg_fits_u32(sr1, n1, 2);
@@ -233,7 +234,10 @@ AttnPlan plan_attn(const sdllm_shape_t& s, int32_t n0, int64_t sr0, int32_t n1, 
     // * fewer grouped-query heads instead of key splits, up to the tile count at which two or more workgroups per head
     //   repay the combine launch: 8 heads 21 tiles 9.6 -> 9.1 us, 28 tiles 9.6 against 10.2; 28 heads 21 tiles 10.6 -> 9.3 us, 28 tiles
     //   10.7 against 10.4, 36 tiles 10.9 against 12.0 us; 56 heads 28 tiles 12.9 -> 10.5 us, 45 tiles 12.4 against 13.4;
-    //   72 heads (three splits) 37 tiles 11.8 against 12.6; 112 heads 45 tiles 14.6 -> 13.9 us, 60 tiles 15.9 against 16.0;
+    //   72 heads (three splits) 37 tiles 11.8 against 12.6; 112 heads 45 tiles 14.6 -> 13.9 us, 60 tiles 15.9 against 16.0.
+    //   Where the merge rides on another launch there is nothing to save (cache-update step, 28 heads x 26 tiles 25.8 us split
+    //   against 27.8; 12 heads, raw-logit scores 20.2 against 24.1), except for the split itself with more than 85 heads
+    //   (128 heads x 22 tiles 29.7 -> 28.7, 112 x 30 30.4 against 31.3);
     // * split grouped-query heads at the cache-update step, where the other kernel masks every tile for the scoring's
     //   statistics, if its waves get three tiles or more (28 heads x 1040 tiles, whole step 88.4 -> 85.8 us); without
     //   statistics that one is as fast or faster (28 heads x 652 tiles 25.1 against 26.9 us);
@@ -243,7 +247,9 @@ AttnPlan plan_attn(const sdllm_shape_t& s, int32_t n0, int64_t sr0, int32_t n1, 
     //   11.7 us unsplit (replayed as a graph 10.7 against 11.8; 10.7 against 9.6 if the cache holds them); the
     //   non-temporal streams of attn_mfma.hip also keep the dense rows of calls that they leave unsplit (they then
     //   sweep the scores as well).
-    const bool unsplit_pays = heads <= 8     ? tiles <= 22
+    const bool stats = update && s.score_mode == SDLLM_SOFTMAX_MEAN;
+    const bool unsplit_pays = update && n_split > 1 ? heads > 85 && tiles <= 26
+                              : heads <= 8   ? tiles <= 22
                               : heads <= 32  ? tiles <= 26
                               : heads <= 85  ? tiles <= 33
                               : heads <= 128 ? tiles <= 48
@@ -301,9 +307,9 @@ bool fuses_columns(const AttnPlan& pl, const sdllm_shape_t& s) {
 // (it gets the launch parameters in *deferred and must run launch_compact_combine or launch_attn_combine on
 // the same stream before the partials' workspace is reused); deferred->n_split == 1 says nothing is left.
 int32_t run_attn(const sdllm_shape_t& s, const void* q, const KvSegment& a, const KvSegment& b, void* out, void* ws,
-                 size_t ws_bytes, hipStream_t stream, float* cand_ml = nullptr, int cand0_end = 0, int cand1_begin = 0,
-                 AttnParams* deferred = nullptr, float* score_out = nullptr, int score_stride = 0) {
-  AttnPlan pl = plan_attn(s, a.n, a.sr, b.n, b.sr, cand_ml != nullptr);
+                 size_t ws_bytes, hipStream_t stream, bool update = false, float* cand_ml = nullptr, int cand0_end = 0,
+                 int cand1_begin = 0, AttnParams* deferred = nullptr, float* score_out = nullptr, int score_stride = 0) {
+  AttnPlan pl = plan_attn(s, a.n, a.sr, b.n, b.sr, update);
   if (pl.ws_bytes() > 0 && (!ws || ws_bytes < pl.ws_bytes())) {
     if (pl.mfma) return SDLLM_ERR_WORKSPACE;
     // the general kernel works without a workspace too: one workgroup per 32 rows walks all keys
@@ -531,12 +537,14 @@ struct BlockStepWs { size_t base, stats_bytes, score_off; int stats_parts; bool 
 
 BlockStepWs plan_block_step(const sdllm_shape_t& s) {
   const Counts c = counts_of(s);
-  const AttnPlan dense = plan_attn(s, s.seq_len, s.kv_stride[2], 0, 0);
+  const AttnPlan full = plan_attn(s, s.seq_len, s.kv_stride[2], 0, 0);
+  const AttnPlan dense = plan_attn(s, s.seq_len, s.kv_stride[2], 0, 0, c.k_total > 0);   // of a cache-update step
   const AttnPlan sparse = plan_attn(s, c.k_total, s.cache_stride[2], s.block_len, s.blk_stride[2]);
   const ScorePlan sc = plan_score(s);
   BlockStepWs w{};
   w.score_off = dense.mfma && dense.n_split > 1 && c.k_total > 0 ? align_up(dense.ws_bytes()) : 0;
   w.base = dense.ws_bytes();
+  if (full.ws_bytes() > w.base) w.base = full.ws_bytes();
   if (sparse.ws_bytes() > w.base) w.base = sparse.ws_bytes();
   if (w.score_off + sc.ws_bytes() > w.base) w.base = w.score_off + sc.ws_bytes();
   w.base = align_up(w.base);
@@ -723,13 +731,14 @@ int32_t sdllm_block_step(const sdllm_shape_t* shape, int32_t step_in_block, int3
   const BlockStepWs w = plan_block_step(s);
   AttnParams pending{};           // split-KV merge still to run (cache-update step only)
   pending.n_split = 1;
-  AttnParams* defer = state == SDLLM_STATE_UPDATE && w.score_off > 0 ? &pending : nullptr;
+  const bool update = state == SDLLM_STATE_UPDATE && c.k_total > 0;
+  AttnParams* defer = update && w.score_off > 0 ? &pending : nullptr;
   if (state == SDLLM_STATE_FULL || !w.fuse)
-    st = run_attn(s, q_blk, a, b, out, ws, ws_bytes, (hipStream_t)stream, nullptr, 0, 0, defer);
+    st = run_attn(s, q_blk, a, b, out, ws, ws_bytes, (hipStream_t)stream, update, nullptr, 0, 0, defer);
   else {
     // cache-update step: the dense attention also leaves the scoring softmax's row statistics
     // ... and, where one workgroup owns a head, the saliency scores themselves (first buffer of the scoring workspace)
-    st = run_attn(s, q_blk, a, b, out, ws, w.base, (hipStream_t)stream, (float*)((char*)ws + w.base), s.block_off, candidates_resume(s),
+    st = run_attn(s, q_blk, a, b, out, ws, w.base, (hipStream_t)stream, update, (float*)((char*)ws + w.base), s.block_off, candidates_resume(s),
                   defer, w.fuse_cols ? (float*)((char*)ws + w.score_off) : nullptr, c.n_cand);
   }
   if (st != SDLLM_OK || state == SDLLM_STATE_FULL) return st;
@@ -807,7 +816,7 @@ int32_t sdllm_launch_plan(const sdllm_shape_t* shape, int32_t call, int32_t n_ca
   AttnPlan pl{};
   if (call == SDLLM_CALL_SPARSE) pl = plan_attn(s, n_cached, s.cache_stride[2], s.block_len, s.blk_stride[2]);
   else if (call == SDLLM_CALL_DENSE) plan_general(pl, s, s.seq_len, (s.seq_len + kTileKeys - 1) / kTileKeys, false);
-  else pl = plan_attn(s, s.seq_len, s.kv_stride[2], 0, 0, call == SDLLM_CALL_UPDATE && true);
+  else pl = plan_attn(s, s.seq_len, s.kv_stride[2], 0, 0, call == SDLLM_CALL_UPDATE && counts_of(s).k_total > 0);
   plan->kernel = !pl.mfma ? SDLLM_KERNEL_GENERAL : pl.gqa ? SDLLM_KERNEL_SHARED_TILE : pl.stream ? SDLLM_KERNEL_STREAM : SDLLM_KERNEL_PER_HEAD;
   plan->key_splits = pl.n_split;
   plan->waves = pl.waves;

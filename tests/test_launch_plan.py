@@ -43,3 +43,20 @@ def test_a_call_or_plan_that_is_not_there_is_rejected():
         with pytest.raises(B.SdllmError):
             B.sdllm_launch_plan(B.make_shape(batch=1, n_q_heads=1, n_kv_heads=1, head_dim=128, seq_len=64, block_off=0, block_len=32,
                                              dtype=B.SDLLM_BF16), call, n_cached)
+
+
+@pytest.mark.parametrize("batch,q_heads,kv_heads,tiles,full,update", [
+    (1, 28, 4, 13, (STREAM, 1), (STREAM, 1)),
+    (1, 28, 4, 20, (STREAM, 1), (PER_HEAD, 2)),
+    (1, 12, 4, 22, (STREAM, 1), (PER_HEAD, 3)),
+    (2, 28, 4, 30, (STREAM, 1), (PER_HEAD, 2)),
+    (4, 28, 4, 38, (STREAM, 1), (PER_HEAD, 2)),
+    (8, 16, 2, 24, (STREAM, 1), (STREAM, 1)),
+    (1, 8, 8, 16, (STREAM, 1), (PER_HEAD, 2)),
+])
+def test_key_splits_of_an_update_step_whose_merge_costs_nothing(batch, q_heads, kv_heads, tiles, full, update):
+    assert route(FULL, batch, q_heads, kv_heads, tiles) == full
+    for mode in (B.SDLLM_SOFTMAX_MEAN, B.SDLLM_LOGIT_MEAN):
+        assert route(UPDATE, batch, q_heads, kv_heads, tiles, block_off=64, score_mode=mode) == update
+    # nothing to compact: the merge is a launch of its own
+    assert route(UPDATE, batch, q_heads, kv_heads, tiles, block_off=64, retention=0.0) == full
