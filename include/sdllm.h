@@ -172,7 +172,10 @@ int32_t sdllm_sparse_attn(const sdllm_shape_t* shape, const void* q_blk, const v
  * that is part of the library's device image (every GPU the library runs on holds one copy until the
  * process ends).  The call allocates nothing and frees nothing.  A shape whose launch plan needs
  * more scratch than that returns SDLLM_ERR_STATIC_LIMIT and enqueues nothing (use sdllm_sparse_attn
- * with a workspace then).  All calls on one GPU share that GPU's array: calls that overlap in time
+ * with a workspace then).  With 7 or 8 query heads per KV head and up to 80 MB of keys and values, a kernel
+ * whose partials do not fit gives way to a slower one that does without (the same happens in
+ * sdllm_sparse_attn when the workspace is too small); its results differ by rounding.  All calls on one GPU
+ * share that GPU's array: calls that overlap in time
  * on one GPU (different streams, or concurrently replayed graphs) race and are not allowed.  The
  * first call on each device resolves the array's address and must not be made under stream capture.
  */

@@ -151,9 +151,61 @@ void plan_general(AttnPlan& pl, const sdllm_shape_t& s, int32_t nq, int tiles, b
   }
 }
 
+// Key splits of the shared-tile kernel: as many as keep the grid within what the CUs hold at once (a few workgroups more
+// would wait for a whole round), but never fewer than 4 tiles (two LDS stages) each.  Four-wave workgroups: two per CU.
+// Two-wave workgroups: four fit, three per CU measured best (G = 4, 768 heads: 79.6 -> 63.9 us with 2 splits; G = 2, 1024
+// heads: 90 us with 1 split, 108 with 2).
+int shared_splits(int rows, int group, int tiles) {
+  const int wg_waves = attn_gqa_waves_per_wg(group);
+  int n = (wg_waves >= 4 ? 2 : 3) * kNumCUs / (rows * ((group + wg_waves - 1) / wg_waves));   // workgroups per KV head and split
+  if (n > tiles / 4) n = tiles / 4;
+  return n < 1 ? 1 : n;
+}
+
+// Whether the shared-tile kernel (K/V read once per group, one wave per head, key splits merged through fp32 partials and a
+// second launch) beats one workgroup per query head and key split (n_split of them, as without it).
+//
+// Two waves per workgroup (G = 2, 4), measured for sparse and dense steps: 256 heads lose (G = 4: 28/51 us per head
+// against 34/50 us shared), 384 heads win (G = 4: 46/82 against 42/68 us; G = 2: 54/97 against 50/80 us), 512 heads tie,
+// 640 win.
+//
+// Four waves (G = 7, 8; sparse steps and dense rows alike, keys from HBM).  It starts 12 us behind (splits, partials, merge)
+// and then takes less per tile, the less of the chip the other kernels fill the more:
+// * up to one workgroup of theirs per CU, from 60 tiles each plus 0.4 per workgroup on: 140 heads from 118 tiles (130: 31.4
+//   against 34.9 us), 168 from 125, 192 from 136 (150: 37.1 against 38.6), 224 from 155, 256 from 165 (150: 43.2 against
+//   41.7, 200: 51.9 against 53.4); with key splits, tiles of one split: 96 heads x 2 from 140, 84 x 3 from 160 (600 tiles in all
+//   57.2 against 58.7), 64 x 4 from 165, 16 x 8 from 112;
+// * up to two per CU (four waves each): 272 heads from 68 tiles (84: 34.7 against 38.5), 320 from 62, 392 from 70, 448 from
+//   76, 512 from 84;
+// * up to four per CU (two waves each): from 40 tiles if its own waves take more than three quarters of the chip's 2048
+//   (532 heads x 3 splits: 46 tiles 37.0 against 38.9 us; 640 x 3: 42 tiles 36.3 against 38.3; 896 x 2: 46 tiles 47.4 against
+//   49.5), else from 50 (616 x 2: 42 tiles 40.2 against 37.9, 52 tiles 44.1 against 44.4; 768 x 2: 42 tiles 41.9 against
+//   39.8).  At a cache-update step, where the merge is free and the others mask every tile for the statistics, from 30
+//   (whole step, 544 heads x 42 tiles 63.7 against 66.6 us, 896 x 30 70.6 against 72.6) and 46 (616 heads: 42 tiles 72.9
+//   against 72.3, 46 tiles 76.3 against 76.5);
+// * beyond that the others need another round and lose from the first tiles on (1036 heads: 4 tiles 16.8 against 13.1 us,
+//   28 tiles 47.8 against 37.9; 1984: 12 tiles 38.1 against 27.8).
+// Below the sizes of the last line its partials, up to 34 MB, would make sdllm_sparse_attn_noalloc refuse calls.
+bool shared_tile_pays(int heads, int rows, int tiles, int n_split, bool update) {
+  const int group = heads / rows;
+  const int64_t wave_tiles = (int64_t)heads * tiles;
+  if (!attn_gqa_supports_group(group)) return false;
+  if (attn_gqa_waves_per_wg(group) < 4) return heads >= 320 && wave_tiles >= 26000;
+  const int own = shared_splits(rows, group, tiles);
+  bool pays;
+  if (heads <= kNumCUs) pays = 5 * (int64_t)tiles >= (int64_t)n_split * (300 + 2 * heads * n_split);
+  else if (heads <= 2 * kNumCUs) pays = tiles >= 66 && 6 * tiles >= heads;
+  else if (heads <= 4 * kNumCUs) pays = tiles >= (heads * own > 6 * kNumCUs ? (update ? 30 : 40) : (update ? 46 : 50));
+  else pays = true;
+  return pays && (own == 1 || wave_tiles >= 30000 || (tiles >= 512 && wave_tiles >= 22000) || (heads >= 128 && wave_tiles >= 18000));
+}
+
 // update: the dense rows of a cache-update step, where the merge of key splits costs no launch of its own (it runs in the
 // compaction's) and the kernel mostly leaves the scoring's row statistics as well.
-AttnPlan plan_attn(const sdllm_shape_t& s, int32_t n0, int64_t sr0, int32_t n1, int64_t sr1, bool update = false) {
+// scratch: the workspace there is.  A shared-tile kernel that does not fit gives way to the others up to 80 MB of keys and
+// values (5000 tiles; it is a matter of speed there, and sdllm_sparse_attn_noalloc has 8 MB); beyond, the call is refused.
+AttnPlan plan_attn(const sdllm_shape_t& s, int32_t n0, int64_t sr0, int32_t n1, int64_t sr1, bool update = false,
+                   size_t scratch = SIZE_MAX) {
   AttnPlan pl{};
   pl.mfma = s.dtype == SDLLM_BF16 && s.head_dim == 128 && s.block_len == 32 && seg_fits_u32(sr0, n0, 2) &&
             seg_fits_u32(sr1, n1, 2);
@@ -167,7 +219,13 @@ AttnPlan plan_attn(const sdllm_shape_t& s, int32_t n0, int64_t sr0, int32_t n1, 
   const int tiles = (n0 + kTileKeys - 1) / kTileKeys + (n1 + kTileKeys - 1) / kTileKeys;
   const int64_t wave_tiles = (int64_t)s.batch * s.n_q_heads * tiles;
   const int group = s.n_q_heads / s.n_kv_heads;
-  const int heads = s.batch * s.n_q_heads;
+  const int heads = s.batch * s.n_q_heads, rows = s.batch * s.n_kv_heads;
+  const auto partials = [&] {
+    if (pl.n_split == 1) return;
+    const size_t slots = (size_t)heads * pl.n_split;
+    pl.part_o_bytes = align_up(slots * s.block_len * s.head_dim * sizeof(float));
+    pl.part_ml_bytes = align_up(slots * 2 * s.block_len * sizeof(float));
+  };
   // Key splits of the kernels with one workgroup per head, only while the grid is small: as many as keep
   // it within one workgroup per CU (an eight-wave workgroup fills a CU's LDS, so workgroup
   // number 257 waits for a whole round: 56 heads x 4 splits 15.1 us, x 5 splits 22.3 us), at most 8
@@ -186,112 +244,74 @@ AttnPlan plan_attn(const sdllm_shape_t& s, int32_t n0, int64_t sr0, int32_t n1, 
   const int max_split = tiles / (heads <= 32 ? 7 : 11);
   if (n_split > max_split) n_split = max_split;
   if (n_split < 1) n_split = 1;
-  // Grouped-query heads with much work: the shared-tile kernel (K/V read once per group, one wave per head, key
-  // splits merged through fp32 partials and a second launch) against one workgroup per query head.
-  // Two waves per workgroup (G = 2, 4), measured for sparse and dense steps: 256 heads lose (G = 4: 28/51 us per
-  // head against 34/50 us shared), 384 heads win (G = 4: 46/82 against 42/68 us; G = 2: 54/97 against 50/80 us),
-  // 512 heads tie, 640 win.
-  // Four waves (G = 7, 8): from 5000 tiles over all KV heads on, 80 MB of keys and values (dense rows, G = 7: 32 KV heads
-  // x 144 tiles 40.1 us shared against 32.5 us per head, x 269 tiles 58.8 against 64.1; 4 x 1040 tiles 39.0 against 35.0,
-  // x 1421 45.3 against 51.9; 448 query heads: 4480 tiles 37.7 against 30.1, 8704 58.2 against 70.9; G = 8: 16 x 269
-  // tiles 41.7 against 35.6), and before that where one workgroup per head (and split) leaves CUs idle over many tiles
-  // (140 heads x 144 tiles 31.1 against 32.5 us; 16 heads in 8 splits: 455 tiles 22.6 against 20.7 us, 652 tiles 26.0
-  // against 25.1 or, from HBM, 26.6 against 28.6, 1040 tiles 30.4 against 33.3; but its partials take up to 34 MB, so
-  // not below 22 000 wave-tiles, where sdllm_sparse_attn_noalloc would have to refuse the call).
-  const int used = heads * n_split;
-  const int64_t all_tiles = (int64_t)s.batch * s.n_kv_heads * tiles;
-  pl.gqa = attn_gqa_supports_group(group) &&
-           (attn_gqa_waves_per_wg(group) < 4 ? heads >= 320 && wave_tiles >= 26000
-            : all_tiles > 5000               ? true
-            : n_split == 1                   ? heads <= kNumCUs && wave_tiles >= 18000 && (int64_t)tiles * (215 - used) > 10000
-                                             : wave_tiles >= 22000 && tiles >= 512 && (int64_t)tiles * (215 - used) > n_split * 6500);
-  if (pl.gqa) {
-    const int rows = s.batch * s.n_kv_heads;
-    // As many key splits as keep the grid within what the CUs hold at once (a few workgroups more
-    // would wait for a whole round), but never fewer than 4 tiles (two LDS stages) each.  Four-wave
-    // workgroups: two per CU.  Two-wave workgroups: four fit, three per CU measured best (G = 4,
-    // 768 heads: 79.6 -> 63.9 us with 2 splits; G = 2, 1024 heads: 90 us with 1 split, 108 with 2).
-    const int wg_waves = attn_gqa_waves_per_wg(group);
-    const int wgs_per_row = (group + wg_waves - 1) / wg_waves;   // head splits
-    const int room = (wg_waves >= 4 ? 2 : 3) * kNumCUs;
-    n_split = room / (rows * wgs_per_row);
-    if (n_split < 1) n_split = 1;
-    const int most_split = tiles / 4 > 1 ? tiles / 4 : 1;
-    if (n_split > most_split) n_split = most_split;
-    pl.tiles_per_split = (tiles + n_split - 1) / n_split;
+  if (shared_tile_pays(heads, rows, tiles, n_split, update)) {
+    const int n_shared = shared_splits(rows, group, tiles);
+    pl.gqa = true;
+    pl.tiles_per_split = (tiles + n_shared - 1) / n_shared;
     pl.n_split = (tiles + pl.tiles_per_split - 1) / pl.tiles_per_split;
-    pl.waves = s.n_q_heads / s.n_kv_heads;
-    if (pl.n_split > 1) {
-      const size_t slots = (size_t)s.batch * s.n_q_heads * pl.n_split;
-      pl.part_o_bytes = align_up(slots * s.block_len * s.head_dim * sizeof(float));
-      pl.part_ml_bytes = align_up(slots * 2 * s.block_len * sizeof(float));
-    }
-  } else {
-    // The kernel that fetches tiles straight into LDS (attn_stream_mfma.hip) takes
-    // * grouped-query heads with one workgroup per head: always with 129 to 256 heads (8 x 28/4 heads: 28 tiles
-    //   11.8 -> 11.3 us, 75 tiles 20.9 -> 19.5 us, 144 tiles 37.1 -> 29.0 us), with more where four of its
-    //   waves beat the shared-tile kernel (above);
-    // * fewer grouped-query heads instead of key splits, up to the tile count at which two or more workgroups per head
-    //   repay the combine launch: 8 heads 21 tiles 9.6 -> 9.1 us, 28 tiles 9.6 against 10.2; 28 heads 21 tiles 10.6 -> 9.3 us, 28 tiles
-    //   10.7 against 10.4, 36 tiles 10.9 against 12.0 us; 56 heads 28 tiles 12.9 -> 10.5 us, 45 tiles 12.4 against 13.4;
-    //   72 heads (three splits) 37 tiles 11.8 against 12.6; 112 heads 45 tiles 14.6 -> 13.9 us, 60 tiles 15.9 against 16.0.
-    //   Where the merge rides on another launch there is nothing to save (cache-update step, 28 heads x 26 tiles 25.8 us split
-    //   against 27.8; 12 heads, raw-logit scores 20.2 against 24.1), except for the split itself with more than 85 heads
-    //   (128 heads x 22 tiles 29.7 -> 28.7, 112 x 30 30.4 against 31.3);
-    // * split grouped-query heads at the cache-update step, where the other kernel masks every tile for the scoring's
-    //   statistics, if its waves get three tiles or more (28 heads x 1040 tiles, whole step 88.4 -> 85.8 us); without
-    //   statistics that one is as fast or faster (28 heads x 652 tiles 25.1 against 26.9 us);
-    // * multi-head calls instead of splits up to 8 MB of keys and values, thirty-two of which (layers) fit the memory-side
-    //   cache: 16 heads x 21 tiles 10.4 -> 9.3 us, 32 heads x 14 10.4 -> 8.0 us, 64 x 8 7.7 -> 6.8 us.  Beyond that a decoder's
-    //   layers evict each other and the keys come from HBM, where 32 heads x 21 tiles take 11.2 us split and
-    //   11.7 us unsplit (replayed as a graph 10.7 against 11.8; 10.7 against 9.6 if the cache holds them); the
-    //   non-temporal streams of attn_mfma.hip also keep the dense rows of calls that they leave unsplit (they then
-    //   sweep the scores as well).
-    const bool stats = update && s.score_mode == SDLLM_SOFTMAX_MEAN;
-    const bool unsplit_pays = update && n_split > 1 ? heads > 85 && tiles <= 26
-                              : heads <= 8   ? tiles <= 22
-                              : heads <= 32  ? tiles <= 26
-                              : heads <= 85  ? tiles <= 33
-                              : heads <= 128 ? tiles <= 48
-                                             : true;
-    if (group > 1)
-      pl.stream = heads > kNumCUs ? attn_gqa_supports_group(group) && attn_gqa_waves_per_wg(group) >= 4 && tiles >= 36
-                                  : unsplit_pays || (stats && tiles >= 24 * n_split);
-    else
-      pl.stream = heads <= 128 && wave_tiles <= 512 && unsplit_pays && (n1 > 0 || n_split > 1);
-    if (pl.stream && unsplit_pays) n_split = 1;
-    pl.tiles_per_split = (tiles + n_split - 1) / n_split;
-    pl.waves = pl.tiles_per_split < kMaxWavesPerWg ? pl.tiles_per_split : kMaxWavesPerWg;
-    // split workgroups: two tiles per wave when there are fewer than sixteen (28 heads x 69 tiles in 6
-    // splits: 12.6 -> 12.35 us with six waves instead of eight; the in-workgroup merge is smaller)
-    if (n_split > 1) { const int w2 = (pl.tiles_per_split + 1) / 2; pl.waves = w2 < kMaxWavesPerWg ? w2 : kMaxWavesPerWg; }
-    // One workgroup per head: fewer, longer-running waves measured faster than eight (smaller merge at
-    // the end, 40-48 KB instead of 64 KB of loads in flight per CU).  With more heads than CUs four
-    // waves let two workgroups share a CU, so one streams while the other merges and writes, and no
-    // workgroup waits for a second round (B=16 LLaDA shape: 94 -> 89 us; B=8: 47.5 -> 46.3 us with
-    // five waves; 280 grouped-query heads, G = 7: 41.4 -> 36.0 us; 320 heads, G = 4: 48.6 -> 43.6 us).
-    // With more than two heads per CU, two waves, so that four workgroups fit (544 heads, MHA:
-    // 117.9 -> 106.0 us; 640 heads: 134.5 -> 113.8 us; 768 heads of G = 3: 88.8 -> 75.0 us).
-    // Up to one head per CU the grouped-query heads keep eight waves: there they are short of
-    // arithmetic throughput, not of bandwidth (B=8 Dream shape: 22 -> 26 us with fewer).
-    if (n_split == 1) {
-      const int cap = heads > 2 * kNumCUs ? 2 : heads > kNumCUs ? 4 : (group == 1 ? 5 : kMaxWavesPerWg);
-      if (pl.waves > cap) pl.waves = cap;
-    }
-    // Fetching into LDS: few tiles are done soonest by waves that take three or four each (28 heads: 8 tiles 6.7 us with
-    // four waves and 7.8 with eight, 14 tiles 8.0 with five and 9.0, 21 tiles 9.3 with six and 10.2, 45 tiles 13.5
-    // and 13.9, 60 tiles 16.4 and 15.6).
-    if (pl.stream) {
-      const int w = heads > kNumCUs ? 4 : n_split > 1 || tiles > 50 ? kMaxWavesPerWg : tiles > 16 ? 6 : tiles > 9 ? 5 : 4;
-      pl.waves = w < pl.tiles_per_split ? w : pl.tiles_per_split;
-    }
-    pl.n_split = (tiles + pl.tiles_per_split - 1) / pl.tiles_per_split;   // no empty split
-    if (pl.n_split > 1) {
-      const size_t slots = (size_t)heads * pl.n_split;
-      pl.part_o_bytes = align_up(slots * s.block_len * s.head_dim * sizeof(float));
-      pl.part_ml_bytes = align_up(slots * 2 * s.block_len * sizeof(float));
-    }
+    pl.waves = group;
+    partials();
+    if (pl.ws_bytes() <= scratch || (int64_t)rows * tiles > 5000) return pl;
+    pl.gqa = false;
+    pl.part_o_bytes = pl.part_ml_bytes = 0;
   }
+  // The kernel that fetches tiles straight into LDS (attn_stream_mfma.hip) takes
+  // * grouped-query heads with one workgroup per head: always with 129 to 256 heads (8 x 28/4 heads: 28 tiles
+  //   11.8 -> 11.3 us, 75 tiles 20.9 -> 19.5 us, 144 tiles 37.1 -> 29.0 us), with more where four of its
+  //   waves beat the shared-tile kernel (above);
+  // * fewer grouped-query heads instead of key splits, up to the tile count at which two or more workgroups per head
+  //   repay the combine launch: 8 heads 21 tiles 9.6 -> 9.1 us, 28 tiles 9.6 against 10.2; 28 heads 21 tiles 10.6 -> 9.3 us, 28 tiles
+  //   10.7 against 10.4, 36 tiles 10.9 against 12.0 us; 56 heads 28 tiles 12.9 -> 10.5 us, 45 tiles 12.4 against 13.4;
+  //   72 heads (three splits) 37 tiles 11.8 against 12.6; 112 heads 45 tiles 14.6 -> 13.9 us, 60 tiles 15.9 against 16.0.
+  //   Where the merge rides on another launch there is nothing to save (cache-update step, 28 heads x 26 tiles 25.8 us split
+  //   against 27.8; 12 heads, raw-logit scores 20.2 against 24.1), except for the split itself with more than 85 heads
+  //   (128 heads x 22 tiles 29.7 -> 28.7, 112 x 30 30.4 against 31.3);
+  // * split grouped-query heads at the cache-update step, where the other kernel masks every tile for the scoring's
+  //   statistics, if its waves get three tiles or more (28 heads x 1040 tiles, whole step 88.4 -> 85.8 us); without
+  //   statistics the two are within 2 % of each other up to 60 tiles a split;
+  // * multi-head calls instead of splits up to 8 MB of keys and values, thirty-two of which (layers) fit the memory-side
+  //   cache: 16 heads x 21 tiles 10.4 -> 9.3 us, 32 heads x 14 10.4 -> 8.0 us, 64 x 8 7.7 -> 6.8 us.  Beyond that a decoder's
+  //   layers evict each other and the keys come from HBM, where 32 heads x 21 tiles take 11.2 us split and
+  //   11.7 us unsplit (replayed as a graph 10.7 against 11.8; 10.7 against 9.6 if the cache holds them); the
+  //   non-temporal streams of attn_mfma.hip also keep the dense rows of calls that they leave unsplit (they then
+  //   sweep the scores as well).
+  const bool unsplit_pays = n_split == 1 || (update ? heads > 85 && tiles <= 26
+                                                    : tiles <= (heads <= 8 ? 22 : heads <= 32 ? 26 : heads <= 85 ? 33 : 48));
+  const bool stats = update && s.score_mode == SDLLM_SOFTMAX_MEAN;
+  if (group > 1 && heads <= kNumCUs)
+    pl.stream = unsplit_pays || (stats && tiles >= 24 * n_split);
+  else if (group > 1)
+    pl.stream = (group == 7 || group == 8) && tiles >= 36;
+  else
+    pl.stream = heads <= 128 && wave_tiles <= 512 && unsplit_pays && (n1 > 0 || n_split > 1);
+  if (pl.stream && unsplit_pays) n_split = 1;
+  pl.tiles_per_split = (tiles + n_split - 1) / n_split;
+  pl.waves = pl.tiles_per_split < kMaxWavesPerWg ? pl.tiles_per_split : kMaxWavesPerWg;
+  // split workgroups: two tiles per wave when there are fewer than sixteen (28 heads x 69 tiles in 6
+  // splits: 12.6 -> 12.35 us with six waves instead of eight; the in-workgroup merge is smaller)
+  if (n_split > 1) { const int w2 = (pl.tiles_per_split + 1) / 2; pl.waves = w2 < kMaxWavesPerWg ? w2 : kMaxWavesPerWg; }
+  // One workgroup per head: fewer, longer-running waves measured faster than eight (smaller merge at
+  // the end, 40-48 KB instead of 64 KB of loads in flight per CU).  With more heads than CUs four
+  // waves let two workgroups share a CU, so one streams while the other merges and writes, and no
+  // workgroup waits for a second round (B=16 LLaDA shape: 94 -> 89 us; B=8: 47.5 -> 46.3 us with
+  // five waves; 280 grouped-query heads, G = 7: 41.4 -> 36.0 us; 320 heads, G = 4: 48.6 -> 43.6 us).
+  // With more than two heads per CU, two waves, so that four workgroups fit (544 heads, MHA:
+  // 117.9 -> 106.0 us; 640 heads: 134.5 -> 113.8 us; 768 heads of G = 3: 88.8 -> 75.0 us).
+  // Up to one head per CU the grouped-query heads keep eight waves: there they are short of
+  // arithmetic throughput, not of bandwidth (B=8 Dream shape: 22 -> 26 us with fewer).
+  if (n_split == 1) {
+    const int cap = heads > 2 * kNumCUs ? 2 : heads > kNumCUs ? 4 : (group == 1 ? 5 : kMaxWavesPerWg);
+    if (pl.waves > cap) pl.waves = cap;
+  }
+  // Fetching into LDS: few tiles are done soonest by waves that take three or four each (28 heads: 8 tiles 6.7 us with
+  // four waves and 7.8 with eight, 14 tiles 8.0 with five and 9.0, 21 tiles 9.3 with six and 10.2, 45 tiles 13.5
+  // and 13.9, 60 tiles 16.4 and 15.6).
+  if (pl.stream) {
+    const int w = heads > kNumCUs ? 4 : n_split > 1 || tiles > 50 ? kMaxWavesPerWg : tiles > 16 ? 6 : tiles > 9 ? 5 : 4;
+    pl.waves = w < pl.tiles_per_split ? w : pl.tiles_per_split;
+  }
+  pl.n_split = (tiles + pl.tiles_per_split - 1) / pl.tiles_per_split;   // no empty split
+  partials();
   return pl;
 }
 
@@ -309,7 +329,7 @@ bool fuses_columns(const AttnPlan& pl, const sdllm_shape_t& s) {
 int32_t run_attn(const sdllm_shape_t& s, const void* q, const KvSegment& a, const KvSegment& b, void* out, void* ws,
                  size_t ws_bytes, hipStream_t stream, bool update = false, float* cand_ml = nullptr, int cand0_end = 0,
                  int cand1_begin = 0, AttnParams* deferred = nullptr, float* score_out = nullptr, int score_stride = 0) {
-  AttnPlan pl = plan_attn(s, a.n, a.sr, b.n, b.sr, update);
+  AttnPlan pl = plan_attn(s, a.n, a.sr, b.n, b.sr, update, ws ? ws_bytes : 0);
   if (pl.ws_bytes() > 0 && (!ws || ws_bytes < pl.ws_bytes())) {
     if (pl.mfma) return SDLLM_ERR_WORKSPACE;
     // the general kernel works without a workspace too: one workgroup per 32 rows walks all keys
@@ -535,6 +555,7 @@ int32_t compact_params(const sdllm_shape_t& s, const void* k_full, const void* v
 // the attention partials stay alive through scoring and selection: those then work behind them (score_off).
 struct BlockStepWs { size_t base, stats_bytes, score_off; int stats_parts; bool fuse, fuse_cols; };
 
+
 BlockStepWs plan_block_step(const sdllm_shape_t& s) {
   const Counts c = counts_of(s);
   const AttnPlan full = plan_attn(s, s.seq_len, s.kv_stride[2], 0, 0);
@@ -695,7 +716,7 @@ int32_t sdllm_sparse_attn_noalloc(const sdllm_shape_t* shape, const void* q_blk,
   if (st != SDLLM_OK) return st;
   if (n_cached < 0) return SDLLM_ERR_INVALID_ARG;
   const sdllm_shape_t& s = *shape;
-  const size_t need = plan_attn(s, n_cached, s.cache_stride[2], s.block_len, s.blk_stride[2]).ws_bytes();
+  const size_t need = plan_attn(s, n_cached, s.cache_stride[2], s.block_len, s.blk_stride[2], false, SDLLM_STATIC_SCRATCH_BYTES).ws_bytes();
   if (need > SDLLM_STATIC_SCRATCH_BYTES) return SDLLM_ERR_STATIC_LIMIT;
   void* ptr = nullptr;
   if (static_scratch(&ptr) != hipSuccess) return SDLLM_ERR_HIP;

@@ -60,3 +60,46 @@ def test_key_splits_of_an_update_step_whose_merge_costs_nothing(batch, q_heads, 
         assert route(UPDATE, batch, q_heads, kv_heads, tiles, block_off=64, score_mode=mode) == update
     # nothing to compact: the merge is a launch of its own
     assert route(UPDATE, batch, q_heads, kv_heads, tiles, block_off=64, retention=0.0) == full
+
+
+# Groups of 7 and 8 heads: the shared-tile kernel from the second tile count on, not yet at the first (short of the line by no
+# more than its slope).  Sparse steps and dense rows alike.
+@pytest.mark.parametrize("batch,q_heads,kv_heads,below,from_", [
+    (5, 28, 4, 128, 129), (6, 28, 4, 127, 128), (10, 16, 2, 123, 124), (7, 28, 4, 138, 139), (8, 28, 4, 149, 150), (9, 28, 4, 160, 161),
+    (8, 32, 4, 162, 163),                                                                  # up to one workgroup per CU
+    (3, 28, 4, 482, 483), (4, 28, 4, 299, 300), (8, 16, 2, 324, 325), (2, 28, 4, 598, 599), (3, 32, 4, 312, 313),   # with key splits
+    (10, 28, 4, 65, 66), (12, 28, 4, 65, 66), (16, 28, 4, 74, 75), (18, 28, 4, 83, 84), (32, 16, 2, 85, 86),          # up to two
+    (19, 28, 4, 39, 40), (20, 32, 4, 39, 40), (32, 28, 4, 39, 40), (17, 32, 4, 39, 40),    # up to four, filling the chip
+    (22, 28, 4, 49, 50), (24, 32, 4, 49, 50), (26, 28, 4, 49, 50),                         # ... and not
+])
+def test_shared_tile_kernel_from_the_measured_line_on(batch, q_heads, kv_heads, below, from_):
+    for call in (SPARSE, FULL):
+        assert plan(call, batch, q_heads, kv_heads, below).kernel != SHARED
+        assert plan(call, batch, q_heads, kv_heads, from_).kernel == SHARED
+
+
+@pytest.mark.parametrize("batch,q_heads,kv_heads", [(37, 28, 4), (33, 32, 4), (129, 8, 1), (65, 16, 2), (150, 7, 1)])
+def test_shared_tile_kernel_always_beyond_four_heads_per_cu(batch, q_heads, kv_heads):
+    for tiles in (2, 5, 20, 35, 60):
+        for call in (SPARSE, FULL, UPDATE):
+            assert route(call, batch, q_heads, kv_heads, tiles, block_off=min(64, 32 * tiles - 32)) == (SHARED, 1)
+
+
+def test_shared_tile_kernel_at_update_steps():
+    for batch, q_heads, kv_heads, below, from_ in ((20, 32, 4, 29, 30), (32, 28, 4, 29, 30), (22, 28, 4, 45, 46), (24, 32, 4, 45, 46)):
+        assert plan(UPDATE, batch, q_heads, kv_heads, below, block_off=64).kernel != SHARED
+        assert plan(UPDATE, batch, q_heads, kv_heads, from_, block_off=64).kernel == SHARED
+
+
+def test_scratch_beyond_a_callers_gives_way_up_to_5000_tiles():
+    # 34 x 16/2 heads x 48 tiles: 26 MB of partials on the faster kernel, none on the other.  A null pointer is enough to see
+    # that the plan is accepted: nothing but the missing output is wrong with these calls.
+    import ctypes
+    shape = B.make_shape(batch=34, n_q_heads=16, n_kv_heads=2, head_dim=128, seq_len=4096, block_off=0, block_len=32, dtype=B.SDLLM_BF16)
+    n = 32 * 47
+    need = B.sdllm_workspace_bytes(shape, B.SDLLM_OP_SPARSE_ATTN, n)
+    assert B.sdllm_launch_plan(shape, SPARSE, n).kernel == SHARED and need > B.SDLLM_STATIC_SCRATCH_BYTES
+    fake, null = ctypes.c_void_p(0x1000), ctypes.c_void_p(None)
+    call = lambda k: B.load().sdllm_sparse_attn_noalloc(ctypes.byref(shape), fake, fake, fake, k, fake, fake, null, null)
+    assert call(32 * 200) == B.SDLLM_ERR_STATIC_LIMIT
+    assert call(n) in (B.SDLLM_ERR_INVALID_ARG, B.SDLLM_ERR_HIP)   # past the limit check (without a GPU the array has no address)
