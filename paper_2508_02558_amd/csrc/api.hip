@@ -257,15 +257,18 @@ AttnPlan plan_attn(const sdllm_shape_t& s, int32_t n0, int64_t sr0, int32_t n1, 
   }
   // The kernel that fetches tiles straight into LDS (attn_stream_mfma.hip) takes
   // * grouped-query heads with one workgroup per head: always with 129 to 256 heads (8 x 28/4 heads: 28 tiles
-  //   11.8 -> 11.3 us, 75 tiles 20.9 -> 19.5 us, 144 tiles 37.1 -> 29.0 us), with more where four of its
-  //   waves beat the shared-tile kernel (above);
+  //   11.8 -> 11.3 us, 75 tiles 20.9 -> 19.5 us, 144 tiles 37.1 -> 29.0 us).  With more, where its four-wave workgroups fit two
+  //   to a CU as the other kernel's do, for groups of 7 and 8: up to 280 heads from 36 tiles on (40 tiles 22.3 -> 20.5 us; at
+  //   336 heads 23.8 against 24.8), and for groups of 8 from 52 tiles on (416 heads 31.3 -> 30.1 us); with
+  //   the statistics of a cache-update step always from 36 (whole step, 448 heads x 52 tiles 65.3 ->
+  //   62.7 us, 616 x 42 77.9 -> 72.3);
   // * fewer grouped-query heads instead of key splits, up to the tile count at which two or more workgroups per head
-  //   repay the combine launch: 8 heads 21 tiles 9.6 -> 9.1 us, 28 tiles 9.6 against 10.2; 28 heads 21 tiles 10.6 -> 9.3 us, 28 tiles
-  //   10.7 against 10.4, 36 tiles 10.9 against 12.0 us; 56 heads 28 tiles 12.9 -> 10.5 us, 45 tiles 12.4 against 13.4;
-  //   72 heads (three splits) 37 tiles 11.8 against 12.6; 112 heads 45 tiles 14.6 -> 13.9 us, 60 tiles 15.9 against 16.0.
-  //   Where the merge rides on another launch there is nothing to save (cache-update step, 28 heads x 26 tiles 25.8 us split
-  //   against 27.8; 12 heads, raw-logit scores 20.2 against 24.1), except for the split itself with more than 85 heads
-  //   (128 heads x 22 tiles 29.7 -> 28.7, 112 x 30 30.4 against 31.3);
+  //   repay the combine launch: 8 to 32 heads 20 tiles 9.6 to 10.7 -> 9.2 us, 22 tiles level, 24 tiles 9.3 to 10.1 against 10.2;
+  //   48 to 80 heads 30 tiles 13.1 -> 11.4 us, 36 tiles 11.6 to 12.7 against 12.3; 96 to 128 heads, groups of 6 to 8, 46 tiles
+  //   15.1 to 15.7 -> 13.9 us, 52 tiles level, and groups of 3 and 4, whose keys are more bytes, 34 tiles 13.8 to 16.0 -> 12.6 to
+  //   14.6, 42 tiles 15.8 to 17.2 against 16.4 to 17.3.  Where the merge rides on another launch there is nothing to save
+  //   (cache-update step, 28 heads x 26 tiles 25.8 us split against 27.8; 12 heads, raw-logit scores 20.2 against 24.1),
+  //   except for the split itself with more than 85 heads (128 heads x 22 tiles 29.7 -> 28.7, 112 x 30 30.4 against 31.3);
   // * split grouped-query heads at the cache-update step, where the other kernel masks every tile for the scoring's
   //   statistics, if its waves get three tiles or more (28 heads x 1040 tiles, whole step 88.4 -> 85.8 us); without
   //   statistics the two are within 2 % of each other up to 60 tiles a split;
@@ -281,7 +284,7 @@ AttnPlan plan_attn(const sdllm_shape_t& s, int32_t n0, int64_t sr0, int32_t n1, 
   if (group > 1 && heads <= kNumCUs)
     pl.stream = unsplit_pays || (stats && tiles >= 24 * n_split);
   else if (group > 1)
-    pl.stream = (group == 7 || group == 8) && tiles >= 36;
+    pl.stream = (group == 7 || group == 8) && tiles >= 36 && (stats || heads <= 280 || (heads <= 2 * kNumCUs && group == 8 && tiles >= 52));
   else
     pl.stream = heads <= 128 && wave_tiles <= 512 && unsplit_pays && (n1 > 0 || n_split > 1);
   if (pl.stream && unsplit_pays) n_split = 1;

@@ -103,3 +103,15 @@ def test_scratch_beyond_a_callers_gives_way_up_to_5000_tiles():
     call = lambda k: B.load().sdllm_sparse_attn_noalloc(ctypes.byref(shape), fake, fake, fake, k, fake, fake, null, null)
     assert call(32 * 200) == B.SDLLM_ERR_STATIC_LIMIT
     assert call(n) in (B.SDLLM_ERR_INVALID_ARG, B.SDLLM_ERR_HIP)   # past the limit check (without a GPU the array has no address)
+
+
+def test_stream_kernel_with_more_heads_than_cus():
+    for batch, q_heads, kv_heads, tiles, want in ((10, 28, 4, 35, PER_HEAD), (10, 28, 4, 36, STREAM), (17, 16, 2, 36, STREAM), (9, 32, 4, 36, PER_HEAD),
+                                                  (12, 28, 4, 52, PER_HEAD), (9, 32, 4, 52, STREAM), (26, 16, 2, 51, PER_HEAD),
+                                                  (26, 16, 2, 52, STREAM), (20, 28, 4, 36, PER_HEAD), (20, 16, 4, 60, PER_HEAD)):
+        for call in (SPARSE, FULL):
+            assert plan(call, batch, q_heads, kv_heads, tiles).kernel == want
+    # with the scoring's statistics
+    for batch, q_heads, kv_heads, tiles, want in ((12, 28, 4, 36, STREAM), (12, 28, 4, 35, PER_HEAD), (22, 28, 4, 40, STREAM), (20, 16, 4, 60, PER_HEAD)):
+        assert plan(UPDATE, batch, q_heads, kv_heads, tiles, block_off=64).kernel == want
+        assert plan(UPDATE, batch, q_heads, kv_heads, tiles, block_off=64, score_mode=B.SDLLM_LOGIT_MEAN).kernel == PER_HEAD
