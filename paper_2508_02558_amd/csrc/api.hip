@@ -279,7 +279,7 @@ AttnPlan plan_attn(const sdllm_shape_t& s, int32_t n0, int64_t sr0, int32_t n1, 
   //   non-temporal streams of attn_mfma.hip also keep the dense rows of calls that they leave unsplit (they then
   //   sweep the scores as well).
   const bool unsplit_pays = n_split == 1 || (update ? heads > 85 && tiles <= 26
-                                                    : tiles <= (heads <= 8 ? 22 : heads <= 32 ? 26 : heads <= 85 ? 33 : 48));
+                                                    : tiles <= (heads <= 32 ? 22 : heads <= 85 ? 33 : group >= 6 ? 48 : 38));
   const bool stats = update && s.score_mode == SDLLM_SOFTMAX_MEAN;
   if (group > 1 && heads <= kNumCUs)
     pl.stream = unsplit_pays || (stats && tiles >= 24 * n_split);

@@ -105,6 +105,15 @@ def test_scratch_beyond_a_callers_gives_way_up_to_5000_tiles():
     assert call(n) in (B.SDLLM_ERR_INVALID_ARG, B.SDLLM_ERR_HIP)   # past the limit check (without a GPU the array has no address)
 
 
+@pytest.mark.parametrize("call", [SPARSE, FULL])
+def test_small_calls_stay_unsplit_up_to_the_measured_line(call):
+    for batch, q_heads, kv_heads, last in ((1, 8, 2, 22), (1, 12, 4, 22), (1, 28, 4, 22), (1, 32, 8, 22), (2, 28, 4, 33), (2, 32, 8, 33),
+                                           (4, 28, 4, 48), (4, 24, 4, 48), (8, 16, 2, 48), (3, 32, 8, 38), (8, 12, 4, 38), (4, 32, 8, 38)):
+        assert route(call, batch, q_heads, kv_heads, last) == (STREAM, 1)
+        kernel, splits = route(call, batch, q_heads, kv_heads, last + 1)
+        assert kernel == PER_HEAD and splits > 1
+
+
 def test_stream_kernel_with_more_heads_than_cus():
     for batch, q_heads, kv_heads, tiles, want in ((10, 28, 4, 35, PER_HEAD), (10, 28, 4, 36, STREAM), (17, 16, 2, 36, STREAM), (9, 32, 4, 36, PER_HEAD),
                                                   (12, 28, 4, 52, PER_HEAD), (9, 32, 4, 52, STREAM), (26, 16, 2, 51, PER_HEAD),
