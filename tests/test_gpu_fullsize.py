@@ -102,7 +102,7 @@ def test_dream_long_full_size():
 
 def test_dream7b_gen512_full_size():
     # the grouped-query bench workload: B=8, 28 query / 4 KV heads, prompt 4096, 512-token generation
-    # (dense step through the shared-tile kernel with key splits, sparse step one workgroup per head), all 32 rows
+    # (dense and sparse step through the LDS-fetching kernel, one workgroup per head), all 32 rows
     _full_block(wl.WORKLOADS["dream7b_gen512"])
 
 

@@ -390,16 +390,6 @@ def test_scores_match_oracle_values():
                 np.testing.assert_allclose(pg, pooled_orc, rtol=0, atol=2e-5)
 
 
-def _shared_kernel_wave_tiles(group):
-    """plan_attn (csrc/api.hip): heads x 32-key tiles from which the shared-tile grouped-query kernel runs
-    (groups of 3, 5 and 6 heads always take the one-workgroup-per-head kernel; groups of 2 and 4
-    also need SHARED_KERNEL_MIN_HEADS query heads in the batch)."""
-    return {7: 30000, 8: 30000, 2: 26000, 4: 26000}[group]
-
-
-SHARED_KERNEL_MIN_HEADS = 320   # two-wave workgroups (groups of 2 and 4 heads) only
-
-
 def _check_selected_rows(gl, shape, w, q, k_full, o, b, rows):
     """Index sets of the batch elements `rows` after a cache-update step, against the oracle."""
     idx_gpu = gl.idx[rows, :, :gl.k_total].cpu().numpy().astype(np.int64)
@@ -409,19 +399,26 @@ def _check_selected_rows(gl, shape, w, q, k_full, o, b, rows):
             U.compare_index_rows(idx_gpu[i, g], idx_orc[i, g], pooled_orc[i, g], w.seq_len, o, b, U.ranked_segments(shape))
 
 
-def _batch_for_shared_kernel(n_q_heads, n_keys_sparse, group=7):
-    tiles = -(-n_keys_sparse // 32) + 1            # cache tiles + the block's own tile
-    batch = -(-_shared_kernel_wave_tiles(group) // (n_q_heads * tiles)) + 1
-    if group in (2, 4):
-        batch = max(batch, -(-SHARED_KERNEL_MIN_HEADS // n_q_heads))
-    return batch
+def _runs_shared_kernel(w, *calls, block_index=0):
+    """Whether every one of the calls (sparse steps over the retained keys) takes the shared-tile grouped-query kernel."""
+    shape = U.shape_for(w, block_index)
+    k_total, _, _ = B.sdllm_retained_count(shape)
+    return all(B.sdllm_launch_plan(shape, c, k_total if c == B.SDLLM_CALL_SPARSE else 0).kernel == B.SDLLM_KERNEL_SHARED_TILE for c in calls)
+
+
+def _at_shared_kernel_batch(w, *calls):
+    """`w` at the smallest batch from which on it does."""
+    batch = 1
+    while not (_runs_shared_kernel(w.scaled(batch=batch), *calls) and _runs_shared_kernel(w.scaled(batch=2 * batch), *calls)):
+        batch += 1
+    return w.scaled(batch=batch)
 
 
 def test_grouped_query_kernel_at_large_batch():
     # enough heads x key tiles switches sdllm_sparse_attn / the dense step to the shared-tile grouped-query kernel
     _note("[case] grouped-query shared-tile kernel")
-    w = wl.WORKLOADS["dream7b_gqa"].scaled(prompt=300, gen=64)               # ragged tiles; 150 + 16 retained keys
-    w = w.scaled(batch=_batch_for_shared_kernel(w.n_q_heads, 166))
+    both = (B.SDLLM_CALL_SPARSE, B.SDLLM_CALL_UPDATE)
+    w = _at_shared_kernel_batch(wl.WORKLOADS["dream7b_gqa"].scaled(prompt=300, gen=64), *both)   # ragged tiles; 150 + 16 retained keys
     inp = wl.make_block_inputs(w, n_steps=3, device=DEV)
     shape = U.shape_for(w)
     gl = U.GpuLayer(shape, DEV)
@@ -445,7 +442,11 @@ def test_grouped_query_kernel_at_large_batch():
     # kernel at any size; they go through the same checks at a batch of that order.
     for G, Hkv, prompt in ((2, 3, 1000), (3, 2, 33), (4, 2, 905), (5, 1, 100), (6, 1, 257), (7, 1, 64), (8, 1, 70)):
         w2 = w.scaled(n_q_heads=G * Hkv, n_kv_heads=Hkv, prompt=prompt, gen=64)
-        w2 = w2.scaled(batch=_batch_for_shared_kernel(G * Hkv, -(-prompt // 2) + 16, G if G in (2, 4, 7, 8) else 7))
+        if G in (2, 4, 7, 8):
+            w2 = _at_shared_kernel_batch(w2, *both)
+        else:
+            w2 = w2.scaled(batch=200)
+            assert not any(_runs_shared_kernel(w2, c) for c in both)
         inp2 = wl.make_block_inputs(w2, n_steps=3, device=DEV)
         gl2 = U.GpuLayer(U.shape_for(w2), DEV)
         q = inp2["q"][1].contiguous()
@@ -463,18 +464,20 @@ def test_grouped_query_kernel_at_large_batch():
         del inp2, gl2
 
 
-@pytest.mark.parametrize("prompt,modes", [
-    (20000, {}),                                              # block on a tile boundary
-    (20011, {}),                                              # the block's keys share two tiles with candidates
-    (20011, {"evict_scope": B.SDLLM_EVICT_PREFIX_ONLY}),      # the suffix is not scored either
+@pytest.mark.parametrize("batch,q_heads,prompt,modes", [
+    (2, 28, 20000, {}),                                              # block on a tile boundary
+    (2, 28, 20011, {}),                                              # the block's keys share two tiles with candidates
+    (2, 28, 20011, {"evict_scope": B.SDLLM_EVICT_PREFIX_ONLY}),      # the suffix is not scored either
+    (3, 32, 10643, {}),                                              # groups of eight
 ])
-def test_grouped_query_kernel_with_key_splits(prompt, modes):
+def test_grouped_query_kernel_with_key_splits(batch, q_heads, prompt, modes):
     # few (batch, KV head) rows but long keys: the shared-tile kernel then splits every row's keys over
     # many workgroups (ragged last split, fp32 partials, combine) in both the dense and the sparse step;
     # at the cache-update step it also supplies the scoring pass's row statistics, so the index sets
     # checked here depend on its candidate-only (max, sum) in every split
-    w = wl.WORKLOADS["dream7b_gqa"].scaled(batch=2, prompt=prompt, gen=64, retention=0.9)
-    assert w.batch * w.n_q_heads * ((18000 + 29) // 32 + 1) >= _shared_kernel_wave_tiles(w.group)
+    w = wl.WORKLOADS["dream7b_gqa"].scaled(batch=batch, n_q_heads=q_heads, prompt=prompt, gen=64, retention=0.99)
+    assert _runs_shared_kernel(w, B.SDLLM_CALL_SPARSE, B.SDLLM_CALL_FULL, B.SDLLM_CALL_UPDATE)
+    assert B.sdllm_launch_plan(U.shape_for(w), B.SDLLM_CALL_UPDATE).key_splits > 1
     _run_block(w, n_steps=3, **modes)
 
 
@@ -500,7 +503,7 @@ def test_fused_row_statistics_ignore_dominant_block_keys():
     _note("[case] fused row statistics under dominant block keys")
     base = wl.WORKLOADS["dream7b_gqa"].scaled(prompt=333, gen=64)
     cases = [wl.WORKLOADS["llada8b_layer"].scaled(n_q_heads=4, n_kv_heads=4, prompt=300, gen=64), base,
-             base.scaled(batch=_batch_for_shared_kernel(base.n_q_heads, 333 + 64 - 32))]   # dense step: 13 tiles
+             _at_shared_kernel_batch(base, B.SDLLM_CALL_UPDATE)]   # dense step: 13 tiles
     for w in cases:
         inp = wl.make_block_inputs(w, n_steps=2, device=DEV)
         shape = U.shape_for(w)

@@ -14,19 +14,23 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda"
 
 
-@pytest.mark.parametrize("batch,q_heads,kv_heads,n_cached", [
-    (1, 7, 1, 0), (1, 7, 1, 1), (1, 7, 1, 96), (1, 7, 1, 97), (2, 8, 2, 255), (1, 14, 2, 512), (3, 6, 2, 671),
-    (1, 32, 32, 77), (4, 8, 8, 400),                        # multi-head calls small enough to go unsplit
-    (8, 28, 4, 1633), (5, 28, 4, 2111),                     # one workgroup per head, eight waves
-    (1, 28, 4, 6211), (4, 28, 4, 1721),                     # split keys, three tiles per wave or more
-    (10, 28, 4, 1185),                                      # more heads than CUs: four waves
+@pytest.mark.parametrize("batch,q_heads,kv_heads,n_cached,waves,touches", [
+    (1, 7, 1, 0, 1, 0), (1, 7, 1, 1, 2, 0), (1, 7, 1, 96, 4, 0), (1, 7, 1, 97, 4, 0), (2, 8, 2, 255, 4, 0), (1, 14, 2, 512, 6, 0),
+    (3, 6, 2, 671, 6, 0),
+    (1, 32, 32, 77, 4, 0), (4, 8, 8, 400, 5, 0),            # multi-head calls small enough to go unsplit
+    (8, 28, 4, 1633, 8, 0), (5, 28, 4, 2111, 8, 0),         # one workgroup per head, eight waves
+    (10, 28, 4, 1185, 4, 0),                                # more heads than CUs: four waves
+    # heads bring tiles into L2 for each other; ragged last tiles in both segments, waves with a tile less than others
+    (8, 28, 4, 3301, 8, 1), (6, 28, 4, 3107, 8, 1), (9, 16, 2, 3333, 8, 1), (10, 28, 4, 1733, 4, 1), (17, 16, 2, 1543, 4, 1),
 ])
-def test_stream_sparse_attn(batch, q_heads, kv_heads, n_cached):
+def test_stream_sparse_attn(batch, q_heads, kv_heads, n_cached, waves, touches):
     print(f"[case] stream sparse_attn B={batch} {q_heads}/{kv_heads} n_cached={n_cached}", flush=True)
     torch.manual_seed(n_cached + batch)
     b, d, rows = 32, 128, max(1, n_cached)
     shape = B.make_shape(batch=batch, n_q_heads=q_heads, n_kv_heads=kv_heads, head_dim=d, seq_len=16384, block_off=8192,
                          block_len=b, dtype=B.SDLLM_BF16, cache_rows=rows)
+    plan = B.sdllm_launch_plan(shape, B.SDLLM_CALL_SPARSE, n_cached)
+    assert (plan.kernel, plan.key_splits, plan.waves, plan.touches_ahead) == (B.SDLLM_KERNEL_STREAM, 1, waves, touches)
     q = (2.0 * torch.randn(batch, q_heads, b, d, device=DEV)).bfloat16()
     kc, vc = (torch.randn(batch, kv_heads, rows, d, device=DEV).bfloat16() for _ in range(2))
     kb, vb = (torch.randn(batch, kv_heads, b, d, device=DEV).bfloat16() for _ in range(2))
@@ -39,14 +43,19 @@ def test_stream_sparse_attn(batch, q_heads, kv_heads, n_cached):
     U.assert_close(out, U.oracle_attention_batch(q, k_all, v_all), "bf16", f"n_cached={n_cached}")
 
 
-@pytest.mark.parametrize("q_heads,kv_heads,batch,prompt,modes", [
-    (14, 2, 1, 333, {}),                                                   # block off the tile grid on both sides
-    (7, 1, 2, 64, dict(evict_scope=B.SDLLM_EVICT_PREFIX_ONLY)),            # few candidate tiles, long mixed tail
-    (28, 4, 2, 3111, {}),                                                  # statistics from key splits
-    (14, 2, 1, 0, {}),                                                     # no prefix
+@pytest.mark.parametrize("q_heads,kv_heads,batch,prompt,splits,touches,modes", [
+    (14, 2, 1, 233, 1, 0, {}),                                             # block off the tile grid on both sides
+    (7, 1, 2, 64, 1, 0, dict(evict_scope=B.SDLLM_EVICT_PREFIX_ONLY)),      # few candidate tiles, long mixed tail
+    (28, 4, 2, 3111, 4, 0, {}),                                            # statistics from key splits
+    (28, 4, 2, 12433, 4, 1, {}),                                           # ... whose heads bring tiles into L2 for each other
+    (14, 2, 1, 0, 1, 0, {}),                                               # no prefix
+    (28, 4, 12, 1171, 1, 0, {}),                                           # more heads than CUs
+    (28, 4, 22, 1109, 1, 0, {}),                                           # more than two four-wave workgroups per CU
 ])
-def test_stream_statistics_at_the_cache_update_step(q_heads, kv_heads, batch, prompt, modes):
+def test_stream_statistics_at_the_cache_update_step(q_heads, kv_heads, batch, prompt, splits, touches, modes):
     w = wl.WORKLOADS["dream7b_gqa"].scaled(batch=batch, n_q_heads=q_heads, n_kv_heads=kv_heads, prompt=prompt, gen=160)
+    plan = B.sdllm_launch_plan(U.shape_for(w, 2, **modes), B.SDLLM_CALL_UPDATE)
+    assert (plan.kernel, plan.key_splits, plan.touches_ahead) == (B.SDLLM_KERNEL_STREAM, splits, touches)
     _run_block(w, block_index=2, n_steps=3, **modes)
 
 
@@ -60,6 +69,7 @@ def test_tiles_of_infinitely_low_keys(n_cached):
     kept = _hide(kc, q, [*range(32, 64), *range(96, 128)])
     shape = B.make_shape(batch=1, n_q_heads=7, n_kv_heads=1, head_dim=128, seq_len=4096, block_off=2048, block_len=32,
                          dtype=B.SDLLM_BF16, cache_rows=n_cached)
+    assert B.sdllm_launch_plan(shape, B.SDLLM_CALL_SPARSE, n_cached).kernel == B.SDLLM_KERNEL_STREAM
     out = torch.zeros_like(q)
     ws = torch.empty(B.sdllm_workspace_bytes(shape, B.SDLLM_OP_SPARSE_ATTN, n_cached), dtype=torch.uint8, device=DEV)
     B.sdllm_sparse_attn(shape, q, kc, vc, n_cached, kb, vb, out, ws)
