@@ -119,17 +119,20 @@ def _ptr(t) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
-_torch = None
+_torch = _raw_stream = None
 
 
 def _current_raw_stream() -> int:
     """Handle of torch's current stream on its current device.  torch.cuda.current_stream() builds a Stream object
-    around the same number on every call: 3.0 us, a third of what a small step costs the host, against 0.3 us."""
-    global _torch
+    around the same number on every call: 3.0 us, a third of what a small step costs the host, against 0.3 us for the
+    function below it.  That one is not public, so a torch without it goes the long way."""
+    global _torch, _raw_stream
     if _torch is None:
         import torch
-        _torch = torch
-    return _torch._C._cuda_getCurrentRawStream(_torch.cuda.current_device())
+        _torch, _raw_stream = torch, getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if _raw_stream is None:
+        return _torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_torch.cuda.current_device())
 
 
 def _stream(stream) -> Optional[int]:

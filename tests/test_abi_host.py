@@ -179,6 +179,20 @@ def test_workspace_sizes(lib):
         B.sdllm_workspace_bytes(s, 9)
 
 
+def test_current_stream_with_and_without_torchs_private_function(monkeypatch):
+    import types
+    import torch
+    cuda = types.SimpleNamespace(current_device=lambda: 3, current_stream=lambda: types.SimpleNamespace(cuda_stream=77))
+    monkeypatch.setattr(torch, "cuda", cuda)
+    for private, handle in ((lambda device: 40 + device, 43), (None, 77)):
+        monkeypatch.setattr(B, "_torch", None)
+        monkeypatch.setattr(B, "_raw_stream", None)
+        monkeypatch.setattr(torch, "_C", types.SimpleNamespace(**({"_cuda_getCurrentRawStream": private} if private else {})))
+        assert B._stream(None) == handle
+    monkeypatch.undo()
+    assert B._stream(5) == 5 and B._stream(0) is None
+
+
 def test_product_path_never_imports_the_oracle():
     pkg = os.path.join(ROOT, "paper_2508_02558_amd")
     for dirpath, _, files in os.walk(pkg):
