@@ -145,6 +145,7 @@ void plan_general(AttnPlan& pl, const sdllm_shape_t& s, int32_t nq, int tiles, b
   }
   if (pl.waves > pl.tiles_per_split) pl.waves = pl.tiles_per_split;
   if (pl.waves < 1) pl.waves = 1;
+  while (pl.waves > 1 && vheads * pl.n_split * pl.waves * kWave > UINT32_MAX) pl.waves /= 2;   // threads of one launch
   if (pl.n_split > 1) {
     pl.part_o_bytes = align_up((size_t)vheads * pl.n_split * block_rows(s.dtype) * s.head_dim * sizeof(float));
     pl.part_ml_bytes = align_up((size_t)vheads * pl.n_split * 2 * block_rows(s.dtype) * sizeof(float));

@@ -124,3 +124,10 @@ def test_stream_kernel_with_more_heads_than_cus():
     for batch, q_heads, kv_heads, tiles, want in ((12, 28, 4, 36, STREAM), (12, 28, 4, 35, PER_HEAD), (22, 28, 4, 40, STREAM), (20, 16, 4, 60, PER_HEAD)):
         assert plan(UPDATE, batch, q_heads, kv_heads, tiles, block_off=64).kernel == want
         assert plan(UPDATE, batch, q_heads, kv_heads, tiles, block_off=64, score_mode=B.SDLLM_LOGIT_MEAN).kernel == PER_HEAD
+
+
+def test_launches_of_the_general_kernel_stay_below_two_to_the_32_threads():
+    # all rows of 65 535 fp32 heads of 64 x 8224 positions (an output of 138 GB): 33 684 990 workgroups
+    p = plan(DENSE, 65535, 1, 1, 257, dtype=B.SDLLM_F32, head_dim=64)
+    assert p.kernel == GENERAL and 65535 * 514 * p.waves * 64 < 1 << 32
+    assert plan(DENSE, 1, 8, 8, 256, dtype=B.SDLLM_F32, head_dim=64).waves > 1
