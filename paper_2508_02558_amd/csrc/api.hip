@@ -334,9 +334,10 @@ int32_t run_attn(const sdllm_shape_t& s, const void* q, const KvSegment& a, cons
                  size_t ws_bytes, hipStream_t stream, bool update = false, float* cand_ml = nullptr, int cand0_end = 0,
                  int cand1_begin = 0, AttnParams* deferred = nullptr, float* score_out = nullptr, int score_stride = 0) {
   AttnPlan pl = plan_attn(s, a.n, a.sr, b.n, b.sr, update, ws ? ws_bytes : 0);
-  if (pl.ws_bytes() > 0 && (!ws || ws_bytes < pl.ws_bytes())) {
-    if (pl.mfma) return SDLLM_ERR_WORKSPACE;
-    // the general kernel works without a workspace too: one workgroup per 32 rows walks all keys
+  const bool fits = ws && ws_bytes >= pl.ws_bytes();
+  if (pl.ws_bytes() > 0 && pl.mfma && !fits) return SDLLM_ERR_WORKSPACE;
+  if (pl.ws_bytes() > 0 && !pl.mfma && !(fits && aligned16(ws))) {
+    // the general kernel works without a usable workspace too: one workgroup per block of rows walks all keys
     plan_general(pl, s, s.block_len, (a.n + kTileKeys - 1) / kTileKeys + (b.n + kTileKeys - 1) / kTileKeys, false);
   }
   AttnParams p{};

@@ -62,11 +62,12 @@ def test_general_sparse_attn_without_a_workspace(dtype, d, block, n_cached):
     kc, vc = (torch.randn(1, 1, n_cached, d, device=DEV).to(t) for _ in range(2))
     kb, vb = (torch.randn(1, 1, block, d, device=DEV).to(t) for _ in range(2))
     ref = U.oracle_attention_batch(q, torch.cat([kc, kb], 2), torch.cat([vc, vb], 2))
-    for ws in (None, torch.empty(need, dtype=torch.uint8, device=DEV)):
+    room = torch.empty(need + 16, dtype=torch.uint8, device=DEV)
+    for ws in (None, room[:need], room[:need - 1], room[1:1 + need]):
         out = torch.full_like(q, float("nan"))
         B.sdllm_sparse_attn(shape, q, kc, vc, n_cached, kb, vb, out, ws)
         torch.cuda.synchronize()
-        U.assert_close(out, ref, dtype, "no workspace" if ws is None else "workspace")
+        U.assert_close(out, ref, dtype, "no workspace" if ws is None else f"workspace of {ws.numel()} at {ws.storage_offset()}")
 
 
 def test_rows_too_far_apart_for_32_bit_offsets():
