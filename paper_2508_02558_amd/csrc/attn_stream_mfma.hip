@@ -84,30 +84,6 @@ __device__ __forceinline__ void read_v_frags(const uint8_t* tile, int lane, PvFr
   for (int i = 0; i < 8; ++i) f.av[i >> 2][i & 3] = __builtin_shufflevector(r[2 * i], r[2 * i + 1], 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
-// Adds the candidates among a tile's keys to a row's running candidate-only (max, sum): register i of
-// the raw logits is key position pos0 + 8*(i/4) + i%4; candidates are the positions before
-// cand0_end or from cand1_begin on, within the sequence.  The reference mc_run is common to the two
-// half-lanes of a row, the sum is per half-lane (like the attention's own pair).
-__device__ __forceinline__ void tile_candidate_stats(const f32x16& sn, int pos0, const AttnParams& p, float& mc_run, float& lc_run) {
-  float sc[16];
-  float mc_loc = -INFINITY;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int pos = pos0 + (i >> 2) * 8 + (i & 3);
-    sc[i] = ((pos < p.cand0_end || pos >= p.cand1_begin) && pos < p.seg[0].n) ? sn[i] * p.scale_log2 : -INFINITY;
-    mc_loc = fmaxf(mc_loc, sc[i]);
-  }
-  mc_loc = fmaxf(mc_loc, __shfl_xor(mc_loc, 32));
-  const float mc_new = fmaxf(mc_run, mc_loc);
-  if (mc_new != -INFINITY) {
-    float lc_loc = 0.f;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) lc_loc += __builtin_amdgcn_exp2f(sc[i] - mc_new);
-    lc_run = lc_run * __builtin_amdgcn_exp2f(mc_run - mc_new) + lc_loc;
-    mc_run = mc_new;
-  }
-}
-
 template <int NSEG, bool STATS, bool TOUCH>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attn_stream_mfma_bf16_kernel(const AttnParams p) {

@@ -185,6 +185,30 @@ __device__ __forceinline__ void softmax_block(f32x16& sn, int rows, float scale_
     for (int j = 0; j < 8; ++j) pb[st][j] = (__bf16)sn[st * 8 + j];
 }
 
+// Adds the candidates among a tile's keys to a row's running candidate-only (max, sum): register i of
+// the raw logits is key position pos0 + 8*(i/4) + i%4; candidates are the positions before
+// cand0_end or from cand1_begin on, within the sequence.  The reference mc_run is common to the two
+// half-lanes of a row, the sum is per half-lane (like the attention's own pair).
+__device__ __forceinline__ void tile_candidate_stats(const f32x16& sn, int pos0, const AttnParams& p, float& mc_run, float& lc_run) {
+  float sc[16];
+  float mc_loc = -INFINITY;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int pos = pos0 + (i >> 2) * 8 + (i & 3);
+    sc[i] = ((pos < p.cand0_end || pos >= p.cand1_begin) && pos < p.seg[0].n) ? sn[i] * p.scale_log2 : -INFINITY;
+    mc_loc = fmaxf(mc_loc, sc[i]);
+  }
+  mc_loc = fmaxf(mc_loc, __shfl_xor(mc_loc, 32));
+  const float mc_new = fmaxf(mc_run, mc_loc);
+  if (mc_new != -INFINITY) {
+    float lc_loc = 0.f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) lc_loc += __builtin_amdgcn_exp2f(sc[i] - mc_new);
+    lc_run = lc_run * __builtin_amdgcn_exp2f(mc_run - mc_new) + lc_loc;
+    mc_run = mc_new;
+  }
+}
+
 // Register (e, i) of a lane is output column 32e + 8*(i/4) + 4*half + i%4 of query row lane%32: four
 // consecutive registers are four consecutive columns.
 __device__ __forceinline__ int out_col0(int e, int i4, int half) { return 32 * e + 8 * i4 + 4 * half; }
