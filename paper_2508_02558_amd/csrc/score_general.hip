@@ -5,8 +5,8 @@
 //
 // logits = Q K_tile^T with Q rows as the A operand, so a lane holds one candidate key against 16 query
 // rows and sums their weights in registers.  A workgroup serves one (batch, KV head) and a few candidate
-// tiles, one per wave at a time; the query rows of the group (blocks of 32 or 16 rows of every head, zero rows as
-// padding, which add nothing to either kind of score) sit in LDS, as many blocks at once as 64 KB hold.
+// tiles, one per wave at a time; the query rows of the group (blocks of 32 or 16 rows of every head, padded with copies of the
+// last row, which count for nothing) sit in LDS, as many blocks at once as 64 KB hold.
 // Batch 2, 32 heads of 128, 64-token block, 1216 candidates: 138 us with one thread per candidate and a
 // scalar loop over all query rows, 9-10 us here; what is left is latency (queries, statistics, one tile).
 #include "general_tile.h"
@@ -51,9 +51,7 @@ __global__ __launch_bounds__(kColWaves * kWave) void score_cols_general_kernel(c
     for (int i = tid; i < here * R * kPerRow; i += kColWaves * kWave) {
       const int c = i % kPerRow, r = i / kPerRow % R, k = i / kPerRow / R;
       const int hh = (blk0 + k) / rblocks, row = (blk0 + k - hh * rblocks) * R + r;
-      u32x4 v = {0u, 0u, 0u, 0u};
-      if (row < p.nq)
-        v = *reinterpret_cast<const u32x4*>((const char*)p.q + sizeof(T) * (b * p.q_sb + (int64_t)(g * p.group + hh) * p.q_sh + row * p.q_sr) + c * 16);
+      const u32x4 v = *reinterpret_cast<const u32x4*>((const char*)p.q + sizeof(T) * (b * p.q_sb + (int64_t)(g * p.group + hh) * p.q_sh + min(row, p.nq - 1) * p.q_sr) + c * 16);
       *reinterpret_cast<u32x4*>(lds_q + k * kQBytes + r * O::kKRow + c * 16) = v;
     }
     if (p.softmax) {
@@ -68,7 +66,7 @@ __global__ __launch_bounds__(kColWaves * kWave) void score_cols_general_kernel(c
           if (m_new != -INFINITY) l_tot = l_tot * __builtin_amdgcn_exp2f(m_tot - m_new) + l_s * __builtin_amdgcn_exp2f(m_s - m_new);
           m_tot = m_new;
         }
-        lds_ml[i] = rb * R + r < p.nq ? make_float2(m_tot, 1.f / l_tot) : make_float2(0.f, 0.f);
+        lds_ml[i] = make_float2(m_tot, rb * R + r < p.nq ? 1.f / l_tot : 0.f);   // the statistics of padding rows are the last row's too
       }
     }
     __syncthreads();
@@ -90,12 +88,6 @@ __global__ __launch_bounds__(kColWaves * kWave) void score_cols_general_kernel(c
       for (int k = 0; k < here; ++k) {
         float s[O::NS], sum[O::kKeysPerLane];
         O::score(lds_q + k * kQBytes, keys, col, part, s);
-        if (p.nq - row0 < R) {   // zero rows meeting an infinite key are NaN
-          asm volatile("");      // a real branch (wave-uniform)
-#pragma unroll
-          for (int i = 0; i < O::NS; ++i) s[i] = row0 + O::query(i, part) < p.nq ? s[i] : 0.f;
-        }
-        row0 = row0 + R < p.nq ? row0 + R : 0;
 #pragma unroll
         for (int n = 0; n < O::kKeysPerLane; ++n) sum[n] = 0.f;
         if (p.softmax) {
@@ -106,12 +98,13 @@ __global__ __launch_bounds__(kColWaves * kWave) void score_cols_general_kernel(c
           }
         } else {
 #pragma unroll
-          for (int i = 0; i < O::NS; ++i) sum[O::key_slot(i)] += s[i];
+          for (int i = 0; i < O::NS; ++i) sum[O::key_slot(i)] += row0 + O::query(i, part) < p.nq ? s[i] : 0.f;
 #pragma unroll
           for (int n = 0; n < O::kKeysPerLane; ++n) sum[n] *= p.scale;
         }
 #pragma unroll
         for (int n = 0; n < O::kKeysPerLane; ++n) total[n] += sum[n];
+        row0 = row0 + R < p.nq ? row0 + R : 0;
       }
 #pragma unroll
       for (int n = 0; n < O::kKeysPerLane; ++n) {
