@@ -12,7 +12,7 @@
 // Measured, against one wave per query row with its dot products on the vector ALU and each lane reading
 // whole key rows: dense rows of a 64-token block (batch 2, 32 heads of 128, 1280 keys, bf16) with row
 // statistics 417 + 299 -> 18 us.  All 1092 rows of 2 x 8 heads: head_dim 64
-// bf16 23.6 us (207 TFLOP/s), head_dim 128 fp32 155 us (63 TFLOP/s; 197 us with 32-row blocks, one wave per SIMD).
+// bf16 23.5 us (208 TFLOP/s), head_dim 128 fp32 155 us (63 TFLOP/s; 197 us with 32-row blocks, one wave per SIMD).
 // fp32 at head_dim 128 fills its 256 registers: the variant that also leaves statistics spills 12 bytes per lane.
 #include "attn_merge.h"
 #include "general_tile.h"

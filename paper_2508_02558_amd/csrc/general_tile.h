@@ -11,8 +11,9 @@
 //   logits^T = K_tile Q^T: register i of a lane is key Ops::key(i, part) for query row `col`.
 //   O^T += V_tile^T P^T: results 4u .. 4u+3 of a lane are four output columns from Ops::unit_col(u, part) on.
 // fp32 probabilities throughout: with bf16 tensors they enter the second product as the sum of three bf16 parts, which
-// together hold all 24 significand bits (two parts, 16 bits, would take 0 to 5 % less time in sparse steps and 2 to 7 %
-// less over all rows of a sequence: 2 x 8 heads of 64 x 1092 rows 21.8 us against 23.6 with the step below).
+// together hold all 24 significand bits.  Against two parts, 16 bits, that takes 2 to 8 % more of a sparse step and 4 to 16 %
+// more over all rows of a sequence (head_dim 64: 8 heads x 300 rows 5.9 -> 6.2 us, 2 x 8 x 1092 21.4 -> 23.5, 28 heads x 4000
+// 260 -> 303), the last step of g_bf16_parts included.
 #pragma once
 
 #include "mfma_tile.h"
@@ -210,7 +211,11 @@ __device__ __forceinline__ void g_v_publish(uint8_t* tile, int lane, const typen
 template <int D>
 __device__ __forceinline__ void g_v_publish(uint8_t*, int, const typename Ops<float, D>::V&) {}
 
-// Eight probabilities as the sum of three bf16 operands: each part is what the one before left, cut off after eight bits.
+// Eight probabilities as the sum of three bf16 operands.  Each part is what the one before left, cut off after eight
+// bits instead of rounded: the sum is exact, and no part of a positive value is negative.  None is zero either (2^-126
+// takes its place), so that an infinity in V stays one: 0 to 5 % of a call.  Finding out afterwards that a result is no
+// number and walking the tiles once more costs small calls as much (the second loop's instructions have to be fetched), a
+// branch around the instructions 5 to 40 % (scratch at head_dim 128).
 __device__ __forceinline__ void g_bf16_parts(const float* p, bf16x8 (&part)[3]) {
   u32x4 out[3];
   const auto cut = [](float x) { return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, x) & 0xffff0000u); };
