@@ -78,8 +78,7 @@ __device__ __forceinline__ float tile_logits(const uint8_t* lds_k, const bf16x8 
 // every tile.  l_run only covers the keys this half-lane holds; the halves are added at the end.
 constexpr float kRescaleSlack = 8.f;
 
-__device__ __forceinline__ void tile_softmax(f32x16& s, float m_loc, float scale_log2, float& m_ref, float& l_run,
-                                             f32x16 (&acc)[4]) {
+__device__ __forceinline__ void move_reference(float m_loc, float& m_ref, float& l_run, f32x16 (&acc)[4]) {
   // m_loc is per half-lane; the vote is over all 64 lanes, so either half exceeding moves both
   if (__ballot(m_loc > m_ref + kRescaleSlack) != 0) {   // wave-uniform; always taken on a wave's first tile
     const float m_row = fmaxf(m_loc, __shfl_xor(m_loc, 32));
@@ -92,6 +91,11 @@ __device__ __forceinline__ void tile_softmax(f32x16& s, float m_loc, float scale
 #pragma unroll
       for (int i = 0; i < 16; ++i) acc[e][i] *= alpha;
   }
+}
+
+__device__ __forceinline__ void tile_softmax(f32x16& s, float m_loc, float scale_log2, float& m_ref, float& l_run,
+                                             f32x16 (&acc)[4]) {
+  move_reference(m_loc, m_ref, l_run, acc);
   float l_loc = 0.f;
 #pragma unroll
   for (int i = 0; i < 16; ++i) {

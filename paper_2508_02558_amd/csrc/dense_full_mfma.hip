@@ -4,17 +4,22 @@
 // cache_state 0 in the cache-management appendix).  Compute-bound (2 L^2 d flops per head against
 // 4 L d bytes), so this one is organised for the matrix cores rather than for HBM:
 //   * a workgroup of 8 waves owns 256 consecutive query rows of one head, wave w the 32-row block w
-//     (one 32x32 MFMA block, same fragment layout as the block-step kernels);
-//   * all L keys stream through a double-buffered LDS stage of two 32-key tiles, loaded once per
-//     workgroup with coalesced 16-byte loads and shared by the 8 waves: each K/V byte fetched from
-//     L2 feeds 256 query rows; one workgroup barrier per 64 keys, the next stage's global loads in
-//     flight meanwhile;
-//   * each wave alternates one block of sixteen MFMAs (logits of tile t+1 interleaved with the PV
-//     product of tile t) with one block of vector-ALU work (softmax of tile t+1), the LDS operand
-//     reads for the next MFMA block requested in between: while one wave of a SIMD is in its MFMA
-//     block the other one's softmax runs under it;
+//     (one 32x32 MFMA block, same fragment layout as the block-step kernels); with KS key groups it owns
+//     256 / KS rows and group k walks tiles k, k + KS, ...;
+//   * all L keys stream through rings of tiles in LDS, fetched once per workgroup and shared by its
+//     waves: each K/V byte from L2 feeds 256 / KS query rows;
+//   * per tile a wave has 512 cycles of matrix work and 380 of vector issue.  Left alone the two waves of a SIMD
+//     drift into the same phase (every barrier puts them there) and then queue for the matrix pipe and for the
+//     vector ALU in turn: 1790 cycles per pair of tiles.  Here they are locked in opposite phases, with a barrier
+//     at each change: while one wave issues its sixteen MFMAs (logits of tile t+1 interleaved with the PV product
+//     of tile t), the LDS reads of the next operands and half of tile t's exponentials between them, the other
+//     finds its row maxima and does the first half of its exponentials: 1600 cycles per pair (28 heads x 1181
+//     positions 38.5 -> 36.0 us, x 735 with two key groups 19.2 -> 17.5; 256 heads x 4352 2450 -> 2350 us, where the clock
+//     falls as the pipes fill: 1.97 GHz at 1790 cycles, 1.82 at 1600).  The start costs 0.3 us more (below 10 tiles);
 //   * the query-block workgroups of one head (and of the G heads of a KV group) are adjacent in the
 //     grid and, after the XCD renumbering, share an L2.
+#include <type_traits>
+
 #include "attn_tile_math.h"
 
 namespace sdllm {
@@ -23,15 +28,11 @@ constexpr int kFullWaves = 8;
 constexpr int kFullKvTileBytes = kTileBytes + kVTileBytes;             // K tile + V tile
 
 // KS key groups: the 8 waves of a workgroup are 8/KS row blocks x KS groups, each group walking its own share of the
-// keys.  A stage holds two tiles (KS = 1) or one tile of every group; four tiles of one group (KS = 2, two tiles each)
-// took the staging registers beyond what two waves per SIMD have.
-constexpr int full_stage_tiles(int ks) { return ks <= 2 ? 2 : 4; }
+// keys.
 constexpr int full_rows_per_wg(int ks) { return kFullWaves / ks * 32; }
-constexpr int full_stage_bytes(int ks) { return full_stage_tiles(ks) * kFullKvTileBytes; }
 constexpr int kFullParkBytes = kWave * kRowBytes + 512;                // a wave's accumulators (padded lanes), (max, sum) per row
-constexpr int full_lds_bytes(int ks) { return ks == 1 || 2 * full_stage_bytes(ks) > kFullWaves * kFullParkBytes ? 2 * full_stage_bytes(ks) : kFullWaves * kFullParkBytes; }
 
-// 512 threads load one stage: thread tid takes 16-byte chunk tid%16 of row tid/16 of K and of V, of
+// 512 threads load one stage (KS = 4): thread tid takes 16-byte chunk tid%16 of row tid/16 of K and of V, of
 // each of the stage's tiles.
 template <int NT>
 __device__ __forceinline__ void full_load_stage(const char* k_base, const char* v_base, uint32_t stride, int first_key,
@@ -55,107 +56,281 @@ __device__ __forceinline__ void full_store_stage(uint8_t* stage, int tid, const 
   }
 }
 
-__global__ __launch_bounds__(512) void dense_full_mfma_bf16_kernel(const DenseFullParams p) {
+// Merge of the KS key groups of each row block through LDS (group k of row block rb is wave k * 8 / KS + rb).
+template <int KS>
+__device__ __forceinline__ void merge_key_groups(uint8_t* smem, const f32x16 (&acc)[4], float m_run, float l_tot, int wave, int lane,
+                                                 int half, int col, bool row_valid, char* out_row) {
+  constexpr int RB = kFullWaves / KS;
+  const int rb = wave % RB, kg = wave / RB;
+  __syncthreads();                          // the tiles are done with
+  uint8_t* mine = smem + wave * kFullParkBytes;
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+#pragma unroll
+    for (int i4 = 0; i4 < 4; ++i4) {
+      const f32x4 v = {acc[e][i4 * 4], acc[e][i4 * 4 + 1], acc[e][i4 * 4 + 2], acc[e][i4 * 4 + 3]};
+      *reinterpret_cast<f32x4*>(mine + lane * kRowBytes + (e * 4 + i4) * 16) = v;
+    }
+  if (lane < 32) {
+    float* ml = reinterpret_cast<float*>(mine + kWave * kRowBytes);
+    ml[lane] = m_run;
+    ml[32 + lane] = l_tot;
+  }
+  __syncthreads();
+  float f_w[KS], m_tot = -INFINITY, l_all = 0.f;
+  auto parked = [&](int k) { return smem + (k * RB + rb) * kFullParkBytes; };
+#pragma unroll
+  for (int k = 0; k < KS; ++k) {
+    f_w[k] = reinterpret_cast<const float*>(parked(k) + kWave * kRowBytes)[col];
+    m_tot = fmaxf(m_tot, f_w[k]);
+  }
+#pragma unroll
+  for (int k = 0; k < KS; ++k) {
+    f_w[k] = __builtin_amdgcn_exp2f(f_w[k] - m_tot);   // a group without tiles: 0
+    l_all += f_w[k] * reinterpret_cast<const float*>(parked(k) + kWave * kRowBytes)[32 + col];
+  }
+  const float inv = 1.f / l_all;
+#pragma unroll
+  for (int j = 0; j < 16 / KS; ++j) {
+    const int i = kg * (16 / KS) + j;
+    f32x4 o4 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < KS; ++k) o4 += *reinterpret_cast<const f32x4*>(parked(k) + lane * kRowBytes + i * 16) * f_w[k];
+    bf16x4 ob;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) ob[r] = (__bf16)(o4[r] * inv);
+    if (row_valid) *reinterpret_cast<bf16x4*>(out_row + out_col0(i >> 2, i & 3, half) * 2) = ob;
+  }
+}
+
+// ---- one and two key groups: waves in opposite phases
+// A tile lies in LDS as eight groups of four rows (r, r + 8, r + 16, r + 24 in group r), each as one fetch instruction
+// leaves it, the groups a little more than 1 KB apart: the operand reads then need one lane address per tensor plus constants,
+// and meet no bank conflict (K: eight rows 32 bytes apart modulo 256, the 16-byte chunks of two rows of a group swapped;
+// V: four rows 64 bytes apart).
+constexpr int kKGroup = 1024 + 32, kVGroup = 1024 + 64;
+constexpr int kRingK = 8 * kKGroup, kRingV = 8 * kVGroup;   // one tile
+constexpr int phase_ring(int ks) { return ks == 1 ? 5 : 4; }   // steps held: 86 and 137 KB
+constexpr int phase_lds_bytes(int ks) {
+  const int ring = phase_ring(ks) * ks * (kRingK + kRingV), parked = ks == 1 ? 0 : kFullWaves * kFullParkBytes;
+  return ring > parked ? ring : parked;
+}
+
+__device__ __forceinline__ bf16x8 phase_k_frag(const uint8_t* at, int i) { return *reinterpret_cast<const bf16x8*>(at + i * 32); }
+__device__ __forceinline__ i16x8 phase_v_frag(const uint8_t* at, int i) {
+  typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
+  at += (i >> 2) * 512 + (i & 3) * 64;
+  const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)at);
+  const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(at + 256));
+  return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
+// Softmax numerators of registers 8 st + r and the one after it.
+__device__ __forceinline__ void numerator_pair(f32x16& s, int st, int r, float scale_log2, float m_ref, float& l, bf16x8 (&pb)[2]) {
+#pragma unroll
+  for (int i = r; i < r + 2; ++i) {
+    const float x = __builtin_amdgcn_exp2f(__builtin_fmaf(s[8 * st + i], scale_log2, -m_ref));
+    l += x;
+    pb[st][i] = (__bf16)x;
+  }
+}
+
+// Vector phase of a tile: row maxima, the reference, numerators of keys 0-15.
+__device__ __forceinline__ void softmax_first_half(f32x16& sn, int rows, float scale_log2, int half, float& m_ref, float& l_run,
+                                                   f32x16 (&acc)[4], bf16x8 (&pb)[2]) {
+  const float m_loc = tile_mask_max(sn, rows, scale_log2, half);
+  move_reference(m_loc, m_ref, l_run, acc);
+  float l = 0.f;
+#pragma unroll
+  for (int r = 0; r < 8; r += 2) numerator_pair(sn, 0, r, scale_log2, m_ref, l, pb);
+  l_run += l;
+}
+
+// Matrix phase: logits of the next tile, PV of the current one, each operand register set reloaded for the
+// next phase once it has been used; the current tile's second eight numerators are done between the first MFMAs.
+__device__ __forceinline__ void matrix_phase(bf16x8 (&a)[8], const bf16x8 (&qf)[8], f32x16& sn, PvFrags& f, bf16x8 (&pb)[2], f32x16 (&acc)[4],
+                                             const uint8_t* k_at, const uint8_t* v_at, float scale_log2, float m_ref, float& l_run) {
+  f32x16 s = sn;
+  float l = 0.f;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) sn[i] = 0.f;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], qf[i], sn, 0, 0, 0);
+    acc[i & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f.av[i >> 2][i & 3]), pb[i >> 2], acc[i & 3], 0, 0, 0);
+    a[i] = phase_k_frag(k_at, i);
+    f.av[i >> 2][i & 3] = phase_v_frag(v_at, i);
+    if (i < 4) numerator_pair(s, 1, 2 * i, scale_log2, m_ref, l, pb);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  l_run += l;
+}
+
+template <int KS>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void dense_phase_mfma_bf16_kernel(const DenseFullParams p) {
+  constexpr int RB = kFullWaves / KS, N = phase_ring(KS), kStepK = KS * kRingK, kStepV = KS * kRingV, kV0 = N * kStepK;
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int half = lane >> 5;
-  const int col = lane & 31;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int half = lane >> 5, col = lane & 31;
+  const int rb = wave % RB, kg = wave / RB;
+  const bool late = wave >= kFullWaves / 2;   // waves w and w + 4 share a SIMD: the second four run one phase behind
 
   // renumber workgroups so that consecutive ids (which go round-robin over the XCDs) of one head's
   // query blocks end up on the same XCD
   const int wg = xcd_contiguous_id(blockIdx.x, gridDim.x);
-  const int qblocks = (p.seq_len + full_rows_per_wg(1) - 1) / full_rows_per_wg(1);
+  const int qblocks = (p.seq_len + full_rows_per_wg(KS) - 1) / full_rows_per_wg(KS);
   const int qb = wg % qblocks;
   const int head = wg / qblocks;
-  const int b = head / p.hq;
-  const int h = head - b * p.hq;
-  const int g = h / p.group;
-
-  // rows past the end of the sequence compute on a copy of the last row and are not written back:
-  // every wave then runs the same program, barriers included
-  const int q_row = qb * full_rows_per_wg(1) + wave * 32 + col;
+  const int b = head / p.hq, h = head - b * p.hq, g = h / p.group;
+  // rows past the end of the sequence compute on a copy of the last row and are not written back
+  const int q_row = qb * full_rows_per_wg(KS) + rb * 32 + col;
   const bool row_valid = q_row < p.seq_len;
-  const int q_row_c = row_valid ? q_row : p.seq_len - 1;
   bf16x8 qf[8];
-  load_q_frags((const char*)p.q + 2 * (b * p.q_sb + h * p.q_sh + (int64_t)q_row_c * p.q_sr), half, qf);
+  load_q_frags((const char*)p.q + 2 * (b * p.q_sb + h * p.q_sh + (int64_t)min(q_row, p.seq_len - 1) * p.q_sr), half, qf);
 
   const char* k_base = (const char*)p.k + 2 * (b * p.k_sb + g * p.k_sh);
   const char* v_base = (const char*)p.v + 2 * (b * p.k_sb + g * p.k_sh);
   const uint32_t stride = (uint32_t)(p.k_sr * 2);
   const int n_keys = p.seq_len;
-  const int stage_keys = full_stage_tiles(1) * kTileKeys;
-  const int nstages = (n_keys + stage_keys - 1) / stage_keys;
   const int ntiles = (n_keys + kTileKeys - 1) / kTileKeys;
+  const int nsteps = (ntiles + KS - 1) / KS;                                 // step j: tiles j KS .. j KS + KS - 1, one per group
+  const int n_mine = nsteps - ((nsteps - 1) * KS + kg < ntiles ? 0 : 1);   // the last step may lack this group's tile
+
+  // A step's fetch, straight into LDS: wave w brings group w of every tile.  Rows past the last key re-read it (masked
+  // later), a step past the last one likewise.  In assembly because the compiler would make every LDS read wait for all
+  // fetches in flight; m0 is used by nothing else here.
+  typedef __attribute__((address_space(3))) uint8_t lds_u8;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_u8*)smem;
+  const uint32_t r0 = lane >> 4, place = lane & 15;
+  const uint32_t k_chunk = (place ^ (r0 & 1)) << 4, v_chunk = place << 4;
+  auto fetch = [&](const char* base, uint32_t chunk, int step, int i, int at) {
+    const uint32_t off = (uint32_t)min((step * KS + i) * kTileKeys + wave + 8 * (int)r0, n_keys - 1) * stride + chunk;
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(lds0 + (uint32_t)at), "v"(off), "s"(base) : "memory");
+  };
+  auto fetch_k = [&](int step, int slot) {
+#pragma unroll
+    for (int i = 0; i < KS; ++i) fetch(k_base, k_chunk, step, i, slot + i * kRingK + wave * kKGroup);
+  };
+  auto fetch_v = [&](int step, int slot) {
+#pragma unroll
+    for (int i = 0; i < KS; ++i) fetch(v_base, v_chunk, step, i, kV0 + slot + i * kRingV + wave * kVGroup);
+  };
+  auto rows_of = [&](int j) { return min(kTileKeys, n_keys - (j * KS + kg) * kTileKeys); };
+  const uint8_t* k_at = smem + kg * kRingK + (col & 7) * kKGroup + (col >> 3) * 256 + ((half ^ ((col >> 3) & 1)) << 4);
+  const uint8_t* v_at = smem + kV0 + kg * kRingV + (half * 4 + ((lane & 15) >> 2)) * kVGroup + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
 
   f32x16 acc[4];
 #pragma unroll
   for (int e = 0; e < 4; ++e)
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[e][i] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;
-
-  // Pipeline state between iterations: pb = softmax numerators of the current tile t (bf16), f = its V
-  // fragments, a = the K fragments of tile t+1.  Iteration t issues one MFMA block (logits of t+1, PV
-  // of t), requests the fragments the next block needs from LDS, and runs the softmax of t+1 while
-  // they arrive.  Tile t lives in stage t/2; stage s+1 is published (and the barrier met) in the even
-  // iteration 2s, after the last read of stage s (V of tile 2s+1) has been requested and before the
-  // first read of stage s+1 (K of tile 2s+2).
-  u32x4 kreg[full_stage_tiles(1)], vreg[full_stage_tiles(1)];
-  full_load_stage(k_base, v_base, stride, 0, n_keys, tid, kreg, vreg);
-  full_store_stage(smem, tid, kreg, vreg);
-  __syncthreads();
-  if (nstages > 1) full_load_stage(k_base, v_base, stride, stage_keys, n_keys, tid, kreg, vreg);
-
+  float m_run = kNoMax, l_run = 0.f;
   bf16x8 a[8], pb[2];
   PvFrags f;
   f32x16 sn;
-  tile_k_load(smem, half, col, a);
-  __builtin_amdgcn_sched_barrier(0);
-  tile_logits_mma(a, qf, sn);
-  tile_pv_load(smem + kTileBytes, lane, f);
-  if (ntiles > 1) tile_k_load(smem + kFullKvTileBytes, half, col, a);
-  __builtin_amdgcn_sched_barrier(0);
-  softmax_block(sn, min(kTileKeys, n_keys), p.scale_log2, half, m_run, l_run, acc, pb);
 
-  for (int t = 0; t + 1 < ntiles; ++t) {   // t = current tile
-    const int s = t >> 1;
-    const bool even = (t & 1) == 0;
-    const uint8_t* stage = smem + (s & 1) * full_stage_bytes(1);
-    uint8_t* next_stage = smem + ((s + 1) & 1) * full_stage_bytes(1);
+  auto in_order = [] {
+    asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
-    mfma_block(a, qf, sn, f, pb, acc);
-    __builtin_amdgcn_sched_barrier(0);
-    // V of tile t+1: second tile of stage s (its last read) or first tile of stage s+1
-    tile_pv_load((even ? stage + kFullKvTileBytes : next_stage) + kTileBytes, lane, f);
-    if (even && s + 1 < nstages) {
-      full_store_stage(next_stage, tid, kreg, vreg);
-      __syncthreads();
-      if (s + 2 < nstages) full_load_stage(k_base, v_base, stride, (s + 2) * stage_keys, n_keys, tid, kreg, vreg);
+  };
+  auto barrier = [&] {
+    in_order();
+    __builtin_amdgcn_s_barrier();
+    in_order();
+  };
+
+  // Requests are counted, in the order K(0), V(0), K(1) (with the query rows), V(1), K(2), ..., V(N-1), K(N) and then V(t+N),
+  // K(t+N+1) for t = 0, 1, ...  The empty statement uses the query rows, so that the compiler waits for them now: its wait is for
+  // everything requested by then.
+  fetch_k(0, 0);
+  fetch_v(0, 0);
+  if (nsteps > 1) fetch_k(1, kStepK);
+  in_order();
+#pragma unroll
+  for (int i = 0; i < 8; ++i) asm volatile("" : "+v"(qf[i]));
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  barrier();
+#pragma unroll
+  for (int j = 1; j < N; ++j)
+    if (j < nsteps || nsteps > 3) { if (j > 1) fetch_k(j, j * kStepK); fetch_v(j, j * kStepV); }
+  in_order();
+#pragma unroll
+  for (int i = 0; i < 8; ++i) a[i] = phase_k_frag(k_at, i);
+  tile_logits_mma(a, qf, sn);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) f.av[i >> 2][i & 3] = phase_v_frag(v_at, i);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) a[i] = phase_k_frag(k_at + kStepK, i);   // a step that is not there: read, never used
+  if (n_mine > 0) softmax_first_half(sn, rows_of(0), p.scale_log2, half, m_run, l_run, acc, pb);
+  // What the early waves read before a wait of the late ones stands between has landed: K(2), K(3), V(1), V(2).
+  if (nsteps <= 3) asm volatile("s_waitcnt lgkmcnt(0) vmcnt(0)" ::: "memory");
+  else if (KS == 1) asm volatile("s_waitcnt lgkmcnt(0) vmcnt(3)" ::: "memory");   // V(3), K(4), V(4)
+  else asm volatile("s_waitcnt lgkmcnt(0) vmcnt(2)" ::: "memory");               // V(3)
+  barrier();
+  if (nsteps > N) fetch_k(N, 0);
+  in_order();
+  if (late) barrier();
+
+  // Iteration t: matrix phase (logits of step t+1, PV of step t; reads K(t+2), V(t+1)), barrier, vector phase (softmax of step
+  // t+1), barrier.  The late waves are one phase behind: vector phase t is the last that they end before the early ones'
+  // matrix phase t+2, so what that reads, K(t+4) and V(t+3), has to have landed by then.  Requested behind those are V(t+N-1),
+  // K(t+N) (KS = 1) and V(t+N), K(t+N+1): four requests either way.  A place in a ring is fetched into in vector phase t at the
+  // earliest after the barrier that ends the late waves' vector phase t-1, at the end of which what they read there, in
+  // matrix phase t-1, is in registers.
+  static_assert(N == (KS == 1 ? 5 : 4), "the waits count on it");
+  int t = 0, v_slot = kStepV, k_slot = 2 * kStepK, v_next = 0, k_next = kStepK;   // places of V(t+1), K(t+2), V(t+N), K(t+N+1)
+  auto advance = [&](int& slot, int by) { slot = slot + by == N * by ? 0 : slot + by; };
+  auto iteration = [&](auto fetches) {
+    __builtin_amdgcn_s_setprio(1);
+    matrix_phase(a, qf, sn, f, pb, acc, k_at + k_slot, v_at + v_slot, p.scale_log2, m_run, l_run);
+    __builtin_amdgcn_s_setprio(0);
+    barrier();
+    if (fetches) {
+      fetch_v(t + N, v_next);
+      fetch_k(t + N + 1, k_next);
     }
-    // K of tile t+2: first or second tile of stage s+1
-    if (t + 2 < ntiles) tile_k_load(even ? next_stage : next_stage + kFullKvTileBytes, half, col, a);
-    __builtin_amdgcn_sched_barrier(0);
-    softmax_block(sn, min(kTileKeys, n_keys - (t + 1) * kTileKeys), p.scale_log2, half, m_run, l_run, acc, pb);
+    in_order();
+    softmax_first_half(sn, rows_of(t + 1), p.scale_log2, half, m_run, l_run, acc, pb);
+    in_order();
+    advance(v_slot, kStepV); advance(k_slot, kStepK); advance(v_next, kStepV); advance(k_next, kStepK);
+    if (fetches) asm volatile("s_waitcnt lgkmcnt(0) vmcnt(4)" ::: "memory");
+    else asm volatile("s_waitcnt lgkmcnt(0) vmcnt(0)" ::: "memory");
+    barrier();
+  };
+  for (; t + N < nsteps; ++t) iteration(std::true_type{});
+  for (; t + 1 < n_mine; ++t) iteration(std::false_type{});
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // nothing may land in LDS that is parked in, or another workgroup's
+  if (n_mine > 0) {
+    float l = 0.f;
+#pragma unroll
+    for (int r = 0; r < 8; r += 2) numerator_pair(sn, 1, r, p.scale_log2, m_run, l, pb);
+    l_run += l;
+    pv_block(f, pb, acc);
   }
-  // PV product of the last tile
-  __builtin_amdgcn_sched_barrier(0);
-  pv_block(f, pb, acc);
+  for (; t + 1 < nsteps; ++t) { barrier(); barrier(); }   // the same barriers for every group
+  if (!late) barrier();
 
   const float l_tot = l_run + __shfl_xor(l_run, 32);
-  if (row_valid) {
-    char* out_row = (char*)p.out + 2 * (b * p.o_sb + h * p.o_sh + (int64_t)q_row * p.o_sr);
-    write_wave_result(acc, m_run, l_tot, lane, half, true, out_row, nullptr, nullptr);
+  char* out_row = (char*)p.out + 2 * (b * p.o_sb + h * p.o_sh + (int64_t)q_row * p.o_sr);
+  if constexpr (KS == 1) {
+    if (row_valid) write_wave_result(acc, m_run, l_tot, lane, half, true, out_row, nullptr, nullptr);
+  } else {
+    merge_key_groups<KS>(smem, acc, m_run, l_tot, wave, lane, half, col, row_valid, out_row);
   }
 }
 
-// The same with KS = 2 or 4 key groups, for sequences whose 256-row workgroups would leave CUs idle.  Group k walks
-// tiles k, k + KS, ... through the pipeline above; all groups meet at the same barriers, one per tile, and their
-// results are merged through LDS at the end.
+// ---- four key groups: short sequences, whose 256-row workgroups would leave CUs idle
+// The tiles of four groups leave no room for rings.  A double-buffered stage of one tile per group, loaded through
+// registers; each wave alternates one block of sixteen MFMAs with the softmax, the LDS requests in between; all groups
+// meet at the same barriers, one per tile.
+constexpr int split_stage_bytes(int ks) { return ks * kFullKvTileBytes; }
+static_assert(2 * split_stage_bytes(4) >= kFullWaves * kFullParkBytes, "the accumulators are parked where the stages were");
+
 template <int KS>
 __global__ __launch_bounds__(512) void dense_split_mfma_bf16_kernel(const DenseFullParams p) {
-  constexpr int NT = full_stage_tiles(KS), RB = kFullWaves / KS, kStage = full_stage_bytes(KS);
+  constexpr int NT = KS, RB = kFullWaves / KS, kStage = split_stage_bytes(KS);
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -232,61 +407,23 @@ __global__ __launch_bounds__(512) void dense_split_mfma_bf16_kernel(const DenseF
   if (n_mine > 0) pv_block(f, pb, acc);
   for (; j + 1 < nstages; ++j) open_stage(j + 2);   // the same barriers for every group
 
-  // merge of the key groups of each row block
   const float l_tot = l_run + __shfl_xor(l_run, 32);
-  __syncthreads();                          // the stages are done with
-  uint8_t* mine = smem + wave * kFullParkBytes;
-#pragma unroll
-  for (int e = 0; e < 4; ++e)
-#pragma unroll
-    for (int i4 = 0; i4 < 4; ++i4) {
-      const f32x4 v = {acc[e][i4 * 4], acc[e][i4 * 4 + 1], acc[e][i4 * 4 + 2], acc[e][i4 * 4 + 3]};
-      *reinterpret_cast<f32x4*>(mine + lane * kRowBytes + (e * 4 + i4) * 16) = v;
-    }
-  if (lane < 32) {
-    float* ml = reinterpret_cast<float*>(mine + kWave * kRowBytes);
-    ml[lane] = m_run;
-    ml[32 + lane] = l_tot;
-  }
-  __syncthreads();
-  float f_w[KS], m_tot = -INFINITY, l_all = 0.f;
-  auto parked = [&](int k) { return smem + (k * RB + rb) * kFullParkBytes; };
-#pragma unroll
-  for (int k = 0; k < KS; ++k) {
-    f_w[k] = reinterpret_cast<const float*>(parked(k) + kWave * kRowBytes)[col];
-    m_tot = fmaxf(m_tot, f_w[k]);
-  }
-#pragma unroll
-  for (int k = 0; k < KS; ++k) {
-    f_w[k] = __builtin_amdgcn_exp2f(f_w[k] - m_tot);   // a group without tiles: 0
-    l_all += f_w[k] * reinterpret_cast<const float*>(parked(k) + kWave * kRowBytes)[32 + col];
-  }
-  const float inv = 1.f / l_all;
   char* out_row = (char*)p.out + 2 * (b * p.o_sb + h * p.o_sh + (int64_t)q_row * p.o_sr);
-#pragma unroll
-  for (int j = 0; j < 16 / KS; ++j) {
-    const int i = kg * (16 / KS) + j;
-    f32x4 o4 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int k = 0; k < KS; ++k) o4 += *reinterpret_cast<const f32x4*>(parked(k) + lane * kRowBytes + i * 16) * f_w[k];
-    bf16x4 ob;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) ob[r] = (__bf16)(o4[r] * inv);
-    if (row_valid) *reinterpret_cast<bf16x4*>(out_row + out_col0(i >> 2, i & 3, half) * 2) = ob;
-  }
+  merge_key_groups<KS>(smem, acc, m_run, l_tot, wave, lane, half, col, row_valid, out_row);
 }
 
 template <int KS>
 static hipError_t launch_full(const DenseFullParams& p, hipStream_t s) {
   static LdsOptIn lds;
+  constexpr int kLds = KS == 4 ? 2 * split_stage_bytes(KS) : phase_lds_bytes(KS);
   const auto kernel = [] {
-    if constexpr (KS == 1) return dense_full_mfma_bf16_kernel;
-    else return dense_split_mfma_bf16_kernel<KS>;
+    if constexpr (KS == 4) return dense_split_mfma_bf16_kernel<KS>;
+    else return dense_phase_mfma_bf16_kernel<KS>;
   }();
-  const hipError_t e = lds.ensure(reinterpret_cast<const void*>(kernel), full_lds_bytes(KS));
+  const hipError_t e = lds.ensure(reinterpret_cast<const void*>(kernel), kLds);
   if (e != hipSuccess) return e;
   const int qblocks = (p.seq_len + full_rows_per_wg(KS) - 1) / full_rows_per_wg(KS);
-  hipLaunchKernelGGL(kernel, dim3(qblocks * p.batch * p.hq), dim3(512), full_lds_bytes(KS), s, p);
+  hipLaunchKernelGGL(kernel, dim3(qblocks * p.batch * p.hq), dim3(512), kLds, s, p);
   return hipGetLastError();
 }
 
