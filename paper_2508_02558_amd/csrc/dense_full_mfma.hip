@@ -104,19 +104,12 @@ __device__ __forceinline__ void merge_key_groups(uint8_t* smem, const f32x16 (&a
 }
 
 // ---- one and two key groups: waves in opposite phases
-// A tile lies in LDS as eight groups of four rows (r, r + 8, r + 16, r + 24 in group r), each as one fetch instruction
-// leaves it, the groups a little more than 1 KB apart: the operand reads then need one lane address per tensor plus constants,
-// and meet no bank conflict (K: eight rows 32 bytes apart modulo 256, the 16-byte chunks of two rows of a group swapped;
-// V: four rows 64 bytes apart).
-constexpr int kKGroup = 1024 + 32, kVGroup = 1024 + 64;
-constexpr int kRingK = 8 * kKGroup, kRingV = 8 * kVGroup;   // one tile
 constexpr int phase_ring(int ks) { return ks == 1 ? 5 : 4; }   // steps held: 86 and 137 KB
 constexpr int phase_lds_bytes(int ks) {
   const int ring = phase_ring(ks) * ks * (kRingK + kRingV), parked = ks == 1 ? 0 : kFullWaves * kFullParkBytes;
   return ring > parked ? ring : parked;
 }
 
-__device__ __forceinline__ bf16x8 phase_k_frag(const uint8_t* at, int i) { return *reinterpret_cast<const bf16x8*>(at + i * 32); }
 __device__ __forceinline__ i16x8 phase_v_frag(const uint8_t* at, int i) {
   typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
   at += (i >> 2) * 512 + (i & 3) * 64;
@@ -158,7 +151,7 @@ __device__ __forceinline__ void matrix_phase(bf16x8 (&a)[8], const bf16x8 (&qf)[
   for (int i = 0; i < 8; ++i) {
     sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], qf[i], sn, 0, 0, 0);
     acc[i & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, f.av[i >> 2][i & 3]), pb[i >> 2], acc[i & 3], 0, 0, 0);
-    a[i] = phase_k_frag(k_at, i);
+    a[i] = shared_k_frag(k_at, i);
     f.av[i >> 2][i & 3] = phase_v_frag(v_at, i);
     if (i < 4) numerator_pair(s, 1, 2 * i, scale_log2, m_ref, l, pb);
     __builtin_amdgcn_sched_barrier(0);
@@ -198,16 +191,12 @@ void dense_phase_mfma_bf16_kernel(const DenseFullParams p) {
   const int nsteps = (ntiles + KS - 1) / KS;                                 // step j: tiles j KS .. j KS + KS - 1, one per group
   const int n_mine = nsteps - ((nsteps - 1) * KS + kg < ntiles ? 0 : 1);   // the last step may lack this group's tile
 
-  // A step's fetch, straight into LDS: wave w brings group w of every tile.  Rows past the last key re-read it (masked
-  // later), a step past the last one likewise.  In assembly because the compiler would make every LDS read wait for all
-  // fetches in flight; m0 is used by nothing else here.
-  typedef __attribute__((address_space(3))) uint8_t lds_u8;
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_u8*)smem;
-  const uint32_t r0 = lane >> 4, place = lane & 15;
-  const uint32_t k_chunk = (place ^ (r0 & 1)) << 4, v_chunk = place << 4;
+  // A step's fetch: wave w brings group w of every tile.  Rows past the last key re-read it (masked later), a step past the
+  // last one likewise.
+  const uint32_t lds0 = lds_address(smem), k_chunk = fetch_k_chunk(lane), v_chunk = fetch_v_chunk(lane);
   auto fetch = [&](const char* base, uint32_t chunk, int step, int i, int at) {
-    const uint32_t off = (uint32_t)min((step * KS + i) * kTileKeys + wave + 8 * (int)r0, n_keys - 1) * stride + chunk;
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(lds0 + (uint32_t)at), "v"(off), "s"(base) : "memory");
+    const int row = min((step * KS + i) * kTileKeys + wave + 8 * (lane >> 4), n_keys - 1);
+    fetch_to_lds(lds0 + (uint32_t)at, base, (uint32_t)row * stride + chunk);
   };
   auto fetch_k = [&](int step, int slot) {
 #pragma unroll
@@ -218,8 +207,8 @@ void dense_phase_mfma_bf16_kernel(const DenseFullParams p) {
     for (int i = 0; i < KS; ++i) fetch(v_base, v_chunk, step, i, kV0 + slot + i * kRingV + wave * kVGroup);
   };
   auto rows_of = [&](int j) { return min(kTileKeys, n_keys - (j * KS + kg) * kTileKeys); };
-  const uint8_t* k_at = smem + kg * kRingK + (col & 7) * kKGroup + (col >> 3) * 256 + ((half ^ ((col >> 3) & 1)) << 4);
-  const uint8_t* v_at = smem + kV0 + kg * kRingV + (half * 4 + ((lane & 15) >> 2)) * kVGroup + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
+  const uint8_t* k_at = shared_k_at(smem + kg * kRingK, half, col);
+  const uint8_t* v_at = shared_v_at(smem + kV0 + kg * kRingV, lane);
 
   f32x16 acc[4];
 #pragma unroll
@@ -231,47 +220,37 @@ void dense_phase_mfma_bf16_kernel(const DenseFullParams p) {
   PvFrags f;
   f32x16 sn;
 
-  auto in_order = [] {
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_sched_barrier(0);
-  };
-  auto barrier = [&] {
-    in_order();
-    __builtin_amdgcn_s_barrier();
-    in_order();
-  };
-
   // Requests are counted, in the order K(0), V(0), K(1) (with the query rows), V(1), K(2), ..., V(N-1), K(N) and then V(t+N),
   // K(t+N+1) for t = 0, 1, ...  The empty statement uses the query rows, so that the compiler waits for them now: its wait is for
   // everything requested by then.
   fetch_k(0, 0);
   fetch_v(0, 0);
   if (nsteps > 1) fetch_k(1, kStepK);
-  in_order();
+  in_issue_order();
 #pragma unroll
   for (int i = 0; i < 8; ++i) asm volatile("" : "+v"(qf[i]));
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  barrier();
+  bare_barrier();
 #pragma unroll
   for (int j = 1; j < N; ++j)
     if (j < nsteps || nsteps > 3) { if (j > 1) fetch_k(j, j * kStepK); fetch_v(j, j * kStepV); }
-  in_order();
+  in_issue_order();
 #pragma unroll
-  for (int i = 0; i < 8; ++i) a[i] = phase_k_frag(k_at, i);
+  for (int i = 0; i < 8; ++i) a[i] = shared_k_frag(k_at, i);
   tile_logits_mma(a, qf, sn);
 #pragma unroll
   for (int i = 0; i < 8; ++i) f.av[i >> 2][i & 3] = phase_v_frag(v_at, i);
 #pragma unroll
-  for (int i = 0; i < 8; ++i) a[i] = phase_k_frag(k_at + kStepK, i);   // a step that is not there: read, never used
+  for (int i = 0; i < 8; ++i) a[i] = shared_k_frag(k_at + kStepK, i);   // a step that is not there: read, never used
   if (n_mine > 0) softmax_first_half(sn, rows_of(0), p.scale_log2, half, m_run, l_run, acc, pb);
   // What the early waves read before a wait of the late ones stands between has landed: K(2), K(3), V(1), V(2).
   if (nsteps <= 3) asm volatile("s_waitcnt lgkmcnt(0) vmcnt(0)" ::: "memory");
   else if (KS == 1) asm volatile("s_waitcnt lgkmcnt(0) vmcnt(3)" ::: "memory");   // V(3), K(4), V(4)
   else asm volatile("s_waitcnt lgkmcnt(0) vmcnt(2)" ::: "memory");               // V(3)
-  barrier();
+  bare_barrier();
   if (nsteps > N) fetch_k(N, 0);
-  in_order();
-  if (late) barrier();
+  in_issue_order();
+  if (late) bare_barrier();
 
   // Iteration t: matrix phase (logits of step t+1, PV of step t; reads K(t+2), V(t+1)), barrier, vector phase (softmax of step
   // t+1), barrier.  The late waves are one phase behind: vector phase t is the last that they end before the early ones'
@@ -286,18 +265,18 @@ void dense_phase_mfma_bf16_kernel(const DenseFullParams p) {
     __builtin_amdgcn_s_setprio(1);
     matrix_phase(a, qf, sn, f, pb, acc, k_at + k_slot, v_at + v_slot, p.scale_log2, m_run, l_run);
     __builtin_amdgcn_s_setprio(0);
-    barrier();
+    bare_barrier();
     if (fetches) {
       fetch_v(t + N, v_next);
       fetch_k(t + N + 1, k_next);
     }
-    in_order();
+    in_issue_order();
     softmax_first_half(sn, rows_of(t + 1), p.scale_log2, half, m_run, l_run, acc, pb);
-    in_order();
+    in_issue_order();
     advance(v_slot, kStepV); advance(k_slot, kStepK); advance(v_next, kStepV); advance(k_next, kStepK);
     if (fetches) asm volatile("s_waitcnt lgkmcnt(0) vmcnt(4)" ::: "memory");
     else asm volatile("s_waitcnt lgkmcnt(0) vmcnt(0)" ::: "memory");
-    barrier();
+    bare_barrier();
   };
   for (; t + N < nsteps; ++t) iteration(std::true_type{});
   for (; t + 1 < n_mine; ++t) iteration(std::false_type{});
@@ -309,8 +288,8 @@ void dense_phase_mfma_bf16_kernel(const DenseFullParams p) {
     l_run += l;
     pv_block(f, pb, acc);
   }
-  for (; t + 1 < nsteps; ++t) { barrier(); barrier(); }   // the same barriers for every group
-  if (!late) barrier();
+  for (; t + 1 < nsteps; ++t) { bare_barrier(); bare_barrier(); }   // the same barriers for every group
+  if (!late) bare_barrier();
 
   const float l_tot = l_run + __shfl_xor(l_run, 32);
   char* out_row = (char*)p.out + 2 * (b * p.o_sb + h * p.o_sh + (int64_t)q_row * p.o_sr);

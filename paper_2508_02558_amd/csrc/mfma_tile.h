@@ -72,6 +72,50 @@ __device__ __forceinline__ void store_rows_v(uint8_t* lds_tile, int lane, const 
     *reinterpret_cast<u32x4*>(lds_tile + vtile_off(j * 4 + (lane >> 4), lane & 15)) = reg[j];
 }
 
+// ---- tiles that several waves share, fetched straight into LDS
+// A tile lies there as eight groups of four rows (r, r + 8, r + 16, r + 24 in group r), each as one fetch instruction
+// leaves it, the groups a little more than 1 KB apart: the operand reads then need one lane address per tensor plus constants,
+// and meet no bank conflict (K: eight rows 32 bytes apart modulo 256, the 16-byte chunks of two rows of a group swapped;
+// V: four rows 64 bytes apart).
+constexpr int kKGroup = 1024 + 32, kVGroup = 1024 + 64;
+constexpr int kRingK = 8 * kKGroup, kRingV = 8 * kVGroup;   // one tile
+
+// 64 lanes x 16 bytes from base + off to 1 KB of LDS at `at` (an LDS byte address, wave-uniform).  In assembly because with
+// the builtin the compiler makes every LDS read wait for all fetches in flight; the caller counts the requests.  m0 is
+// written and used here only.
+__device__ __forceinline__ void fetch_to_lds(uint32_t at, const char* base, uint32_t off) {
+  const uint64_t addr = (uint64_t)base;   // wave-uniform too; said again, as the compiler may hold it in vector registers
+  const uint64_t sbase = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)addr) |
+                         (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(addr >> 32)) << 32;
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(at), "v"(off), "s"(sbase) : "memory");
+}
+__device__ __forceinline__ uint32_t lds_address(const void* p) {
+  typedef __attribute__((address_space(3))) const uint8_t lds_u8;
+  return (uint32_t)(uintptr_t)(lds_u8*)p;
+}
+// Which 16 bytes of its row a lane of a fetch brings, and where a lane's operands of a tile begin (K operand i: 32 i bytes on).
+__device__ __forceinline__ uint32_t fetch_k_chunk(int lane) { return (uint32_t)((lane & 15) ^ ((lane >> 4) & 1)) << 4; }
+__device__ __forceinline__ uint32_t fetch_v_chunk(int lane) { return (uint32_t)(lane & 15) << 4; }
+__device__ __forceinline__ const uint8_t* shared_k_at(const uint8_t* tile, int half, int col) {
+  return tile + (col & 7) * kKGroup + (col >> 3) * 256 + ((half ^ ((col >> 3) & 1)) << 4);
+}
+__device__ __forceinline__ const uint8_t* shared_v_at(const uint8_t* tile, int lane) {
+  return tile + ((lane >> 5) * 4 + ((lane & 15) >> 2)) * kVGroup + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
+}
+__device__ __forceinline__ bf16x8 shared_k_frag(const uint8_t* at, int i) { return *reinterpret_cast<const bf16x8*>(at + i * 32); }
+
+// Memory and scheduling barrier for the compiler: what is requested before it is issued before what comes after.
+__device__ __forceinline__ void in_issue_order() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+// Workgroup barrier without the compiler's waits: the caller has waited for what the others are to see.
+__device__ __forceinline__ void bare_barrier() {
+  in_issue_order();
+  __builtin_amdgcn_s_barrier();
+  in_issue_order();
+}
+
 // Softmax reference of a row before its first key of finite logit.  Finite itself: against -inf the numerators of a tile
 // whose logits are all -inf would be exp2(-inf + inf).  Everything scaled by exp2(kNoMax - m) is zero, as with -inf.
 constexpr float kNoMax = -3.0e38f;

@@ -7,11 +7,13 @@
 //   pass 1 (row_stats): logits^T = K_tile Q_h^T, lane = query row, online (max, sum) per row;
 //   pass 2 (col_reduce): logits = Q_h K_tile^T, lane = candidate key, p = exp2(s - max)/sum summed
 //                        over the 32 rows (in registers) and over the G query heads of the group.
-// A workgroup serves one (batch, KV head) and a contiguous range of candidate tiles; its waves take
-// tiles round-robin into wave-private LDS tiles (no barrier in the loop) and the Q fragments of all G
-// heads sit in LDS once per workgroup, so K is read from HBM once per pass however large G is.
+// A workgroup serves one (batch, KV head) and a contiguous range of candidate tiles, so K is read from HBM once per
+// pass however large G is.  Its waves take tiles round-robin into wave-private LDS tiles (no barrier in the loop), the Q
+// fragments of all G heads in LDS; or, in pass 2 of grouped-query heads as a launch of its own, one head each.
 // Probabilities stay fp32 end to end: the retained set must match a float64 reference except for
 // scores within 1e-4 relative of the k-th value.
+#include <type_traits>
+
 #include "mfma_tile.h"
 
 namespace sdllm {
@@ -288,6 +290,25 @@ __global__ __launch_bounds__(512) void score_stats_mfma_kernel(const ScoreParams
 }
 
 // ------------------------------------------------------------------ pass 2: column reduction
+// (max, 1 / sum) of one row of a head from the partials of pass 1, in one sweep (there can be dozens per row and every load is
+// a trip to L2: UNROLL pairs are requested together, then folded in).
+template <int UNROLL>
+__device__ __forceinline__ float2 row_statistics(const ScoreParams& p, size_t head, int row) {
+  const float* src = p.part_ml + head * p.n_stat_part * 64 + row;
+  float m_tot = -INFINITY, l_tot = 0.f;
+#pragma unroll UNROLL
+  for (int s = 0; s < p.n_stat_part; ++s) {
+    const float m_s = src[s * 64];
+    const float l_s = src[s * 64 + 32];
+    const float m_new = fmaxf(m_tot, m_s);
+    if (m_new != -INFINITY)
+      l_tot = l_tot * __builtin_amdgcn_exp2f(m_tot - m_new) + l_s * __builtin_amdgcn_exp2f(m_s - m_new);
+    m_tot = m_new;
+  }
+  return make_float2(m_tot, 1.f / l_tot);
+}
+
+// One query head per KV head (G = 1): a wave per tile.
 template <int G>
 __global__ __launch_bounds__(512) void score_cols_mfma_kernel(const ScoreParams p) {
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
@@ -304,29 +325,173 @@ __global__ __launch_bounds__(512) void score_cols_mfma_kernel(const ScoreParams 
   // per (head, row): max (log2 domain) and 1/sum of the whole row, from the partials of pass 1
   float2* lds_ml = reinterpret_cast<float2*>(smem + (G + nw) * kTileBytes);
   stage_queries<G>(p, b, g, lds_q);
-  if (p.softmax) {
-    for (int i = threadIdx.x; i < G * 32; i += blockDim.x) {
-      const int hh = i >> 5, row = i & 31;
-      const size_t head = (size_t)b * p.hq + g * G + hh;
-      const float* src = p.part_ml + head * p.n_stat_part * 64;
-      // merge the partial (max, sum) pairs of pass 1 in one sweep (there can be dozens per row and
-      // every load is a trip to L2: sixteen pairs are requested together, then folded in)
-      float m_tot = -INFINITY, l_tot = 0.f;
-#pragma unroll 16
-      for (int s = 0; s < p.n_stat_part; ++s) {
-        const float m_s = src[s * 64 + row];
-        const float l_s = src[s * 64 + 32 + row];
-        const float m_new = fmaxf(m_tot, m_s);
-        if (m_new != -INFINITY)
-          l_tot = l_tot * __builtin_amdgcn_exp2f(m_tot - m_new) + l_s * __builtin_amdgcn_exp2f(m_s - m_new);
-        m_tot = m_new;
-      }
-      lds_ml[i] = make_float2(m_tot, 1.f / l_tot);
-    }
-  }
+  if (p.softmax)
+    for (int i = threadIdx.x; i < G * 32; i += blockDim.x) lds_ml[i] = row_statistics<16>(p, (size_t)b * p.hq + g * G + (i >> 5), i & 31);
   __syncthreads();
 
   score_columns<G, false>(p, b, g, bg, part, lds_q, lds_k, lds_ml, wave, nw, lane, half, col);
+}
+
+template <int N>
+__device__ __forceinline__ void wait_requests() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+
+// A head's query rows as fragments.
+__device__ __forceinline__ void load_head_queries(const ScoreParams& p, int b, int h, int half, int col, bf16x8 (&qf)[8]) {
+  const u32x4* qp = reinterpret_cast<const u32x4*>((const char*)p.q + 2 * (b * p.q_sb + (int64_t)h * p.q_sh + col * p.q_sr));
+#pragma unroll
+  for (int t = 0; t < 8; ++t) qf[t] = __builtin_bit_cast(bf16x8, qp[t * 2 + half]);
+}
+
+// The statistics of the rows that the registers of a lane's products belong to, 8*(i/4) + 4*half + i%4, from 32 pairs in LDS.
+__device__ __forceinline__ void rows_of_registers(const float2* ml, int half, float (&row_m)[16], float (&row_il)[16]) {
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const float2 x = ml[(i >> 2) * 8 + half * 4 + (i & 3)];
+    row_m[i] = x.x;
+    row_il[i] = x.y;
+  }
+}
+
+// ------------------------------------------------------------------ pass 2 for grouped-query heads: one wave per query head
+// With the statistics there already (the dense attention of the same step left them) or not needed, a wave takes one of the
+// G heads and keeps its 32 query rows and their statistics in registers; a tile of keys is fetched once for its G waves, into a
+// ring in LDS, and the heads' sums of a tile meet in LDS.  One more wave does the fetching and the writing of the scores, so that
+// the others, which meet at a barrier per tile, have nothing else between two barriers.
+// Against a wave per tile that walks the heads: a third of the LDS reads (a tile's keys once per head instead of the head's
+// queries and statistics once per tile: 0.5 us per tile and head on eight waves), and one round trip at the start instead of
+// four, as queries, statistics and the first tiles are requested together.  Kernel, 28/4 heads: 4320 candidates 11.0 -> 6.2 us,
+// 33 248 18.5 -> 15.0; whole cache-update step, 3 x 28/4 x 1200 positions 31.1 -> 26.6, 8 x 28/4 x 4600 77.9 -> 75.8, 4 x 32/8 x
+// 1500 34.7 -> 33.3, 2 x 16/2 x 3000 33.1 -> 27.0, 8 x 8/4 x 5000 level.
+constexpr int heads_streams(int g) { return g <= 4 ? 2 : 1; }       // tiles worked on side by side
+constexpr int heads_ring(int g) { return g <= 4 ? 4 : 6; }          // tiles of a stream in LDS
+constexpr int heads_waves(int g) { return g * heads_streams(g); }   // and the one that fetches and writes
+constexpr int heads_ring_bytes(int g) { return heads_streams(g) * heads_ring(g) * kRingK; }
+constexpr int heads_lds_bytes(int g) { return heads_ring_bytes(g) + heads_waves(g) * (32 * 8 + 2 * 64 * 4); }
+
+template <int G>
+__global__ __launch_bounds__((heads_waves(G) + 1) * kWave) void score_cols_heads_kernel(const ScoreParams p, const int tiles_per_wg) {
+  constexpr int T = heads_streams(G), R = heads_ring(G), W = heads_waves(G);
+  extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int half = lane >> 5, col = lane & 31;
+  const int bg = blockIdx.y, b = bg / p.hkv, g = bg - b * p.hkv;
+
+  const CandTiles ct = cand_tiles(p, b, g);
+  const int ntiles = ct.tiles0 + (ct.n1 + kTileKeys - 1) / kTileKeys;
+  const int t0 = blockIdx.x * tiles_per_wg, t1 = min(ntiles, t0 + tiles_per_wg);   // not empty: launch_heads
+  const int nsteps = (t1 - t0 + T - 1) / T;                                        // step j: tiles t0 + T j + stream
+
+  float2* ml = reinterpret_cast<float2*>(smem + heads_ring_bytes(G));               // [W][32] (max, 1 / sum) of a head's rows
+  float* sums = reinterpret_cast<float*>(smem + heads_ring_bytes(G) + W * 32 * 8);   // [2][W][64] a tile's sums, per head and lane
+
+  if (wave == W) {
+    const uint32_t ring_at = lds_address(smem), k_chunk = fetch_k_chunk(lane);
+    auto fetch = [&](int j) {
+#pragma unroll
+      for (int st = 0; st < T; ++st) {
+        int rows, cand0;
+        const char* base = tile_rows(ct, min(t0 + T * j + st, t1 - 1), rows, cand0);   // past the end the last tile again, which is not written
+#pragma unroll
+        for (int c = 0; c < 8; ++c)
+          fetch_to_lds(ring_at + (uint32_t)((st * R + j % R) * kRingK + c * kKGroup), base,
+                       (uint32_t)min(c + 8 * (lane >> 4), rows - 1) * ct.stride + k_chunk);
+      }
+    };
+    float* score_row = p.score + (size_t)bg * p.score_stride;
+    const float inv_count = 1.f / (float)(G * 32);
+    auto write = [&](int j) {   // the scores of step j: a half-lane per stream
+      const int tile = t0 + T * j + half;
+      int rows, cand0;
+      tile_rows(ct, min(tile, t1 - 1), rows, cand0);
+      if (half >= T || tile >= t1 || col >= rows) return;
+      const float* part = sums + ((j & 1) * W + half * G) * 64 + col;
+      float total = 0.f;
+#pragma unroll
+      for (int k = 0; k < G; ++k) total += part[k * 64] + part[k * 64 + 32];
+      score_row[cand0 + col] = total * inv_count;
+    };
+    for (int j = 0; j < R - 1; ++j)
+      if (j < nsteps) fetch(j);
+    in_issue_order();
+    wait_requests<0>();
+    bare_barrier();                        // tiles 0 .. R-2 are there
+    for (int j = 0; j < nsteps; ++j) {
+      bare_barrier();                      // tile j is in the others' registers, the sums of step j-1 are written
+      if (j + R - 1 < nsteps) fetch(j + R - 1);
+      in_issue_order();
+      if (j > 0) write(j - 1);
+      in_issue_order();
+      // tile j+2, which is read behind the next barrier, has landed; behind it are at most R - 3 tiles and a few scores
+      if (j + R - 1 < nsteps) wait_requests<(R - 3) * 8 * T>();
+      else wait_requests<0>();
+    }
+    bare_barrier();
+    write(nsteps - 1);
+    return;
+  }
+
+  const int hh = wave % G, stream = wave / G, h = g * G + hh;
+  bf16x8 qf[8];
+  load_head_queries(p, b, h, half, col, qf);
+  float row_m[16], row_il[16];
+  if (p.softmax) {
+    const float2 x = row_statistics<8>(p, (size_t)b * p.hq + h, col);
+    if (half == 0) ml[wave * 32 + col] = x;
+    wave_lds_sync();
+    rows_of_registers(ml + wave * 32, half, row_m, row_il);
+  }
+
+  // Step j: products of tile j, whose operands are in registers, requests for those of tile j + 1, then tile j's weights.
+  const uint8_t* k_at = shared_k_at(smem + stream * R * kRingK, half, col);
+  float* my_sum = sums + wave * 64 + lane;
+  bf16x8 kf[8];
+  bare_barrier();
+#pragma unroll
+  for (int i = 0; i < 8; ++i) kf[i] = shared_k_frag(k_at, i);
+  int slot = kRingK;                       // of tile j + 1
+  for (int j = 0; j < nsteps; ++j) {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    bare_barrier();
+    f32x16 sc;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) sc[i] = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[i], kf[i], sc, 0, 0, 0);   // rows = queries, columns = keys
+#pragma unroll
+    for (int i = 0; i < 8; ++i) kf[i] = shared_k_frag(k_at + slot, i);   // behind the last step: read, not used
+    slot = slot + kRingK == R * kRingK ? 0 : slot + kRingK;
+    __builtin_amdgcn_sched_barrier(0);
+    float total = 0.f;
+    if (p.softmax) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) total += __builtin_amdgcn_exp2f(__builtin_fmaf(sc[i], p.scale_log2, -row_m[i])) * row_il[i];
+    } else {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) total += sc[i];
+      total *= p.scale;
+    }
+    my_sum[(j & 1) * W * 64] = total;
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  bare_barrier();
+}
+
+template <int G>
+static hipError_t launch_heads(const ScoreParams& p, hipStream_t s) {
+  static LdsOptIn lds;
+  const auto kernel = score_cols_heads_kernel<G>;
+  const hipError_t e = lds.ensure(reinterpret_cast<const void*>(kernel), heads_lds_bytes(G));
+  if (e != hipSuccess) return e;
+  const int n0 = p.n_cand < p.block_off ? p.n_cand : p.block_off, n1 = p.n_cand - n0;
+  const int tiles = (n0 + kTileKeys - 1) / kTileKeys + (n1 + kTileKeys - 1) / kTileKeys;
+  const int rows = p.batch * p.hkv;
+  int parts = kNumCUs / rows;              // a workgroup per CU (two: the whole step 0 to 10 % slower below 32 rows, level above)
+  if (parts < 1) parts = 1;
+  const int per_wg = (tiles + parts - 1) / parts;
+  parts = (tiles + per_wg - 1) / per_wg;   // none empty
+  hipLaunchKernelGGL(kernel, dim3(parts, rows), dim3((heads_waves(G) + 1) * kWave), heads_lds_bytes(G), s, p, per_wg);
+  return hipGetLastError();
 }
 
 static size_t score_lds_bytes(int group, int waves) { return (size_t)(group + waves) * kTileBytes + (size_t)group * 32 * 8; }
@@ -334,21 +499,27 @@ static size_t score_lds_bytes(int group, int waves) { return (size_t)(group + wa
 template <int G>
 static hipError_t launch_g(const ScoreParams& p, hipStream_t s) {
   const size_t lds = score_lds_bytes(G, p.waves);
-  static LdsOptIn lds_stats, lds_cols;
   const int max_lds = (int)score_lds_bytes(G, kMaxWavesPerWg);
-  hipError_t e = lds_stats.ensure(reinterpret_cast<const void*>(score_stats_mfma_kernel<G>), max_lds);
-  if (e != hipSuccess) return e;
-  e = lds_cols.ensure(reinterpret_cast<const void*>(score_cols_mfma_kernel<G>), max_lds);
-  if (e != hipSuccess) return e;
   const dim3 grid(p.n_part, p.batch * p.hkv), block(p.waves * kWave);
   if (p.softmax && !p.skip_stats) {
+    static LdsOptIn lds_stats;
+    const hipError_t e = lds_stats.ensure(reinterpret_cast<const void*>(score_stats_mfma_kernel<G>), max_lds);
+    if (e != hipSuccess) return e;
     ScoreParams q = p;
     q.cols_follow = p.n_part == 1;   // statistics final inside the workgroup: one launch does both passes
     hipLaunchKernelGGL(score_stats_mfma_kernel<G>, grid, block, lds, s, q);
-    if (q.cols_follow) return hipGetLastError();
+    const hipError_t launched = hipGetLastError();
+    if (launched != hipSuccess || q.cols_follow) return launched;
   }
-  hipLaunchKernelGGL(score_cols_mfma_kernel<G>, grid, block, lds, s, p);
-  return hipGetLastError();
+  if constexpr (G > 1) {
+    return launch_heads<G>(p, s);
+  } else {
+    static LdsOptIn lds_cols;
+    const hipError_t e = lds_cols.ensure(reinterpret_cast<const void*>(score_cols_mfma_kernel<G>), max_lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(score_cols_mfma_kernel<G>, grid, block, lds, s, p);
+    return hipGetLastError();
+  }
 }
 
 bool score_mfma_supports_group(int group) { return group >= 1 && group <= 8; }

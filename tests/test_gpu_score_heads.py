@@ -1,0 +1,58 @@
+"""Column pass of the scoring with a wave per query head: every group size, step counts from one to beyond the ring of tiles in
+LDS, ragged last tiles on both sides of the block, candidates on one side only, streams without a tile of their own.
+Tolerance: a score sums at most 256 logits or weights in fp32, each from a 128-term fp32 dot product of bf16 values (error
+about 2^-24 * sqrt(128 * 256) of its size, 1e-5 with a factor of five)."""
+import math
+
+import pytest
+import torch
+
+from paper_2508_02558_amd import binding as B
+from paper_2508_02558_amd import workloads as wl
+from tests.test_gpu_parity import _run_block
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def _reference(q, k, group, off, softmax):
+    keys = torch.cat([k[:, :, :off], k[:, :, off + 32:]], 2).double()
+    out = []
+    for g in range(k.shape[1]):
+        a = q[:, g * group:(g + 1) * group].double().flatten(1, 2) @ keys[:, g].transpose(1, 2) / math.sqrt(128)
+        out.append((torch.softmax(a, -1) if softmax else a).mean(1))
+    return torch.stack(out, 1)
+
+
+@pytest.mark.parametrize("batch,q_heads,kv_heads,L,off", [
+    (1, 4, 2, 33, 0), (1, 4, 2, 97, 32), (2, 6, 2, 800, 415), (1, 8, 2, 1056, 1024), (1, 5, 1, 230, 31), (1, 6, 1, 2090, 700),
+    (1, 7, 1, 64, 32), (1, 7, 1, 65, 1), (1, 14, 2, 4300, 2111), (8, 28, 4, 700, 333), (3, 8, 1, 3001, 0), (2, 16, 2, 7001, 6000),
+    (70, 8, 4, 500, 100),                                          # more rows than CUs: a workgroup walks all tiles
+])
+@pytest.mark.parametrize("mode", [B.SDLLM_LOGIT_MEAN, B.SDLLM_SOFTMAX_MEAN])
+def test_scores_of_grouped_heads(batch, q_heads, kv_heads, L, off, mode):
+    print(f"[case] score heads B={batch} {q_heads}/{kv_heads} L={L} off={off} mode={mode}", flush=True)
+    torch.manual_seed(L + off)
+    q = (2.0 * torch.randn(batch, q_heads, 32, 128, device=DEV)).bfloat16()
+    k = torch.randn(batch, kv_heads, L, 128, device=DEV).bfloat16()
+    shape = B.make_shape(batch=batch, n_q_heads=q_heads, n_kv_heads=kv_heads, head_dim=128, seq_len=L, block_off=off, block_len=32,
+                         dtype=B.SDLLM_BF16, score_mode=mode)
+    kt = B.sdllm_retained_count(shape)[0]
+    idx = torch.zeros(batch, kv_heads, kt, dtype=torch.int32, device=DEV)
+    pooled, score = (torch.full((batch, kv_heads, L - 32), float("nan"), device=DEV) for _ in range(2))
+    ws = torch.empty(B.sdllm_workspace_bytes(shape, B.SDLLM_OP_SCORE_SELECT), dtype=torch.uint8, device=DEV)
+    B.sdllm_score_select(shape, q, k, idx, pooled, score, ws)
+    torch.cuda.synchronize()
+    ref = _reference(q, k, q_heads // kv_heads, off, mode == B.SDLLM_SOFTMAX_MEAN)
+    err = (score.double() - ref).norm() / ref.norm()
+    assert err < 1e-5, f"relative error {err:.2e}"
+
+
+# With the statistics left by the dense attention (key splits or not, one or two kernels): index sets and cache against the oracle.
+@pytest.mark.parametrize("q_heads,kv_heads,batch,prompt,modes", [
+    (4, 2, 1, 70, {}), (6, 2, 2, 333, {}), (8, 2, 1, 1500, {}), (10, 2, 1, 64, {}), (12, 2, 1, 701, {}), (14, 2, 1, 2600, {}),
+    (16, 2, 3, 300, {}), (28, 4, 2, 900, dict(evict_scope=B.SDLLM_EVICT_PREFIX_ONLY)),
+])
+def test_cache_update_with_grouped_heads(q_heads, kv_heads, batch, prompt, modes):
+    w = wl.WORKLOADS["dream7b_gqa"].scaled(batch=batch, n_q_heads=q_heads, n_kv_heads=kv_heads, prompt=prompt, gen=160)
+    _run_block(w, block_index=1, n_steps=3, **modes)
