@@ -22,9 +22,14 @@
 
 namespace sdllm {
 
-constexpr int kWaveLds = kTileBytes + kVTileBytes + 512;    // K tile, V tile (later: 64 lanes x 272 B of accumulators), (max, sum)
+constexpr int kWaveLds = kTileBytes + kVTileBytes;    // K tile, V tile; later 64 lanes x 272 B of accumulators and 512 B of (max, sum)
+static_assert(kWaveLds >= 64 * kRowBytes + 512 && kVTileBytes >= kRingK, "what shares a wave's LDS");
 
-size_t attn_mfma_lds_bytes(int waves) { return (size_t)waves * kWaveLds; }
+// Whether the queries have LDS of their own: where a CU holds one workgroup anyway.  With two or four to a CU they come by
+// way of wave 0's V tile.
+__host__ __device__ inline bool queries_apart(int waves, int wgs) { return waves > 4 || wgs <= kNumCUs; }
+
+static size_t attn_mfma_lds_bytes(int waves, int wgs) { return (size_t)waves * kWaveLds + (queries_apart(waves, wgs) ? kRingK : 0); }
 
 // NSEG = 2: keys are Concat(cache, block) (sparse step); NSEG = 1: one key tensor (dense step, or a
 // sparse step with an empty cache).  The two instantiations also show up as separate kernels in a
@@ -39,7 +44,12 @@ size_t attn_mfma_lds_bytes(int waves) { return (size_t)waves * kWaveLds; }
 // with plain loads by the statistics launches: the scoring that follows (the column sweep at the end of
 // this kernel, or the scoring kernel) reads the same rows again and finds part of them in L2 and the
 // memory-side cache (B=8 LLaDA shape, cache-update step: 234 -> 226 us).
-template <int NSEG, bool STATS, bool DEEP, bool SHARED_KV, bool BY_SPLIT>
+// SHARED_Q: the query rows come once per workgroup, through LDS.  As fragments that every wave loads from memory they are 32
+// rows x 32 bytes an instruction and keep the CU's address path from the first keys for about 1 us (28 heads x 69 tiles in 8
+// splits 11.4 -> 11.0 us, 32 x 21 in 3 10.1 -> 9.6, 336 x 11 11.2 -> 10.1, dense rows of 96 heads x 72 24.8 -> 23.6).  Multi-head calls
+// without key splits stay with the fragments: the barrier that the other way takes holds their waves' streams together
+// (64 heads x 21 tiles 11.5 against 11.8 us, 224 x 8 8.7 against 9.0, 256 x 69 45.1 against 45.3).
+template <int NSEG, bool STATS, bool DEEP, bool SHARED_KV, bool BY_SPLIT, bool SHARED_Q>
 __global__ __launch_bounds__(512) void attn_mfma_bf16_kernel(const AttnParams p) {
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
   const int lane = threadIdx.x & 63;
@@ -68,7 +78,10 @@ __global__ __launch_bounds__(512) void attn_mfma_bf16_kernel(const AttnParams p)
 
   // Q^T fragments (B operand): lane (col = query row, half) holds head-dim [16t + 8 half, +8)
   bf16x8 qf[8];
-  load_q_frags((const char*)p.q + 2 * (b * p.q_sb + h * p.q_sh + col * p.q_sr), half, qf);
+  const bool q_apart = queries_apart(nw, gridDim.x);
+  uint8_t* lds_q = smem + (q_apart ? nw * kWaveLds : kTileBytes);
+  if (SHARED_Q) request_queries(p, b, h, lds_address(lds_q), wave, nw, lane);
+  else load_q_frags((const char*)p.q + 2 * (b * p.q_sb + h * p.q_sh + col * p.q_sr), half, qf);
 
   uint8_t* lds_k = smem + wave * kWaveLds;
   uint8_t* lds_v = lds_k + kTileBytes;
@@ -94,6 +107,19 @@ __global__ __launch_bounds__(512) void attn_mfma_bf16_kernel(const AttnParams p)
     ts = tile_src(sp, t, stride);
     load_rows<!(SHARED_KV || STATS)>(ts.k, ts.rows, stride, lane, reg);
     if (DEEP) load_rows<!SHARED_KV>(ts.v, ts.rows, stride, lane, reinterpret_cast<u32x4(&)[8]>(reg2));
+  }
+  if (SHARED_Q) {
+    in_issue_order();   // the queries are there when only the first tile's requests are left
+    if (t >= t_end) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    else if (DEEP) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+    bare_barrier();
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) qf[kk] = shared_k_frag(shared_k_at(lds_q, half, col), kk);
+    if (!q_apart) {     // before wave 0's V tile goes there
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      bare_barrier();
+    }
   }
 
   for (; t < t_end; t += nw) {
@@ -324,15 +350,15 @@ __global__ __launch_bounds__(512) void attn_mfma_bf16_kernel(const AttnParams p)
   }
 }
 
-template <int NSEG, bool STATS, bool DEEP, bool SHARED_KV, bool BY_SPLIT = false>
+template <int NSEG, bool STATS, bool DEEP, bool SHARED_KV, bool SHARED_Q, bool BY_SPLIT = false>
 static hipError_t launch_variant(const AttnParams& p, hipStream_t s) {
   const int nwg = p.batch * p.hq * p.n_split;
   static LdsOptIn lds;
-  const hipError_t e = lds.ensure(reinterpret_cast<const void*>(attn_mfma_bf16_kernel<NSEG, STATS, DEEP, SHARED_KV, BY_SPLIT>),
-                                  (int)attn_mfma_lds_bytes(kMaxWavesPerWg));
+  const hipError_t e = lds.ensure(reinterpret_cast<const void*>(attn_mfma_bf16_kernel<NSEG, STATS, DEEP, SHARED_KV, BY_SPLIT, SHARED_Q>),
+                                  (int)attn_mfma_lds_bytes(kMaxWavesPerWg, 0));
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((attn_mfma_bf16_kernel<NSEG, STATS, DEEP, SHARED_KV, BY_SPLIT>), dim3(nwg), dim3(p.waves * kWave),
-                     attn_mfma_lds_bytes(p.waves), s, p);
+  hipLaunchKernelGGL((attn_mfma_bf16_kernel<NSEG, STATS, DEEP, SHARED_KV, BY_SPLIT, SHARED_Q>), dim3(nwg), dim3(p.waves * kWave),
+                     attn_mfma_lds_bytes(p.waves, nwg), s, p);
   return hipGetLastError();
 }
 
@@ -346,9 +372,10 @@ static hipError_t launch_nseg(const AttnParams& p, hipStream_t s) {
   // -> 36.5), longer dense rows 1 to 4 % (28 x 700 tiles 31.2 -> 30.2).
   if constexpr (!STATS)
     if (p.group > 1 && !deep && p.n_split > 1 && p.tiles_per_split >= 24 && (NSEG == 2 || p.tiles_per_split < 40))
-      return launch_variant<NSEG, false, false, true, true>(p, s);
-  if (p.group > 1) return deep ? launch_variant<NSEG, STATS, true, true>(p, s) : launch_variant<NSEG, STATS, false, true>(p, s);
-  return deep ? launch_variant<NSEG, STATS, true, false>(p, s) : launch_variant<NSEG, STATS, false, false>(p, s);
+      return launch_variant<NSEG, false, false, true, true, true>(p, s);
+  if (p.group > 1) return deep ? launch_variant<NSEG, STATS, true, true, true>(p, s) : launch_variant<NSEG, STATS, false, true, true>(p, s);
+  if (p.n_split > 1) return deep ? launch_variant<NSEG, STATS, true, false, true>(p, s) : launch_variant<NSEG, STATS, false, false, true>(p, s);
+  return deep ? launch_variant<NSEG, STATS, true, false, false>(p, s) : launch_variant<NSEG, STATS, false, false, false>(p, s);
 }
 
 hipError_t launch_attn_mfma_bf16(const AttnParams& p, hipStream_t s) {

@@ -84,6 +84,17 @@ __device__ __forceinline__ void read_v_frags(const uint8_t* tile, int lane, PvFr
   for (int i = 0; i < 8; ++i) f.av[i >> 2][i & 3] = __builtin_shufflevector(r[2 * i], r[2 * i + 1], 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
+__device__ __forceinline__ void read_q_frags(uint32_t at, int half, int col, bf16x8 (&q)[8]) {
+  at += (uint32_t)((col & 7) * kKGroup + (col >> 3) * 256 + ((half ^ ((col >> 3) & 1)) << 4));
+  asm volatile(
+      "ds_read_b128 %0, %8\n\tds_read_b128 %1, %8 offset:32\n\tds_read_b128 %2, %8 offset:64\n\tds_read_b128 %3, %8 offset:96\n\t"
+      "ds_read_b128 %4, %8 offset:128\n\tds_read_b128 %5, %8 offset:160\n\tds_read_b128 %6, %8 offset:192\n\t"
+      "ds_read_b128 %7, %8 offset:224\n\ts_waitcnt lgkmcnt(0)"
+      : "=&v"(q[0]), "=&v"(q[1]), "=&v"(q[2]), "=&v"(q[3]), "=&v"(q[4]), "=&v"(q[5]), "=&v"(q[6]), "=&v"(q[7])
+      : "v"(at)
+      : "memory");
+}
+
 template <int NSEG, bool STATS, bool TOUCH>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attn_stream_mfma_bf16_kernel(const AttnParams p) {
@@ -174,15 +185,24 @@ void attn_stream_mfma_bf16_kernel(const AttnParams p) {
     wave_lds_sync();
   };
 
-  bf16x8 qf[8];
-  load_q_frags((const char*)p.q + 2 * (b * p.q_sb + h * p.q_sh + col * p.q_sr), half, qf);
+  // The query rows come once per workgroup, through LDS: as fragments straight from memory (32 rows x 32 bytes an
+  // instruction, the same for every wave) they kept the CU's address path from the first keys for about 1 us (8 heads x 11
+  // tiles 7.25 -> 6.5 us, 84 x 21 9.55 -> 8.45, 224 x 73 23.9 -> 22.7).
+  const uint32_t q_lds = lds_address(smem) + (uint32_t)(nw * kStreamWaveLds);
+  request_queries(p, b, h, q_lds, wave, nw, lane);
+  in_order();
   if (n_mine > 0) {
-    in_order();
     fetch_k(0);
     in_order();
     fetch_v(0);
     in_order();
+    asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+  } else {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   }
+  bare_barrier();
+  bf16x8 qf[8];
+  read_q_frags(q_lds, half, col, qf);
 
   f32x16 acc[4];
 #pragma unroll
@@ -349,10 +369,10 @@ template <int NSEG, bool STATS, bool TOUCH>
 static hipError_t launch_touch(const AttnParams& p, hipStream_t s) {
   static LdsOptIn lds;
   const auto kernel = attn_stream_mfma_bf16_kernel<NSEG, STATS, TOUCH>;
-  const hipError_t e = lds.ensure(reinterpret_cast<const void*>(kernel), kMaxWavesPerWg * kStreamWaveLds);
+  const hipError_t e = lds.ensure(reinterpret_cast<const void*>(kernel), kMaxWavesPerWg * kStreamWaveLds + kRingK);
   if (e != hipSuccess) return e;
   if (p.waves < 1 || p.waves > kMaxWavesPerWg) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(kernel, dim3(p.n_split * p.batch * p.hq), dim3(p.waves * kWave), p.waves * kStreamWaveLds, s, p);
+  hipLaunchKernelGGL(kernel, dim3(p.n_split * p.batch * p.hq), dim3(p.waves * kWave), p.waves * kStreamWaveLds + kRingK, s, p);
   return hipGetLastError();
 }
 

@@ -24,6 +24,13 @@ __device__ __forceinline__ void load_q_frags(const char* q_row, int half, bf16x8
   }
 }
 
+// The 32 query rows of a head to LDS, as a K tile of mfma_tile.h lies there: the waves of a workgroup share the eight requests.
+__device__ __forceinline__ void request_queries(const AttnParams& p, int b, int h, uint32_t lds_at, int wave, int nw, int lane) {
+  for (int c = wave; c < 8; c += nw)
+    fetch_to_lds(lds_at + (uint32_t)(c * kKGroup),
+                 (const char*)p.q + 2 * (b * p.q_sb + h * p.q_sh + (c + 8 * (lane >> 4)) * p.q_sr) + fetch_k_chunk(lane));
+}
+
 // The eight K fragments (A operands) of one tile, all requested together.
 __device__ __forceinline__ void tile_k_load(const uint8_t* lds_k, int half, int col, bf16x8 (&a)[8]) {
 #pragma unroll

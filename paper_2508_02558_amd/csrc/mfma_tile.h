@@ -89,6 +89,10 @@ __device__ __forceinline__ void fetch_to_lds(uint32_t at, const char* base, uint
                          (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(addr >> 32)) << 32;
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(at), "v"(off), "s"(sbase) : "memory");
 }
+// The same from an address per lane.
+__device__ __forceinline__ void fetch_to_lds(uint32_t at, const char* lane_src) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(at), "v"(lane_src) : "memory");
+}
 __device__ __forceinline__ uint32_t lds_address(const void* p) {
   typedef __attribute__((address_space(3))) const uint8_t lds_u8;
   return (uint32_t)(uintptr_t)(lds_u8*)p;
