@@ -107,7 +107,7 @@ __device__ __forceinline__ void merge_key_groups(uint8_t* smem, const f32x16 (&a
 constexpr int phase_ring(int ks) { return ks == 1 ? 5 : 4; }   // steps held: 86 and 137 KB
 constexpr int phase_lds_bytes(int ks) {
   const int ring = phase_ring(ks) * ks * (kRingK + kRingV), parked = ks == 1 ? 0 : kFullWaves * kFullParkBytes;
-  return ring > parked ? ring : parked;
+  return ks == 1 ? ring + kFullWaves * kRingK : ring > parked ? ring : parked;
 }
 
 __device__ __forceinline__ i16x8 phase_v_frag(const uint8_t* at, int i) {
@@ -180,8 +180,18 @@ void dense_phase_mfma_bf16_kernel(const DenseFullParams p) {
   // rows past the end of the sequence compute on a copy of the last row and are not written back
   const int q_row = qb * full_rows_per_wg(KS) + rb * 32 + col;
   const bool row_valid = q_row < p.seq_len;
+  // With one key group the query rows come whole rows at a time, through LDS of the wave's own (there is none left with two)
   bf16x8 qf[8];
-  load_q_frags((const char*)p.q + 2 * (b * p.q_sb + h * p.q_sh + (int64_t)min(q_row, p.seq_len - 1) * p.q_sr), half, qf);
+  [[maybe_unused]] uint8_t* lds_q = smem + phase_ring(1) * (kRingK + kRingV) + wave * kRingK;
+  if constexpr (KS == 1) {
+#pragma unroll
+    for (int c = 0; c < 8; ++c)
+      fetch_to_lds(lds_address(lds_q) + (uint32_t)(c * kKGroup),
+                   (const char*)p.q + 2 * (b * p.q_sb + h * p.q_sh + (int64_t)min(q_row - col + c + 8 * (lane >> 4), p.seq_len - 1) * p.q_sr) +
+                       fetch_k_chunk(lane));
+  } else {
+    load_q_frags((const char*)p.q + 2 * (b * p.q_sb + h * p.q_sh + (int64_t)min(q_row, p.seq_len - 1) * p.q_sr), half, qf);
+  }
 
   const char* k_base = (const char*)p.k + 2 * (b * p.k_sb + g * p.k_sh);
   const char* v_base = (const char*)p.v + 2 * (b * p.k_sb + g * p.k_sh);
@@ -221,15 +231,21 @@ void dense_phase_mfma_bf16_kernel(const DenseFullParams p) {
   f32x16 sn;
 
   // Requests are counted, in the order K(0), V(0), K(1) (with the query rows), V(1), K(2), ..., V(N-1), K(N) and then V(t+N),
-  // K(t+N+1) for t = 0, 1, ...  The empty statement uses the query rows, so that the compiler waits for them now: its wait is for
-  // everything requested by then.
+  // K(t+N+1) for t = 0, 1, ...  The empty statement (KS = 2) uses the query rows, so that the compiler waits for them now: its wait
+  // is for everything requested by then.
   fetch_k(0, 0);
   fetch_v(0, 0);
   if (nsteps > 1) fetch_k(1, kStepK);
   in_issue_order();
+  if constexpr (KS > 1) {
 #pragma unroll
-  for (int i = 0; i < 8; ++i) asm volatile("" : "+v"(qf[i]));
+    for (int i = 0; i < 8; ++i) asm volatile("" : "+v"(qf[i]));
+  }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  if constexpr (KS == 1) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) qf[i] = shared_k_frag(shared_k_at(lds_q, half, col), i);
+  }
   bare_barrier();
 #pragma unroll
   for (int j = 1; j < N; ++j)

@@ -80,18 +80,21 @@ __device__ __forceinline__ void store_rows_v(uint8_t* lds_tile, int lane, const 
 constexpr int kKGroup = 1024 + 32, kVGroup = 1024 + 64;
 constexpr int kRingK = 8 * kKGroup, kRingV = 8 * kVGroup;   // one tile
 
-// 64 lanes x 16 bytes from base + off to 1 KB of LDS at `at` (an LDS byte address, wave-uniform).  In assembly because with
+// 64 lanes x 16 bytes from base + off to 1 KB of LDS at `at` (an LDS byte address; it and base wave-uniform).  In assembly because with
 // the builtin the compiler makes every LDS read wait for all fetches in flight; the caller counts the requests.  m0 is
 // written and used here only.
 __device__ __forceinline__ void fetch_to_lds(uint32_t at, const char* base, uint32_t off) {
-  const uint64_t addr = (uint64_t)base;   // wave-uniform too; said again, as the compiler may hold it in vector registers
-  const uint64_t sbase = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)addr) |
-                         (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(addr >> 32)) << 32;
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(at), "v"(off), "s"(sbase) : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(at), "v"(off), "s"(base) : "memory");
 }
 // The same from an address per lane.
 __device__ __forceinline__ void fetch_to_lds(uint32_t at, const char* lane_src) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(at), "v"(lane_src) : "memory");
+}
+// A wave-uniform address in scalar registers, where the compiler would keep it in vector registers.
+__device__ __forceinline__ const char* in_scalars(const char* p) {
+  const uint64_t a = (uint64_t)p;
+  return (const char*)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)a) |
+                       (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(a >> 32)) << 32);
 }
 __device__ __forceinline__ uint32_t lds_address(const void* p) {
   typedef __attribute__((address_space(3))) const uint8_t lds_u8;

@@ -335,13 +335,6 @@ __global__ __launch_bounds__(512) void score_cols_mfma_kernel(const ScoreParams 
 template <int N>
 __device__ __forceinline__ void wait_requests() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 
-// A head's query rows as fragments.
-__device__ __forceinline__ void load_head_queries(const ScoreParams& p, int b, int h, int half, int col, bf16x8 (&qf)[8]) {
-  const u32x4* qp = reinterpret_cast<const u32x4*>((const char*)p.q + 2 * (b * p.q_sb + (int64_t)h * p.q_sh + col * p.q_sr));
-#pragma unroll
-  for (int t = 0; t < 8; ++t) qf[t] = __builtin_bit_cast(bf16x8, qp[t * 2 + half]);
-}
-
 // The statistics of the rows that the registers of a lane's products belong to, 8*(i/4) + 4*half + i%4, from 32 pairs in LDS.
 __device__ __forceinline__ void rows_of_registers(const float2* ml, int half, float (&row_m)[16], float (&row_il)[16]) {
 #pragma unroll
@@ -366,7 +359,7 @@ constexpr int heads_streams(int g) { return g <= 4 ? 2 : 1; }       // tiles wor
 constexpr int heads_ring(int g) { return g <= 4 ? 4 : 6; }          // tiles of a stream in LDS
 constexpr int heads_waves(int g) { return g * heads_streams(g); }   // and the one that fetches and writes
 constexpr int heads_ring_bytes(int g) { return heads_streams(g) * heads_ring(g) * kRingK; }
-constexpr int heads_lds_bytes(int g) { return heads_ring_bytes(g) + heads_waves(g) * (32 * 8 + 2 * 64 * 4); }
+constexpr int heads_lds_bytes(int g) { return heads_ring_bytes(g) + heads_waves(g) * (32 * 8 + 2 * 64 * 4 + kRingK); }
 
 template <int G>
 __global__ __launch_bounds__((heads_waves(G) + 1) * kWave) void score_cols_heads_kernel(const ScoreParams p, const int tiles_per_wg) {
@@ -391,7 +384,8 @@ __global__ __launch_bounds__((heads_waves(G) + 1) * kWave) void score_cols_heads
 #pragma unroll
       for (int st = 0; st < T; ++st) {
         int rows, cand0;
-        const char* base = tile_rows(ct, min(t0 + T * j + st, t1 - 1), rows, cand0);   // past the end the last tile again, which is not written
+        // past the end the last tile again, which is not written
+        const char* base = in_scalars(tile_rows(ct, min(t0 + T * j + st, t1 - 1), rows, cand0));
 #pragma unroll
         for (int c = 0; c < 8; ++c)
           fetch_to_lds(ring_at + (uint32_t)((st * R + j % R) * kRingK + c * kKGroup), base,
@@ -432,8 +426,12 @@ __global__ __launch_bounds__((heads_waves(G) + 1) * kWave) void score_cols_heads
   }
 
   const int hh = wave % G, stream = wave / G, h = g * G + hh;
-  bf16x8 qf[8];
-  load_head_queries(p, b, h, half, col, qf);
+  // the head's query rows, whole rows at a time through LDS of the wave's own
+  uint8_t* lds_q = smem + heads_ring_bytes(G) + W * (32 * 8 + 2 * 64 * 4) + wave * kRingK;
+#pragma unroll
+  for (int c = 0; c < 8; ++c)
+    fetch_to_lds(lds_address(lds_q) + (uint32_t)(c * kKGroup),
+                 (const char*)p.q + 2 * (b * p.q_sb + (int64_t)h * p.q_sh + (c + 8 * (lane >> 4)) * p.q_sr) + fetch_k_chunk(lane));
   float row_m[16], row_il[16];
   if (p.softmax) {
     const float2 x = row_statistics<8>(p, (size_t)b * p.hq + h, col);
@@ -441,6 +439,12 @@ __global__ __launch_bounds__((heads_waves(G) + 1) * kWave) void score_cols_heads
     wave_lds_sync();
     rows_of_registers(ml + wave * 32, half, row_m, row_il);
   }
+
+  wait_requests<0>();
+  wave_lds_sync();
+  bf16x8 qf[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) qf[i] = shared_k_frag(shared_k_at(lds_q, half, col), i);
 
   // Step j: products of tile j, whose operands are in registers, requests for those of tile j + 1, then tile j's weights.
   const uint8_t* k_at = shared_k_at(smem + stream * R * kRingK, half, col);
