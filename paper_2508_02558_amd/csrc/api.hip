@@ -363,13 +363,11 @@ int32_t run_attn(const sdllm_shape_t& s, const void* q, const KvSegment& a, cons
   hipError_t e;
   if (pl.mfma) {
     e = pl.stream ? launch_attn_stream_mfma_bf16(p, stream) : pl.gqa ? launch_attn_gqa_mfma_bf16(p, stream) : launch_attn_mfma_bf16(p, stream);
-    if (deferred) *deferred = p;
-    if (e == hipSuccess && pl.n_split > 1 && !deferred) e = launch_attn_combine(p, s.dtype, stream);
   } else {
     e = launch_attn_general(p, s.dtype, false, stream);
-    if (deferred) deferred->n_split = 1;
-    if (e == hipSuccess && pl.n_split > 1) e = launch_attn_combine(p, s.dtype, stream);
   }
+  if (deferred) *deferred = p;
+  if (e == hipSuccess && pl.n_split > 1 && !deferred) e = launch_attn_combine(p, s.dtype, stream);
   return e == hipSuccess ? SDLLM_OK : SDLLM_ERR_HIP;
 }
 
@@ -557,7 +555,8 @@ int32_t compact_params(const sdllm_shape_t& s, const void* k_full, const void* v
 }
 
 // With split keys at the cache-update step the merge of the splits runs in the compaction's launch, so
-// the attention partials stay alive through scoring and selection: those then work behind them (score_off).
+// the attention partials stay alive through scoring and selection: those then work behind them (score_off).  Also for
+// the general kernels: 2 x 32 heads, block of 64, 1280 positions 41.3 -> 39.7 us, 2 x 8 of head_dim 64, 1200 positions 24.3 -> 21.7.
 struct BlockStepWs { size_t base, stats_bytes, score_off; int stats_parts; bool fuse, fuse_cols; };
 
 
@@ -568,7 +567,7 @@ BlockStepWs plan_block_step(const sdllm_shape_t& s) {
   const AttnPlan sparse = plan_attn(s, c.k_total, s.cache_stride[2], s.block_len, s.blk_stride[2]);
   const ScorePlan sc = plan_score(s);
   BlockStepWs w{};
-  w.score_off = dense.mfma && dense.n_split > 1 && c.k_total > 0 ? align_up(dense.ws_bytes()) : 0;
+  w.score_off = dense.n_split > 1 && c.k_total > 0 ? align_up(dense.ws_bytes()) : 0;
   w.base = dense.ws_bytes();
   if (full.ws_bytes() > w.base) w.base = full.ws_bytes();
   if (sparse.ws_bytes() > w.base) w.base = sparse.ws_bytes();
@@ -781,7 +780,7 @@ int32_t sdllm_block_step(const sdllm_shape_t* shape, int32_t step_in_block, int3
   if (pending.n_split == 1) return sdllm_compact_kv(shape, k_in, v_in, idx, k_cache, v_cache, stream);
   CompactParams cp{};
   if ((st = compact_params(s, k_in, v_in, idx, k_cache, v_cache, cp)) != SDLLM_OK) return finish_pending(st);
-  return launch_compact_combine(cp, pending, (hipStream_t)stream) == hipSuccess ? SDLLM_OK : SDLLM_ERR_HIP;
+  return launch_compact_combine(cp, pending, s.dtype, (hipStream_t)stream) == hipSuccess ? SDLLM_OK : SDLLM_ERR_HIP;
 }
 
 int32_t sdllm_dense_attn(const sdllm_shape_t* shape, const void* q_full, const int64_t* q_full_stride,

@@ -62,11 +62,11 @@ __device__ __forceinline__ void compact_block(const CompactParams& p, int64_t bl
 
 __global__ __launch_bounds__(kCompactThreads) void compact_kernel(const CompactParams p) { compact_block(p, blockIdx.x); }
 
-// blocks [0, n_combine): split-KV merge of the attention described by `a` (bf16 output); the rest: the gather
-template <int TPI>
+// blocks [0, n_combine): split-KV merge of the attention described by `a` (output of type T); the rest: the gather
+template <typename T, int TPI>
 __global__ __launch_bounds__(kCompactThreads) void compact_combine_kernel(const CompactParams p, const AttnParams a,
                                                                           const int n_combine) {
-  if ((int)blockIdx.x < n_combine) combine_block<__bf16, TPI>(a, blockIdx.x);
+  if ((int)blockIdx.x < n_combine) combine_block<T, TPI>(a, blockIdx.x);
   else compact_block(p, (int64_t)blockIdx.x - n_combine);
 }
 
@@ -84,14 +84,17 @@ hipError_t launch_compact(const CompactParams& p, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_compact_combine(const CompactParams& p, const AttnParams& a, hipStream_t s) {
+template <typename T>
+static hipError_t launch_compact_combine_t(const CompactParams& p, const AttnParams& a, hipStream_t s) {
   const int64_t n_combine = combine_blocks(a);
   const int64_t blocks = n_combine + compact_blocks(p);
-  if (combine_tpi(a.n_split) == 4)
-    hipLaunchKernelGGL(compact_combine_kernel<4>, dim3((unsigned)blocks), dim3(kCompactThreads), 0, s, p, a, (int)n_combine);
-  else
-    hipLaunchKernelGGL(compact_combine_kernel<1>, dim3((unsigned)blocks), dim3(kCompactThreads), 0, s, p, a, (int)n_combine);
+  const auto kernel = combine_tpi(a.n_split) == 4 ? compact_combine_kernel<T, 4> : compact_combine_kernel<T, 1>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kCompactThreads), 0, s, p, a, (int)n_combine);
   return hipGetLastError();
+}
+
+hipError_t launch_compact_combine(const CompactParams& p, const AttnParams& a, int dtype, hipStream_t s) {
+  return dtype == 0 ? launch_compact_combine_t<__bf16>(p, a, s) : launch_compact_combine_t<float>(p, a, s);
 }
 
 }  // namespace sdllm

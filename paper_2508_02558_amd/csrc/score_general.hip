@@ -44,6 +44,19 @@ __global__ __launch_bounds__(kColWaves * kWave) void score_cols_general_kernel(c
   float* score_row = p.score + (size_t)bg * p.score_stride;
   const float inv_count = 1.f / (float)(p.group * p.nq);
 
+  // one candidate tile: first row, valid rows and candidates before it; its rows are requested
+  u32x4 kreg[O::kLoads];
+  int rows = 0, cand0 = 0;
+  auto request = [&](int t) {
+    const bool suf = t >= tiles0;
+    const int first = (suf ? t - tiles0 : t) * kTileKeys;
+    rows = min(kTileKeys, (suf ? n1 : n0) - first);
+    cand0 = (suf ? n0 : 0) + first;
+    g_load_rows<O, false>(k_base + (int64_t)(suf ? p.block_off + p.block_len + first : first) * stride, rows, stride, lane, kreg);
+  };
+  const int t_first = blockIdx.x * kColWaves + wave;
+  if (t_first < ntiles) request(t_first);   // flies while the queries are staged
+
   for (int blk0 = 0; blk0 < n_blk; blk0 += kBlocks) {
     const int here = min(kBlocks, n_blk - blk0);
     if (blk0) __syncthreads();   // the previous blocks are done with
@@ -70,13 +83,8 @@ __global__ __launch_bounds__(kColWaves * kWave) void score_cols_general_kernel(c
       }
     }
     __syncthreads();
-    for (int t = blockIdx.x * kColWaves + wave; t < ntiles; t += step) {
-      const bool suf = t >= tiles0;
-      const int first = (suf ? t - tiles0 : t) * kTileKeys;
-      const int rows = min(kTileKeys, (suf ? n1 : n0) - first), cand0 = (suf ? n0 : 0) + first;
-      const char* src = k_base + (int64_t)(suf ? p.block_off + p.block_len + first : first) * stride;
-      u32x4 kreg[O::kLoads];
-      g_load_rows<O, false>(src, rows, stride, lane, kreg);
+    for (int t = t_first; t < ntiles; t += step) {
+      if (blk0 > 0 || t > t_first) request(t);
       g_store_rows<O>(lds_k, O::kKRow, lane, kreg);
       wave_lds_sync();
       typename O::KTile keys;

@@ -194,3 +194,17 @@ def test_tiles_of_infinitely_low_keys(dtype, d, block, n_cached):
     B.sdllm_sparse_attn(shape, q, kc, vc, n_cached, kb, vb, out, ws)
     torch.cuda.synchronize()
     U.assert_close(out, U.oracle_attention_batch(q, torch.cat([kc[:, :, kept], kb], 2), torch.cat([vc[:, :, kept], vb], 2)), dtype, "kept keys")
+
+
+# Cache-update steps whose key splits are merged in the compaction's launch: both types, row blocks that are not full, more than
+# one block of rows per head, no softmax in the score.
+@pytest.mark.parametrize("dtype,d,block,q_heads,kv_heads,batch,prompt,modes", [
+    ("bf16", 128, 64, 8, 8, 1, 1300, {}), ("bf16", 128, 24, 14, 2, 1, 900, {}), ("bf16", 64, 32, 4, 2, 1, 1500, {}),
+    ("bf16", 128, 48, 4, 4, 2, 1200, dict(score_mode=B.SDLLM_LOGIT_MEAN)), ("f32", 64, 32, 4, 4, 1, 700, {}), ("f32", 128, 17, 4, 2, 2, 600, {}),
+    ("f32", 64, 64, 2, 2, 1, 800, dict(evict_scope=B.SDLLM_EVICT_PREFIX_ONLY)),
+])
+def test_update_steps_merge_their_splits_with_the_compaction(dtype, d, block, q_heads, kv_heads, batch, prompt, modes):
+    w = wl.WORKLOADS["llada8b_layer"].scaled(dtype=dtype, head_dim=d, block=block, n_q_heads=q_heads, n_kv_heads=kv_heads,
+                                             batch=batch, prompt=prompt, gen=4 * block)
+    assert B.sdllm_launch_plan(U.shape_for(w, 1, **modes), B.SDLLM_CALL_UPDATE).key_splits > 1
+    _run_block(w, block_index=1, n_steps=3, **modes)
