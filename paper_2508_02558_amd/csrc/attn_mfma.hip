@@ -80,7 +80,7 @@ __global__ __launch_bounds__(512) void attn_mfma_bf16_kernel(const AttnParams p)
   bf16x8 qf[8];
   const bool q_apart = queries_apart(nw, gridDim.x);
   uint8_t* lds_q = smem + (q_apart ? nw * kWaveLds : kTileBytes);
-  if (SHARED_Q) request_queries(p, b, h, lds_address(lds_q), wave, nw, lane);
+  if (SHARED_Q) request_queries<false>(p, b, h, lds_q, wave, nw, lane);
   else load_q_frags((const char*)p.q + 2 * (b * p.q_sb + h * p.q_sh + col * p.q_sr), half, qf);
 
   uint8_t* lds_k = smem + wave * kWaveLds;

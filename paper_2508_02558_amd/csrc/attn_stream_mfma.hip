@@ -188,8 +188,8 @@ void attn_stream_mfma_bf16_kernel(const AttnParams p) {
   // The query rows come once per workgroup, through LDS: as fragments straight from memory (32 rows x 32 bytes an
   // instruction, the same for every wave) they kept the CU's address path from the first keys for about 1 us (8 heads x 11
   // tiles 7.25 -> 6.5 us, 84 x 21 9.55 -> 8.45, 224 x 73 23.9 -> 22.7).
-  const uint32_t q_lds = lds_address(smem) + (uint32_t)(nw * kStreamWaveLds);
-  request_queries(p, b, h, q_lds, wave, nw, lane);
+  uint8_t* q_lds = smem + nw * kStreamWaveLds;
+  request_queries<true>(p, b, h, q_lds, wave, nw, lane);
   in_order();
   if (n_mine > 0) {
     fetch_k(0);
@@ -202,7 +202,7 @@ void attn_stream_mfma_bf16_kernel(const AttnParams p) {
   }
   bare_barrier();
   bf16x8 qf[8];
-  read_q_frags(q_lds, half, col, qf);
+  read_q_frags(lds_address(q_lds), half, col, qf);
 
   f32x16 acc[4];
 #pragma unroll

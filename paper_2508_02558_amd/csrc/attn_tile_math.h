@@ -25,10 +25,16 @@ __device__ __forceinline__ void load_q_frags(const char* q_row, int half, bf16x8
 }
 
 // The 32 query rows of a head to LDS, as a K tile of mfma_tile.h lies there: the waves of a workgroup share the eight requests.
-__device__ __forceinline__ void request_queries(const AttnParams& p, int b, int h, uint32_t lds_at, int wave, int nw, int lane) {
-  for (int c = wave; c < 8; c += nw)
-    fetch_to_lds(lds_at + (uint32_t)(c * kKGroup),
-                 (const char*)p.q + 2 * (b * p.q_sb + h * p.q_sh + (c + 8 * (lane >> 4)) * p.q_sr) + fetch_k_chunk(lane));
+// BUILTIN: in a kernel that fetches its tiles with the builtin, where the compiler keeps m0 itself.
+template <bool BUILTIN>
+__device__ __forceinline__ void request_queries(const AttnParams& p, int b, int h, uint8_t* lds_at, int wave, int nw, int lane) {
+  typedef __attribute__((address_space(1))) const void gvoid;
+  typedef __attribute__((address_space(3))) void lvoid;
+  for (int c = wave; c < 8; c += nw) {
+    const char* src = (const char*)p.q + 2 * (b * p.q_sb + h * p.q_sh + (c + 8 * (lane >> 4)) * p.q_sr) + fetch_k_chunk(lane);
+    if constexpr (BUILTIN) __builtin_amdgcn_global_load_lds((gvoid*)src, (lvoid*)(lds_at + c * kKGroup), 16, 0, 0);
+    else fetch_to_lds(lds_address(lds_at) + (uint32_t)(c * kKGroup), src);
+  }
 }
 
 // The eight K fragments (A operands) of one tile, all requested together.
