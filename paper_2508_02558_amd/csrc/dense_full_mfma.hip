@@ -15,7 +15,8 @@
 //     of tile t), the LDS reads of the next operands and half of tile t's exponentials between them, the other
 //     finds its row maxima and does the first half of its exponentials: 1600 cycles per pair (28 heads x 1181
 //     positions 38.5 -> 36.0 us, x 735 with two key groups 19.2 -> 17.5; 256 heads x 4352 2450 -> 2350 us, where the clock
-//     falls as the pipes fill: 1.97 GHz at 1790 cycles, 1.82 at 1600).  The start costs 0.3 us more (below 10 tiles);
+//     falls as the pipes fill: 1.97 GHz at 1790 cycles, 1.82 at 1600).  The start costs 0.3 us more, so that sequences of up to
+//     eight tiles go without (kStagedKeys);
 //   * the query-block workgroups of one head (and of the G heads of a KV group) are adjacent in the
 //     grid and, after the XCD renumbering, share an L2.
 #include <type_traits>
@@ -104,7 +105,10 @@ __device__ __forceinline__ void merge_key_groups(uint8_t* smem, const f32x16 (&a
 }
 
 // ---- one and two key groups: waves in opposite phases
+// For sequences of more steps than the rings hold, that is beyond this many positions (why there: launch_dense_full_mfma_bf16).
+constexpr int kStagedKeys = 256;
 constexpr int phase_ring(int ks) { return ks == 1 ? 5 : 4; }   // steps held: 86 and 137 KB
+static_assert((kStagedKeys / kTileKeys + 1) > phase_ring(1) && (kStagedKeys / kTileKeys + 2) / 2 > phase_ring(2), "the prologue fills the rings");
 constexpr int phase_lds_bytes(int ks) {
   const int ring = phase_ring(ks) * ks * (kRingK + kRingV), parked = ks == 1 ? 0 : kFullWaves * kFullParkBytes;
   return ks == 1 ? ring + kFullWaves * kRingK : ring > parked ? ring : parked;
@@ -198,7 +202,7 @@ void dense_phase_mfma_bf16_kernel(const DenseFullParams p) {
   const uint32_t stride = (uint32_t)(p.k_sr * 2);
   const int n_keys = p.seq_len;
   const int ntiles = (n_keys + kTileKeys - 1) / kTileKeys;
-  const int nsteps = (ntiles + KS - 1) / KS;                                 // step j: tiles j KS .. j KS + KS - 1, one per group
+  const int nsteps = (ntiles + KS - 1) / KS;                                 // step j: tiles j KS .. j KS + KS - 1, one per group; > N
   const int n_mine = nsteps - ((nsteps - 1) * KS + kg < ntiles ? 0 : 1);   // the last step may lack this group's tile
 
   // A step's fetch: wave w brings group w of every tile.  Rows past the last key re-read it (masked later), a step past the
@@ -235,7 +239,7 @@ void dense_phase_mfma_bf16_kernel(const DenseFullParams p) {
   // is for everything requested by then.
   fetch_k(0, 0);
   fetch_v(0, 0);
-  if (nsteps > 1) fetch_k(1, kStepK);
+  fetch_k(1, kStepK);
   in_issue_order();
   if constexpr (KS > 1) {
 #pragma unroll
@@ -248,8 +252,10 @@ void dense_phase_mfma_bf16_kernel(const DenseFullParams p) {
   }
   bare_barrier();
 #pragma unroll
-  for (int j = 1; j < N; ++j)
-    if (j < nsteps || nsteps > 3) { if (j > 1) fetch_k(j, j * kStepK); fetch_v(j, j * kStepV); }
+  for (int j = 1; j < N; ++j) {
+    if (j > 1) fetch_k(j, j * kStepK);
+    fetch_v(j, j * kStepV);
+  }
   in_issue_order();
 #pragma unroll
   for (int i = 0; i < 8; ++i) a[i] = shared_k_frag(k_at, i);
@@ -257,14 +263,13 @@ void dense_phase_mfma_bf16_kernel(const DenseFullParams p) {
 #pragma unroll
   for (int i = 0; i < 8; ++i) f.av[i >> 2][i & 3] = phase_v_frag(v_at, i);
 #pragma unroll
-  for (int i = 0; i < 8; ++i) a[i] = shared_k_frag(k_at + kStepK, i);   // a step that is not there: read, never used
-  if (n_mine > 0) softmax_first_half(sn, rows_of(0), p.scale_log2, half, m_run, l_run, acc, pb);
+  for (int i = 0; i < 8; ++i) a[i] = shared_k_frag(k_at + kStepK, i);
+  softmax_first_half(sn, rows_of(0), p.scale_log2, half, m_run, l_run, acc, pb);
   // What the early waves read before a wait of the late ones stands between has landed: K(2), K(3), V(1), V(2).
-  if (nsteps <= 3) asm volatile("s_waitcnt lgkmcnt(0) vmcnt(0)" ::: "memory");
-  else if (KS == 1) asm volatile("s_waitcnt lgkmcnt(0) vmcnt(3)" ::: "memory");   // V(3), K(4), V(4)
-  else asm volatile("s_waitcnt lgkmcnt(0) vmcnt(2)" ::: "memory");               // V(3)
+  if (KS == 1) asm volatile("s_waitcnt lgkmcnt(0) vmcnt(3)" ::: "memory");   // V(3), K(4), V(4)
+  else asm volatile("s_waitcnt lgkmcnt(0) vmcnt(2)" ::: "memory");           // V(3)
   bare_barrier();
-  if (nsteps > N) fetch_k(N, 0);
+  fetch_k(N, 0);
   in_issue_order();
   if (late) bare_barrier();
 
@@ -297,13 +302,11 @@ void dense_phase_mfma_bf16_kernel(const DenseFullParams p) {
   for (; t + N < nsteps; ++t) iteration(std::true_type{});
   for (; t + 1 < n_mine; ++t) iteration(std::false_type{});
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // nothing may land in LDS that is parked in, or another workgroup's
-  if (n_mine > 0) {
-    float l = 0.f;
+  float l = 0.f;
 #pragma unroll
-    for (int r = 0; r < 8; r += 2) numerator_pair(sn, 1, r, p.scale_log2, m_run, l, pb);
-    l_run += l;
-    pv_block(f, pb, acc);
-  }
+  for (int r = 0; r < 8; r += 2) numerator_pair(sn, 1, r, p.scale_log2, m_run, l, pb);
+  l_run += l;
+  pv_block(f, pb, acc);
   for (; t + 1 < nsteps; ++t) { bare_barrier(); bare_barrier(); }   // the same barriers for every group
   if (!late) bare_barrier();
 
@@ -316,16 +319,20 @@ void dense_phase_mfma_bf16_kernel(const DenseFullParams p) {
   }
 }
 
-// ---- four key groups: short sequences, whose 256-row workgroups would leave CUs idle
-// The tiles of four groups leave no room for rings.  A double-buffered stage of one tile per group, loaded through
-// registers; each wave alternates one block of sixteen MFMAs with the softmax, the LDS requests in between; all groups
-// meet at the same barriers, one per tile.
-constexpr int split_stage_bytes(int ks) { return ks * kFullKvTileBytes; }
-static_assert(2 * split_stage_bytes(4) >= kFullWaves * kFullParkBytes, "the accumulators are parked where the stages were");
+// ---- short sequences: stages loaded through registers
+// Two stages in LDS, of two tiles (KS = 1) or one tile per group; each wave alternates one block of sixteen MFMAs with the
+// softmax, the LDS requests in between; a barrier per stage, at which all groups meet.  Always with four key groups, whose
+// tiles leave no room for rings.
+constexpr int split_stage_tiles(int ks) { return ks == 1 ? 2 : ks; }
+constexpr int split_stage_bytes(int ks) { return split_stage_tiles(ks) * kFullKvTileBytes; }
+constexpr int split_lds_bytes(int ks) {
+  const int stages = 2 * split_stage_bytes(ks), parked = ks == 1 ? 0 : kFullWaves * kFullParkBytes;   // where the stages were
+  return stages > parked ? stages : parked;
+}
 
 template <int KS>
 __global__ __launch_bounds__(512) void dense_split_mfma_bf16_kernel(const DenseFullParams p) {
-  constexpr int NT = KS, RB = kFullWaves / KS, kStage = split_stage_bytes(KS);
+  constexpr int NT = split_stage_tiles(KS), T = NT / KS, RB = kFullWaves / KS, kStage = split_stage_bytes(KS);   // T tiles of a group
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -340,8 +347,9 @@ __global__ __launch_bounds__(512) void dense_split_mfma_bf16_kernel(const DenseF
   const int b = head / p.hq, h = head - b * p.hq, g = h / p.group;
   const int q_row = qb * full_rows_per_wg(KS) + rb * 32 + col;
   const bool row_valid = q_row < p.seq_len;
-  bf16x8 qf[8];
-  load_q_frags((const char*)p.q + 2 * (b * p.q_sb + h * p.q_sh + (int64_t)min(q_row, p.seq_len - 1) * p.q_sr), half, qf);
+  bf16x8 qf[8] = {};
+  if (KS > 1 || q_row - col < p.seq_len)   // of eight row blocks a short sequence leaves up to seven without rows: they ask for none
+    load_q_frags((const char*)p.q + 2 * (b * p.q_sb + h * p.q_sh + (int64_t)min(q_row, p.seq_len - 1) * p.q_sr), half, qf);
 
   const char* k_base = (const char*)p.k + 2 * (b * p.k_sb + g * p.k_sh);
   const char* v_base = (const char*)p.v + 2 * (b * p.k_sb + g * p.k_sh);
@@ -349,9 +357,9 @@ __global__ __launch_bounds__(512) void dense_split_mfma_bf16_kernel(const DenseF
   const int n_keys = p.seq_len;
   const int ntiles = (n_keys + kTileKeys - 1) / kTileKeys;
   const int nstages = (ntiles + NT - 1) / NT;
-  const int n_mine = nstages - ((nstages - 1) * NT + kg < ntiles ? 0 : 1);   // the last stage may lack this group's tile
-  auto tile_lds = [&](int j) { return smem + (j & 1) * kStage + kg * kFullKvTileBytes; };
-  auto rows_of = [&](int j) { return min(kTileKeys, n_keys - (j * NT + kg) * kTileKeys); };
+  const int n_mine = (ntiles - kg + KS - 1) / KS;                           // tiles kg, kg + KS, ...: the last stage may lack one
+  auto tile_lds = [&](int j) { return smem + (j / T & 1) * kStage + (kg + j % T * KS) * kFullKvTileBytes; };
+  auto rows_of = [&](int j) { return min(kTileKeys, n_keys - (j * KS + kg) * kTileKeys); };
 
   f32x16 acc[4];
 #pragma unroll
@@ -369,18 +377,19 @@ __global__ __launch_bounds__(512) void dense_split_mfma_bf16_kernel(const DenseF
   bf16x8 a[8], pb[2];
   PvFrags f;
   f32x16 sn;
-  // Publishes stage j: its buffer held stage j-2, whose last read every wave had requested, and waited for, before the
-  // barrier of stage j-1.
-  auto open_stage = [&](int j) {
-    if (j >= nstages) return;
-    full_store_stage<NT>(smem + (j & 1) * kStage, tid, kreg, vreg);
+  // Publishes stage s: its buffer held stage s-2, whose last read every wave had requested, and waited for, before the
+  // barrier of stage s-1.
+  auto open_stage = [&](int s) {
+    if (s >= nstages) return;
+    full_store_stage<NT>(smem + (s & 1) * kStage, tid, kreg, vreg);
     __syncthreads();
-    if (j + 1 < nstages) full_load_stage<NT>(k_base, v_base, stride, (j + 1) * NT * kTileKeys, n_keys, tid, kreg, vreg);
+    if (s + 1 < nstages) full_load_stage<NT>(k_base, v_base, stride, (s + 1) * NT * kTileKeys, n_keys, tid, kreg, vreg);
   };
-  // tile j's logits are in sn: request V(j), open the next stage, request K(j+1), then the softmax of tile j
+  // tile j's logits are in sn: request V(j), open the next stage if tile j was this one's last, request K(j+1), then the
+  // softmax of tile j
   auto after_logits = [&](int j) {
     if (j < n_mine) tile_pv_load(tile_lds(j) + kTileBytes, lane, f);
-    open_stage(j + 1);
+    if ((j + 1) % T == 0) open_stage((j + 1) / T);
     if (j + 1 < n_mine) tile_k_load(tile_lds(j + 1), half, col, a);
     __builtin_amdgcn_sched_barrier(0);
     if (j < n_mine) softmax_block(sn, rows_of(j), p.scale_log2, half, m_run, l_run, acc, pb);
@@ -400,20 +409,25 @@ __global__ __launch_bounds__(512) void dense_split_mfma_bf16_kernel(const DenseF
     after_logits(j + 1);
   }
   if (n_mine > 0) pv_block(f, pb, acc);
-  for (; j + 1 < nstages; ++j) open_stage(j + 2);   // the same barriers for every group
+  if constexpr (KS > 1)
+    for (; j + 1 < nstages; ++j) open_stage(j + 2);   // the same barriers for every group
 
   const float l_tot = l_run + __shfl_xor(l_run, 32);
   char* out_row = (char*)p.out + 2 * (b * p.o_sb + h * p.o_sh + (int64_t)q_row * p.o_sr);
-  merge_key_groups<KS>(smem, acc, m_run, l_tot, wave, lane, half, col, row_valid, out_row);
+  if constexpr (KS == 1) {
+    if (row_valid) write_wave_result(acc, m_run, l_tot, lane, half, true, out_row, nullptr, nullptr);
+  } else {
+    merge_key_groups<KS>(smem, acc, m_run, l_tot, wave, lane, half, col, row_valid, out_row);
+  }
 }
 
-template <int KS>
+template <int KS, bool PHASE>
 static hipError_t launch_full(const DenseFullParams& p, hipStream_t s) {
   static LdsOptIn lds;
-  constexpr int kLds = KS == 4 ? 2 * split_stage_bytes(KS) : phase_lds_bytes(KS);
+  constexpr int kLds = PHASE ? phase_lds_bytes(KS) : split_lds_bytes(KS);
   const auto kernel = [] {
-    if constexpr (KS == 4) return dense_split_mfma_bf16_kernel<KS>;
-    else return dense_phase_mfma_bf16_kernel<KS>;
+    if constexpr (PHASE) return dense_phase_mfma_bf16_kernel<KS>;
+    else return dense_split_mfma_bf16_kernel<KS>;
   }();
   const hipError_t e = lds.ensure(reinterpret_cast<const void*>(kernel), kLds);
   if (e != hipSuccess) return e;
@@ -440,12 +454,16 @@ int dense_full_key_groups(int heads, int seq_len) {
   return best;
 }
 
+// Up to kStagedKeys positions one or two key groups load their stages through registers as well: locked phases cost half an iteration at the
+// start and pay it back from some ten tiles on, and a wave without rows still fetches its share of the rings and of the queries.
+// Phases / stages: 28 heads x 32 positions 4.07 / 3.60 us, x 64 5.49 / 4.82, x 96 6.76 / 6.55; 224 x 224 16.8 / 16.3; 256 x 128 11.65 /
+// 11.08, x 256 20.7 / 20.3; two groups, 128 x 256 13.62 / 13.31.  Beyond, where 256-row workgroups come in twos: 256 x 288 34.9 / 35.2,
+// 28 x 735 with two groups 17.6 / 19.2.
 hipError_t launch_dense_full_mfma_bf16(const DenseFullParams& p, hipStream_t s) {
-  switch (dense_full_key_groups(p.batch * p.hq, p.seq_len)) {
-    case 2: return launch_full<2>(p, s);
-    case 4: return launch_full<4>(p, s);
-    default: return launch_full<1>(p, s);
-  }
+  const int ks = dense_full_key_groups(p.batch * p.hq, p.seq_len);
+  if (ks == 4) return launch_full<4, false>(p, s);
+  if (p.seq_len <= kStagedKeys) return ks == 2 ? launch_full<2, false>(p, s) : launch_full<1, false>(p, s);
+  return ks == 2 ? launch_full<2, true>(p, s) : launch_full<1, true>(p, s);
 }
 
 }  // namespace sdllm
