@@ -436,20 +436,24 @@ static hipError_t launch_full(const DenseFullParams& p, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Key groups per workgroup: what a workgroup takes for its tiles (us, fitted to 1 to 8 x 8 to 32 heads, 65 to 2049
-// positions), times the rounds in which the CUs, one workgroup each, go through the grid.  28 heads: 200 positions
-// 12.2 -> 8.5 us (4 groups), 400 18.1 -> 11.0 (4), 735 26.1 -> 19.2 (2); 24 heads x 1277 39.6 -> 28.6 (2); 8 heads x 1277
-// 38.8 -> 18.9 (4).  28 heads x 1277 stay whole: 280 half workgroups need a second round (53.8 against 39.8 us).
+// Key groups per workgroup: what a workgroup takes for its tiles (us), times the rounds in which the CUs, one workgroup each, go
+// through the grid.  The costs are fitted to the kernels on either side of kStagedKeys.  Beyond it (4 to 512 heads, 257 to 2049
+// positions, 1 / 2 / 4 groups): 28 heads x 735 24.2 / 17.8 / 26.4 us, 8 x 1277 35.4 / 23.3 / 19.0, 8 x 2049 53.1 / 33.2 / 52.7, 24 x
+// 1277 37.3 / 27.5 / 37.6, 56 x 1277 78.7 / 74.7 / 91.0; 28 x 1277 stay whole, as 280 half workgroups need a second round (37.7 /
+// 48.7 / 54.8).  The choice is the fastest of the three or within 1 % of it at 645 of 665 sizes, within 8 % at the others.  Up to
+// kStagedKeys 28 x 192 10.6 / 9.7 / 7.9; the fit misses up to a fifth with five tiles (28 x 160 9.4 / 9.4 / 7.9).
 int dense_full_key_groups(int heads, int seq_len) {
   const int tiles = (seq_len + kTileKeys - 1) / kTileKeys;
+  const bool rings = seq_len > kStagedKeys;
   int best = 1;
   double least = 0;
   for (int ks = 1; ks <= 4; ks *= 2) {
     const int64_t wgs = (int64_t)((seq_len + full_rows_per_wg(ks) - 1) / full_rows_per_wg(ks)) * heads;
     const int64_t rounds = (wgs + kNumCUs - 1) / kNumCUs;
     const int mine = (tiles + ks - 1) / ks;
-    const double us = (double)rounds * (ks == 1 ? 4.3 + 0.9 * mine : ks == 2 ? 6.2 + 1.08 * mine : 5.8 + 1.3 * mine);
-    if (ks == 1 || us < 0.95 * least) { best = ks; least = us; }
+    const double us = (double)rounds * (rings ? (ks == 1 ? 10.2 + 0.76 * mine : ks == 2 ? 8.9 + 0.86 * mine : 4.9 + 1.49 * mine)
+                                              : (ks == 1 ? 4.3 + 0.9 * mine : ks == 2 ? 6.2 + 1.08 * mine : 5.8 + 1.3 * mine));
+    if (ks == 1 || us < (rings ? 0.97 : 0.95) * least) { best = ks; least = us; }
   }
   return best;
 }

@@ -38,6 +38,14 @@ def test_key_groups_of_whole_sequences(heads, L, groups):
     assert B.sdllm_launch_plan(shape, DENSE).key_groups == groups
 
 
+# Beyond 256 positions, where the ring kernels' costs decide: the sizes at which they and those of the kernels before them differ.
+@pytest.mark.parametrize("heads,L,groups", [(84, 800, 1), (140, 800, 2), (112, 1025, 2), (56, 1277, 2), (64, 1277, 2), (40, 1537, 2), (40, 1793, 2),
+                                            (32, 2049, 2), (8, 2049, 2), (28, 1181, 1), (84, 1277, 1), (28, 300, 4), (56, 300, 2), (224, 300, 1)])
+def test_key_groups_of_the_ring_kernels(heads, L, groups):
+    shape = B.make_shape(batch=1, n_q_heads=heads, n_kv_heads=heads, head_dim=128, seq_len=L, block_off=0, block_len=32, dtype=B.SDLLM_BF16)
+    assert B.sdllm_launch_plan(shape, DENSE).key_groups == groups
+
+
 def test_a_call_or_plan_that_is_not_there_is_rejected():
     for call, n_cached in ((-1, 0), (4, 0), (SPARSE, -1)):
         with pytest.raises(B.SdllmError):
