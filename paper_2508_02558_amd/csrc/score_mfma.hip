@@ -9,7 +9,7 @@
 //                        over the 32 rows (in registers) and over the G query heads of the group.
 // A workgroup serves one (batch, KV head) and a contiguous range of candidate tiles, so K is read from HBM once per
 // pass however large G is.  Its waves take tiles round-robin into wave-private LDS tiles (no barrier in the loop), the Q
-// fragments of all G heads in LDS; or, in pass 2 of grouped-query heads as a launch of its own, one head each.
+// fragments of all G heads in LDS; or, in pass 2 of grouped-query heads as a launch of its own, one head each while there is little work per CU.
 // Probabilities stay fp32 end to end: the retained set must match a float64 reference except for
 // scores within 1e-4 relative of the k-th value.
 #include <type_traits>
@@ -308,7 +308,7 @@ __device__ __forceinline__ float2 row_statistics(const ScoreParams& p, size_t he
   return make_float2(m_tot, 1.f / l_tot);
 }
 
-// One query head per KV head (G = 1): a wave per tile.
+// One query head per KV head, and grouped-query heads with much work per CU (heads_pay): a wave per tile, which walks the heads.
 template <int G>
 __global__ __launch_bounds__(512) void score_cols_mfma_kernel(const ScoreParams p) {
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
@@ -481,14 +481,44 @@ __global__ __launch_bounds__((heads_waves(G) + 1) * kWave) void score_cols_heads
   bare_barrier();
 }
 
+static int candidate_tiles(const ScoreParams& p) {
+  const int n0 = p.n_cand < p.block_off ? p.n_cand : p.block_off, n1 = p.n_cand - n0;
+  return (n0 + kTileKeys - 1) / kTileKeys + (n1 + kTileKeys - 1) / kTileKeys;
+}
+
+// Which of the two kernels runs the column pass of grouped-query heads.  A wave per head starts sooner and reads LDS less per tile, but
+// fills a CU with one workgroup of G or 2 G waves; from some number of tiles per CU on, eight waves that walk the heads, or two
+// such workgroups, take less.  The line lies there, in rows ((batch, KV head) pairs) x tiles, by how many waves there are and by
+// what a weight costs the other kernel (softmax: statistics from LDS for each).  us, walking / wave per head:
+// * column pass and selection, raw logits: 2 heads, 8 rows x 46 tiles 9.4 / 8.3, 32 x 24 8.9 / 9.2, 192 x 187 67.3 / 86.0; 4 heads,
+//   8 x 46 10.1 / 9.0, 96 x 93 23.3 / 25.4; 5 heads, 16 x 24 9.8 / 9.0, 192 x 24 17.6 / 20.7; 7 heads, 16 x 93 15.4 / 14.3, 96 x 93 29.9 / 33.0;
+// * whole cache-update step, softmax with the statistics there: 2 heads, 16 x 93 29.9 / 27.0, 192 x 46 67.0 / 68.4, 256 x 187 244.7 /
+//   260.8; 7 heads, 32 x 46 35.6 / 32.8, 192 x 93 179.5 / 183.1; with few rows at any length: 7 heads, 2 x 1190 77.1 / 68.6;
+// * statistics from a launch of this file: 2 heads, 8 x 71 18.6 / 16.7, 48 x 12 13.9 / 14.5; 7 heads, 8 x 94 26.8 / 22.7.  That leaves up to
+//   256 partials a row, which a wave per head folds by itself: 1 x 1814 with 7 heads 53.3 / 56.9, 1 x 1948 with 2 43.9 / 48.0.
+// Beyond 256 rows the kernel that walks the heads has one workgroup per row, of ever fewer waves, of which from six heads on
+// the queries' LDS lets a CU hold one: 7 heads, 512 rows x 24 tiles, raw logits 51.3 / 41.8.
+static bool heads_pay(const ScoreParams& p, int tiles) {
+  const int rows = p.batch * p.hkv, g = p.group;
+  const bool own_stats = p.softmax && !p.skip_stats;
+  if (own_stats && p.n_stat_part > (g <= 3 ? 16 : g <= 5 ? 48 : 64)) return false;
+  //                                                                   G = 2, 3   4     5     6 and more
+  static constexpr int kMost[3][4] = {/* raw logits                  */ {600,  1300, 1300, 3500},    // rows x tiles
+                                      /* softmax, own statistics     */ {0,    5000, 1000, 5000},
+                                      /* softmax, statistics given   */ {2500, 5000, 4000, 5000}};
+  static constexpr int kFewRows[3][4] = {{0, 0, 0, 4}, {12, 12, 0, 12}, {12, 12, 12, 12}};           // at any length
+  const int kind = !p.softmax ? 0 : own_stats ? 1 : 2, by_g = g <= 3 ? 0 : g == 4 ? 1 : g == 5 ? 2 : 3;
+  const bool little = (int64_t)rows * tiles <= kMost[kind][by_g];
+  if (rows > kNumCUs) return g >= 6 && (p.softmax || rows >= 400 || little);
+  return little || rows <= kFewRows[kind][by_g];
+}
+
 template <int G>
-static hipError_t launch_heads(const ScoreParams& p, hipStream_t s) {
+static hipError_t launch_heads(const ScoreParams& p, int tiles, hipStream_t s) {
   static LdsOptIn lds;
   const auto kernel = score_cols_heads_kernel<G>;
   const hipError_t e = lds.ensure(reinterpret_cast<const void*>(kernel), heads_lds_bytes(G));
   if (e != hipSuccess) return e;
-  const int n0 = p.n_cand < p.block_off ? p.n_cand : p.block_off, n1 = p.n_cand - n0;
-  const int tiles = (n0 + kTileKeys - 1) / kTileKeys + (n1 + kTileKeys - 1) / kTileKeys;
   const int rows = p.batch * p.hkv;
   int parts = kNumCUs / rows;              // a workgroup per CU (two: the whole step 0 to 10 % slower below 32 rows, level above)
   if (parts < 1) parts = 1;
@@ -516,14 +546,14 @@ static hipError_t launch_g(const ScoreParams& p, hipStream_t s) {
     if (launched != hipSuccess || q.cols_follow) return launched;
   }
   if constexpr (G > 1) {
-    return launch_heads<G>(p, s);
-  } else {
-    static LdsOptIn lds_cols;
-    const hipError_t e = lds_cols.ensure(reinterpret_cast<const void*>(score_cols_mfma_kernel<G>), max_lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(score_cols_mfma_kernel<G>, grid, block, lds, s, p);
-    return hipGetLastError();
+    const int tiles = candidate_tiles(p);
+    if (heads_pay(p, tiles)) return launch_heads<G>(p, tiles, s);
   }
+  static LdsOptIn lds_cols;
+  const hipError_t e = lds_cols.ensure(reinterpret_cast<const void*>(score_cols_mfma_kernel<G>), max_lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(score_cols_mfma_kernel<G>, grid, block, lds, s, p);
+  return hipGetLastError();
 }
 
 bool score_mfma_supports_group(int group) { return group >= 1 && group <= 8; }

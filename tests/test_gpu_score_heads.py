@@ -1,5 +1,6 @@
 """Column pass of the scoring with a wave per query head: every group size, step counts from one to beyond the ring of tiles in
-LDS, ragged last tiles on both sides of the block, candidates on one side only, streams without a tile of their own.
+LDS, ragged last tiles on both sides of the block, candidates on one side only, streams without a tile of their own; and the waves that
+walk the heads, which take the pass over where the rows are many.
 Tolerance: a score sums at most 256 logits or weights in fp32, each from a 128-term fp32 dot product of bf16 values (error
 about 2^-24 * sqrt(128 * 256) of its size, 1e-5 with a factor of five)."""
 import math
@@ -27,7 +28,8 @@ def _reference(q, k, group, off, softmax):
 @pytest.mark.parametrize("batch,q_heads,kv_heads,L,off", [
     (1, 4, 2, 33, 0), (1, 4, 2, 97, 32), (2, 6, 2, 800, 415), (1, 8, 2, 1056, 1024), (1, 5, 1, 230, 31), (1, 6, 1, 2090, 700),
     (1, 7, 1, 64, 32), (1, 7, 1, 65, 1), (1, 14, 2, 4300, 2111), (8, 28, 4, 700, 333), (3, 8, 1, 3001, 0), (2, 16, 2, 7001, 6000),
-    (70, 8, 4, 500, 100),                                          # more rows than CUs: a workgroup walks all tiles
+    (70, 8, 4, 500, 100), (70, 28, 4, 300, 101), (103, 28, 4, 230, 64),   # more rows than CUs: a workgroup walks all tiles
+    (20, 8, 4, 330, 0), (8, 24, 8, 500, 77), (24, 16, 4, 1501, 1400), (48, 20, 4, 900, 31), (20, 28, 4, 1633, 800),   # waves that walk the heads
 ])
 @pytest.mark.parametrize("mode", [B.SDLLM_LOGIT_MEAN, B.SDLLM_SOFTMAX_MEAN])
 def test_scores_of_grouped_heads(batch, q_heads, kv_heads, L, off, mode):
@@ -52,6 +54,7 @@ def test_scores_of_grouped_heads(batch, q_heads, kv_heads, L, off, mode):
 @pytest.mark.parametrize("q_heads,kv_heads,batch,prompt,modes", [
     (4, 2, 1, 70, {}), (6, 2, 2, 333, {}), (8, 2, 1, 1500, {}), (10, 2, 1, 64, {}), (12, 2, 1, 701, {}), (14, 2, 1, 2600, {}),
     (16, 2, 3, 300, {}), (28, 4, 2, 900, dict(evict_scope=B.SDLLM_EVICT_PREFIX_ONLY)),
+    (16, 8, 32, 200, {}), (16, 4, 24, 1400, {}), (28, 4, 24, 1300, {}), (28, 4, 65, 70, {}),   # many rows: either kernel
 ])
 def test_cache_update_with_grouped_heads(q_heads, kv_heads, batch, prompt, modes):
     w = wl.WORKLOADS["dream7b_gqa"].scaled(batch=batch, n_q_heads=q_heads, n_kv_heads=kv_heads, prompt=prompt, gen=160)
