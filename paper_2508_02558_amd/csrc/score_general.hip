@@ -9,6 +9,9 @@
 // last row, which count for nothing) sit in LDS, as many blocks at once as 64 KB hold.
 // Batch 2, 32 heads of 128, 64-token block, 1216 candidates: 138 us with one thread per candidate and a
 // scalar loop over all query rows, 9-10 us here; what is left is latency (queries, statistics, one tile).
+// A wave's first tile is requested behind the staging on purpose: held in registers meanwhile it costs a wave per SIMD, which is
+// up to 1 % of a small cache-update step gained and 3 to 9 % lost where many workgroups share a CU (9 x 32 heads of 64 x 616
+// positions 43.9 us, 45.8 with the tile first; fp32 2 x 8/1 x 1624 59.5, 65.4).
 #include "general_tile.h"
 
 namespace sdllm {
@@ -44,19 +47,6 @@ __global__ __launch_bounds__(kColWaves * kWave) void score_cols_general_kernel(c
   float* score_row = p.score + (size_t)bg * p.score_stride;
   const float inv_count = 1.f / (float)(p.group * p.nq);
 
-  // one candidate tile: first row, valid rows and candidates before it; its rows are requested
-  u32x4 kreg[O::kLoads];
-  int rows = 0, cand0 = 0;
-  auto request = [&](int t) {
-    const bool suf = t >= tiles0;
-    const int first = (suf ? t - tiles0 : t) * kTileKeys;
-    rows = min(kTileKeys, (suf ? n1 : n0) - first);
-    cand0 = (suf ? n0 : 0) + first;
-    g_load_rows<O, false>(k_base + (int64_t)(suf ? p.block_off + p.block_len + first : first) * stride, rows, stride, lane, kreg);
-  };
-  const int t_first = blockIdx.x * kColWaves + wave;
-  if (t_first < ntiles) request(t_first);   // flies while the queries are staged
-
   for (int blk0 = 0; blk0 < n_blk; blk0 += kBlocks) {
     const int here = min(kBlocks, n_blk - blk0);
     if (blk0) __syncthreads();   // the previous blocks are done with
@@ -83,8 +73,13 @@ __global__ __launch_bounds__(kColWaves * kWave) void score_cols_general_kernel(c
       }
     }
     __syncthreads();
-    for (int t = t_first; t < ntiles; t += step) {
-      if (blk0 > 0 || t > t_first) request(t);
+    for (int t = blockIdx.x * kColWaves + wave; t < ntiles; t += step) {
+      const bool suf = t >= tiles0;
+      const int first = (suf ? t - tiles0 : t) * kTileKeys;
+      const int rows = min(kTileKeys, (suf ? n1 : n0) - first), cand0 = (suf ? n0 : 0) + first;
+      const char* src = k_base + (int64_t)(suf ? p.block_off + p.block_len + first : first) * stride;
+      u32x4 kreg[O::kLoads];
+      g_load_rows<O, false>(src, rows, stride, lane, kreg);
       g_store_rows<O>(lds_k, O::kKRow, lane, kreg);
       wave_lds_sync();
       typename O::KTile keys;
