@@ -374,7 +374,11 @@ static hipError_t launch_nseg(const AttnParams& p, hipStream_t s) {
     if (p.group > 1 && !deep && p.n_split > 1 && p.tiles_per_split >= 24 && (NSEG == 2 || p.tiles_per_split < 40))
       return launch_variant<NSEG, false, false, true, true, true>(p, s);
   if (p.group > 1) return deep ? launch_variant<NSEG, STATS, true, true, true>(p, s) : launch_variant<NSEG, STATS, false, true, true>(p, s);
-  if (p.n_split > 1) return deep ? launch_variant<NSEG, STATS, true, false, true>(p, s) : launch_variant<NSEG, STATS, false, false, true>(p, s);
+  // Multi-head sparse steps whose splits have five waves (nine or ten tiles, two to a wave) lose by the shared rows what those of
+  // four, seven and eight gain: 32 heads x 66 tiles 13.6 us with fragments, 14.0, x 80 14.4, 14.8, 16 heads x 27 10.0, 10.3 (against
+  // 13.3, 13.1 for 32 x 64, four waves, and 16.75, 16.45 for 32 x 105, seven).
+  const bool shared_q = p.n_split > 1 && !(NSEG == 2 && p.waves == 5);
+  if (shared_q) return deep ? launch_variant<NSEG, STATS, true, false, true>(p, s) : launch_variant<NSEG, STATS, false, false, true>(p, s);
   return deep ? launch_variant<NSEG, STATS, true, false, false>(p, s) : launch_variant<NSEG, STATS, false, false, false>(p, s);
 }
 
