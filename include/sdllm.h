@@ -193,7 +193,9 @@ int32_t sdllm_sparse_attn_noalloc(const sdllm_shape_t* shape, const void* q_blk,
  *   state 2: k_in/v_in are the block's K_n,V_n [B,Hkv,b,d] (blk_stride); out = sparse attention
  *            over the cache (k_total rows per KV head, as sdllm_retained_count reports) + block.
  * idx [B,Hkv,k_total] int32; ws sized by SDLLM_OP_BLOCK_STEP.  `state_out` (host, may be NULL)
- * receives the state that was executed.
+ * receives the state that was executed.  For fp32 tensors, head_dim 64, block lengths other than 32 and other shapes of
+ * the general kernels that size lets state 1 keep its key-split partials until the compaction; a workspace
+ * that holds the partials and the scoring buffers one after the other is accepted too (same results, one more launch).
  */
 int32_t sdllm_block_step(const sdllm_shape_t* shape, int32_t step_in_block, int32_t delay, const void* q_blk,
                          const void* k_in, const void* v_in, int32_t* idx, void* k_cache, void* v_cache, void* out,

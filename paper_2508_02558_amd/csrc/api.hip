@@ -534,9 +534,6 @@ int32_t score_select_impl(const sdllm_shape_t& s, const void* q_blk, const void*
   return e == hipSuccess ? SDLLM_OK : SDLLM_ERR_HIP;
 }
 
-// Workspace of sdllm_block_step: [0, base) is shared by the attention partials and the scoring
-// buffers (used one after the other on the stream); the fused row statistics of the cache-update
-// step live behind it because they are written by the attention and read by the scoring.
 // Argument checks and launch parameters of the gather (k_total > 0).
 int32_t compact_params(const sdllm_shape_t& s, const void* k_full, const void* v_full, const int32_t* idx, void* k_cache,
                        void* v_cache, CompactParams& p) {
@@ -554,20 +551,28 @@ int32_t compact_params(const sdllm_shape_t& s, const void* k_full, const void* v
   return SDLLM_OK;
 }
 
+// Workspace of sdllm_block_step: [0, base) is shared by the attention partials and the scoring
+// buffers (used one after the other on the stream); the fused row statistics of the cache-update
+// step live behind it because they are written by the attention and read by the scoring.
 // With split keys at the cache-update step the merge of the splits runs in the compaction's launch, so
 // the attention partials stay alive through scoring and selection: those then work behind them (score_off).  Also for
-// the general kernels: 2 x 32 heads, block of 64, 1280 positions 41.3 -> 39.7 us, 2 x 8 of head_dim 64, 1200 positions 24.3 -> 21.7.
-struct BlockStepWs { size_t base, stats_bytes, score_off; int stats_parts; bool fuse, fuse_cols; };
+// the general kernels (2 x 32 heads, block of 64, 1280 positions 43.2 -> 41.0 us, 2 x 8 of head_dim 64, 1200 positions 24.3 -> 21.7),
+// whose partials may as well be merged before the scoring: with a workspace that has no room for both (beside = false).
+struct BlockStepWs {
+  size_t base, stats_bytes, score_off;
+  int stats_parts;
+  bool fuse, fuse_cols;
+  size_t bytes() const { return base + stats_bytes; }
+};
 
-
-BlockStepWs plan_block_step(const sdllm_shape_t& s) {
+BlockStepWs plan_block_step(const sdllm_shape_t& s, bool beside = true) {
   const Counts c = counts_of(s);
   const AttnPlan full = plan_attn(s, s.seq_len, s.kv_stride[2], 0, 0);
   const AttnPlan dense = plan_attn(s, s.seq_len, s.kv_stride[2], 0, 0, c.k_total > 0);   // of a cache-update step
   const AttnPlan sparse = plan_attn(s, c.k_total, s.cache_stride[2], s.block_len, s.blk_stride[2]);
   const ScorePlan sc = plan_score(s);
   BlockStepWs w{};
-  w.score_off = dense.n_split > 1 && c.k_total > 0 ? align_up(dense.ws_bytes()) : 0;
+  w.score_off = (beside || dense.mfma) && dense.n_split > 1 && c.k_total > 0 ? align_up(dense.ws_bytes()) : 0;
   w.base = dense.ws_bytes();
   if (full.ws_bytes() > w.base) w.base = full.ws_bytes();
   if (sparse.ws_bytes() > w.base) w.base = sparse.ws_bytes();
@@ -661,11 +666,7 @@ int32_t sdllm_workspace_bytes(const sdllm_shape_t* shape, int32_t op, int32_t n_
       if (n_cached < 0) return SDLLM_ERR_INVALID_ARG;
       need = plan_attn(s, n_cached, s.cache_stride[2], s.block_len, s.blk_stride[2]).ws_bytes();
       break;
-    case SDLLM_OP_BLOCK_STEP: {
-      const BlockStepWs w = plan_block_step(s);
-      need = w.base + w.stats_bytes;
-      break;
-    }
+    case SDLLM_OP_BLOCK_STEP: need = plan_block_step(s).bytes(); break;
     default: return SDLLM_ERR_INVALID_ARG;
   }
   *bytes = need > 0 ? need : kAlign;   // never zero, so callers can always allocate
@@ -735,8 +736,9 @@ int32_t sdllm_block_step(const sdllm_shape_t* shape, int32_t step_in_block, int3
   const sdllm_shape_t& s = *shape;
   int32_t state;
   if ((st = sdllm_cache_state(step_in_block, delay, &state)) != SDLLM_OK) return st;
-  size_t need;
-  if ((st = sdllm_workspace_bytes(shape, SDLLM_OP_BLOCK_STEP, 0, &need)) != SDLLM_OK) return st;
+  BlockStepWs w = plan_block_step(s);
+  if (ws_bytes < w.bytes()) w = plan_block_step(s, false);
+  const size_t need = w.bytes() > 0 ? w.bytes() : kAlign;   // as sdllm_workspace_bytes says
   if (!ws || ws_bytes < need || (reinterpret_cast<uintptr_t>(ws) % kAlign) != 0) return SDLLM_ERR_WORKSPACE;
   if ((st = check_q(s, q_blk)) != SDLLM_OK) return st;
   if (!k_in || !v_in || !out || !aligned16(k_in) || !aligned16(v_in) || !aligned16(out) ||
@@ -753,7 +755,6 @@ int32_t sdllm_block_step(const sdllm_shape_t* shape, int32_t step_in_block, int3
   if (state == SDLLM_STATE_UPDATE && c.k_total > 0 && (!idx || !k_cache || !v_cache)) return SDLLM_ERR_INVALID_ARG;
   KvSegment a{k_in, v_in, s.kv_stride[0], s.kv_stride[1], s.kv_stride[2], s.seq_len};
   KvSegment b{nullptr, nullptr, 0, 0, 0, 0};
-  const BlockStepWs w = plan_block_step(s);
   AttnParams pending{};           // split-KV merge still to run (cache-update step only)
   pending.n_split = 1;
   const bool update = state == SDLLM_STATE_UPDATE && c.k_total > 0;

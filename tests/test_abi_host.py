@@ -179,6 +179,43 @@ def test_workspace_sizes(lib):
         B.sdllm_workspace_bytes(s, 9)
 
 
+def sequential_step_bytes(shape, q_rows_per_block):
+    """What a block step of the general kernels needs when the partials of its key splits are merged before the scoring."""
+    up = lambda n: (n + 255) // 256 * 256
+    blocks = shape.batch * shape.n_q_heads * -(-shape.block_len // q_rows_per_block)
+    def partials(plan):
+        if plan.key_splits == 1:
+            return 0
+        return up(blocks * plan.key_splits * q_rows_per_block * shape.head_dim * 4) + up(blocks * plan.key_splits * 2 * q_rows_per_block * 4)
+    kt = B.sdllm_retained_count(shape)[0]
+    update = B.sdllm_launch_plan(shape, B.SDLLM_CALL_UPDATE)
+    parts = max(partials(update), partials(B.sdllm_launch_plan(shape, B.SDLLM_CALL_FULL)), partials(B.sdllm_launch_plan(shape, B.SDLLM_CALL_SPARSE, kt)))
+    stats = up(blocks * update.key_splits * 2 * q_rows_per_block * 4) if shape.score_mode == B.SDLLM_SOFTMAX_MEAN else 0
+    return up(max(parts, B.sdllm_workspace_bytes(shape, B.SDLLM_OP_SCORE_SELECT))) + stats
+
+
+@pytest.mark.parametrize("kw,rows", [
+    (dict(dtype=B.SDLLM_BF16, head_dim=128, block_len=64, n_q_heads=8, n_kv_heads=8, seq_len=1500), 32),
+    (dict(dtype=B.SDLLM_BF16, head_dim=64, block_len=32, n_q_heads=4, n_kv_heads=2, seq_len=1600, score_mode=B.SDLLM_LOGIT_MEAN), 32),
+    (dict(dtype=B.SDLLM_F32, head_dim=128, block_len=40, n_q_heads=6, n_kv_heads=2, seq_len=900), 16),
+])
+def test_block_step_takes_a_workspace_without_room_for_partials_and_scores_side_by_side(lib, kw, rows):
+    s = B.make_shape(batch=1, block_off=500, **kw)
+    assert B.sdllm_launch_plan(s, B.SDLLM_CALL_UPDATE).key_splits > 1
+    less, full = sequential_step_bytes(s, rows), B.sdllm_workspace_bytes(s, B.SDLLM_OP_BLOCK_STEP)
+    assert less < full
+    fake, z = ctypes.c_void_p(0x1000), ctypes.c_void_p(None)
+    # past the size check the missing queries are the error
+    step = lambda n: lib.sdllm_block_step(ctypes.byref(s), 1, 1, z, fake, fake, fake, fake, fake, fake, fake, n, z, None)
+    assert step(full) == step(less) == B.SDLLM_ERR_INVALID_ARG
+    assert step(less - 1) == B.SDLLM_ERR_WORKSPACE
+    # the 32-row kernels need it all
+    m = B.make_shape(batch=1, n_q_heads=8, n_kv_heads=8, head_dim=128, seq_len=1500, block_off=500, block_len=32, dtype=B.SDLLM_BF16)
+    assert B.sdllm_launch_plan(m, B.SDLLM_CALL_UPDATE).key_splits > 1
+    need = B.sdllm_workspace_bytes(m, B.SDLLM_OP_BLOCK_STEP)
+    assert lib.sdllm_block_step(ctypes.byref(m), 1, 1, z, fake, fake, fake, fake, fake, fake, fake, need - 1, z, None) == B.SDLLM_ERR_WORKSPACE
+
+
 def test_current_stream_with_and_without_torchs_private_function(monkeypatch):
     import types
     import torch

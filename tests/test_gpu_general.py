@@ -8,6 +8,7 @@ import torch
 from paper_2508_02558_amd import binding as B
 from paper_2508_02558_amd import workloads as wl
 from tests import parity_util as U
+from tests.test_abi_host import sequential_step_bytes
 from tests.test_gpu_parity import _run_block
 
 pytestmark = pytest.mark.gpu
@@ -208,3 +209,30 @@ def test_update_steps_merge_their_splits_with_the_compaction(dtype, d, block, q_
                                              batch=batch, prompt=prompt, gen=4 * block)
     assert B.sdllm_launch_plan(U.shape_for(w, 1, **modes), B.SDLLM_CALL_UPDATE).key_splits > 1
     _run_block(w, block_index=1, n_steps=3, **modes)
+
+
+# The same steps with a workspace in which the partials and the scoring buffers take turns: the merge is a launch of its own then.
+@pytest.mark.parametrize("dtype,d,block,q_heads,kv_heads,L,rows,mode", [
+    ("bf16", 128, 64, 8, 8, 1500, 32, B.SDLLM_SOFTMAX_MEAN), ("bf16", 64, 32, 4, 2, 1600, 32, B.SDLLM_LOGIT_MEAN),
+    ("f32", 128, 40, 6, 2, 900, 16, B.SDLLM_SOFTMAX_MEAN),
+])
+def test_update_step_in_less_workspace(dtype, d, block, q_heads, kv_heads, L, rows, mode):
+    print(f"[case] update step, less workspace: {dtype} d={d} b={block} L={L}", flush=True)
+    torch.manual_seed(L)
+    t = torch.float32 if dtype == "f32" else torch.bfloat16
+    shape = B.make_shape(batch=1, n_q_heads=q_heads, n_kv_heads=kv_heads, head_dim=d, seq_len=L, block_off=500, block_len=block,
+                         dtype=U.DT[dtype], score_mode=mode)
+    kt = B.sdllm_retained_count(shape)[0]
+    q, k, v = (torch.randn(1, h, n, d, device=DEV).to(t) for h, n in ((q_heads, block), (kv_heads, L), (kv_heads, L)))
+    results = []
+    for nbytes in (B.sdllm_workspace_bytes(shape, B.SDLLM_OP_BLOCK_STEP), sequential_step_bytes(shape, rows)):
+        room = torch.full((nbytes + 4096,), 0x5A, dtype=torch.uint8, device=DEV)
+        idx = torch.zeros(1, kv_heads, kt, dtype=torch.int32, device=DEV)
+        kc, vc = (torch.zeros(1, kv_heads, L - block, d, device=DEV, dtype=t) for _ in range(2))
+        out = torch.zeros_like(q)
+        assert B.sdllm_block_step(shape, 1, 1, q, k, v, idx, kc, vc, out, room[:nbytes]) == B.SDLLM_STATE_UPDATE
+        torch.cuda.synchronize()
+        assert (room[nbytes:] == 0x5A).all()
+        results.append((out, idx, kc, vc))
+    assert all(torch.equal(a, b) for a, b in zip(*results))
+    U.assert_close(results[1][0], U.oracle_attention_batch(q, k, v), dtype, "dense rows")
