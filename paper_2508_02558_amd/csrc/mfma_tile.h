@@ -81,14 +81,14 @@ constexpr int kKGroup = 1024 + 32, kVGroup = 1024 + 64;
 constexpr int kRingK = 8 * kKGroup, kRingV = 8 * kVGroup;   // one tile
 
 // 64 lanes x 16 bytes from base + off to 1 KB of LDS at `at` (an LDS byte address; it and base wave-uniform).  In assembly because with
-// the builtin the compiler makes every LDS read wait for all fetches in flight; the caller counts the requests.  Writes m0,
-// which nothing else uses in the kernels that call it (none of them fetches with the builtin).
+// the builtin the compiler makes every LDS read wait for all fetches in flight; the caller counts the requests.  m0 holds the
+// LDS address.
 __device__ __forceinline__ void fetch_to_lds(uint32_t at, const char* base, uint32_t off) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(at), "v"(off), "s"(base) : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(at), "v"(off), "s"(base) : "memory", "m0");
 }
 // The same from an address per lane.
 __device__ __forceinline__ void fetch_to_lds(uint32_t at, const char* lane_src) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(at), "v"(lane_src) : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(at), "v"(lane_src) : "memory", "m0");
 }
 // A wave-uniform address in scalar registers, where the compiler would keep it in vector registers.
 __device__ __forceinline__ const char* in_scalars(const char* p) {
