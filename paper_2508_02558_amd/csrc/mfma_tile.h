@@ -80,6 +80,8 @@ __device__ __forceinline__ void store_rows_v(uint8_t* lds_tile, int lane, const 
 constexpr int kKGroup = 1024 + 32, kVGroup = 1024 + 64;
 constexpr int kRingK = 8 * kKGroup, kRingV = 8 * kVGroup;   // one tile
 
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"   // m0 is a reserved register: named so that no use of it is moved across
 // 64 lanes x 16 bytes from base + off to 1 KB of LDS at `at` (an LDS byte address; it and base wave-uniform).  In assembly because with
 // the builtin the compiler makes every LDS read wait for all fetches in flight; the caller counts the requests.  m0 holds the
 // LDS address.
@@ -90,6 +92,7 @@ __device__ __forceinline__ void fetch_to_lds(uint32_t at, const char* base, uint
 __device__ __forceinline__ void fetch_to_lds(uint32_t at, const char* lane_src) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(at), "v"(lane_src) : "memory", "m0");
 }
+#pragma clang diagnostic pop
 // A wave-uniform address in scalar registers, where the compiler would keep it in vector registers.
 __device__ __forceinline__ const char* in_scalars(const char* p) {
   const uint64_t a = (uint64_t)p;
