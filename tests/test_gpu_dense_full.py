@@ -33,8 +33,8 @@ def test_dense_attn_bf16_matches_oracle(Bt, Hq, Hkv, L):
 
 @pytest.mark.parametrize("L", [31, 32, 64, 65, 96, 97, 128, 129, 191, 257])
 def test_dense_attn_tile_and_stage_boundaries(L):
-    # the kernel pipelines 32-key tiles through 64-key stages: every parity of tile and stage count,
-    # with and without a ragged last tile
+    # two heads: whole rows up to 96 positions and at 129, four key groups elsewhere; every parity of tile and stage count, with and
+    # without a ragged last tile (more heads, and longer sequences by step count: test_gpu_dense_steps.py)
     print(f"[case] dense_attn boundaries L={L}", flush=True)
     torch.manual_seed(1000 + L)
     Bt, Hq, Hkv, d = 1, 2, 1, 128

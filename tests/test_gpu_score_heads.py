@@ -37,8 +37,14 @@ def test_scores_of_grouped_heads(batch, q_heads, kv_heads, L, off, mode):
     torch.manual_seed(L + off)
     q = (2.0 * torch.randn(batch, q_heads, 32, 128, device=DEV)).bfloat16()
     k = torch.randn(batch, kv_heads, L, 128, device=DEV).bfloat16()
+    _check_scores(q, k, off, mode)
+
+
+def _check_scores(q, k, off, mode):
+    batch, q_heads = q.shape[:2]
+    kv_heads, L = k.shape[1:3]
     shape = B.make_shape(batch=batch, n_q_heads=q_heads, n_kv_heads=kv_heads, head_dim=128, seq_len=L, block_off=off, block_len=32,
-                         dtype=B.SDLLM_BF16, score_mode=mode)
+                         dtype=B.SDLLM_BF16, score_mode=mode, q_stride=B.strides_of(q), kv_stride=B.strides_of(k))
     kt = B.sdllm_retained_count(shape)[0]
     idx = torch.zeros(batch, kv_heads, kt, dtype=torch.int32, device=DEV)
     pooled, score = (torch.full((batch, kv_heads, L - 32), float("nan"), device=DEV) for _ in range(2))
@@ -48,6 +54,29 @@ def test_scores_of_grouped_heads(batch, q_heads, kv_heads, L, off, mode):
     ref = _reference(q, k, q_heads // kv_heads, off, mode == B.SDLLM_SOFTMAX_MEAN)
     err = (score.double() - ref).norm() / ref.norm()
     assert err < 1e-5, f"relative error {err:.2e}"
+
+
+# Queries and keys stored [B, rows, H, d], and query rows further apart than 32 bits of bytes reach: both kernels of the pass.
+@pytest.mark.parametrize("batch,q_heads,kv_heads,L,off", [(1, 14, 2, 2300, 1111), (3, 8, 4, 777, 100), (24, 16, 4, 1501, 1400), (20, 20, 4, 1433, 8)])
+@pytest.mark.parametrize("mode", [B.SDLLM_LOGIT_MEAN, B.SDLLM_SOFTMAX_MEAN])
+def test_scores_of_tensors_stored_by_rows(batch, q_heads, kv_heads, L, off, mode):
+    print(f"[case] score heads, stored by rows B={batch} {q_heads}/{kv_heads} L={L} off={off} mode={mode}", flush=True)
+    torch.manual_seed(L)
+    q = (2.0 * torch.randn(batch, 32, q_heads, 128, device=DEV)).bfloat16().permute(0, 2, 1, 3)
+    k = torch.randn(batch, L, kv_heads, 128, device=DEV).bfloat16().permute(0, 2, 1, 3)
+    _check_scores(q, k, off, mode)
+
+
+@pytest.mark.parametrize("kv_heads,L", [(1, 1500), (10, 12900)])
+def test_scores_of_query_rows_far_apart(kv_heads, L):
+    # rows 144 MB apart: 29 rows on, the offset is beyond 2^32 bytes
+    print(f"[case] score heads, far rows, {kv_heads} KV heads L={L}", flush=True)
+    torch.manual_seed(L)
+    heads = 7 * kv_heads
+    q = torch.zeros(32, 72 * 1024 * 1024, device=DEV, dtype=torch.bfloat16)[:, :heads * 128].unflatten(1, (heads, 128))
+    q.copy_(2.0 * torch.randn(32, heads, 128, device=DEV))
+    k = torch.randn(1, kv_heads, L, 128, device=DEV).bfloat16()
+    _check_scores(q.permute(1, 0, 2)[None], k, 200, B.SDLLM_LOGIT_MEAN)
 
 
 # With the statistics left by the dense attention (key splits or not, one or two kernels): index sets and cache against the oracle.
