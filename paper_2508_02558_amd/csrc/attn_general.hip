@@ -262,15 +262,10 @@ hipError_t launch_attn_general(const AttnParams& p, int dtype, bool stats_only, 
 }
 
 hipError_t launch_attn_combine(const AttnParams& p, int dtype, hipStream_t s) {
-  const int tpi = combine_tpi(p.n_split);
-  const dim3 grid((unsigned)combine_blocks(p)), block(kCombineThreads);
-  if (dtype == 0) {
-    if (tpi == 4) hipLaunchKernelGGL((attn_combine_kernel<__bf16, 4>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((attn_combine_kernel<__bf16, 1>), grid, block, 0, s, p);
-  } else {
-    if (tpi == 4) hipLaunchKernelGGL((attn_combine_kernel<float, 4>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((attn_combine_kernel<float, 1>), grid, block, 0, s, p);
-  }
+  const bool four = combine_tpi(p.n_split) == 4;
+  if (dtype != 0 && four) return hipErrorInvalidValue;   // fp32 has plan_general's splits, eight at most
+  const auto kernel = dtype != 0 ? attn_combine_kernel<float, 1> : four ? attn_combine_kernel<__bf16, 4> : attn_combine_kernel<__bf16, 1>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)combine_blocks(p)), dim3(kCombineThreads), 0, s, p);
   return hipGetLastError();
 }
 

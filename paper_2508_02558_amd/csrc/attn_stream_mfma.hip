@@ -84,8 +84,8 @@ __device__ __forceinline__ void read_v_frags(const uint8_t* tile, int lane, PvFr
   for (int i = 0; i < 8; ++i) f.av[i >> 2][i & 3] = __builtin_shufflevector(r[2 * i], r[2 * i + 1], 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
-__device__ __forceinline__ void read_q_frags(uint32_t at, int half, int col, bf16x8 (&q)[8]) {
-  at += (uint32_t)((col & 7) * kKGroup + (col >> 3) * 256 + ((half ^ ((col >> 3) & 1)) << 4));
+// Likewise; `at` is the lane's place of shared_k_at.
+__device__ __forceinline__ void read_q_frags(uint32_t at, bf16x8 (&q)[8]) {
   asm volatile(
       "ds_read_b128 %0, %8\n\tds_read_b128 %1, %8 offset:32\n\tds_read_b128 %2, %8 offset:64\n\tds_read_b128 %3, %8 offset:96\n\t"
       "ds_read_b128 %4, %8 offset:128\n\tds_read_b128 %5, %8 offset:160\n\tds_read_b128 %6, %8 offset:192\n\t"
@@ -172,12 +172,8 @@ void attn_stream_mfma_bf16_kernel(const AttnParams p) {
     if (touched) { touch(touch_next); touch_next += p.group; }
   };
   // The waits below count requests, so they hang on the order of issue: K(0), V(0), K(1), touch, and from then on for each
-  // tile K(j+2), touch, V(j+1), every one of them whole before the next begins.  Memory and scheduling barriers between
-  // them keep the compiler from interleaving requests whose LDS destinations it can tell apart.
-  auto in_order = [] {
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_sched_barrier(0);
-  };
+  // tile K(j+2), touch, V(j+1), every one of them whole before the next begins.  in_issue_order between
+  // them keeps the compiler from interleaving requests whose LDS destinations it can tell apart.
   auto landed = [&](bool all) {   // every fetch of this wave is in LDS, or all but the eight (and the touch) requested last
     if (all) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     else if (TOUCH && touched) asm volatile("s_waitcnt vmcnt(10)" ::: "memory");
@@ -190,19 +186,19 @@ void attn_stream_mfma_bf16_kernel(const AttnParams p) {
   // tiles 7.25 -> 6.5 us, 84 x 21 9.55 -> 8.45, 224 x 73 23.9 -> 22.7).
   uint8_t* q_lds = smem + nw * kStreamWaveLds;
   request_queries<true>(p, b, h, q_lds, wave, nw, lane);
-  in_order();
+  in_issue_order();
   if (n_mine > 0) {
     fetch_k(0);
-    in_order();
+    in_issue_order();
     fetch_v(0);
-    in_order();
+    in_issue_order();
     asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
   } else {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   }
   bare_barrier();
   bf16x8 qf[8];
-  read_q_frags(lds_address(q_lds), half, col, qf);
+  read_q_frags(lds_address(shared_k_at(q_lds, half, col)), qf);
 
   f32x16 acc[4];
 #pragma unroll
@@ -231,9 +227,9 @@ void attn_stream_mfma_bf16_kernel(const AttnParams p) {
     read_k_frags(k_lds, half, col, a);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     if (j + 1 < n_mine) fetch_k(j + 1);
-    in_order();
+    in_issue_order();
     touch_up_to(j + kAhead);
-    in_order();
+    in_issue_order();
     tile_logits_mma(a, qf, sn);
     __builtin_amdgcn_sched_barrier(0);
   };
@@ -250,7 +246,7 @@ void attn_stream_mfma_bf16_kernel(const AttnParams p) {
       landed(j + 2 >= n_mine);              // V(j); K(j+2), if there is one, may still fly
       read_v_frags(v_lds, lane, f);
       fetch_v(j + 1);
-      in_order();
+      in_issue_order();
       pv_block(f, pb, acc);
       __builtin_amdgcn_sched_barrier(0);
       softmax(j + 1);

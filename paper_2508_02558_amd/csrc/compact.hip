@@ -84,17 +84,14 @@ hipError_t launch_compact(const CompactParams& p, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <typename T>
-static hipError_t launch_compact_combine_t(const CompactParams& p, const AttnParams& a, hipStream_t s) {
+hipError_t launch_compact_combine(const CompactParams& p, const AttnParams& a, int dtype, hipStream_t s) {
+  const bool four = combine_tpi(a.n_split) == 4;
+  if (dtype != 0 && four) return hipErrorInvalidValue;   // fp32 has plan_general's splits, eight at most
   const int64_t n_combine = combine_blocks(a);
   const int64_t blocks = n_combine + compact_blocks(p);
-  const auto kernel = combine_tpi(a.n_split) == 4 ? compact_combine_kernel<T, 4> : compact_combine_kernel<T, 1>;
+  const auto kernel = dtype != 0 ? compact_combine_kernel<float, 1> : four ? compact_combine_kernel<__bf16, 4> : compact_combine_kernel<__bf16, 1>;
   hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kCompactThreads), 0, s, p, a, (int)n_combine);
   return hipGetLastError();
-}
-
-hipError_t launch_compact_combine(const CompactParams& p, const AttnParams& a, int dtype, hipStream_t s) {
-  return dtype == 0 ? launch_compact_combine_t<__bf16>(p, a, s) : launch_compact_combine_t<float>(p, a, s);
 }
 
 }  // namespace sdllm
