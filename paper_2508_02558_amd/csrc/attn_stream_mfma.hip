@@ -183,7 +183,7 @@ void attn_stream_mfma_bf16_kernel(const AttnParams p) {
 
   // The query rows come once per workgroup, through LDS: as fragments straight from memory (32 rows x 32 bytes an
   // instruction, the same for every wave) they kept the CU's address path from the first keys for about 1 us (8 heads x 11
-  // tiles 7.25 -> 6.5 us, 84 x 21 9.55 -> 8.45, 224 x 73 23.9 -> 22.7).
+  // tiles 7.25 -> 6.5 us, 84 x 21 9.55 -> 8.45, 224 x 73 18.5 -> 17.2 and, with the keys in HBM, 24.0 -> 22.6).
   uint8_t* q_lds = smem + nw * kStreamWaveLds;
   request_queries<true>(p, b, h, q_lds, wave, nw, lane);
   in_issue_order();

@@ -10,13 +10,14 @@
 //     waves: each K/V byte from L2 feeds 256 / KS query rows;
 //   * per tile a wave has 512 cycles of matrix work and 380 of vector issue.  Left alone the two waves of a SIMD
 //     drift into the same phase (every barrier puts them there) and then queue for the matrix pipe and for the
-//     vector ALU in turn: 1790 cycles per pair of tiles.  Here they are locked in opposite phases, with a barrier
+//     vector ALU in turn: 1790 cycles per pair of tiles in the loop, by time stamps, 2026 of a whole launch of 256 heads x
+//     4352 positions, by counters.  Here they are locked in opposite phases, with a barrier
 //     at each change: while one wave issues its sixteen MFMAs (logits of tile t+1 interleaved with the PV product
 //     of tile t), the LDS reads of the next operands and half of tile t's exponentials between them, the other
-//     finds its row maxima and does the first half of its exponentials: 1600 cycles per pair (28 heads x 1181
-//     positions 38.5 -> 36.0 us, x 735 with two key groups 19.2 -> 17.5; 256 heads x 4352 2450 -> 2350 us, where the clock
-//     falls as the pipes fill: 1.97 GHz at 1790 cycles, 1.82 at 1600).  The start costs 0.3 us more, so that sequences of up to
-//     eight tiles go without (kStagedKeys);
+//     finds its row maxima and does the first half of its exponentials: 1600 and 1848 cycles (matrix pipe 50.5 -> 55.4 %
+//     busy).  The clock falls meanwhile (2.0 -> 1.9 GHz): 2412 -> 2315 us in trains of calls, 2320 -> 2255 by kernel trace; 28
+//     heads x 1181 positions, half the chip, 39.9 -> 37.0, x 735 with two key groups 19.1 -> 17.4.  The start costs 0.3 us
+//     more, so that sequences of up to eight tiles go without (kStagedKeys);
 //   * the query-block workgroups of one head (and of the G heads of a KV group) are adjacent in the
 //     grid and, after the XCD renumbering, share an L2.
 #include <type_traits>

@@ -353,8 +353,8 @@ __device__ __forceinline__ void rows_of_registers(const float2* ml, int half, fl
 // Against a wave per tile that walks the heads: a third of the LDS reads (a tile's keys once per head instead of the head's
 // queries and statistics once per tile: 0.5 us per tile and head on eight waves), and one round trip at the start instead of
 // four, as queries, statistics and the first tiles are requested together.  Kernel, 28/4 heads: 4320 candidates 11.0 -> 5.2 us,
-// 33 248 18.5 -> 13.3; whole cache-update step, 3 x 28/4 x 1200 positions 31.1 -> 26.6, 8 x 28/4 x 4600 77.9 -> 75.8, 4 x 32/8 x
-// 1500 34.7 -> 33.3, 2 x 16/2 x 3000 33.1 -> 27.0, 8 x 8/4 x 5000 level.
+// 33 248 18.5 -> 13.7; whole cache-update step, 3 x 28/4 x 1200 positions 31.3 -> 26.2, 8 x 28/4 x 4600 80.3 -> 76.5, 4 x 32/8 x
+// 1500 35.0 -> 32.8, 2 x 16/2 x 3000 33.3 -> 26.2.  Where it does not pay: heads_pay.
 constexpr int heads_streams(int g) { return g <= 4 ? 2 : 1; }       // tiles worked on side by side
 constexpr int heads_ring(int g) { return g <= 4 ? 4 : 6; }          // tiles of a stream in LDS
 constexpr int heads_waves(int g) { return g * heads_streams(g); }   // and the one that fetches and writes
