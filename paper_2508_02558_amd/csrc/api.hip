@@ -461,10 +461,11 @@ int32_t check_q(const sdllm_shape_t& s, const void* q) {
 
 // Alg. 1 steps 2-10.  ext_ml != null: the softmax row statistics over the candidates were already
 // produced (ext_parts partials per row) and only the column reduction and the selection run.
+// in_step: called by a cache-update step (ext_ml only there, for softmax scores).
 // scores_ready: the scores are in the workspace's score buffer already; only the selection runs.
 int32_t score_select_impl(const sdllm_shape_t& s, const void* q_blk, const void* k_full, int32_t* idx_out,
                           float* pooled_out, float* score_out, void* ws, size_t ws_bytes, hipStream_t hs,
-                          float* ext_ml, int ext_parts, bool scores_ready = false) {
+                          float* ext_ml, int ext_parts, bool in_step = false, bool scores_ready = false) {
   const Counts c = counts_of(s);
   const ScorePlan pl = plan_score(s);
   if (!ws || ws_bytes < pl.ws_bytes() || (reinterpret_cast<uintptr_t>(ws) % kAlign) != 0) return SDLLM_ERR_WORKSPACE;
@@ -504,6 +505,7 @@ int32_t score_select_impl(const sdllm_shape_t& s, const void* q_blk, const void*
   sp.part_ml = ext_ml ? ext_ml : ml;
   sp.n_stat_part = ext_ml ? ext_parts : pl.n_part;
   sp.skip_stats = ext_ml != nullptr;
+  sp.in_step = in_step;
   // scores_ready: the dense attention of this step already left the scores in the workspace's score buffer
   hipError_t e = hipSuccess;
   if (!scores_ready && pl.mfma) {
@@ -776,7 +778,7 @@ int32_t sdllm_block_step(const sdllm_shape_t* shape, int32_t step_in_block, int3
   };
   if (!row_stride_ok(s.q_stride, s.head_dim)) return finish_pending(SDLLM_ERR_INVALID_ARG);
   st = score_select_impl(s, q_blk, k_in, idx, nullptr, nullptr, (char*)ws + w.score_off, w.base - w.score_off,
-                         (hipStream_t)stream, w.fuse ? (float*)((char*)ws + w.base) : nullptr, w.stats_parts, w.fuse_cols);
+                         (hipStream_t)stream, w.fuse ? (float*)((char*)ws + w.base) : nullptr, w.stats_parts, true, w.fuse_cols);
   if (st != SDLLM_OK) return finish_pending(st);
   if (pending.n_split == 1) return sdllm_compact_kv(shape, k_in, v_in, idx, k_cache, v_cache, stream);
   CompactParams cp{};

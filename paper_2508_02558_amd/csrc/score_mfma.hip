@@ -488,29 +488,36 @@ static int candidate_tiles(const ScoreParams& p) {
 
 // Which of the two kernels runs the column pass of grouped-query heads.  A wave per head starts sooner and reads LDS less per tile, but
 // fills a CU with one workgroup of G or 2 G waves; from some number of tiles per CU on, eight waves that walk the heads, or two
-// such workgroups, take less.  The line lies there, in rows ((batch, KV head) pairs) x tiles, by how many waves there are and by
-// what a weight costs the other kernel (softmax: statistics from LDS for each).  us, walking / wave per head:
-// * column pass and selection, raw logits: 2 heads, 8 rows x 46 tiles 9.4 / 8.3, 32 x 24 8.9 / 9.2, 192 x 187 67.3 / 86.0; 4 heads,
-//   8 x 46 10.1 / 9.0, 96 x 93 23.3 / 25.4; 5 heads, 16 x 24 9.8 / 9.0, 192 x 24 17.6 / 20.7; 7 heads, 16 x 93 15.4 / 14.3, 96 x 93 29.9 / 33.0;
-// * whole cache-update step, softmax with the statistics there: 2 heads, 16 x 93 29.9 / 27.0, 192 x 46 67.0 / 68.4, 256 x 187 244.7 /
-//   260.8; 7 heads, 32 x 46 35.6 / 32.8, 192 x 93 179.5 / 183.1; with few rows at any length: 7 heads, 2 x 1190 77.1 / 68.6;
-// * statistics from a launch of this file: 2 heads, 8 x 71 18.6 / 16.7, 48 x 12 13.9 / 14.5; 7 heads, 8 x 94 26.8 / 22.7.  That leaves up to
-//   256 partials a row, which a wave per head folds by itself: 1 x 1814 with 7 heads 53.3 / 56.9, 1 x 1948 with 2 43.9 / 48.0.
+// such workgroups, take less.  The line lies there, in rows ((batch, KV head) pairs) x tiles, by how many waves there are.
+// us, walking / wave per head:
+// * whole cache-update step, whose other kernels leave less of either one's code in the instruction cache: 2 heads, 16 rows x 93
+//   tiles 29.9 / 27.0, 192 x 46 67.0 / 68.4, 256 x 187 244.7 / 260.8; 7 heads, 32 x 46 35.6 / 32.8, 192 x 93 179.5 / 183.1; with few
+//   rows at any length, 7 heads, 2 x 1190 77.1 / 68.6; raw logits, 3 heads, 68 x 14 24.9 / 22.5;
+// * on its own, raw logits, with the selection: 2 heads, 8 x 46 9.4 / 8.3, 32 x 24 8.9 / 9.2, 192 x 187 67.3 / 86.0; 4 heads,
+//   8 x 46 10.1 / 9.0, 91 x 13 10.9 / 11.9, 96 x 93 23.3 / 25.4; 5 heads, 16 x 24 9.8 / 9.0, 192 x 24 17.6 / 20.7; 7 heads, 16 x 93
+//   15.4 / 14.3, 96 x 93 29.9 / 33.0;
+// * softmax with statistics from a launch of this file, which leaves the keys where they are read again soonest: 2 heads, 8 x 71
+//   18.6 / 16.7, 48 x 12 13.9 / 14.5; 5 heads, 70 x 13 20.6 / 21.8; 7 heads, 8 x 94 26.8 / 22.7.  That leaves up to 256 partials a
+//   row too, which a wave per head folds by itself: 1 x 1814 with 7 heads 53.3 / 56.9, 1 x 1948 with 2 43.9 / 48.0.
 // Beyond 256 rows the kernel that walks the heads has one workgroup per row, of ever fewer waves, of which from six heads on
 // the queries' LDS lets a CU hold one: 7 heads, 512 rows x 24 tiles, raw logits 51.3 / 41.8.
 static bool heads_pay(const ScoreParams& p, int tiles) {
   const int rows = p.batch * p.hkv, g = p.group;
-  const bool own_stats = p.softmax && !p.skip_stats;
-  if (own_stats && p.n_stat_part > (g <= 3 ? 16 : g <= 5 ? 48 : 64)) return false;
-  //                                                                   G = 2, 3   4     5     6 and more
-  static constexpr int kMost[3][4] = {/* raw logits                  */ {600,  1300, 1300, 3500},    // rows x tiles
-                                      /* softmax, own statistics     */ {0,    5000, 1000, 5000},
-                                      /* softmax, statistics given   */ {2500, 5000, 4000, 5000}};
-  static constexpr int kFewRows[3][4] = {{0, 0, 0, 4}, {12, 12, 0, 12}, {12, 12, 12, 12}};           // at any length
-  const int kind = !p.softmax ? 0 : own_stats ? 1 : 2, by_g = g <= 3 ? 0 : g == 4 ? 1 : g == 5 ? 2 : 3;
-  const bool little = (int64_t)rows * tiles <= kMost[kind][by_g];
-  if (rows > kNumCUs) return g >= 6 && (p.softmax || rows >= 400 || little);
-  return little || rows <= kFewRows[kind][by_g];
+  const int64_t work = (int64_t)rows * tiles;
+  if (p.in_step) {
+    static constexpr int kMost[9] = {0, 0, 3000, 4000, 6000, 3500, 6000, 5000, 4000};   // by heads per group
+    if (rows > kNumCUs) return g >= 6 || (g >= 4 && tiles <= 9) || (g == 4 && p.softmax);
+    return work <= kMost[g] || rows <= 8;
+  }
+  if (!p.softmax) {
+    const int most = g <= 3 ? 600 : g <= 5 ? 1000 : 3000;
+    if (rows > kNumCUs) return g >= 6 && (rows >= 400 || work <= most);
+    if (rows > kNumCUs / 3) return tiles <= (g <= 5 ? 4 : 12);   // one or two workgroups per row
+    return work <= most || (g >= 6 && rows <= 4);
+  }
+  if (p.n_stat_part > (g <= 3 ? 16 : g <= 5 ? 48 : 64)) return false;
+  if (rows > (g == 4 ? 40 : g >= 6 ? 36 : 22)) return g >= 6 && rows <= 64 && tiles >= 24 && work <= 4000;
+  return work <= (g == 5 ? 2500 : 5000) || (rows <= 12 && (g == 4 || g >= 6));
 }
 
 template <int G>

@@ -29,7 +29,7 @@ def _reference(q, k, group, off, softmax):
     (1, 4, 2, 33, 0), (1, 4, 2, 97, 32), (2, 6, 2, 800, 415), (1, 8, 2, 1056, 1024), (1, 5, 1, 230, 31), (1, 6, 1, 2090, 700),
     (1, 7, 1, 64, 32), (1, 7, 1, 65, 1), (1, 14, 2, 4300, 2111), (8, 28, 4, 700, 333), (3, 8, 1, 3001, 0), (2, 16, 2, 7001, 6000),
     (70, 8, 4, 500, 100), (70, 28, 4, 300, 101), (103, 28, 4, 230, 64),   # more rows than CUs: a workgroup walks all tiles
-    (20, 8, 4, 330, 0), (8, 24, 8, 500, 77), (24, 16, 4, 1501, 1400), (48, 20, 4, 900, 31), (20, 28, 4, 1633, 800),   # waves that walk the heads
+    (20, 8, 4, 330, 0), (8, 24, 8, 500, 77), (6, 16, 4, 300, 90), (24, 16, 4, 1501, 1400), (48, 20, 4, 900, 31), (20, 28, 4, 1633, 800),   # waves that walk the heads
 ])
 @pytest.mark.parametrize("mode", [B.SDLLM_LOGIT_MEAN, B.SDLLM_SOFTMAX_MEAN])
 def test_scores_of_grouped_heads(batch, q_heads, kv_heads, L, off, mode):
