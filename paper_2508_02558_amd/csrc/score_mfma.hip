@@ -498,7 +498,8 @@ static int candidate_tiles(const ScoreParams& p) {
 //   15.4 / 14.3, 96 x 93 29.9 / 33.0;
 // * softmax with statistics from a launch of this file, which leaves the keys where they are read again soonest: 2 heads, 8 x 71
 //   18.6 / 16.7, 48 x 12 13.9 / 14.5; 5 heads, 70 x 13 20.6 / 21.8; 7 heads, 8 x 94 26.8 / 22.7.  That leaves up to 256 partials a
-//   row too, which a wave per head folds by itself: 1 x 1814 with 7 heads 53.3 / 56.9, 1 x 1948 with 2 43.9 / 48.0.
+//   row too, which a wave per head folds by itself: 1 x 1814 with 7 heads 53.3 / 56.9, 1 x 1948 with 2 43.9 / 48.0.  With 7 heads
+//   and 45 to 64 rows of 24 to 50 tiles a wave per head takes 2 to 7 % less again.
 // Beyond 256 rows the kernel that walks the heads has one workgroup per row, of ever fewer waves, of which from six heads on
 // the queries' LDS lets a CU hold one: 7 heads, 512 rows x 24 tiles, raw logits 51.3 / 41.8.
 static bool heads_pay(const ScoreParams& p, int tiles) {
