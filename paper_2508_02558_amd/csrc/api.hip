@@ -493,6 +493,7 @@ int32_t score_select_impl(const sdllm_shape_t& s, const void* q_blk, const void*
   sp.q_sb = s.q_stride[0]; sp.q_sh = s.q_stride[1]; sp.q_sr = s.q_stride[2];
   sp.k_sb = s.kv_stride[0]; sp.k_sh = s.kv_stride[1]; sp.k_sr = s.kv_stride[2];
   sp.batch = s.batch; sp.hq = s.n_q_heads; sp.hkv = s.n_kv_heads; sp.group = s.n_q_heads / s.n_kv_heads;
+  sp.by_hkv = Divisor(s.n_kv_heads);
   sp.nq = s.block_len; sp.d = s.head_dim;
   sp.block_off = s.block_off; sp.block_len = s.block_len;
   sp.n_cand = pl.n_scored;

@@ -29,8 +29,10 @@ constexpr int g_wave_lds() {
   return (tiles > parked ? tiles : parked) + 512;
 }
 
+struct GeneralDivisors { Divisor per_key, n_split, hkv, rblocks; };
+
 template <typename T, int D, int MODE>
-__global__ __launch_bounds__(kGeneralMaxWaves * kWave) void attn_general_kernel(const AttnParams p, const int rblocks) {
+__global__ __launch_bounds__(kGeneralMaxWaves * kWave) void attn_general_kernel(const AttnParams p, const int rblocks, const GeneralDivisors by) {
   using O = Ops<T, D>;
   constexpr int R = O::kRows, NS = O::NS, kWaveBytes = g_wave_lds<T, D>(), kPark = O::NACC * 4 + 16, kUnits = O::NACC / 4;
   constexpr float kSlack = 8.f;   // as in attn_tile_math.h: the softmax reference moves when a maximum exceeds it by more
@@ -43,12 +45,11 @@ __global__ __launch_bounds__(kGeneralMaxWaves * kWave) void attn_general_kernel(
   // workgroups that read the same keys (the query heads of a KV group, their row blocks) sit on one XCD
   const int wg = xcd_contiguous_id(blockIdx.x, gridDim.x);
   const int per_key = p.group * rblocks;
-  const int pair = wg / per_key;
-  const int split = pair % p.n_split;
-  const int bg = pair / p.n_split;
-  const int b = bg / p.hkv, g = bg - b * p.hkv;
+  const int pair = by.per_key.quotient(wg);
+  const int bg = by.n_split.quotient(pair), split = pair - bg * p.n_split;
+  const int b = by.hkv.quotient(bg), g = bg - b * p.hkv;
   const int vhead = bg * per_key + wg - pair * per_key;   // (batch, query head, block of R rows)
-  const int head = vhead / rblocks, h = head - b * p.hq;
+  const int head = by.rblocks.quotient(vhead), h = head - b * p.hq;
   const int row = (vhead - head * rblocks) * R + col;
   const bool row_valid = row < p.nq;
 
@@ -236,38 +237,9 @@ __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(const Att
   combine_block<T, TPI>(p, blockIdx.x);
 }
 
-// The same for 32 rows of 128 columns (the bf16 kernels for blocks of 32) and up to MAX splits: a block per quarter of a head.  A
-// merge is a launch, a round trip to memory and the instructions before it, which mostly were divisions of indexes; here the grid
-// says which head it is, and every load is requested at once.  28 heads x 8 splits 3.9 -> 3.35 us with its launch, whole sparse
-// steps: 28 heads x 69 tiles 10.4 -> 9.8 us, 32 x 21 9.4 -> 8.9.  MAX is a step of four: loads past the last split repeat it.
 template <int MAX>
 __global__ __launch_bounds__(kCombineThreads) void attn_combine32_kernel(const AttnParams p) {
-  const int h = blockIdx.x >> 2, b = blockIdx.y;
-  const int row = (blockIdx.x & 3) * 8 + (threadIdx.x >> 5), c4 = (threadIdx.x & 31) << 2;
-  const size_t slot0 = (size_t)(b * p.hq + h) * p.n_split;
-  const float* ml = p.part_ml + slot0 * 64 + row;
-  const float* po = p.part_o + (slot0 * 32 + row) * 128 + c4;
-  float m_s[MAX], l_s[MAX];
-  mf32x4 o_s[MAX];
-#pragma unroll
-  for (int i = 0; i < MAX; ++i) {
-    const int s = min(i, p.n_split - 1);   // past the end: re-read the last one, left out below
-    m_s[i] = ml[s * 64];
-    l_s[i] = ml[s * 64 + 32];
-    o_s[i] = *reinterpret_cast<const mf32x4*>(po + s * 4096);
-  }
-  RowPiece r;
-#pragma unroll
-  for (int i = 0; i < MAX; ++i) r.m = fmaxf(r.m, m_s[i]);
-  r.l = 0.f;
-#pragma unroll
-  for (int i = 0; i < MAX; ++i) {
-    const float f = __builtin_amdgcn_exp2f(m_s[i] - r.m);
-    r.l = i < p.n_split ? __builtin_fmaf(f, l_s[i], r.l) : r.l;
-#pragma unroll
-    for (int c = 0; c < 4; ++c) r.o[c] = i < p.n_split ? __builtin_fmaf(f, o_s[i][c], r.o[c]) : r.o[c];
-  }
-  store_piece<__bf16>(r, (__bf16*)p.out + b * p.o_sb + h * p.o_sh + row * p.o_sr + c4);
+  combine32_block<MAX>(p, blockIdx.y, blockIdx.x >> 2, blockIdx.x & 3);
 }
 
 template <typename T, int D, int MODE>
@@ -280,7 +252,8 @@ static hipError_t launch_mode(const AttnParams& p, hipStream_t s) {
   const int rblocks = (p.nq + Ops<T, D>::kRows - 1) / Ops<T, D>::kRows;
   const int64_t nwg = (int64_t)p.batch * p.hq * rblocks * p.n_split;
   if (nwg > INT32_MAX || p.waves < 1 || p.waves > kGeneralMaxWaves) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(kernel, dim3((unsigned)nwg), dim3(p.waves * kWave), p.waves * kWaveBytes, s, p, rblocks);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)nwg), dim3(p.waves * kWave), p.waves * kWaveBytes, s, p, rblocks,
+                     GeneralDivisors{Divisor(p.group * rblocks), Divisor(p.n_split), Divisor(p.hkv), Divisor(rblocks)});
   return hipGetLastError();
 }
 
@@ -296,9 +269,9 @@ hipError_t launch_attn_general(const AttnParams& p, int dtype, bool stats_only, 
 }
 
 hipError_t launch_attn_combine(const AttnParams& p, int dtype, hipStream_t s) {
-  if (dtype == 0 && p.nq == 32 && p.d == 128 && p.n_split <= 16 && p.batch <= 65535) {
-    const auto kernel = p.n_split <= 4 ? attn_combine32_kernel<4> : p.n_split <= 8 ? attn_combine32_kernel<8>
-                        : p.n_split <= 12 ? attn_combine32_kernel<12> : attn_combine32_kernel<16>;
+  if (const int most = combine32_max(p, dtype); most > 0 && p.batch <= 65535) {
+    const auto kernel = most == 4 ? attn_combine32_kernel<4> : most == 8 ? attn_combine32_kernel<8>
+                        : most == 12 ? attn_combine32_kernel<12> : attn_combine32_kernel<16>;
     hipLaunchKernelGGL(kernel, dim3((unsigned)(4 * p.hq), (unsigned)p.batch), dim3(kCombineThreads), 0, s, p);
     return hipGetLastError();
   }

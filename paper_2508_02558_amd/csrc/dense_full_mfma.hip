@@ -178,10 +178,8 @@ void dense_phase_mfma_bf16_kernel(const DenseFullParams p) {
   // renumber workgroups so that consecutive ids (which go round-robin over the XCDs) of one head's
   // query blocks end up on the same XCD
   const int wg = xcd_contiguous_id(blockIdx.x, gridDim.x);
-  const int qblocks = (p.seq_len + full_rows_per_wg(KS) - 1) / full_rows_per_wg(KS);
-  const int qb = wg % qblocks;
-  const int head = wg / qblocks;
-  const int b = head / p.hq, h = head - b * p.hq, g = h / p.group;
+  const int head = p.by_qblocks.quotient(wg), qb = wg - head * p.qblocks;
+  const int b = p.by_hq.quotient(head), h = head - b * p.hq, g = p.by_group.quotient(h);
   // rows past the end of the sequence compute on a copy of the last row and are not written back
   const int q_row = qb * full_rows_per_wg(KS) + rb * 32 + col;
   const bool row_valid = q_row < p.seq_len;
@@ -342,10 +340,8 @@ __global__ __launch_bounds__(512) void dense_split_mfma_bf16_kernel(const DenseF
   const int rb = wave % RB, kg = wave / RB;
 
   const int wg = xcd_contiguous_id(blockIdx.x, gridDim.x);
-  const int qblocks = (p.seq_len + full_rows_per_wg(KS) - 1) / full_rows_per_wg(KS);
-  const int qb = wg % qblocks;
-  const int head = wg / qblocks;
-  const int b = head / p.hq, h = head - b * p.hq, g = h / p.group;
+  const int head = p.by_qblocks.quotient(wg), qb = wg - head * p.qblocks;
+  const int b = p.by_hq.quotient(head), h = head - b * p.hq, g = p.by_group.quotient(h);
   const int q_row = qb * full_rows_per_wg(KS) + rb * 32 + col;
   const bool row_valid = q_row < p.seq_len;
   bf16x8 qf[8] = {};
@@ -432,8 +428,10 @@ static hipError_t launch_full(const DenseFullParams& p, hipStream_t s) {
   }();
   const hipError_t e = lds.ensure(reinterpret_cast<const void*>(kernel), kLds);
   if (e != hipSuccess) return e;
-  const int qblocks = (p.seq_len + full_rows_per_wg(KS) - 1) / full_rows_per_wg(KS);
-  hipLaunchKernelGGL(kernel, dim3(qblocks * p.batch * p.hq), dim3(512), kLds, s, p);
+  DenseFullParams q = p;
+  q.qblocks = (p.seq_len + full_rows_per_wg(KS) - 1) / full_rows_per_wg(KS);
+  q.by_qblocks = Divisor(q.qblocks); q.by_hq = Divisor(p.hq); q.by_group = Divisor(p.group);
+  hipLaunchKernelGGL(kernel, dim3(q.qblocks * p.batch * p.hq), dim3(512), kLds, s, q);
   return hipGetLastError();
 }
 

@@ -24,14 +24,14 @@ template <typename T, int D>
 constexpr int col_blocks() { return 65536 / col_block_bytes<T, D>(); }                   // blocks held in LDS at once
 
 template <typename T, int D>
-__global__ __launch_bounds__(kColWaves * kWave) void score_cols_general_kernel(const ScoreParams p, const int rblocks) {
+__global__ __launch_bounds__(kColWaves * kWave) void score_cols_general_kernel(const ScoreParams p, const int rblocks, const Divisor by_rblocks) {
   using O = Ops<T, D>;
   constexpr int kBlocks = col_blocks<T, D>(), R = O::kRows, kQBytes = R * O::kKRow;
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int part = lane / R, col = lane % R;
-  const int bg = blockIdx.y, b = bg / p.hkv, g = bg - b * p.hkv;
+  const int bg = blockIdx.y, b = p.by_hkv.quotient(bg), g = bg - b * p.hkv;
   const int n_blk = p.group * rblocks;
   const int held = min(n_blk, kBlocks);
   uint8_t* lds_q = smem;
@@ -53,14 +53,14 @@ __global__ __launch_bounds__(kColWaves * kWave) void score_cols_general_kernel(c
     constexpr int kPerRow = O::kRow / 16;
     for (int i = tid; i < here * R * kPerRow; i += kColWaves * kWave) {
       const int c = i % kPerRow, r = i / kPerRow % R, k = i / kPerRow / R;
-      const int hh = (blk0 + k) / rblocks, row = (blk0 + k - hh * rblocks) * R + r;
+      const int hh = by_rblocks.quotient(blk0 + k), row = (blk0 + k - hh * rblocks) * R + r;
       const u32x4 v = *reinterpret_cast<const u32x4*>((const char*)p.q + sizeof(T) * (b * p.q_sb + (int64_t)(g * p.group + hh) * p.q_sh + min(row, p.nq - 1) * p.q_sr) + c * 16);
       *reinterpret_cast<u32x4*>(lds_q + k * kQBytes + r * O::kKRow + c * 16) = v;
     }
     if (p.softmax) {
       for (int i = tid; i < here * R; i += kColWaves * kWave) {
         const int r = i % R, k = i / R;
-        const int hh = (blk0 + k) / rblocks, rb = blk0 + k - hh * rblocks;
+        const int hh = by_rblocks.quotient(blk0 + k), rb = blk0 + k - hh * rblocks;
         float m_tot = -INFINITY, l_tot = 0.f;
         const float* src = p.part_ml + (((size_t)b * p.hq + g * p.group + hh) * rblocks + rb) * p.n_stat_part * 2 * R + r;
 #pragma unroll 8
@@ -87,7 +87,7 @@ __global__ __launch_bounds__(kColWaves * kWave) void score_cols_general_kernel(c
       float total[O::kKeysPerLane];
 #pragma unroll
       for (int n = 0; n < O::kKeysPerLane; ++n) total[n] = 0.f;
-      int row0 = blk0 % rblocks * R;   // of block k, in its head
+      int row0 = (blk0 - by_rblocks.quotient(blk0) * rblocks) * R;   // of block k, in its head
       for (int k = 0; k < here; ++k) {
         float s[O::NS], sum[O::kKeysPerLane];
         O::score(lds_q + k * kQBytes, keys, col, part, s);
@@ -141,7 +141,7 @@ static hipError_t launch_cols(const ScoreParams& p, hipStream_t s) {
   const int most = (4 * kNumCUs + rows - 1) / rows;
   if (parts > most) parts = most;
   const size_t bytes = (size_t)held * kBlockBytes + kColWaves * O::kKTile;
-  hipLaunchKernelGGL(kernel, dim3(parts, rows), dim3(kColWaves * kWave), bytes, s, p, rblocks);
+  hipLaunchKernelGGL(kernel, dim3(parts, rows), dim3(kColWaves * kWave), bytes, s, p, rblocks, Divisor(rblocks));
   return hipGetLastError();
 }
 

@@ -183,7 +183,7 @@ __global__ __launch_bounds__(512) void score_stats_mfma_kernel(const ScoreParams
   const int half = lane >> 5, col = lane & 31;
   const int part = blockIdx.x;
   const int bg = blockIdx.y;
-  const int b = bg / p.hkv, g = bg - b * p.hkv;
+  const int b = p.by_hkv.quotient(bg), g = bg - b * p.hkv;
 
   uint8_t* lds_q = smem;
   uint8_t* lds_k = smem + G * kTileBytes + wave * kTileBytes;
@@ -318,7 +318,7 @@ __global__ __launch_bounds__(512) void score_cols_mfma_kernel(const ScoreParams 
   const int half = lane >> 5, col = lane & 31;
   const int part = blockIdx.x;
   const int bg = blockIdx.y;
-  const int b = bg / p.hkv, g = bg - b * p.hkv;
+  const int b = p.by_hkv.quotient(bg), g = bg - b * p.hkv;
 
   uint8_t* lds_q = smem;
   uint8_t* lds_k = smem + G * kTileBytes + wave * kTileBytes;
@@ -368,7 +368,7 @@ __global__ __launch_bounds__((heads_waves(G) + 1) * kWave) void score_cols_heads
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int half = lane >> 5, col = lane & 31;
-  const int bg = blockIdx.y, b = bg / p.hkv, g = bg - b * p.hkv;
+  const int bg = blockIdx.y, b = p.by_hkv.quotient(bg), g = bg - b * p.hkv;
 
   const CandTiles ct = cand_tiles(p, b, g);
   const int ntiles = ct.tiles0 + (ct.n1 + kTileKeys - 1) / kTileKeys;

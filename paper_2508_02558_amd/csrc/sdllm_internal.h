@@ -29,6 +29,26 @@ __host__ __device__ inline int xcd_contiguous_id(int dealt, int n) {
   return x * q + (x < r ? x : r) + dealt / kNumXCDs;
 }
 
+// Exact n / d of 0 <= n < 2^31 by a d in [1, 2^31) that the host knows: with 2^(l-1) < d <= 2^l and mul = ceil(2^(31+l) / d), that is
+// 2^(31+l) / d plus less than 1, n mul / 2^(31+l) exceeds n / d by less than n / 2^(31+l), and so by less than 1 / d.  Three scalar
+// instructions where the compiler's division by a kernel parameter is some thirty vector ones in a chain.  In front of a kernel's
+// first load that is worth 1 to 4 % of calls of 6 to 14 us (general kernels 10.0 -> 9.7 us, 8.1 -> 8.0, full-sequence attention of
+// 28 heads x 100 positions 6.8 -> 6.7).  Not so in attn_mfma.hip, 2 to 5 % slower with it (28 heads x 69 tiles 10.2 -> 10.4,
+// 256 x 8 8.8 -> 9.2), and level in the other two kernels of block queries: they divide as the compiler does.
+struct Divisor {
+  uint32_t mul, shift;
+  Divisor() = default;
+  constexpr explicit Divisor(uint32_t d) : mul(0), shift(31) {
+    while (((uint64_t)1 << (shift - 31)) < d) ++shift;
+    mul = (uint32_t)((((uint64_t)1 << shift) + d - 1) / d);
+  }
+  __host__ __device__ constexpr int quotient(int n) const { return (int)(((uint64_t)(uint32_t)n * mul) >> shift); }
+};
+static_assert(Divisor(1).quotient(INT32_MAX) == INT32_MAX && Divisor(7).quotient(48) == 6 && Divisor(7).quotient(49) == 7 &&
+                  Divisor(3).quotient(INT32_MAX) == INT32_MAX / 3 && Divisor(INT32_MAX).quotient(INT32_MAX - 1) == 0 &&
+                  Divisor(INT32_MAX).quotient(INT32_MAX) == 1 && Divisor(1 << 30).quotient(INT32_MAX) == 1,
+              "exact at the ends");
+
 // Kernels that need more than the default 64 KB of dynamic LDS have to opt in, once per device (the
 // attribute belongs to the device's copy of the kernel).  One object per kernel remembers which
 // devices are done; concurrent host threads at worst both set the same value.
@@ -111,6 +131,7 @@ struct ScoreParams {
   int32_t n_stat_part;  // partial (max, sum) pairs per query row in part_ml
   int32_t skip_stats;   // 1: part_ml was already filled (by the dense attention of the same step)
   int32_t in_step;      // 1: between the other launches of a cache-update step
+  Divisor by_hkv;
   int32_t cols_follow;  // set by the launcher: the statistics kernel runs the column pass itself (n_part == 1)
   int32_t waves;
 };
@@ -149,6 +170,8 @@ struct CompactParams {
   int64_t c_sb, c_sh, c_sr;  // cache strides in BYTES
   int32_t batch, hkv, k_total, seq_len;
   int32_t row_bytes;
+  Divisor by_hkv, by_row_blocks;   // set by the launcher: KV heads, blocks per row of the index set
+  int32_t row_blocks;
 };
 
 // Full-sequence bidirectional attention: L query rows per head over all L keys.
@@ -162,6 +185,8 @@ struct DenseFullParams {
   int64_t o_sb, o_sh, o_sr;
   int32_t batch, hq, hkv, group, seq_len, d;
   float scale_log2;
+  int32_t qblocks;                        // set by the launcher: workgroups per head
+  Divisor by_qblocks, by_hq, by_group;
 };
 
 // kernel launchers (each returns hipGetLastError() after its launches)
