@@ -147,22 +147,25 @@ __device__ __forceinline__ void combine32_block(const AttnParams& p, int b, int 
   const float* po = p.part_o + (slot0 * 32 + row) * 128 + c4;
   float m_s[MAX], l_s[MAX];
   mf32x4 o_s[MAX];
+  auto split = [&](int i) { return min(i, p.n_split - 1); };   // past the end: left out below
+#pragma unroll
+  for (int i = 0; i < MAX; ++i) m_s[i] = ml[split(i) * 64];
 #pragma unroll
   for (int i = 0; i < MAX; ++i) {
-    const int s = min(i, p.n_split - 1);   // past the end: left out below
-    m_s[i] = ml[s * 64];
-    l_s[i] = ml[s * 64 + 32];
-    o_s[i] = *reinterpret_cast<const mf32x4*>(po + s * 4096);
+    l_s[i] = ml[split(i) * 64 + 32];
+    o_s[i] = *reinterpret_cast<const mf32x4*>(po + split(i) * 4096);
   }
+  __builtin_amdgcn_sched_barrier(0);
   RowPiece r;
 #pragma unroll
   for (int i = 0; i < MAX; ++i) r.m = fmaxf(r.m, m_s[i]);
 #pragma unroll
   for (int i = 0; i < MAX; ++i) {
     const float f = __builtin_amdgcn_exp2f(m_s[i] - r.m);
-    r.l = i < p.n_split ? __builtin_fmaf(f, l_s[i], r.l) : r.l;
+    const bool there = i == 0 || i < p.n_split;
+    r.l = there ? __builtin_fmaf(f, l_s[i], r.l) : r.l;
 #pragma unroll
-    for (int c = 0; c < 4; ++c) r.o[c] = i < p.n_split ? __builtin_fmaf(f, o_s[i][c], r.o[c]) : r.o[c];
+    for (int c = 0; c < 4; ++c) r.o[c] = there ? __builtin_fmaf(f, o_s[i][c], r.o[c]) : r.o[c];
   }
   store_piece<__bf16>(r, (__bf16*)p.out + b * p.o_sb + h * p.o_sh + row * p.o_sr + c4);
 }
