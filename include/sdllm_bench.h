@@ -46,8 +46,14 @@ typedef struct sdllm_launch_plan {
 } sdllm_launch_plan_t;
 
 /* How an attention call of this shape is launched (n_cached: SDLLM_CALL_SPARSE only), given all the workspace it asks
- * for.  Host only; the pointers are host pointers. */
+ * for, unless sdllm_burst_splits gives it to another kernel.  Host only; the pointers are host pointers. */
 int32_t sdllm_launch_plan(const sdllm_shape_t* shape, int32_t call, int32_t n_cached, sdllm_launch_plan_t* plan);
+
+/* Small calls of SDLLM_CALL_SPARSE and SDLLM_CALL_FULL run a kernel that fetches all tiles of a workgroup at once, ahead of what
+ * sdllm_launch_plan says: *splits is the number of workgroups that share a head's keys then, 0 for a call that it does not take.  A
+ * workspace with less room takes fewer, and the plan of sdllm_launch_plan if there is no room for those that it needs at least, or
+ * if it is not aligned to 16 bytes.  Host only. */
+int32_t sdllm_burst_splits(const sdllm_shape_t* shape, int32_t call, int32_t n_cached, int32_t* splits);
 
 #ifdef __cplusplus
 }

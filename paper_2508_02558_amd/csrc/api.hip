@@ -92,6 +92,7 @@ struct AttnPlan {
   bool mfma;  // one of the kernels for bf16, head_dim 128, 32 query rows; otherwise the general one
   bool gqa;   // grouped-query kernel: one workgroup per (batch, KV head), wave = query head
   bool stream;   // one workgroup per head with tiles fetched straight into LDS
+  bool burst;    // at most nine tiles per workgroup, all of them fetched at once
   int n_split, tiles_per_split, waves;
   size_t part_o_bytes, part_ml_bytes;
   size_t ws_bytes() const { return part_o_bytes + part_ml_bytes; }
@@ -104,6 +105,11 @@ bool seg_fits_u32(int64_t row_stride, int32_t n, int esize) {
 // Whether sdllm_dense_attn runs the bf16 kernel for whole sequences; otherwise the general one.
 bool dense_full_takes(const sdllm_shape_t& s) {
   return s.dtype == SDLLM_BF16 && s.head_dim == 128 && seg_fits_u32(s.kv_stride[2], s.seq_len, 2);
+}
+
+// Whether an attention call of the block's rows runs one of the kernels for bf16, head_dim 128, 32 rows.
+bool takes_mfma(const sdllm_shape_t& s, int32_t n0, int64_t sr0, int32_t n1, int64_t sr1) {
+  return s.dtype == SDLLM_BF16 && s.head_dim == 128 && s.block_len == 32 && seg_fits_u32(sr0, n0, 2) && seg_fits_u32(sr1, n1, 2);
 }
 
 int row_blocks(const sdllm_shape_t& s, int32_t rows) { return (rows + block_rows(s.dtype) - 1) / block_rows(s.dtype); }
@@ -201,15 +207,22 @@ bool shared_tile_pays(int heads, int rows, int tiles, int n_split, bool update) 
   return pays && (own == 1 || wave_tiles >= 30000 || (tiles >= 512 && wave_tiles >= 22000) || (heads >= 128 && wave_tiles >= 18000));
 }
 
+// Room for the key splits' partials of a kernel for 32 rows
+void size_partials(AttnPlan& pl, const sdllm_shape_t& s) {
+  if (pl.n_split == 1) return;
+  const size_t slots = (size_t)s.batch * s.n_q_heads * pl.n_split;
+  pl.part_o_bytes = align_up(slots * s.block_len * s.head_dim * sizeof(float));
+  pl.part_ml_bytes = align_up(slots * 2 * s.block_len * sizeof(float));
+}
+
 // update: the dense rows of a cache-update step, where the merge of key splits costs no launch of its own (it runs in the
 // compaction's) and the kernel mostly leaves the scoring's row statistics as well.
 // scratch: the workspace there is.  A shared-tile kernel that does not fit gives way to the others up to 80 MB of keys and
 // values (5000 tiles; it is a matter of speed there, and sdllm_sparse_attn_noalloc has 8 MB); beyond, the call is refused.
-AttnPlan plan_attn(const sdllm_shape_t& s, int32_t n0, int64_t sr0, int32_t n1, int64_t sr1, bool update = false,
-                   size_t scratch = SIZE_MAX) {
+AttnPlan plan_streams(const sdllm_shape_t& s, int32_t n0, int64_t sr0, int32_t n1, int64_t sr1, bool update = false,
+                      size_t scratch = SIZE_MAX) {
   AttnPlan pl{};
-  pl.mfma = s.dtype == SDLLM_BF16 && s.head_dim == 128 && s.block_len == 32 && seg_fits_u32(sr0, n0, 2) &&
-            seg_fits_u32(sr1, n1, 2);
+  pl.mfma = takes_mfma(s, n0, sr0, n1, sr1);
   pl.n_split = 1;
   pl.tiles_per_split = 0;
   pl.waves = 1;
@@ -221,12 +234,7 @@ AttnPlan plan_attn(const sdllm_shape_t& s, int32_t n0, int64_t sr0, int32_t n1, 
   const int64_t wave_tiles = (int64_t)s.batch * s.n_q_heads * tiles;
   const int group = s.n_q_heads / s.n_kv_heads;
   const int heads = s.batch * s.n_q_heads, rows = s.batch * s.n_kv_heads;
-  const auto partials = [&] {
-    if (pl.n_split == 1) return;
-    const size_t slots = (size_t)heads * pl.n_split;
-    pl.part_o_bytes = align_up(slots * s.block_len * s.head_dim * sizeof(float));
-    pl.part_ml_bytes = align_up(slots * 2 * s.block_len * sizeof(float));
-  };
+  const auto partials = [&] { size_partials(pl, s); };
   // Key splits of the kernels with one workgroup per head, only while the grid is small: as many as keep
   // it within one workgroup per CU (an eight-wave workgroup fills a CU's LDS, so workgroup
   // number 257 waits for a whole round: 56 heads x 4 splits 15.1 us, x 5 splits 22.3 us), at most 8
@@ -319,6 +327,54 @@ AttnPlan plan_attn(const sdllm_shape_t& s, int32_t n0, int64_t sr0, int32_t n1, 
   return pl;
 }
 
+// Key splits with which the kernel that fetches all of a workgroup's tiles at once (attn_burst_mfma.hip) takes a call ahead of the
+// kernels above, 0 if it does not.  It wins as long as its workgroups fit one to a CU, except
+// * unsplit, 225 to 256 multi-head heads with eight or nine tiles (256 x 8 +7 %, x 9 0 to +11 %; 224 x 9 8.9 -> 8.5 us, 128 x 9 8.0 -> 7.1);
+// * where the others go unsplit and it would have to split, up to: 10 heads' worth of tiles with few heads (16 x 10 6.1 -> 5.7 us, 20 x
+//   10 6.2 -> 5.9, 28 x 10 level, 28 x 11 6.5 -> 6.0, 32 x 10 +3 %), multi-head from 11 (49 x 10 6.8 / 7.5, x 11 8.3 -> 7.6) and with more
+//   than 64 heads 15 (72 x 15 9.7 -> 9.25, 80 x 22 11.9 -> 11.0, 96 x 18 10.6 / 11.2), grouped-query from 17 with more than 40
+//   heads (48 x 15 7.2 / 7.1, x 19 8.0 -> 7.4, 56 x 18 7.5 / 7.65, x 23 8.6 -> 7.85), 24 with more than 56 (64 x 22 8.4 / 8.7, x 26 9.6 ->
+//   8.9) and not at all with more than 64 (80 x 10 6.3 / 7.5, x 27 9.5 / 9.8).
+// More than one round of workgroups, whose second round waits for the first, is a quarter to a half slower (28 x 90 11.1 / 13.8).
+// The splits are those of least modelled time: a tile in a workgroup 0.22 us, the ninth 0.08 more (a third wave on one SIMD), four
+// splits to fold 0.16, and 0.94 for 16 KB of partials on each of 100 workgroups, fitted to 460 calls of 2 to 96 heads x 10 to 280
+// tiles (rms 0.2 us; half a per cent lost to the best count on average, 5 % at 2 of 130 sizes).
+// most: no more of them.
+int burst_splits(int heads, int tiles, int group, int most) {
+  if (tiles <= kBurstMaxTiles) return heads <= (group > 1 || tiles <= 7 ? kNumCUs : 224) ? 1 : 0;
+  if (heads > (group > 1 ? 64 : 85)) return 0;
+  const int from = heads <= 20 ? 10 : group == 1 ? (heads <= 64 ? 11 : 15) : heads <= 40 ? 11 : heads <= 56 ? 17 : 24;
+  if (tiles < from) return 0;
+  int best = 0, least = INT32_MAX;
+  for (int n = (tiles + kBurstMaxTiles - 1) / kBurstMaxTiles; n <= most && n * heads <= kNumCUs; ++n) {
+    const int mine = (tiles + n - 1) / n;
+    const int cost = 22 * mine + (mine > kMaxWavesPerWg ? 8 : 0) + 16 * ((n + 3) / 4) + 15 * heads * n / 16;   // 0.01 us
+    if (cost < least) { least = cost; best = n; }
+  }
+  return best;
+}
+
+// Whether that kernel takes a call without by-products (pl is the plan then), given `scratch` bytes of workspace aligned to 16.  It
+// makes do with fewer splits where those of the rule do not fit: sdllm_block_step asks for no more workspace for its sake, but nearly
+// always has it, for scores and for the partials of the longer dense rows.
+constexpr size_t kBurstPartialBytes = 32 * (128 + 2) * sizeof(float);
+bool plan_burst(AttnPlan& pl, const sdllm_shape_t& s, int32_t n0, int64_t sr0, int32_t n1, int64_t sr1, size_t scratch) {
+  if (!takes_mfma(s, n0, sr0, n1, sr1)) return false;
+  const int64_t heads = (int64_t)s.batch * s.n_q_heads;
+  const int tiles = (n0 + kTileKeys - 1) / kTileKeys + (n1 + kTileKeys - 1) / kTileKeys;
+  if (heads > kNumCUs) return false;
+  const size_t fit = scratch / (heads * kBurstPartialBytes);
+  const int n = burst_splits((int)heads, tiles, s.n_q_heads / s.n_kv_heads, fit < 32 ? (int)fit : 32);
+  if (n == 0) return false;
+  pl = AttnPlan{};
+  pl.mfma = pl.burst = true;
+  pl.tiles_per_split = (tiles + n - 1) / n;
+  pl.n_split = (tiles + pl.tiles_per_split - 1) / pl.tiles_per_split;
+  pl.waves = pl.tiles_per_split > kMaxWavesPerWg ? pl.tiles_per_split : kMaxWavesPerWg;
+  size_partials(pl, s);
+  return pl.ws_bytes() <= scratch;   // two buffers, each a multiple of 256 bytes
+}
+
 // Whether the dense launch of a cache-update step can also leave the saliency scores: multi-head attention
 // (one query head per KV head) on the one-workgroup-per-head kernel, no key splits, at least two waves.
 bool fuses_columns(const AttnPlan& pl, const sdllm_shape_t& s) {
@@ -333,7 +389,9 @@ bool fuses_columns(const AttnPlan& pl, const sdllm_shape_t& s) {
 int32_t run_attn(const sdllm_shape_t& s, const void* q, const KvSegment& a, const KvSegment& b, void* out, void* ws,
                  size_t ws_bytes, hipStream_t stream, bool update = false, float* cand_ml = nullptr, int cand0_end = 0,
                  int cand1_begin = 0, AttnParams* deferred = nullptr, float* score_out = nullptr, int score_stride = 0) {
-  AttnPlan pl = plan_attn(s, a.n, a.sr, b.n, b.sr, update, ws ? ws_bytes : 0);
+  AttnPlan pl;
+  if (update || cand_ml || !plan_burst(pl, s, a.n, a.sr, b.n, b.sr, aligned16(ws) && ws ? ws_bytes : 0))
+    pl = plan_streams(s, a.n, a.sr, b.n, b.sr, update, ws ? ws_bytes : 0);
   const bool fits = ws && ws_bytes >= pl.ws_bytes();
   if (pl.ws_bytes() > 0 && pl.mfma && !fits) return SDLLM_ERR_WORKSPACE;
   if (pl.ws_bytes() > 0 && !pl.mfma && !(fits && aligned16(ws))) {
@@ -362,7 +420,8 @@ int32_t run_attn(const sdllm_shape_t& s, const void* q, const KvSegment& a, cons
   p.score_inv_count = 1.f / (float)(s.block_len * (s.n_q_heads / s.n_kv_heads));
   hipError_t e;
   if (pl.mfma) {
-    e = pl.stream ? launch_attn_stream_mfma_bf16(p, stream) : pl.gqa ? launch_attn_gqa_mfma_bf16(p, stream) : launch_attn_mfma_bf16(p, stream);
+    e = pl.burst ? launch_attn_burst_mfma_bf16(p, stream) : pl.stream ? launch_attn_stream_mfma_bf16(p, stream)
+        : pl.gqa ? launch_attn_gqa_mfma_bf16(p, stream) : launch_attn_mfma_bf16(p, stream);
   } else {
     e = launch_attn_general(p, s.dtype, false, stream);
   }
@@ -570,9 +629,9 @@ struct BlockStepWs {
 
 BlockStepWs plan_block_step(const sdllm_shape_t& s, bool beside = true) {
   const Counts c = counts_of(s);
-  const AttnPlan full = plan_attn(s, s.seq_len, s.kv_stride[2], 0, 0);
-  const AttnPlan dense = plan_attn(s, s.seq_len, s.kv_stride[2], 0, 0, c.k_total > 0);   // of a cache-update step
-  const AttnPlan sparse = plan_attn(s, c.k_total, s.cache_stride[2], s.block_len, s.blk_stride[2]);
+  const AttnPlan full = plan_streams(s, s.seq_len, s.kv_stride[2], 0, 0);
+  const AttnPlan dense = plan_streams(s, s.seq_len, s.kv_stride[2], 0, 0, c.k_total > 0);   // of a cache-update step
+  const AttnPlan sparse = plan_streams(s, c.k_total, s.cache_stride[2], s.block_len, s.blk_stride[2]);
   const ScorePlan sc = plan_score(s);
   BlockStepWs w{};
   w.score_off = (beside || dense.mfma) && dense.n_split > 1 && c.k_total > 0 ? align_up(dense.ws_bytes()) : 0;
@@ -667,7 +726,9 @@ int32_t sdllm_workspace_bytes(const sdllm_shape_t* shape, int32_t op, int32_t n_
     case SDLLM_OP_COMPACT_KV: need = 0; break;
     case SDLLM_OP_SPARSE_ATTN:
       if (n_cached < 0) return SDLLM_ERR_INVALID_ARG;
-      need = plan_attn(s, n_cached, s.cache_stride[2], s.block_len, s.blk_stride[2]).ws_bytes();
+      need = plan_streams(s, n_cached, s.cache_stride[2], s.block_len, s.blk_stride[2]).ws_bytes();
+      if (AttnPlan b; plan_burst(b, s, n_cached, s.cache_stride[2], s.block_len, s.blk_stride[2], SIZE_MAX) && b.ws_bytes() > need)
+        need = b.ws_bytes();
       break;
     case SDLLM_OP_BLOCK_STEP: need = plan_block_step(s).bytes(); break;
     default: return SDLLM_ERR_INVALID_ARG;
@@ -724,7 +785,7 @@ int32_t sdllm_sparse_attn_noalloc(const sdllm_shape_t* shape, const void* q_blk,
   if (st != SDLLM_OK) return st;
   if (n_cached < 0) return SDLLM_ERR_INVALID_ARG;
   const sdllm_shape_t& s = *shape;
-  const size_t need = plan_attn(s, n_cached, s.cache_stride[2], s.block_len, s.blk_stride[2], false, SDLLM_STATIC_SCRATCH_BYTES).ws_bytes();
+  const size_t need = plan_streams(s, n_cached, s.cache_stride[2], s.block_len, s.blk_stride[2], false, SDLLM_STATIC_SCRATCH_BYTES).ws_bytes();
   if (need > SDLLM_STATIC_SCRATCH_BYTES) return SDLLM_ERR_STATIC_LIMIT;
   void* ptr = nullptr;
   if (static_scratch(&ptr) != hipSuccess) return SDLLM_ERR_HIP;
@@ -843,13 +904,25 @@ int32_t sdllm_launch_plan(const sdllm_shape_t* shape, int32_t call, int32_t n_ca
     return SDLLM_OK;
   }
   AttnPlan pl{};
-  if (call == SDLLM_CALL_SPARSE) pl = plan_attn(s, n_cached, s.cache_stride[2], s.block_len, s.blk_stride[2]);
+  if (call == SDLLM_CALL_SPARSE) pl = plan_streams(s, n_cached, s.cache_stride[2], s.block_len, s.blk_stride[2]);
   else if (call == SDLLM_CALL_DENSE) plan_general(pl, s, s.seq_len, (s.seq_len + kTileKeys - 1) / kTileKeys, false);
-  else pl = plan_attn(s, s.seq_len, s.kv_stride[2], 0, 0, call == SDLLM_CALL_UPDATE && counts_of(s).k_total > 0);
+  else pl = plan_streams(s, s.seq_len, s.kv_stride[2], 0, 0, call == SDLLM_CALL_UPDATE && counts_of(s).k_total > 0);
   plan->kernel = !pl.mfma ? SDLLM_KERNEL_GENERAL : pl.gqa ? SDLLM_KERNEL_SHARED_TILE : pl.stream ? SDLLM_KERNEL_STREAM : SDLLM_KERNEL_PER_HEAD;
   plan->key_splits = pl.n_split;
   plan->waves = pl.waves;
   plan->touches_ahead = pl.stream && stream_touches_ahead(s.n_q_heads / s.n_kv_heads, pl.tiles_per_split, pl.waves);
+  return SDLLM_OK;
+}
+
+int32_t sdllm_burst_splits(const sdllm_shape_t* shape, int32_t call, int32_t n_cached, int32_t* splits) {
+  const int32_t st = check_shape(shape);
+  if (st != SDLLM_OK) return st;
+  const sdllm_shape_t& s = *shape;
+  if (!splits || call < SDLLM_CALL_SPARSE || call > SDLLM_CALL_DENSE || n_cached < 0) return SDLLM_ERR_INVALID_ARG;
+  AttnPlan pl;
+  const bool taken = call == SDLLM_CALL_SPARSE ? plan_burst(pl, s, n_cached, s.cache_stride[2], s.block_len, s.blk_stride[2], SIZE_MAX)
+                                               : call == SDLLM_CALL_FULL && plan_burst(pl, s, s.seq_len, s.kv_stride[2], 0, 0, SIZE_MAX);
+  *splits = taken ? pl.n_split : 0;
   return SDLLM_OK;
 }
 

@@ -269,17 +269,18 @@ hipError_t launch_attn_general(const AttnParams& p, int dtype, bool stats_only, 
 }
 
 hipError_t launch_attn_combine(const AttnParams& p, int dtype, hipStream_t s) {
-  if (const int most = combine32_max(p, dtype); most > 0 && p.batch <= 65535) {
-    const auto kernel = most == 4 ? attn_combine32_kernel<4> : most == 8 ? attn_combine32_kernel<8>
-                        : most == 12 ? attn_combine32_kernel<12> : attn_combine32_kernel<16>;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(4 * p.hq), (unsigned)p.batch), dim3(kCombineThreads), 0, s, p);
+  return with_combine32(p, p.batch <= 65535 ? dtype : -1, [&](auto max) {
+    constexpr int MAX = decltype(max)::value;
+    if constexpr (MAX > 0) {
+      hipLaunchKernelGGL(attn_combine32_kernel<MAX>, dim3((unsigned)(4 * p.hq), (unsigned)p.batch), dim3(kCombineThreads), 0, s, p);
+    } else {
+      const bool four = combine_tpi(p.n_split) == 4;
+      if (dtype != 0 && four) return hipErrorInvalidValue;   // fp32 has plan_general's splits, eight at most
+      const auto kernel = dtype != 0 ? attn_combine_kernel<float, 1> : four ? attn_combine_kernel<__bf16, 4> : attn_combine_kernel<__bf16, 1>;
+      hipLaunchKernelGGL(kernel, dim3((unsigned)combine_blocks(p)), dim3(kCombineThreads), 0, s, p);
+    }
     return hipGetLastError();
-  }
-  const bool four = combine_tpi(p.n_split) == 4;
-  if (dtype != 0 && four) return hipErrorInvalidValue;   // fp32 has plan_general's splits, eight at most
-  const auto kernel = dtype != 0 ? attn_combine_kernel<float, 1> : four ? attn_combine_kernel<__bf16, 4> : attn_combine_kernel<__bf16, 1>;
-  hipLaunchKernelGGL(kernel, dim3((unsigned)combine_blocks(p)), dim3(kCombineThreads), 0, s, p);
-  return hipGetLastError();
+  });
 }
 
 }  // namespace sdllm

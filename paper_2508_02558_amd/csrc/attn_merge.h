@@ -137,7 +137,7 @@ __device__ __forceinline__ void combine_block(const AttnParams& p, int block_id)
 // The same for 32 rows of 128 columns (the bf16 kernels for blocks of 32) and up to MAX splits: a block is rows 8 quarter .. of a
 // head.  A merge is a launch, a round trip to memory and the instructions before it, which mostly were divisions of indexes;
 // here the caller says which head it is, and every load is requested at once.  28 heads x 8 splits 3.9 -> 3.35 us with its launch,
-// whole sparse steps: 28 heads x 69 tiles 10.4 -> 9.8 us, 32 x 21 9.4 -> 8.9.  MAX is a step of four: loads past the last split
+// whole sparse steps: 28 heads x 69 tiles 10.4 -> 9.8 us, 32 x 21 9.4 -> 8.9.  MAX is one of a few: loads past the last split
 // repeat it.
 template <int MAX>
 __device__ __forceinline__ void combine32_block(const AttnParams& p, int b, int h, int quarter) {
@@ -170,9 +170,13 @@ __device__ __forceinline__ void combine32_block(const AttnParams& p, int b, int 
   store_piece<__bf16>(r, (__bf16*)p.out + b * p.o_sb + h * p.o_sh + row * p.o_sr + c4);
 }
 
-// Splits that combine32_block is instantiated for, 0: combine_block
-inline int combine32_max(const AttnParams& p, int dtype) {
-  return dtype == 0 && p.nq == 32 && p.d == 128 && p.n_split <= 16 ? (p.n_split + 3) / 4 * 4 : 0;
+// Calls f with the number of splits, as a constant, that combine32_block is instantiated for; 0: combine_block
+template <class F>
+inline auto with_combine32(const AttnParams& p, int dtype, F&& f) {
+  const int n = dtype == 0 && p.nq == 32 && p.d == 128 ? p.n_split : INT32_MAX;
+  return n <= 4 ? f(std::integral_constant<int, 4>{}) : n <= 8 ? f(std::integral_constant<int, 8>{}) : n <= 12 ? f(std::integral_constant<int, 12>{})
+         : n <= 16 ? f(std::integral_constant<int, 16>{}) : n <= 24 ? f(std::integral_constant<int, 24>{})
+         : n <= 32 ? f(std::integral_constant<int, 32>{}) : f(std::integral_constant<int, 0>{});
 }
 
 }  // namespace sdllm

@@ -100,17 +100,19 @@ hipError_t launch_compact(const CompactParams& p, hipStream_t s) {
 hipError_t launch_compact_combine(const CompactParams& p, const AttnParams& a, int dtype, hipStream_t s) {
   const bool four = combine_tpi(a.n_split) == 4;
   if (dtype != 0 && four) return hipErrorInvalidValue;   // fp32 has plan_general's splits, eight at most
-  const int most = combine32_max(a, dtype);
-  const int64_t n_combine = most > 0 ? (int64_t)4 * a.batch * a.hq : combine_blocks(a);
-  CompactParams c = p;
-  const int64_t blocks = n_combine + plan_compact(c);
-  if (blocks > INT32_MAX) return hipErrorInvalidValue;
-  const auto kernel = dtype != 0 ? compact_combine_kernel<float, 1, 0>
-                      : most == 4 ? compact_combine_kernel<__bf16, 1, 4> : most == 8 ? compact_combine_kernel<__bf16, 1, 8>
-                      : most == 12 ? compact_combine_kernel<__bf16, 1, 12> : most == 16 ? compact_combine_kernel<__bf16, 1, 16>
-                      : four ? compact_combine_kernel<__bf16, 4, 0> : compact_combine_kernel<__bf16, 1, 0>;
-  hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kCompactThreads), 0, s, c, a, Divisor(a.hq), (int)n_combine);
-  return hipGetLastError();
+  return with_combine32(a, dtype, [&](auto max) {
+    constexpr int MAX = decltype(max)::value;
+    const int64_t n_combine = MAX > 0 ? (int64_t)4 * a.batch * a.hq : combine_blocks(a);
+    CompactParams c = p;
+    const int64_t blocks = n_combine + plan_compact(c);
+    if (blocks > INT32_MAX) return hipErrorInvalidValue;
+    const auto kernel = [&] {
+      if constexpr (MAX > 0) return compact_combine_kernel<__bf16, 1, MAX>;
+      else return dtype != 0 ? compact_combine_kernel<float, 1, 0> : four ? compact_combine_kernel<__bf16, 4, 0> : compact_combine_kernel<__bf16, 1, 0>;
+    }();
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kCompactThreads), 0, s, c, a, Divisor(a.hq), (int)n_combine);
+    return hipGetLastError();
+  });
 }
 
 }  // namespace sdllm

@@ -193,6 +193,8 @@ struct DenseFullParams {
 hipError_t launch_attn_mfma_bf16(const AttnParams& p, hipStream_t s);
 hipError_t launch_attn_gqa_mfma_bf16(const AttnParams& p, hipStream_t s);
 hipError_t launch_attn_stream_mfma_bf16(const AttnParams& p, hipStream_t s);
+constexpr int kBurstMaxTiles = 9;    // tiles per workgroup of the next: 9 x 16.75 KB and the query rows fill the 160 KB of LDS
+hipError_t launch_attn_burst_mfma_bf16(const AttnParams& p, hipStream_t s);   // no statistics, no scores
 // Touching tiles ahead (attn_stream_mfma.hip) pays from about a dozen tiles per wave on (8 x 28/4 heads: 144 tiles 36.0 -> 34.3 us,
 // 74 tiles 19.8 -> 20.8) and for groups that share the requests out thinly (6 x 32/8 heads x 243 tiles, every fourth tile
 // each: 70.1 -> 71.6 us).

@@ -1,0 +1,90 @@
+"""The attention kernel that fetches all of a workgroup's tiles at once: one tile to nine (a ninth wave), ragged last tiles of either key
+segment, no cached keys, key splits of which the last has fewer tiles, workgroup numbers that no XCD count divides, rows, heads and batches
+in any order, tiles of infinitely low keys, and workspaces in which its partials do not fit.  Tolerances: tests/parity_util.py."""
+import pytest
+import torch
+
+from paper_2508_02558_amd import binding as B
+from tests import parity_util as U
+from tests.test_gpu_general import _hide
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def _strided(x):
+    return x.permute(0, 2, 1, 3).contiguous().permute(0, 2, 1, 3)      # [B, rows, H, d] storage
+
+
+def _setup(batch, q_heads, kv_heads, n_cached, splits, layout=lambda x: x):
+    torch.manual_seed(n_cached + q_heads)
+    d, b = 128, 32
+    q = layout((2.0 * torch.randn(batch, q_heads, b, d, device=DEV)).bfloat16())
+    kc, vc = (layout(torch.randn(batch, kv_heads, max(1, n_cached), d, device=DEV).bfloat16()) for _ in range(2))
+    kb, vb = (layout(torch.randn(batch, kv_heads, b, d, device=DEV).bfloat16()) for _ in range(2))
+    out = layout(torch.full((batch, q_heads, b, d), float("nan"), device=DEV, dtype=torch.bfloat16))
+    shape = B.make_shape(batch=batch, n_q_heads=q_heads, n_kv_heads=kv_heads, head_dim=d, seq_len=16384, block_off=8192, block_len=b,
+                         dtype=B.SDLLM_BF16, q_stride=B.strides_of(q), blk_stride=B.strides_of(kb), cache_stride=B.strides_of(kc),
+                         out_stride=B.strides_of(out))
+    assert B.sdllm_burst_splits(shape, B.SDLLM_CALL_SPARSE, n_cached) == splits
+    ref = U.oracle_attention_batch(q, torch.cat([kc[:, :, :n_cached], kb], 2), torch.cat([vc[:, :, :n_cached], vb], 2))
+    return shape, q, kc, vc, kb, vb, out, ref
+
+
+@pytest.mark.parametrize("batch,q_heads,kv_heads,n_cached,splits", [
+    (1, 1, 1, 0, 1), (1, 7, 1, 1, 1), (1, 3, 3, 32, 1), (2, 5, 5, 33, 1), (1, 28, 4, 97, 1), (1, 14, 2, 160, 1), (3, 6, 2, 191, 1),
+    (1, 9, 9, 223, 1), (2, 8, 2, 224, 1), (5, 4, 4, 225, 1), (1, 28, 4, 256, 1), (8, 28, 4, 100, 1), (8, 32, 32, 190, 1),
+    (1, 5, 1, 257, 5), (1, 2, 2, 400, 7), (1, 3, 1, 544, 6), (1, 28, 4, 700, 4), (1, 28, 4, 2160, 8), (3, 7, 7, 1500, 8),
+    (1, 32, 32, 2270, 8), (2, 28, 4, 1100, 4), (1, 4, 2, 5700, 23), (1, 1, 1, 8100, 32),
+])
+def test_sparse_step(batch, q_heads, kv_heads, n_cached, splits):
+    print(f"[case] burst B={batch} {q_heads}/{kv_heads} n_cached={n_cached}", flush=True)
+    for layout in (lambda x: x, _strided):
+        shape, q, kc, vc, kb, vb, out, ref = _setup(batch, q_heads, kv_heads, n_cached, splits, layout)
+        ws = torch.full((B.sdllm_workspace_bytes(shape, B.SDLLM_OP_SPARSE_ATTN, n_cached),), 0xff, dtype=torch.uint8, device=DEV)
+        B.sdllm_sparse_attn(shape, q, kc, vc, n_cached, kb, vb, out, ws)
+        torch.cuda.synchronize()
+        U.assert_close(out, ref, "bf16", f"B={batch} {q_heads}/{kv_heads} n_cached={n_cached}")
+
+
+@pytest.mark.parametrize("batch,q_heads,kv_heads,seq_len,splits", [(1, 28, 4, 64, 1), (2, 6, 2, 257, 1), (1, 28, 4, 1200, 5), (1, 4, 4, 2047, 16)])
+def test_dense_rows(batch, q_heads, kv_heads, seq_len, splits):
+    print(f"[case] burst dense rows B={batch} {q_heads}/{kv_heads} L={seq_len}", flush=True)
+    torch.manual_seed(seq_len)
+    q = (2.0 * torch.randn(batch, q_heads, 32, 128, device=DEV)).bfloat16()
+    k, v = (torch.randn(batch, kv_heads, seq_len, 128, device=DEV).bfloat16() for _ in range(2))
+    shape = B.make_shape(batch=batch, n_q_heads=q_heads, n_kv_heads=kv_heads, head_dim=128, seq_len=seq_len, block_off=32, block_len=32,
+                         dtype=B.SDLLM_BF16)
+    assert B.sdllm_burst_splits(shape, B.SDLLM_CALL_FULL) == splits
+    out = torch.full_like(q, float("nan"))
+    # room for every split, which a block step's workspace may not have
+    ws = torch.empty(max(B.sdllm_workspace_bytes(shape, B.SDLLM_OP_BLOCK_STEP), batch * q_heads * splits * 16640 + 512), dtype=torch.uint8, device=DEV)
+    B.sdllm_block_step(shape, 0, 1, q, k, v, None, None, None, out, ws)
+    torch.cuda.synchronize()
+    U.assert_close(out, U.oracle_attention_batch(q, k, v), "bf16", f"L={seq_len}")
+
+
+@pytest.mark.parametrize("n_cached", [128, 200, 600])
+def test_tiles_of_infinitely_low_keys(n_cached):
+    print(f"[case] burst, -inf tiles n_cached={n_cached}", flush=True)
+    shape, q, kc, vc, kb, vb, out, _ = _setup(1, 7, 1, n_cached, 1 if n_cached < 256 else 7)
+    kept = _hide(kc, q, [*range(0, 64), *range(96, 128)])
+    ws = torch.empty(B.sdllm_workspace_bytes(shape, B.SDLLM_OP_SPARSE_ATTN, n_cached), dtype=torch.uint8, device=DEV)
+    B.sdllm_sparse_attn(shape, q, kc, vc, n_cached, kb, vb, out, ws)
+    torch.cuda.synchronize()
+    U.assert_close(out, U.oracle_attention_batch(q, torch.cat([kc[:, :, kept], kb], 2), torch.cat([vc[:, :, kept], vb], 2)), "bf16", "kept keys")
+
+
+def test_workspace_without_room_for_all_splits():
+    # 4 splits asked for; room for three, for two, which are too few, for none, at an odd address, and no workspace at all, which a call of
+    # 14 heads x 20 tiles can do without
+    print("[case] burst, small workspaces", flush=True)
+    n = 19 * 32
+    shape, q, kc, vc, kb, vb, out, ref = _setup(2, 7, 1, n, 4)
+    need = B.sdllm_workspace_bytes(shape, B.SDLLM_OP_SPARSE_ATTN, n)
+    big = torch.empty(need + 256, dtype=torch.uint8, device=DEV)
+    for ws in (big, big[:14 * 3 * 16640 + 256], big[:14 * 2 * 16640 + 256], big[:256], big[4:], None):
+        out.fill_(float("nan"))
+        B.sdllm_sparse_attn(shape, q, kc, vc, n, kb, vb, out, ws)
+        torch.cuda.synchronize()
+        U.assert_close(out, ref, "bf16", f"{0 if ws is None else ws.numel()} bytes")

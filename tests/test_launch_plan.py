@@ -139,3 +139,22 @@ def test_launches_of_the_general_kernel_stay_below_two_to_the_32_threads():
     p = plan(DENSE, 65535, 1, 1, 257, dtype=B.SDLLM_F32, head_dim=64)
     assert p.kernel == GENERAL and 65535 * 514 * p.waves * 64 < 1 << 32
     assert plan(DENSE, 1, 8, 8, 256, dtype=B.SDLLM_F32, head_dim=64).waves > 1
+
+
+# Small calls that go to the kernel that fetches all tiles of a workgroup at once, ahead of the routes above, with how many splits.
+@pytest.mark.parametrize("batch,q_heads,kv_heads,tiles,splits", [
+    (1, 1, 1, 1, 1), (8, 28, 4, 9, 1), (8, 32, 8, 9, 1), (9, 32, 8, 2, 0), (8, 32, 32, 7, 1), (8, 32, 32, 8, 0), (7, 32, 32, 9, 1),
+    (1, 16, 2, 10, 4), (1, 28, 4, 10, 0), (1, 28, 4, 11, 3), (1, 32, 32, 10, 0), (1, 32, 32, 11, 3), (2, 32, 32, 11, 2), (5, 16, 16, 14, 0),
+    (5, 16, 16, 15, 2), (3, 32, 32, 18, 0), (3, 16, 2, 16, 0), (3, 16, 2, 17, 3), (2, 32, 8, 23, 0), (2, 32, 8, 24, 3), (5, 16, 2, 24, 0),
+    (1, 28, 4, 69, 8), (1, 28, 4, 81, 9), (1, 28, 4, 82, 0), (1, 32, 8, 72, 8), (1, 32, 8, 73, 0), (1, 2, 2, 288, 32), (1, 2, 2, 289, 0),
+])
+def test_small_calls_whose_tiles_are_fetched_at_once(batch, q_heads, kv_heads, tiles, splits):
+    shape = dict(batch=batch, n_q_heads=q_heads, n_kv_heads=kv_heads, head_dim=128, seq_len=32 * tiles, block_off=0, block_len=32, dtype=B.SDLLM_BF16)
+    assert B.sdllm_burst_splits(B.make_shape(**shape), SPARSE, 32 * (tiles - 1)) == splits
+    assert B.sdllm_burst_splits(B.make_shape(**shape), FULL) == splits
+    for call in (UPDATE, DENSE):
+        assert B.sdllm_burst_splits(B.make_shape(**shape), call) == 0
+    for more in (dict(dtype=B.SDLLM_F32), dict(head_dim=64), dict(block_len=16)):
+        assert B.sdllm_burst_splits(B.make_shape(**{**shape, **more}), SPARSE, 32 * (tiles - 1)) == 0
+    if splits > 1:   # never more partials than the static scratch holds
+        assert batch * q_heads * splits * 16640 <= B.SDLLM_STATIC_SCRATCH_BYTES
