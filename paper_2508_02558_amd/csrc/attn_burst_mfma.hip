@@ -208,8 +208,7 @@ static hipError_t launch_nseg(const AttnParams& p, hipStream_t s) {
   if (p.tiles_per_split < 1 || p.tiles_per_split > kBurstMaxTiles || p.waves > kBurstMaxTiles) return hipErrorInvalidValue;
   if (p.waves < kBurstOutWaves || p.waves < p.tiles_per_split) return hipErrorInvalidValue;
   const BurstDivisors by{Divisor(p.group), Divisor(p.n_split), Divisor(p.hkv)};
-  hipLaunchKernelGGL(kernel, dim3(nwg), dim3(p.waves * kWave), burst_lds_bytes(p.tiles_per_split), s, p, by);
-  return hipGetLastError();
+  return launch(kernel, dim3(nwg), dim3(p.waves * kWave), burst_lds_bytes(p.tiles_per_split), s, p, by);
 }
 
 hipError_t launch_attn_burst_mfma_bf16(const AttnParams& p, hipStream_t s) {

@@ -252,9 +252,8 @@ static hipError_t launch_mode(const AttnParams& p, hipStream_t s) {
   const int rblocks = (p.nq + Ops<T, D>::kRows - 1) / Ops<T, D>::kRows;
   const int64_t nwg = (int64_t)p.batch * p.hq * rblocks * p.n_split;
   if (nwg > INT32_MAX || p.waves < 1 || p.waves > kGeneralMaxWaves) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(kernel, dim3((unsigned)nwg), dim3(p.waves * kWave), p.waves * kWaveBytes, s, p, rblocks,
+  return launch(kernel, dim3((unsigned)nwg), dim3(p.waves * kWave), p.waves * kWaveBytes, s, p, rblocks,
                      GeneralDivisors{Divisor(p.group * rblocks), Divisor(p.n_split), Divisor(p.hkv), Divisor(rblocks)});
-  return hipGetLastError();
 }
 
 template <typename T, int D>
@@ -272,14 +271,13 @@ hipError_t launch_attn_combine(const AttnParams& p, int dtype, hipStream_t s) {
   return with_combine32(p, p.batch <= 65535 ? dtype : -1, [&](auto max) {
     constexpr int MAX = decltype(max)::value;
     if constexpr (MAX > 0) {
-      hipLaunchKernelGGL(attn_combine32_kernel<MAX>, dim3((unsigned)(4 * p.hq), (unsigned)p.batch), dim3(kCombineThreads), 0, s, p);
+      return launch(attn_combine32_kernel<MAX>, dim3((unsigned)(4 * p.hq), (unsigned)p.batch), dim3(kCombineThreads), 0, s, p);
     } else {
       const bool four = combine_tpi(p.n_split) == 4;
       if (dtype != 0 && four) return hipErrorInvalidValue;   // fp32 has plan_general's splits, eight at most
       const auto kernel = dtype != 0 ? attn_combine_kernel<float, 1> : four ? attn_combine_kernel<__bf16, 4> : attn_combine_kernel<__bf16, 1>;
-      hipLaunchKernelGGL(kernel, dim3((unsigned)combine_blocks(p)), dim3(kCombineThreads), 0, s, p);
+      return launch(kernel, dim3((unsigned)combine_blocks(p)), dim3(kCombineThreads), 0, s, p);
     }
-    return hipGetLastError();
   });
 }
 

@@ -235,9 +235,8 @@ static hipError_t launch_w(const AttnParams& p, int head_splits, hipStream_t s) 
   static LdsOptIn lds;
   const hipError_t e = lds.ensure(reinterpret_cast<const void*>(attn_gqa_mfma_bf16_kernel<NSEG, W, STATS>), (int)gqa_lds_bytes(W));
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((attn_gqa_mfma_bf16_kernel<NSEG, W, STATS>), dim3(p.n_split * p.batch * p.hkv * head_splits), dim3(W * kWave),
+  return launch(attn_gqa_mfma_bf16_kernel<NSEG, W, STATS>, dim3(p.n_split * p.batch * p.hkv * head_splits), dim3(W * kWave),
                      gqa_lds_bytes(W), s, p, head_splits);
-  return hipGetLastError();
 }
 
 template <int NSEG, bool STATS>

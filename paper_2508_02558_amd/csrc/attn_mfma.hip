@@ -357,9 +357,8 @@ static hipError_t launch_variant(const AttnParams& p, hipStream_t s) {
   const hipError_t e = lds.ensure(reinterpret_cast<const void*>(attn_mfma_bf16_kernel<NSEG, STATS, DEEP, SHARED_KV, BY_SPLIT, SHARED_Q>),
                                   (int)attn_mfma_lds_bytes(kMaxWavesPerWg, 0));
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((attn_mfma_bf16_kernel<NSEG, STATS, DEEP, SHARED_KV, BY_SPLIT, SHARED_Q>), dim3(nwg), dim3(p.waves * kWave),
+  return launch(attn_mfma_bf16_kernel<NSEG, STATS, DEEP, SHARED_KV, BY_SPLIT, SHARED_Q>, dim3(nwg), dim3(p.waves * kWave),
                      attn_mfma_lds_bytes(p.waves, nwg), s, p);
-  return hipGetLastError();
 }
 
 template <int NSEG, bool STATS>

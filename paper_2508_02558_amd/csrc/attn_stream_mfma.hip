@@ -368,8 +368,7 @@ static hipError_t launch_touch(const AttnParams& p, hipStream_t s) {
   const hipError_t e = lds.ensure(reinterpret_cast<const void*>(kernel), kMaxWavesPerWg * kStreamWaveLds + kRingK);
   if (e != hipSuccess) return e;
   if (p.waves < 1 || p.waves > kMaxWavesPerWg) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(kernel, dim3(p.n_split * p.batch * p.hq), dim3(p.waves * kWave), p.waves * kStreamWaveLds + kRingK, s, p);
-  return hipGetLastError();
+  return launch(kernel, dim3(p.n_split * p.batch * p.hq), dim3(p.waves * kWave), p.waves * kStreamWaveLds + kRingK, s, p);
 }
 
 template <int NSEG, bool STATS>

@@ -93,8 +93,7 @@ hipError_t launch_compact(const CompactParams& p, hipStream_t s) {
   const int64_t blocks = plan_compact(c);
   if (blocks == 0) return hipSuccess;
   if (blocks > INT32_MAX) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(compact_kernel, dim3((unsigned)blocks), dim3(kCompactThreads), 0, s, c);
-  return hipGetLastError();
+  return launch(compact_kernel, dim3((unsigned)blocks), dim3(kCompactThreads), 0, s, c);
 }
 
 hipError_t launch_compact_combine(const CompactParams& p, const AttnParams& a, int dtype, hipStream_t s) {
@@ -110,8 +109,7 @@ hipError_t launch_compact_combine(const CompactParams& p, const AttnParams& a, i
       if constexpr (MAX > 0) return compact_combine_kernel<__bf16, 1, MAX>;
       else return dtype != 0 ? compact_combine_kernel<float, 1, 0> : four ? compact_combine_kernel<__bf16, 4, 0> : compact_combine_kernel<__bf16, 1, 0>;
     }();
-    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kCompactThreads), 0, s, c, a, Divisor(a.hq), (int)n_combine);
-    return hipGetLastError();
+    return launch(kernel, dim3((unsigned)blocks), dim3(kCompactThreads), 0, s, c, a, Divisor(a.hq), (int)n_combine);
   });
 }
 

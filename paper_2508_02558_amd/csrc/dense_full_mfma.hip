@@ -431,8 +431,7 @@ static hipError_t launch_full(const DenseFullParams& p, hipStream_t s) {
   DenseFullParams q = p;
   q.qblocks = (p.seq_len + full_rows_per_wg(KS) - 1) / full_rows_per_wg(KS);
   q.by_qblocks = Divisor(q.qblocks); q.by_hq = Divisor(p.hq); q.by_group = Divisor(p.group);
-  hipLaunchKernelGGL(kernel, dim3(q.qblocks * p.batch * p.hq), dim3(512), kLds, s, q);
-  return hipGetLastError();
+  return launch(kernel, dim3(q.qblocks * p.batch * p.hq), dim3(512), kLds, s, q);
 }
 
 // Key groups per workgroup: what a workgroup takes for its tiles (us), times the rounds in which the CUs, one workgroup each, go

@@ -141,8 +141,7 @@ static hipError_t launch_cols(const ScoreParams& p, hipStream_t s) {
   const int most = (4 * kNumCUs + rows - 1) / rows;
   if (parts > most) parts = most;
   const size_t bytes = (size_t)held * kBlockBytes + kColWaves * O::kKTile;
-  hipLaunchKernelGGL(kernel, dim3(parts, rows), dim3(kColWaves * kWave), bytes, s, p, rblocks, Divisor(rblocks));
-  return hipGetLastError();
+  return launch(kernel, dim3(parts, rows), dim3(kColWaves * kWave), bytes, s, p, rblocks, Divisor(rblocks));
 }
 
 hipError_t launch_score_cols_general(const ScoreParams& p, int dtype, hipStream_t s) {

@@ -532,8 +532,7 @@ static hipError_t launch_heads(const ScoreParams& p, int tiles, hipStream_t s) {
   if (parts < 1) parts = 1;
   const int per_wg = (tiles + parts - 1) / parts;
   parts = (tiles + per_wg - 1) / per_wg;   // none empty
-  hipLaunchKernelGGL(kernel, dim3(parts, rows), dim3((heads_waves(G) + 1) * kWave), heads_lds_bytes(G), s, p, per_wg);
-  return hipGetLastError();
+  return launch(kernel, dim3(parts, rows), dim3((heads_waves(G) + 1) * kWave), heads_lds_bytes(G), s, p, per_wg);
 }
 
 static size_t score_lds_bytes(int group, int waves) { return (size_t)(group + waves) * kTileBytes + (size_t)group * 32 * 8; }
@@ -549,8 +548,7 @@ static hipError_t launch_g(const ScoreParams& p, hipStream_t s) {
     if (e != hipSuccess) return e;
     ScoreParams q = p;
     q.cols_follow = p.n_part == 1;   // statistics final inside the workgroup: one launch does both passes
-    hipLaunchKernelGGL(score_stats_mfma_kernel<G>, grid, block, lds, s, q);
-    const hipError_t launched = hipGetLastError();
+    const hipError_t launched = launch(score_stats_mfma_kernel<G>, grid, block, lds, s, q);
     if (launched != hipSuccess || q.cols_follow) return launched;
   }
   if constexpr (G > 1) {
@@ -560,8 +558,7 @@ static hipError_t launch_g(const ScoreParams& p, hipStream_t s) {
   static LdsOptIn lds_cols;
   const hipError_t e = lds_cols.ensure(reinterpret_cast<const void*>(score_cols_mfma_kernel<G>), max_lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(score_cols_mfma_kernel<G>, grid, block, lds, s, p);
-  return hipGetLastError();
+  return launch(score_cols_mfma_kernel<G>, grid, block, lds, s, p);
 }
 
 bool score_mfma_supports_group(int group) { return group >= 1 && group <= 8; }

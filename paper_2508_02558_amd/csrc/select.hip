@@ -715,13 +715,13 @@ SelectWorkspace select_workspace(const SelectParams& p) {
 int select_max_segment() { return kMaxChunks * kSelThreads; }
 
 template <int ITEMS>
-static void launch_items(const SelectParams& p, dim3 grid, hipStream_t s) {
+static hipError_t launch_items(const SelectParams& p, dim3 grid, hipStream_t s) {
   const dim3 block(kSelThreads);
   switch (p.pool_half) {
-    case 0: hipLaunchKernelGGL((select_kernel<ITEMS, 0>), grid, block, 0, s, p); break;
-    case 1: hipLaunchKernelGGL((select_kernel<ITEMS, 1>), grid, block, 0, s, p); break;
-    case 2: hipLaunchKernelGGL((select_kernel<ITEMS, 2>), grid, block, 0, s, p); break;
-    default: hipLaunchKernelGGL((select_kernel<ITEMS, -1>), grid, block, 0, s, p); break;   // wider windows: generic pooling
+    case 0: return launch(select_kernel<ITEMS, 0>, grid, block, 0, s, p);
+    case 1: return launch(select_kernel<ITEMS, 1>, grid, block, 0, s, p);
+    case 2: return launch(select_kernel<ITEMS, 2>, grid, block, 0, s, p);
+    default: return launch(select_kernel<ITEMS, -1>, grid, block, 0, s, p);   // wider windows: generic pooling
   }
 }
 
@@ -740,25 +740,26 @@ hipError_t launch_select(const SelectParams& q, hipStream_t s) {
   if (!p.idx && p.k_total > 0) return hipErrorInvalidValue;
   const int longest = longest_ranked(p);
   const dim3 grid(nx, p.rows);
-  if (longest <= 1 * kSelThreads) launch_items<1>(p, grid, s);
-  else if (longest <= 2 * kSelThreads) launch_items<2>(p, grid, s);
-  else if (longest <= 4 * kSelThreads) launch_items<4>(p, grid, s);
-  else if (longest <= kSelRegItems * kSelThreads) launch_items<kSelRegItems>(p, grid, s);
+  if (longest <= 1 * kSelThreads) return launch_items<1>(p, grid, s);
+  else if (longest <= 2 * kSelThreads) return launch_items<2>(p, grid, s);
+  else if (longest <= 4 * kSelThreads) return launch_items<4>(p, grid, s);
+  else if (longest <= kSelRegItems * kSelThreads) return launch_items<kSelRegItems>(p, grid, s);
   else {
     if (!p.keys || !p.sorted || !p.bins || longest > select_max_segment()) return hipErrorInvalidValue;
     p.chunks = (longest + kSelThreads - 1) / kSelThreads;
     const dim3 pgrid((longest + kPartLen - 1) / kPartLen, p.n_seg, p.rows), block(kSelThreads);
+    hipError_t e;
     switch (p.pool_half) {
-      case 0: hipLaunchKernelGGL(select_pool_kernel<0>, pgrid, block, 0, s, p); break;
-      case 1: hipLaunchKernelGGL(select_pool_kernel<1>, pgrid, block, 0, s, p); break;
-      case 2: hipLaunchKernelGGL(select_pool_kernel<2>, pgrid, block, 0, s, p); break;
-      default: hipLaunchKernelGGL(select_pool_kernel<-1>, pgrid, block, 0, s, p); break;
+      case 0: e = launch(select_pool_kernel<0>, pgrid, block, 0, s, p); break;
+      case 1: e = launch(select_pool_kernel<1>, pgrid, block, 0, s, p); break;
+      case 2: e = launch(select_pool_kernel<2>, pgrid, block, 0, s, p); break;
+      default: e = launch(select_pool_kernel<-1>, pgrid, block, 0, s, p); break;
     }
     const int longest_any = p.tail_len > longest ? p.tail_len : longest;
     const int per_wg = kFinishChunks * kSelThreads;
-    if (p.k_total > 0) hipLaunchKernelGGL(select_finish_kernel, dim3((longest_any + per_wg - 1) / per_wg, nx, p.rows), block, 0, s, p);
+    if (e != hipSuccess || p.k_total == 0) return e;
+    return launch(select_finish_kernel, dim3((longest_any + per_wg - 1) / per_wg, nx, p.rows), block, 0, s, p);
   }
-  return hipGetLastError();
 }
 
 }  // namespace sdllm
