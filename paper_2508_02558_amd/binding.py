@@ -147,8 +147,26 @@ def _stream(stream) -> Optional[int]:
 
 def strides_of(t) -> Tuple[int, int, int]:
     """{batch, head, row} element strides of a [B, H, n, d] tensor whose last axis is contiguous."""
-    assert t.dim() == 4 and (t.shape[3] == 1 or t.stride(3) == 1), "last axis must be contiguous"
-    return (t.stride(0), t.stride(1), t.stride(2))
+    st = t.stride()
+    assert len(st) == 4 and (st[3] == 1 or t.shape[3] == 1), "last axis must be contiguous"
+    return st[:3]
+
+
+try:
+    from . import _pycall   # tensors to the per-layer entry points without ctypes; built next to the library
+except ImportError:
+    _pycall = None
+
+
+def _address(name: str) -> int:
+    """Address of an entry point of the loaded library, looked up once per library."""
+    lib = load()
+    known = lib.__dict__.get("addresses")
+    if known is None:
+        known = lib.addresses = {}
+    if name not in known:
+        known[name] = ctypes.cast(getattr(lib, name), ctypes.c_void_p).value
+    return known[name]
 
 
 def make_shape(*, batch: int, n_q_heads: int, n_kv_heads: int, head_dim: int, seq_len: int, block_off: int,
@@ -218,6 +236,10 @@ def sdllm_compact_kv(shape, k_full, v_full, idx, k_cache, v_cache, stream=None) 
 
 
 def sdllm_sparse_attn(shape, q_blk, k_cache, v_cache, n_cached, k_blk, v_blk, out, ws, stream=None) -> None:
+    if _pycall is not None and isinstance(shape, sdllm_shape_t):
+        _check(_pycall.sparse_attn(_address("sdllm_sparse_attn"), ctypes.addressof(shape), q_blk, k_cache, v_cache, n_cached, k_blk, v_blk,
+                                   out, ws, _stream(stream) or 0), "sdllm_sparse_attn")
+        return
     _check(load().sdllm_sparse_attn(ctypes.byref(shape), _ptr(q_blk), _ptr(k_cache), _ptr(v_cache), n_cached,
                                     _ptr(k_blk), _ptr(v_blk), _ptr(out), _ptr(ws),
                                     ws.numel() * ws.element_size() if ws is not None else 0, _stream(stream)),
@@ -232,6 +254,12 @@ def sdllm_sparse_attn_noalloc(shape, q_blk, k_cache, v_cache, n_cached, k_blk, v
 
 def sdllm_block_step(shape, step_in_block, delay, q_blk, k_in, v_in, idx, k_cache, v_cache, out, ws,
                      stream=None) -> int:
+    if _pycall is not None and isinstance(shape, sdllm_shape_t):
+        state = _pycall.block_step(_address("sdllm_block_step"), ctypes.addressof(shape), step_in_block, delay, q_blk, k_in, v_in, idx,
+                                   k_cache, v_cache, out, ws, _stream(stream) or 0)
+        if state < 0:
+            raise SdllmError(state, "sdllm_block_step")
+        return state
     st = ctypes.c_int32(-1)
     _check(load().sdllm_block_step(ctypes.byref(shape), step_in_block, delay, _ptr(q_blk), _ptr(k_in), _ptr(v_in),
                                    _ptr(idx), _ptr(k_cache), _ptr(v_cache), _ptr(out), _ptr(ws),
@@ -241,6 +269,10 @@ def sdllm_block_step(shape, step_in_block, delay, q_blk, k_in, v_in, idx, k_cach
 
 
 def sdllm_dense_attn(shape, q_full, k_full, v_full, out_full, stream=None) -> None:
+    if _pycall is not None and isinstance(shape, sdllm_shape_t):
+        _check(_pycall.dense_attn(_address("sdllm_dense_attn"), ctypes.addressof(shape), q_full, strides_of(q_full), k_full, v_full, out_full,
+                                  strides_of(out_full), _stream(stream) or 0), "sdllm_dense_attn")
+        return
     qs = (ctypes.c_int64 * 3)(*strides_of(q_full))
     os_ = (ctypes.c_int64 * 3)(*strides_of(out_full))
     _check(load().sdllm_dense_attn(ctypes.byref(shape), _ptr(q_full), qs, _ptr(k_full), _ptr(v_full), _ptr(out_full), os_,

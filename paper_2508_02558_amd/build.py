@@ -7,12 +7,14 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB_PATH = os.path.join(HERE, "libsdllm.so")
+PYCALL_PATH = os.path.join(HERE, "_pycall.so")   # tensors to entry points without ctypes (binding.py)
 BUILD_DIR = os.path.join(HERE, "_build")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -37,6 +39,20 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _build_pycall() -> None:
+    """Host code for the running interpreter.  Without its headers there is none, and the binding goes through ctypes."""
+    include = sysconfig.get_paths()["include"]
+    if not os.path.exists(os.path.join(include, "Python.h")):
+        return
+    tmp = PYCALL_PATH + ".tmp"
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-shared", "-fPIC", "-std=c++17", "-I", INCLUDE, "-I", include,
+           os.path.join(CSRC, "pycall.cpp"), "-o", tmp]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"{cmd[0]} failed for pycall.cpp:\n{r.stdout}\n{r.stderr}")
+    os.replace(tmp, PYCALL_PATH)
+
+
 def build_library(verbose: bool = True) -> str:
     os.makedirs(BUILD_DIR, exist_ok=True)
     srcs = sources()
@@ -48,6 +64,7 @@ def build_library(verbose: bool = True) -> str:
     if r.returncode != 0:
         raise RuntimeError(f"link failed:\n{r.stdout}\n{r.stderr}")
     os.replace(tmp, LIB_PATH)
+    _build_pycall()
     if verbose:
         print(f"built {LIB_PATH} from {len(srcs)} sources", file=sys.stderr)
     return LIB_PATH
