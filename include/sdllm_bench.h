@@ -42,7 +42,7 @@ typedef struct sdllm_launch_plan {
   int32_t key_splits;    /* workgroups that share a head's keys; merged by a second launch if more than one */
   int32_t waves;         /* per workgroup (SHARED_TILE: query heads per KV head) */
   int32_t touches_ahead; /* STREAM: 1 if the heads of a group bring tiles into L2 for each other */
-  int32_t key_groups;    /* DENSE: groups of waves that share a row block's keys */
+  int32_t key_groups;    /* DENSE: groups of waves that share a row block's keys (a last, small round of workgroups may have more) */
 } sdllm_launch_plan_t;
 
 /* How an attention call of this shape is launched (n_cached: SDLLM_CALL_SPARSE only), given all the workspace it asks

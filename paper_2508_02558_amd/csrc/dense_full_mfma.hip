@@ -177,8 +177,9 @@ void dense_phase_mfma_bf16_kernel(const DenseFullParams p) {
 
   // renumber workgroups so that consecutive ids (which go round-robin over the XCDs) of one head's
   // query blocks end up on the same XCD
-  const int wg = xcd_contiguous_id(blockIdx.x, gridDim.x);
+  const int wg = p.first_wg + xcd_contiguous_id(blockIdx.x, gridDim.x);
   const int head = p.by_qblocks.quotient(wg), qb = wg - head * p.qblocks;
+  if (qb * full_rows_per_wg(KS) >= p.seq_len) return;   // key groups of a part of the grid: a 256-row block may end in blocks without rows
   const int b = p.by_hq.quotient(head), h = head - b * p.hq, g = p.by_group.quotient(h);
   // rows past the end of the sequence compute on a copy of the last row and are not written back
   const int q_row = qb * full_rows_per_wg(KS) + rb * 32 + col;
@@ -339,8 +340,9 @@ __global__ __launch_bounds__(512) void dense_split_mfma_bf16_kernel(const DenseF
   const int half = lane >> 5, col = lane & 31;
   const int rb = wave % RB, kg = wave / RB;
 
-  const int wg = xcd_contiguous_id(blockIdx.x, gridDim.x);
+  const int wg = p.first_wg + xcd_contiguous_id(blockIdx.x, gridDim.x);
   const int head = p.by_qblocks.quotient(wg), qb = wg - head * p.qblocks;
+  if (qb * full_rows_per_wg(KS) >= p.seq_len) return;   // key groups of a part of the grid: a 256-row block may end in blocks without rows
   const int b = p.by_hq.quotient(head), h = head - b * p.hq, g = p.by_group.quotient(h);
   const int q_row = qb * full_rows_per_wg(KS) + rb * 32 + col;
   const bool row_valid = q_row < p.seq_len;
@@ -418,8 +420,9 @@ __global__ __launch_bounds__(512) void dense_split_mfma_bf16_kernel(const DenseF
   }
 }
 
+// Workgroups [first, first + count) of those that `qblocks` of them per head make
 template <int KS, bool PHASE>
-static hipError_t launch_full(const DenseFullParams& p, hipStream_t s) {
+static hipError_t launch_full(const DenseFullParams& p, int qblocks, int first, int count, hipStream_t s) {
   static LdsOptIn lds;
   constexpr int kLds = PHASE ? phase_lds_bytes(KS) : split_lds_bytes(KS);
   const auto kernel = [] {
@@ -429,9 +432,16 @@ static hipError_t launch_full(const DenseFullParams& p, hipStream_t s) {
   const hipError_t e = lds.ensure(reinterpret_cast<const void*>(kernel), kLds);
   if (e != hipSuccess) return e;
   DenseFullParams q = p;
-  q.qblocks = (p.seq_len + full_rows_per_wg(KS) - 1) / full_rows_per_wg(KS);
-  q.by_qblocks = Divisor(q.qblocks); q.by_hq = Divisor(p.hq); q.by_group = Divisor(p.group);
-  return launch(kernel, dim3(q.qblocks * p.batch * p.hq), dim3(512), kLds, s, q);
+  q.qblocks = qblocks;
+  q.first_wg = first;
+  q.by_qblocks = Divisor(qblocks); q.by_hq = Divisor(p.hq); q.by_group = Divisor(p.group);
+  return launch(kernel, dim3(count), dim3(512), kLds, s, q);
+}
+
+template <int KS, bool PHASE>
+static hipError_t launch_full(const DenseFullParams& p, hipStream_t s) {
+  const int qblocks = (p.seq_len + full_rows_per_wg(KS) - 1) / full_rows_per_wg(KS);
+  return launch_full<KS, PHASE>(p, qblocks, 0, qblocks * p.batch * p.hq, s);
 }
 
 // Key groups per workgroup: what a workgroup takes for its tiles (us), times the rounds in which the CUs, one workgroup each, go
@@ -456,16 +466,41 @@ int dense_full_key_groups(int heads, int seq_len) {
   return best;
 }
 
+// Whole workgroups in rounds of the chip leave a last round that may be nearly empty: 280 of them take as long as 512.  If at most half of a
+// round is left, those rows run as a launch of their own with two key groups per workgroup, with four if it is a quarter, in less than a
+// round's time: tiles x 0.27 - 3.5 or x 0.38 - 2 us gained.  Returns the groups of that launch, 0 if there is none; main_groups, the
+// choice without it, becomes 1 where there is.  Measured, before / with: 48 heads x 1364 positions (256 + 32 workgroups) 82.7 / 68.2 us, 64 x
+// 1100 (+ 64) 69.2 / 59.4, 84 x 916 (+ 80) 60.7 / 55.0, 28 x 4700 (2 x 256 + 20) 388 / 339, 48 x 2985 (2 x 256 + 64) 259 / 229, 56 x 4078 (3 x
+// 256 + 128) 469 / 450, 224 x 1174 (4 x 256 + 96) 194 / 187; where two groups throughout were the choice, 28 x 2393 119.5 / 108.3, 56 x 1200
+// 69.9 / 62.7, but 192 x 600 58.9 / 60.4.  More than half a round left: 28 x 3684 (+ 164) 204 / 228.  Short: 364 x 513 (+ 68) 90.9 / 95.1.
+static int dense_full_tail_groups(int heads, int seq_len, int& main_groups) {
+  const int tiles = (seq_len + kTileKeys - 1) / kTileKeys;
+  const int64_t wgs = (int64_t)((seq_len + full_rows_per_wg(1) - 1) / full_rows_per_wg(1)) * heads;
+  const int left = (int)(wgs % kNumCUs);
+  if (main_groups == 4 || wgs < kNumCUs || left == 0 || left > kNumCUs / 2) return 0;
+  const int groups = left <= kNumCUs / 4 ? 4 : 2;
+  if (tiles < (main_groups == 2 ? 32 : groups == 4 ? 9 : 24)) return 0;
+  main_groups = 1;
+  return groups;
+}
+
 // Up to kStagedKeys positions one or two key groups load their stages through registers as well: locked phases cost half an iteration at the
 // start and pay it back from some ten tiles on, and a wave without rows still fetches its share of the rings and of the queries.
 // Phases / stages: 28 heads x 32 positions 4.07 / 3.60 us, x 64 5.49 / 4.82, x 96 6.76 / 6.55; 224 x 224 16.8 / 16.3; 256 x 128 11.65 /
 // 11.08, x 256 20.7 / 20.3; two groups, 128 x 256 13.62 / 13.31.  Beyond, where 256-row workgroups come in twos: 256 x 288 34.9 / 35.2,
 // 28 x 735 with two groups 17.6 / 19.2.
 hipError_t launch_dense_full_mfma_bf16(const DenseFullParams& p, hipStream_t s) {
-  const int ks = dense_full_key_groups(p.batch * p.hq, p.seq_len);
-  if (ks == 4) return launch_full<4, false>(p, s);
-  if (p.seq_len <= kStagedKeys) return ks == 2 ? launch_full<2, false>(p, s) : launch_full<1, false>(p, s);
-  return ks == 2 ? launch_full<2, true>(p, s) : launch_full<1, true>(p, s);
+  int ks = dense_full_key_groups(p.batch * p.hq, p.seq_len);
+  if (p.seq_len <= kStagedKeys)
+    return ks == 4 ? launch_full<4, false>(p, s) : ks == 2 ? launch_full<2, false>(p, s) : launch_full<1, false>(p, s);
+  const int tail = dense_full_tail_groups(p.batch * p.hq, p.seq_len, ks);
+  if (tail == 0) return ks == 4 ? launch_full<4, false>(p, s) : ks == 2 ? launch_full<2, true>(p, s) : launch_full<1, true>(p, s);
+  const int qblocks = (p.seq_len + full_rows_per_wg(1) - 1) / full_rows_per_wg(1), all = qblocks * p.batch * p.hq;
+  const int whole = all / kNumCUs * kNumCUs;
+  const hipError_t e = launch_full<1, true>(p, qblocks, 0, whole, s);
+  if (e != hipSuccess) return e;
+  return tail == 2 ? launch_full<2, true>(p, qblocks * 2, whole * 2, (all - whole) * 2, s)
+                   : launch_full<4, false>(p, qblocks * 4, whole * 4, (all - whole) * 4, s);
 }
 
 }  // namespace sdllm

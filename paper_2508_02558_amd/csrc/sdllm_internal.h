@@ -197,7 +197,7 @@ struct DenseFullParams {
   int64_t o_sb, o_sh, o_sr;
   int32_t batch, hq, hkv, group, seq_len, d;
   float scale_log2;
-  int32_t qblocks;                        // set by the launcher: workgroups per head
+  int32_t qblocks, first_wg;              // set by the launcher: workgroups per head, number of the first one
   Divisor by_qblocks, by_hq, by_group;
 };
 
