@@ -464,6 +464,21 @@ void fill_segments(const sdllm_shape_t& s, const Counts& c, SelectParams& q) {
   }
 }
 
+// Workgroups per row of the 32-row kernels' column pass, their tiles and waves
+void plan_columns(size_t rows, int tiles, int& waves, int& n_part, int& tiles_per_part) {
+  if (tiles < 1) tiles = 1;
+  int waves_per_row = (int)((kNumCUs * kMaxWavesPerWg + rows - 1) / rows);
+  if (waves_per_row > tiles) waves_per_row = tiles;
+  if (waves_per_row < 1) waves_per_row = 1;
+  waves = waves_per_row < kMaxWavesPerWg ? waves_per_row : kMaxWavesPerWg;
+  n_part = (waves_per_row + waves - 1) / waves;
+  // never a few workgroups more than there are CUs: with several heads' Q staged in LDS a CU holds
+  // one scoring workgroup, and the extra ones would wait for a whole round
+  if (rows < (size_t)kNumCUs && n_part > kNumCUs / (int)rows) n_part = kNumCUs / (int)rows;
+  tiles_per_part = (tiles + n_part - 1) / n_part;
+  n_part = (tiles + tiles_per_part - 1) / tiles_per_part;   // no empty part
+}
+
 ScorePlan plan_score(const sdllm_shape_t& s) {
   const Counts c = counts_of(s);
   ScorePlan pl{};
@@ -486,18 +501,7 @@ ScorePlan plan_score(const sdllm_shape_t& s) {
   if (pl.mfma) {
     const int n0 = pl.n_scored < c.n_pre ? pl.n_scored : c.n_pre;
     const int n1 = pl.n_scored - n0;
-    int tiles = (n0 + kTileKeys - 1) / kTileKeys + (n1 + kTileKeys - 1) / kTileKeys;
-    if (tiles < 1) tiles = 1;
-    int waves_per_row = (int)((kNumCUs * kMaxWavesPerWg + rows - 1) / rows);
-    if (waves_per_row > tiles) waves_per_row = tiles;
-    if (waves_per_row < 1) waves_per_row = 1;
-    pl.waves = waves_per_row < kMaxWavesPerWg ? waves_per_row : kMaxWavesPerWg;
-    int n_part = (waves_per_row + pl.waves - 1) / pl.waves;
-    // never a few workgroups more than there are CUs: with several heads' Q staged in LDS a CU holds
-    // one scoring workgroup, and the extra ones would wait for a whole round
-    if (rows < (size_t)kNumCUs && n_part > kNumCUs / (int)rows) n_part = kNumCUs / (int)rows;
-    pl.tiles_per_part = (tiles + n_part - 1) / n_part;
-    pl.n_part = (tiles + pl.tiles_per_part - 1) / pl.tiles_per_part;   // no empty part
+    plan_columns(rows, (n0 + kTileKeys - 1) / kTileKeys + (n1 + kTileKeys - 1) / kTileKeys, pl.waves, pl.n_part, pl.tiles_per_part);
   } else {
     // row statistics: a statistics-only run of the general attention kernel over the whole sequence
     AttnPlan st{};
@@ -506,6 +510,19 @@ ScorePlan plan_score(const sdllm_shape_t& s) {
   }
   pl.ml_bytes = align_up((size_t)s.batch * s.n_q_heads * row_blocks(s, s.block_len) * pl.n_part * 2 * block_rows(s.dtype) * sizeof(float));
   return pl;
+}
+
+// Whether the column pass of a block length other than 32 runs the kernels for 32 rows: every block of 32 rows of a head as a head of its
+// own, rows that are not there with no weight (of a softmax; raw logits take full blocks).  Those keep a tile's keys in registers and
+// fetch tiles for all heads at once, where the general kernel reads queries and keys from LDS for each.  Cache-update steps, general / as
+// heads: block of 64, 2 x 32 heads x 1280 positions 38.9 / 37.9 us, 1 x 8 x 1100 26.0 / 23.2, 1 x 8/2 x 600 31.0 / 22.6, 8 x 32/8 x 4000 220 / 173;
+// block of 16, 1 x 14/2 x 600 27.0 / 21.8, 8 x 28/4 x 3000 84 / 68, 4 x 32 x 2000 72.1 / 70.4, but one block per KV head and few of them, where the
+// general kernel's smaller workgroups are more: 16 x 900 23.8 / 24.8.
+bool blocks_as_heads(const sdllm_shape_t& s) {
+  const int group = row_blocks(s, s.block_len) * (s.n_q_heads / s.n_kv_heads);
+  return s.dtype == SDLLM_BF16 && s.head_dim == 128 && (s.block_len % 32 == 0 || s.score_mode == SDLLM_SOFTMAX_MEAN) &&
+         s.batch * (int64_t)s.n_kv_heads <= 65535 && seg_fits_u32(s.kv_stride[2], s.seq_len, 2) &&
+         score_mfma_supports_group(group) && (group > 1 || s.batch * (int64_t)s.n_kv_heads >= 64);
 }
 
 // The position from which keys are scored again after the prefix: past the block, or never (prefix-only eviction).
@@ -553,6 +570,7 @@ int32_t score_select_impl(const sdllm_shape_t& s, const void* q_blk, const void*
   sp.k_sb = s.kv_stride[0]; sp.k_sh = s.kv_stride[1]; sp.k_sr = s.kv_stride[2];
   sp.batch = s.batch; sp.hq = s.n_q_heads; sp.hkv = s.n_kv_heads; sp.group = s.n_q_heads / s.n_kv_heads;
   sp.by_hkv = Divisor(s.n_kv_heads);
+  sp.inv_count = 1.f / (float)(sp.group * s.block_len);
   sp.nq = s.block_len; sp.d = s.head_dim;
   sp.block_off = s.block_off; sp.block_len = s.block_len;
   sp.n_cand = pl.n_scored;
@@ -584,7 +602,18 @@ int32_t score_select_impl(const sdllm_shape_t& s, const void* q_blk, const void*
       p.cand1_begin = candidates_resume(s);
       e = launch_attn_general(p, s.dtype, true, hs);
     }
-    if (e == hipSuccess) e = launch_score_cols_general(sp, s.dtype, hs);
+    if (e == hipSuccess && blocks_as_heads(s)) {
+      // blocks of 32 rows are heads to the column pass, and their statistics lie as it reads them
+      sp.q_shift = row_blocks(s, s.block_len) - 1;
+      sp.hq <<= sp.q_shift; sp.group <<= sp.q_shift;
+      sp.skip_stats = 1;
+      const int n0 = sp.n_cand < s.block_off ? sp.n_cand : s.block_off, n1 = sp.n_cand - n0;
+      plan_columns((size_t)s.batch * s.n_kv_heads, (n0 + kTileKeys - 1) / kTileKeys + (n1 + kTileKeys - 1) / kTileKeys, sp.waves, sp.n_part,
+                   sp.tiles_per_part);
+      e = launch_score_mfma_bf16(sp, hs);
+    } else if (e == hipSuccess) {
+      e = launch_score_cols_general(sp, s.dtype, hs);
+    }
   }
   if (e != hipSuccess) return SDLLM_ERR_HIP;
 

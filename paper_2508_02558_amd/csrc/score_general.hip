@@ -1,14 +1,13 @@
 // Saliency scoring (Sec. 3.3 second equation, aggregated as in Alg. 1) for the shapes score_mfma.hip does
-// not take: fp32 tensors, head_dim 64, block lengths other than 32, groups of more than eight heads, rows
-// too far apart for 32-bit offsets.  The softmax's row statistics come from attn_general_kernel (by-product
+// not take: fp32 tensors, head_dim 64, groups of more than eight heads or blocks of 32 query rows, raw logits of blocks that are not
+// full, a few KV heads with one block each, rows too far apart for 32-bit offsets.  The softmax's row statistics come from attn_general_kernel (by-product
 // of the dense step, or a statistics-only launch); this file reduces the columns.
 //
 // logits = Q K_tile^T with Q rows as the A operand, so a lane holds one candidate key against 16 query
 // rows and sums their weights in registers.  A workgroup serves one (batch, KV head) and a few candidate
 // tiles, one per wave at a time; the query rows of the group (blocks of 32 or 16 rows of every head, padded with copies of the
 // last row, which count for nothing) sit in LDS, as many blocks at once as 64 KB hold.
-// Batch 2, 32 heads of 128, 64-token block, 1216 candidates: 138 us with one thread per candidate and a
-// scalar loop over all query rows, 9-10 us here; what is left is latency (queries, statistics, one tile).
+// 2 x 8 heads of 64 x 1200 positions: what is left is latency (queries, statistics, one tile).
 // A wave's first tile is requested behind the staging on purpose: held in registers meanwhile it costs a wave per SIMD, which is
 // up to 1 % of a small cache-update step gained and 3 to 9 % lost where many workgroups share a CU (9 x 32 heads of 64 x 616
 // positions 43.9 us, 45.8 with the tile first; fp32 2 x 8/1 x 1624 59.5, 65.4).

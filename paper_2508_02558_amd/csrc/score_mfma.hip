@@ -50,11 +50,17 @@ __device__ __forceinline__ const char* tile_rows(const CandTiles& ct, int tile, 
 }
 
 // Q rows of all G heads of the group -> LDS, padded like a K tile so both are read the same way.
+// Row `row` of head h; with two blocks of query rows per head (q_shift 1) h counts blocks.  Rows past the end are copies of the last one:
+// they weigh nothing (row_statistics).
+__device__ __forceinline__ const char* query_row(const ScoreParams& p, int b, int h, int row) {
+  return (const char*)p.q + 2 * (b * p.q_sb + (int64_t)(h >> p.q_shift) * p.q_sh + (int64_t)min((h & p.q_shift) * 32 + row, p.nq - 1) * p.q_sr);
+}
+
 template <int G>
 __device__ __forceinline__ void stage_queries(const ScoreParams& p, int b, int g, uint8_t* lds_q) {
   for (int i = threadIdx.x; i < G * 32 * 16; i += blockDim.x) {
     const int chunk = i & 15, row = (i >> 4) & 31, hh = i >> 9;
-    const char* src = (const char*)p.q + 2 * (b * p.q_sb + (int64_t)(g * G + hh) * p.q_sh + row * p.q_sr) + chunk * 16;
+    const char* src = query_row(p, b, g * G + hh, row) + chunk * 16;
     *reinterpret_cast<u32x4*>(lds_q + hh * kTileBytes + tile_off(row, chunk)) = *reinterpret_cast<const u32x4*>(src);
   }
 }
@@ -69,7 +75,7 @@ __device__ __forceinline__ void score_columns(const ScoreParams& p, int b, int g
   const int ntiles = ct.tiles0 + (ct.n1 + kTileKeys - 1) / kTileKeys;
   const int t_begin = part * p.tiles_per_part;
   const int t_end = min(ntiles, t_begin + p.tiles_per_part);
-  const float inv_count = 1.f / (float)(G * 32);
+  const float inv_count = p.inv_count;
   float* score_row = p.score + (size_t)bg * p.score_stride;
 
   u32x4 kreg[8];
@@ -305,7 +311,7 @@ __device__ __forceinline__ float2 row_statistics(const ScoreParams& p, size_t he
       l_tot = l_tot * __builtin_amdgcn_exp2f(m_tot - m_new) + l_s * __builtin_amdgcn_exp2f(m_s - m_new);
     m_tot = m_new;
   }
-  return make_float2(m_tot, 1.f / l_tot);
+  return make_float2(m_tot, (int)(head & p.q_shift) * 32 + row < p.nq ? 1.f / l_tot : 0.f);
 }
 
 // One query head per KV head, and grouped-query heads with much work per CU (heads_pay): a wave per tile, which walks the heads.
@@ -393,7 +399,7 @@ __global__ __launch_bounds__((heads_waves(G) + 1) * kWave) void score_cols_heads
       }
     };
     float* score_row = p.score + (size_t)bg * p.score_stride;
-    const float inv_count = 1.f / (float)(G * 32);
+    const float inv_count = p.inv_count;
     auto write = [&](int j) {   // the scores of step j: a half-lane per stream
       const int tile = t0 + T * j + half;
       int rows, cand0;
@@ -431,7 +437,7 @@ __global__ __launch_bounds__((heads_waves(G) + 1) * kWave) void score_cols_heads
 #pragma unroll
   for (int c = 0; c < 8; ++c)
     fetch_to_lds(lds_address(lds_q) + (uint32_t)(c * kKGroup),
-                 (const char*)p.q + 2 * (b * p.q_sb + (int64_t)h * p.q_sh + (c + 8 * (lane >> 4)) * p.q_sr) + fetch_k_chunk(lane));
+                 query_row(p, b, h, c + 8 * (lane >> 4)) + fetch_k_chunk(lane));
   float row_m[16], row_il[16];
   if (p.softmax) {
     const float2 x = row_statistics<8>(p, (size_t)b * p.hq + h, col);

@@ -129,6 +129,8 @@ struct ScoreParams {
   int64_t q_sb, q_sh, q_sr;
   int64_t k_sb, k_sh, k_sr;
   int32_t batch, hq, hkv, group, nq, d;
+  int32_t q_shift;      // kernels for blocks of 32 rows: 1 if hq and group count blocks, two to a head of 33 to 64 query rows; else 0
+  float inv_count;      // 1 / (query rows x heads of a group)
   int32_t block_off, block_len;
   int32_t n_cand;       // candidates scored (N, or N_pre for prefix-only eviction)
   int32_t softmax;      // 1: SOFTMAX_MEAN, 0: LOGIT_MEAN
