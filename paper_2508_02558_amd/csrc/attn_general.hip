@@ -29,10 +29,17 @@ constexpr int g_wave_lds() {
   return (tiles > parked ? tiles : parked) + 512;
 }
 
-struct GeneralDivisors { Divisor per_key, n_split, hkv, rblocks; };
+// What a workgroup finds its place with.  The fp32 kernels multiply, which makes calls of 5 to 14 us 1 to 4 % shorter.  The bf16 ones
+// divide as the compiler does: with multiplications 64 heads x 2 row blocks x 19 tiles gained 2 % (13.85 -> 13.6 us), 16 x 2 x 9 and
+// 16 x 2 x 23 lost 3 % (8.05 -> 8.35, 11.2 -> 11.55), by the order in which the first requests then come; the arguments alone cost
+// 0.06 us there.
+template <typename T>
+struct RowBlocks { int n; };
+template <>
+struct RowBlocks<float> { int n; Divisor by[4]; };   // per_key, n_split, hkv, n
 
 template <typename T, int D, int MODE>
-__global__ __launch_bounds__(kGeneralMaxWaves * kWave) void attn_general_kernel(const AttnParams p, const int rblocks, const GeneralDivisors by) {
+__global__ __launch_bounds__(kGeneralMaxWaves * kWave) void attn_general_kernel(const AttnParams p, const RowBlocks<T> blocks) {
   using O = Ops<T, D>;
   constexpr int R = O::kRows, NS = O::NS, kWaveBytes = g_wave_lds<T, D>(), kPark = O::NACC * 4 + 16, kUnits = O::NACC / 4;
   constexpr float kSlack = 8.f;   // as in attn_tile_math.h: the softmax reference moves when a maximum exceeds it by more
@@ -44,12 +51,16 @@ __global__ __launch_bounds__(kGeneralMaxWaves * kWave) void attn_general_kernel(
 
   // workgroups that read the same keys (the query heads of a KV group, their row blocks) sit on one XCD
   const int wg = xcd_contiguous_id(blockIdx.x, gridDim.x);
-  const int per_key = p.group * rblocks;
-  const int pair = by.per_key.quotient(wg);
-  const int bg = by.n_split.quotient(pair), split = pair - bg * p.n_split;
-  const int b = by.hkv.quotient(bg), g = bg - b * p.hkv;
+  const int rblocks = blocks.n, per_key = p.group * rblocks;
+  auto quotient = [&](int n, int d, int i) {
+    if constexpr (sizeof(T) == 4) return blocks.by[i].quotient(n);
+    else return n / d;
+  };
+  const int pair = quotient(wg, per_key, 0);
+  const int bg = quotient(pair, p.n_split, 1), split = pair - bg * p.n_split;
+  const int b = quotient(bg, p.hkv, 2), g = bg - b * p.hkv;
   const int vhead = bg * per_key + wg - pair * per_key;   // (batch, query head, block of R rows)
-  const int head = by.rblocks.quotient(vhead), h = head - b * p.hq;
+  const int head = quotient(vhead, rblocks, 3), h = head - b * p.hq;
   const int row = (vhead - head * rblocks) * R + col;
   const bool row_valid = row < p.nq;
 
@@ -252,8 +263,12 @@ static hipError_t launch_mode(const AttnParams& p, hipStream_t s) {
   const int rblocks = (p.nq + Ops<T, D>::kRows - 1) / Ops<T, D>::kRows;
   const int64_t nwg = (int64_t)p.batch * p.hq * rblocks * p.n_split;
   if (nwg > INT32_MAX || p.waves < 1 || p.waves > kGeneralMaxWaves) return hipErrorInvalidValue;
-  return launch(kernel, dim3((unsigned)nwg), dim3(p.waves * kWave), p.waves * kWaveBytes, s, p, rblocks,
-                     GeneralDivisors{Divisor(p.group * rblocks), Divisor(p.n_split), Divisor(p.hkv), Divisor(rblocks)});
+  RowBlocks<T> blocks{rblocks};
+  if constexpr (sizeof(T) == 4) {
+    const int by[4] = {p.group * rblocks, p.n_split, p.hkv, rblocks};
+    for (int i = 0; i < 4; ++i) blocks.by[i] = Divisor(by[i]);
+  }
+  return launch(kernel, dim3((unsigned)nwg), dim3(p.waves * kWave), p.waves * kWaveBytes, s, p, blocks);
 }
 
 template <typename T, int D>

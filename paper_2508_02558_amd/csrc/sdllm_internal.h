@@ -32,9 +32,10 @@ __host__ __device__ inline int xcd_contiguous_id(int dealt, int n) {
 // Exact n / d of 0 <= n < 2^31 by a d in [1, 2^31) that the host knows: with 2^(l-1) < d <= 2^l and mul = ceil(2^(31+l) / d), that is
 // 2^(31+l) / d plus less than 1, n mul / 2^(31+l) exceeds n / d by less than n / 2^(31+l), and so by less than 1 / d.  Three scalar
 // instructions where the compiler's division by a kernel parameter is some thirty vector ones in a chain.  In front of a kernel's
-// first load that is worth 1 to 4 % of calls of 6 to 14 us (general kernels 10.0 -> 9.7 us, 8.1 -> 8.0, full-sequence attention of
+// first load that is worth 1 to 4 % of calls of 6 to 14 us (general fp32 kernels 13.4 -> 13.1, full-sequence attention of
 // 28 heads x 100 positions 6.8 -> 6.7).  Not so in attn_mfma.hip, 2 to 5 % slower with it (28 heads x 69 tiles 10.2 -> 10.4,
-// 256 x 8 8.8 -> 9.2), and level in the other two kernels of block queries: they divide as the compiler does.
+// 256 x 8 8.8 -> 9.2), in the general bf16 kernels, 3 % slower to 2 % faster, and level in the other two kernels of block queries:
+// they divide as the compiler does.
 struct Divisor {
   uint32_t mul, shift;
   Divisor() = default;
