@@ -389,11 +389,11 @@ bool fuses_columns(const AttnPlan& pl, const sdllm_shape_t& s) {
 int32_t run_attn(const sdllm_shape_t& s, const void* q, const KvSegment& a, const KvSegment& b, void* out, void* ws,
                  size_t ws_bytes, hipStream_t stream, bool update = false, float* cand_ml = nullptr, int cand0_end = 0,
                  int cand1_begin = 0, AttnParams* deferred = nullptr, float* score_out = nullptr, int score_stride = 0) {
-  AttnPlan pl;
-  if (update || cand_ml || !plan_burst(pl, s, a.n, a.sr, b.n, b.sr, aligned16(ws) && ws ? ws_bytes : 0))
-    pl = plan_streams(s, a.n, a.sr, b.n, b.sr, update, ws ? ws_bytes : 0);
+  AttnPlan pl = plan_streams(s, a.n, a.sr, b.n, b.sr, update, ws ? ws_bytes : 0);
   const bool fits = ws && ws_bytes >= pl.ws_bytes();
+  // also where the next kernel, with fewer splits, would make do with less: what a call has to bring depends on its sizes only
   if (pl.ws_bytes() > 0 && pl.mfma && !fits) return SDLLM_ERR_WORKSPACE;
+  if (AttnPlan at_once; !update && !cand_ml && plan_burst(at_once, s, a.n, a.sr, b.n, b.sr, ws && aligned16(ws) ? ws_bytes : 0)) pl = at_once;
   if (pl.ws_bytes() > 0 && !pl.mfma && !(fits && aligned16(ws))) {
     // the general kernel works without a usable workspace too: one workgroup per block of rows walks all keys
     plan_general(pl, s, s.block_len, (a.n + kTileKeys - 1) / kTileKeys + (b.n + kTileKeys - 1) / kTileKeys, false);

@@ -122,6 +122,17 @@ def test_null_pointers_and_small_workspace_are_rejected_before_any_launch(lib):
     assert lib.sdllm_sparse_attn(sp, fake, z, z, -1, fake, fake, fake, z, 0, z) == B.SDLLM_ERR_INVALID_ARG
 
 
+@pytest.mark.parametrize("heads,kv_heads,n_cached,splits", [(32, 32, 1120, 5), (28, 4, 1760, 8)])
+def test_a_sparse_step_asks_for_the_same_workspace_whichever_kernel_would_take_it(lib, heads, kv_heads, n_cached, splits):
+    # the kernel for small calls would make do with four and seven splits here
+    s = B.make_shape(batch=1, n_q_heads=heads, n_kv_heads=kv_heads, head_dim=128, seq_len=16384, block_off=8192, block_len=32, dtype=B.SDLLM_BF16)
+    assert B.sdllm_launch_plan(s, B.SDLLM_CALL_SPARSE, n_cached).key_splits == splits > B.sdllm_burst_splits(s, B.SDLLM_CALL_SPARSE, n_cached)
+    fake, need = ctypes.c_void_p(0x1000), heads * splits * 32 * (128 + 2) * 4
+    assert B.sdllm_workspace_bytes(s, B.SDLLM_OP_SPARSE_ATTN, n_cached) == need
+    for ws, n in ((fake, need - 1), (fake, need * (splits - 1) // splits), (ctypes.c_void_p(0), need)):
+        assert lib.sdllm_sparse_attn(ctypes.byref(s), fake, fake, fake, n_cached, fake, fake, fake, ws, n, ctypes.c_void_p(0)) == B.SDLLM_ERR_WORKSPACE
+
+
 def test_noalloc_entry_rejects_requests_beyond_its_static_scratch(lib):
     # batch 8 of a 28/4-head shape with 8000 cached keys runs the shared-tile kernel with 8 key splits:
     # 1792 partial slots of 16.25 KB, far beyond the 8 MiB array.  Rejected on the host, nothing enqueued.
