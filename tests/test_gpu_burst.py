@@ -90,7 +90,7 @@ def test_workspace_without_room_for_all_splits():
         U.assert_close(out, ref, "bf16", f"{0 if ws is None else ws.numel()} bytes")
 
 
-@pytest.mark.parametrize("q_heads,kv_heads,n_cached,splits", [(32, 32, 640, 4), (28, 4, 200, 1), (28, 4, 800, 5)])
+@pytest.mark.parametrize("q_heads,kv_heads,n_cached,splits", [(32, 32, 640, 3), (28, 4, 200, 1), (28, 4, 800, 4)])
 def test_error_is_no_larger_than_that_of_the_kernels_that_stream_tiles(q_heads, kv_heads, n_cached, splits):
     # Numerators and results rounded to bf16: 2.07e-3 to 2.08e-3 there, 1.92e-3 to 1.94e-3 here, where a tile's largest numerators are exact, and
     # 2.15e-3 to 2.19e-3 with one reference for all tiles.  The mean over 100 thousand values varies by less than 1 %.
