@@ -52,7 +52,8 @@ int32_t sdllm_launch_plan(const sdllm_shape_t* shape, int32_t call, int32_t n_ca
 /* Small calls of SDLLM_CALL_SPARSE and SDLLM_CALL_FULL run a kernel that fetches all tiles of a workgroup at once, ahead of what
  * sdllm_launch_plan says: *splits is the number of workgroups that share a head's keys then, 0 for a call that it does not take.  A
  * workspace with less room takes fewer, and the plan of sdllm_launch_plan if there is no room for those that it needs at least, or
- * if it is not aligned to 16 bytes.  Host only. */
+ * if it is not aligned to 16 bytes; less than that plan needs is refused either way.
+ * Host only. */
 int32_t sdllm_burst_splits(const sdllm_shape_t* shape, int32_t call, int32_t n_cached, int32_t* splits);
 
 #ifdef __cplusplus
