@@ -42,7 +42,7 @@ typedef struct sdllm_launch_plan {
   int32_t key_splits;    /* workgroups that share a head's keys; merged by a second launch if more than one */
   int32_t waves;         /* per workgroup (SHARED_TILE: query heads per KV head) */
   int32_t touches_ahead; /* STREAM: 1 if the heads of a group bring tiles into L2 for each other */
-  int32_t key_groups;    /* DENSE: groups of waves that share a row block's keys (a last, small round of workgroups may have more) */
+  int32_t key_groups;    /* DENSE: groups of waves that share a row block's keys, but for a last round with more (sdllm_dense_tail_groups) */
 } sdllm_launch_plan_t;
 
 /* How an attention call of this shape is launched (n_cached: SDLLM_CALL_SPARSE only), given all the workspace it asks
@@ -55,6 +55,10 @@ int32_t sdllm_launch_plan(const sdllm_shape_t* shape, int32_t call, int32_t n_ca
  * if it is not aligned to 16 bytes; less than that plan needs is refused either way.
  * Host only. */
 int32_t sdllm_burst_splits(const sdllm_shape_t* shape, int32_t call, int32_t n_cached, int32_t* splits);
+
+/* SDLLM_CALL_DENSE on SDLLM_KERNEL_DENSE: *groups is the key groups of the launch that the workgroups of a last, small round are, 0 for a
+ * call (or a shape) without such a launch.  Host only. */
+int32_t sdllm_dense_tail_groups(const sdllm_shape_t* shape, int32_t* groups);
 
 #ifdef __cplusplus
 }

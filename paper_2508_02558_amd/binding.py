@@ -30,7 +30,7 @@ SDLLM_OP_SCORE_SELECT, SDLLM_OP_COMPACT_KV, SDLLM_OP_SPARSE_ATTN, SDLLM_OP_BLOCK
 EXPORTED = ("sdllm_error_string", "sdllm_version", "sdllm_retained_count", "sdllm_workspace_bytes",
             "sdllm_cache_state", "sdllm_score_select", "sdllm_compact_kv", "sdllm_sparse_attn",
             "sdllm_sparse_attn_noalloc", "sdllm_block_step", "sdllm_dense_attn", "sdllm_stream_read_probe",
-            "sdllm_launch_plan", "sdllm_burst_splits")
+            "sdllm_launch_plan", "sdllm_burst_splits", "sdllm_dense_tail_groups")
 
 # constants of include/sdllm_bench.h
 SDLLM_CALL_SPARSE, SDLLM_CALL_FULL, SDLLM_CALL_UPDATE, SDLLM_CALL_DENSE = 0, 1, 2, 3
@@ -104,6 +104,8 @@ def load() -> ctypes.CDLL:
     lib.sdllm_launch_plan.argtypes = [shp, i32, i32, ctypes.POINTER(sdllm_launch_plan_t)]
     lib.sdllm_burst_splits.restype = i32
     lib.sdllm_burst_splits.argtypes = [shp, i32, i32, i32p]
+    lib.sdllm_dense_tail_groups.restype = i32
+    lib.sdllm_dense_tail_groups.argtypes = [shp, i32p]
     _lib = lib
     return lib
 
@@ -294,3 +296,9 @@ def sdllm_burst_splits(shape: sdllm_shape_t, call: int, n_cached: int = 0) -> in
     splits = ctypes.c_int32(-1)
     _check(load().sdllm_burst_splits(ctypes.byref(shape), call, n_cached, ctypes.byref(splits)), "sdllm_burst_splits")
     return splits.value
+
+
+def sdllm_dense_tail_groups(shape: sdllm_shape_t) -> int:
+    groups = ctypes.c_int32(-1)
+    _check(load().sdllm_dense_tail_groups(ctypes.byref(shape), ctypes.byref(groups)), "sdllm_dense_tail_groups")
+    return groups.value

@@ -929,7 +929,7 @@ int32_t sdllm_launch_plan(const sdllm_shape_t* shape, int32_t call, int32_t n_ca
     plan->kernel = SDLLM_KERNEL_DENSE;
     plan->key_splits = 1;
     plan->waves = kMaxWavesPerWg;
-    plan->key_groups = dense_full_key_groups(s.batch * s.n_q_heads, s.seq_len);
+    plan->key_groups = dense_full_groups(s.batch * s.n_q_heads, s.seq_len).main;
     return SDLLM_OK;
   }
   AttnPlan pl{};
@@ -952,6 +952,14 @@ int32_t sdllm_burst_splits(const sdllm_shape_t* shape, int32_t call, int32_t n_c
   const bool taken = call == SDLLM_CALL_SPARSE ? plan_burst(pl, s, n_cached, s.cache_stride[2], s.block_len, s.blk_stride[2], SIZE_MAX)
                                                : call == SDLLM_CALL_FULL && plan_burst(pl, s, s.seq_len, s.kv_stride[2], 0, 0, SIZE_MAX);
   *splits = taken ? pl.n_split : 0;
+  return SDLLM_OK;
+}
+
+int32_t sdllm_dense_tail_groups(const sdllm_shape_t* shape, int32_t* groups) {
+  const int32_t st = check_shape(shape);
+  if (st != SDLLM_OK) return st;
+  if (!groups) return SDLLM_ERR_INVALID_ARG;
+  *groups = dense_full_takes(*shape) ? dense_full_groups(shape->batch * shape->n_q_heads, shape->seq_len).tail : 0;
   return SDLLM_OK;
 }
 

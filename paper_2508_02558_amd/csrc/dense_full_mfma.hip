@@ -450,7 +450,7 @@ static hipError_t launch_full(const DenseFullParams& p, hipStream_t s) {
 // 1277 37.3 / 27.5 / 37.6, 56 x 1277 78.7 / 74.7 / 91.0; 28 x 1277 stay whole, as 280 half workgroups need a second round (37.7 /
 // 48.7 / 54.8).  The choice is the fastest of the three or within 1 % of it at 645 of 665 sizes, within 8 % at the others.  Up to
 // kStagedKeys 28 x 192 10.6 / 9.7 / 7.9; the fit misses up to a fifth with five tiles (28 x 160 9.4 / 9.4 / 7.9).
-int dense_full_key_groups(int heads, int seq_len) {
+static int key_groups_throughout(int heads, int seq_len) {
   const int tiles = (seq_len + kTileKeys - 1) / kTileKeys;
   const bool rings = seq_len > kStagedKeys;
   int best = 1;
@@ -468,20 +468,19 @@ int dense_full_key_groups(int heads, int seq_len) {
 
 // Whole workgroups in rounds of the chip leave a last round that may be nearly empty: 280 of them take as long as 512.  If at most half of a
 // round is left, those rows run as a launch of their own with two key groups per workgroup, with four if it is a quarter, in less than a
-// round's time: tiles x 0.27 - 3.5 or x 0.38 - 2 us gained.  Returns the groups of that launch, 0 if there is none; main_groups, the
-// choice without it, becomes 1 where there is.  Measured, before / with: 48 heads x 1364 positions (256 + 32 workgroups) 82.7 / 68.2 us, 64 x
+// round's time: tiles x 0.27 - 3.5 or x 0.38 - 2 us gained.  Measured, before / with: 48 heads x 1364 positions (256 + 32 workgroups) 82.7 / 68.2 us, 64 x
 // 1100 (+ 64) 69.2 / 59.4, 84 x 916 (+ 80) 60.7 / 55.0, 28 x 4700 (2 x 256 + 20) 388 / 339, 48 x 2985 (2 x 256 + 64) 259 / 229, 56 x 4078 (3 x
 // 256 + 128) 469 / 450, 224 x 1174 (4 x 256 + 96) 194 / 187; where two groups throughout were the choice, 28 x 2393 119.5 / 108.3, 56 x 1200
 // 69.9 / 62.7, but 192 x 600 58.9 / 60.4.  More than half a round left: 28 x 3684 (+ 164) 204 / 228.  Short: 364 x 513 (+ 68) 90.9 / 95.1.
-static int dense_full_tail_groups(int heads, int seq_len, int& main_groups) {
+DenseFullGroups dense_full_groups(int heads, int seq_len) {
+  const int throughout = key_groups_throughout(heads, seq_len);
   const int tiles = (seq_len + kTileKeys - 1) / kTileKeys;
   const int64_t wgs = (int64_t)((seq_len + full_rows_per_wg(1) - 1) / full_rows_per_wg(1)) * heads;
   const int left = (int)(wgs % kNumCUs);
-  if (main_groups == 4 || wgs < kNumCUs || left == 0 || left > kNumCUs / 2) return 0;
+  if (seq_len <= kStagedKeys || throughout == 4 || wgs < kNumCUs || left == 0 || left > kNumCUs / 2) return {throughout, 0};
   const int groups = left <= kNumCUs / 4 ? 4 : 2;
-  if (tiles < (main_groups == 2 ? 32 : groups == 4 ? 9 : 24)) return 0;
-  main_groups = 1;
-  return groups;
+  if (tiles < (throughout == 2 ? 32 : groups == 4 ? 9 : 24)) return {throughout, 0};
+  return {1, groups};
 }
 
 // Up to kStagedKeys positions one or two key groups load their stages through registers as well: locked phases cost half an iteration at the
@@ -490,10 +489,9 @@ static int dense_full_tail_groups(int heads, int seq_len, int& main_groups) {
 // 11.08, x 256 20.7 / 20.3; two groups, 128 x 256 13.62 / 13.31.  Beyond, where 256-row workgroups come in twos: 256 x 288 34.9 / 35.2,
 // 28 x 735 with two groups 17.6 / 19.2.
 hipError_t launch_dense_full_mfma_bf16(const DenseFullParams& p, hipStream_t s) {
-  int ks = dense_full_key_groups(p.batch * p.hq, p.seq_len);
+  const auto [ks, tail] = dense_full_groups(p.batch * p.hq, p.seq_len);
   if (p.seq_len <= kStagedKeys)
     return ks == 4 ? launch_full<4, false>(p, s) : ks == 2 ? launch_full<2, false>(p, s) : launch_full<1, false>(p, s);
-  const int tail = dense_full_tail_groups(p.batch * p.hq, p.seq_len, ks);
   if (tail == 0) return ks == 4 ? launch_full<4, false>(p, s) : ks == 2 ? launch_full<2, true>(p, s) : launch_full<1, true>(p, s);
   const int qblocks = (p.seq_len + full_rows_per_wg(1) - 1) / full_rows_per_wg(1), all = qblocks * p.batch * p.hq;
   const int whole = all / kNumCUs * kNumCUs;

@@ -229,7 +229,10 @@ hipError_t launch_compact(const CompactParams& p, hipStream_t s);
 // the gather plus the split-KV merge of an attention launch whose partials are still in the workspace
 hipError_t launch_compact_combine(const CompactParams& p, const AttnParams& a, int dtype, hipStream_t s);
 hipError_t launch_dense_full_mfma_bf16(const DenseFullParams& p, hipStream_t s);
-int dense_full_key_groups(int heads, int seq_len);   // key groups its workgroups are divided into
+// Key groups that its workgroups are divided into: all of them, or all but those of a last round that is a launch of its own (tail: that
+// one's groups, 0 without it).
+struct DenseFullGroups { int main, tail; };
+DenseFullGroups dense_full_groups(int heads, int seq_len);
 hipError_t launch_stream_read(const void* src, size_t bytes, uint32_t* sink, hipStream_t s);
 
 }  // namespace sdllm

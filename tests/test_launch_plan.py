@@ -38,12 +38,28 @@ def test_key_groups_of_whole_sequences(heads, L, groups):
     assert B.sdllm_launch_plan(shape, DENSE).key_groups == groups
 
 
-# Beyond 256 positions, where the ring kernels' costs decide: the sizes at which they and those of the kernels before them differ.
-@pytest.mark.parametrize("heads,L,groups", [(84, 800, 1), (140, 800, 2), (112, 1025, 2), (56, 1277, 2), (64, 1277, 2), (40, 1537, 2), (40, 1793, 2),
-                                            (32, 2049, 2), (8, 2049, 2), (28, 1181, 1), (84, 1277, 1), (28, 300, 4), (56, 300, 2), (224, 300, 1)])
+def dense_groups(heads, L, **more):
+    shape = dict(batch=1, n_q_heads=heads, n_kv_heads=heads, head_dim=128, seq_len=L, block_off=0, block_len=32, dtype=B.SDLLM_BF16)
+    shape.update(more)
+    shape = B.make_shape(**shape)
+    return B.sdllm_launch_plan(shape, DENSE).key_groups, B.sdllm_dense_tail_groups(shape)
+
+
+# Beyond 256 positions, where the ring kernels' costs decide: the sizes at which they and those of the kernels before them differ, with the
+# groups of a last round that is a launch of its own, whose other rounds have one group.
+@pytest.mark.parametrize("heads,L,groups", [(84, 800, (1, 2)), (140, 800, (2, 0)), (112, 1025, (1, 4)), (56, 1277, (1, 4)), (64, 1277, (1, 4)),
+                                            (40, 1537, (1, 4)), (40, 1793, (1, 4)), (32, 2049, (1, 4)), (8, 2049, (2, 0)), (28, 1181, (1, 0)),
+                                            (84, 1277, (1, 0)), (28, 300, (4, 0)), (56, 300, (2, 0)), (224, 300, (1, 0))])
 def test_key_groups_of_the_ring_kernels(heads, L, groups):
-    shape = B.make_shape(batch=1, n_q_heads=heads, n_kv_heads=heads, head_dim=128, seq_len=L, block_off=0, block_len=32, dtype=B.SDLLM_BF16)
-    assert B.sdllm_launch_plan(shape, DENSE).key_groups == groups
+    assert dense_groups(heads, L) == groups
+
+
+# Workgroups left after whole rounds of 256 (1, 64, 65, 128, 129) and the tiles from which that pays
+@pytest.mark.parametrize("heads,L,groups", [(205, 1100, (1, 4)), (160, 512, (1, 4)), (160, 300, (2, 0)), (107, 768, (1, 2)), (128, 768, (1, 2)), (128, 736, (1, 0)),
+                                            (77, 1100, (1, 0)), (192, 600, (2, 0)), (256, 1200, (1, 0)), (160, 256, (1, 0))])
+def test_last_round_of_whole_sequences(heads, L, groups):
+    assert dense_groups(heads, L) == groups
+    assert dense_groups(heads, L, head_dim=64)[1] == dense_groups(heads, L, dtype=B.SDLLM_F32)[1] == 0      # the general kernel
 
 
 def test_a_call_or_plan_that_is_not_there_is_rejected():
