@@ -472,6 +472,9 @@ static int key_groups_throughout(int heads, int seq_len) {
 // 1100 (+ 64) 69.2 / 59.4, 84 x 916 (+ 80) 60.7 / 55.0, 28 x 4700 (2 x 256 + 20) 388 / 339, 48 x 2985 (2 x 256 + 64) 259 / 229, 56 x 4078 (3 x
 // 256 + 128) 469 / 450, 224 x 1174 (4 x 256 + 96) 194 / 187; where two groups throughout were the choice, 28 x 2393 119.5 / 108.3, 56 x 1200
 // 69.9 / 62.7, but 192 x 600 58.9 / 60.4.  More than half a round left: 28 x 3684 (+ 164) 204 / 228.  Short: 364 x 513 (+ 68) 90.9 / 95.1.
+// Nor where two groups throughout need no round more than the whole rounds do, as a last block of at most 128 rows is one of their workgroups
+// instead of two: 24 x 2599 (504 of 512 half workgroups) 94.8 / 117.8, 56 x 1075 48.2 / 61.0, 112 x 1048 90.0 / 96.1,
+// 60 x 3120 317 / 326.
 DenseFullGroups dense_full_groups(int heads, int seq_len) {
   const int throughout = key_groups_throughout(heads, seq_len);
   const int tiles = (seq_len + kTileKeys - 1) / kTileKeys;
@@ -480,6 +483,8 @@ DenseFullGroups dense_full_groups(int heads, int seq_len) {
   if (seq_len <= kStagedKeys || throughout == 4 || wgs < kNumCUs || left == 0 || left > kNumCUs / 2) return {throughout, 0};
   const int groups = left <= kNumCUs / 4 ? 4 : 2;
   if (tiles < (throughout == 2 ? 32 : groups == 4 ? 9 : 24)) return {throughout, 0};
+  const int64_t halves = (int64_t)((seq_len + full_rows_per_wg(2) - 1) / full_rows_per_wg(2)) * heads;
+  if (throughout == 2 && halves <= 2 * (wgs - left)) return {throughout, 0};
   return {1, groups};
 }
 

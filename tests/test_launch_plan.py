@@ -47,7 +47,7 @@ def dense_groups(heads, L, **more):
 
 # Beyond 256 positions, where the ring kernels' costs decide: the sizes at which they and those of the kernels before them differ, with the
 # groups of a last round that is a launch of its own, whose other rounds have one group.
-@pytest.mark.parametrize("heads,L,groups", [(84, 800, (1, 2)), (140, 800, (2, 0)), (112, 1025, (1, 4)), (56, 1277, (1, 4)), (64, 1277, (1, 4)),
+@pytest.mark.parametrize("heads,L,groups", [(84, 800, (1, 2)), (140, 800, (2, 0)), (112, 1025, (2, 0)), (56, 1277, (1, 4)), (64, 1277, (1, 4)),
                                             (40, 1537, (1, 4)), (40, 1793, (1, 4)), (32, 2049, (1, 4)), (8, 2049, (2, 0)), (28, 1181, (1, 0)),
                                             (84, 1277, (1, 0)), (28, 300, (4, 0)), (56, 300, (2, 0)), (224, 300, (1, 0))])
 def test_key_groups_of_the_ring_kernels(heads, L, groups):
@@ -56,7 +56,9 @@ def test_key_groups_of_the_ring_kernels(heads, L, groups):
 
 # Workgroups left after whole rounds of 256 (1, 64, 65, 128, 129) and the tiles from which that pays
 @pytest.mark.parametrize("heads,L,groups", [(205, 1100, (1, 4)), (160, 512, (1, 4)), (160, 300, (2, 0)), (107, 768, (1, 2)), (128, 768, (1, 2)), (128, 736, (1, 0)),
-                                            (77, 1100, (1, 0)), (192, 600, (2, 0)), (256, 1200, (1, 0)), (160, 256, (1, 0))])
+                                            (77, 1100, (1, 0)), (192, 600, (2, 0)), (256, 1200, (1, 0)), (160, 256, (1, 0)),
+                                            # a last block of at most 128 rows, without which two groups throughout need a round less
+                                            (56, 1152, (2, 0)), (56, 1153, (1, 4)), (24, 2599, (2, 0)), (60, 3120, (2, 0)), (112, 1153, (1, 4))])
 def test_last_round_of_whole_sequences(heads, L, groups):
     assert dense_groups(heads, L) == groups
     assert dense_groups(heads, L, head_dim=64)[1] == dense_groups(heads, L, dtype=B.SDLLM_F32)[1] == 0      # the general kernel
