@@ -328,22 +328,27 @@ AttnPlan plan_streams(const sdllm_shape_t& s, int32_t n0, int64_t sr0, int32_t n
 }
 
 // Key splits with which the kernel that fetches all of a workgroup's tiles at once (attn_burst_mfma.hip) takes a call ahead of the
-// kernels above, 0 if it does not.  It wins as long as its workgroups fit one to a CU, except
-// * unsplit, 225 to 256 multi-head heads with eight or nine tiles (256 x 8 +7 %, x 9 0 to +11 %; 224 x 9 8.9 -> 8.5 us, 128 x 9 8.0 -> 7.1);
-// * where the others go unsplit and it would have to split, up to: 10 heads' worth of tiles with few heads (16 x 10 6.1 -> 5.7 us, 20 x
-//   10 6.2 -> 5.9, 28 x 10 level, 28 x 11 6.5 -> 6.0, 32 x 10 +3 %), multi-head from 11 (49 x 10 6.8 / 7.5, x 11 8.3 -> 7.6) and with more
-//   than 64 heads 15 (72 x 15 9.7 -> 9.25, 80 x 22 11.9 -> 11.0, 96 x 18 10.6 / 11.2), grouped-query from 17 with more than 40
-//   heads (48 x 15 7.2 / 7.1, x 19 8.0 -> 7.4, 56 x 18 7.5 / 7.65, x 23 8.6 -> 7.85), 24 with more than 56 (64 x 22 8.4 / 8.7, x 26 9.6 ->
-//   8.9) and not at all with more than 64 (80 x 10 6.3 / 7.5, x 27 9.5 / 9.8).
+// kernels above, 0 if it does not.  It wins as long as its workgroups fit one to a CU, except (other kernel / this one, us, calls one after
+// the other on 32 layers' keys and values, which come from memory where they are more than the memory-side cache holds)
+// * unsplit multi-head heads, whose keys are all different, from some 20 MB on, where streams of a wave's tiles keep memory busier than
+//   one burst: 136 heads x 9 tiles 8.35 / 8.29, 144 x 9 8.41 / 8.50, 224 x 9 9.26 / 10.3; 176 x 8 8.46 / 8.39, 192 x 8 8.53 / 8.76; 216 x 7 8.57 /
+//   8.53, 232 x 7 8.72 / 8.90; 240 x 5 7.61 / 7.62, 256 x 5 7.73 / 7.88; 216 x 4 6.82 / 6.79, 256 x 4 7.03 / 7.21; 256 x 6 8.63 / 8.67, x 3 6.6 / 6.24;
+// * where the others go unsplit and it would have to split: multi-head 20 heads x 10 6.72 / 6.51, 32 x 11 7.17 / 7.16, 40 x 11 7.42 / 7.59, x 12
+//   7.99 / 7.81, 48 x 14 9.09 / 9.32, x 15 9.63 / 9.14, 64 x 15 9.98 / 10.2, x 16 10.4 / 10.25, 72 x 20 11.6 / 11.8, x 21 12.05 / 11.95, 80 x 17 10.65 /
+//   11.7, x 21 12.2 / 12.35, x 22 12.8 / 12.4; grouped-query 28 x 11 7.18 / 6.64, 40 x 13 7.36 / 7.58, x 15 7.63 / 7.49, 48 x 17 7.93 / 7.90, 56 x 17 7.94 /
+//   8.08, x 18 8.19 / 8.20, 64 x 24 9.5 / 8.9, and not at all with more than 64 heads (80 x 10 6.3 / 7.5, x 27 9.5 / 9.8).
 // More than one round of workgroups, whose second round waits for the first, is a quarter to a half slower (28 x 90 11.1 / 13.8).
 // The splits are those of least modelled time: a tile in a workgroup 0.22 us, the ninth 0.08 more (a third wave on one SIMD), four
 // splits to fold 0.16, and 0.94 for 16 KB of partials on each of 100 workgroups, fitted to 460 calls of 2 to 96 heads x 10 to 280
 // tiles (rms 0.2 us; half a per cent lost to the best count on average, 5 % at 2 of 130 sizes).
 // most: no more of them.
 int burst_splits(int heads, int tiles, int group, int most) {
-  if (tiles <= kBurstMaxTiles) return heads <= (group > 1 || tiles <= 7 ? kNumCUs : 224) ? 1 : 0;
+  static constexpr int kMostMultiHead[kBurstMaxTiles + 1] = {kNumCUs, kNumCUs, kNumCUs, kNumCUs, 216, 240, kNumCUs, 216, 176, 136};   // by tiles
+  if (tiles <= kBurstMaxTiles) return heads <= (group > 1 ? kNumCUs : kMostMultiHead[tiles]) ? 1 : 0;
   if (heads > (group > 1 ? 64 : 85)) return 0;
-  const int from = heads <= 20 ? 10 : group == 1 ? (heads <= 64 ? 11 : 15) : heads <= 40 ? 11 : heads <= 56 ? 17 : 24;
+  const int from = heads <= 20 ? 10 : heads <= 32 ? 11
+                   : group > 1 ? (heads <= 36 ? 11 : heads <= 40 ? 15 : heads <= 48 ? 17 : heads <= 56 ? 18 : 24)
+                               : (heads <= 44 ? 12 : heads <= 56 ? 15 : heads <= 64 ? 16 : heads <= 72 ? 21 : 22);
   if (tiles < from) return 0;
   int best = 0, least = INT32_MAX;
   for (int n = (tiles + kBurstMaxTiles - 1) / kBurstMaxTiles; n <= most && n * heads <= kNumCUs; ++n) {
