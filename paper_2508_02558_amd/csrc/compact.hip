@@ -60,7 +60,7 @@ __device__ __forceinline__ void compact_block(const CompactParams& p, int block_
   }
 }
 
-__global__ __launch_bounds__(kCompactThreads) void compact_kernel(const CompactParams p) { compact_block(p, (int)blockIdx.x); }
+__global__ __launch_bounds__(kCompactThreads) void compact_kernel(const CompactParams p) { compact_block(p, p.first_block + (int)blockIdx.x); }
 
 // blocks [0, n_combine): split-KV merge of the attention described by `a` (output of type T); the rest: the gather.
 // MAX > 0: combine32_block, else combine_block with TPI threads per item
@@ -79,7 +79,7 @@ __global__ __launch_bounds__(kCompactThreads) void compact_combine_kernel(const 
   }
 }
 
-// Blocks of the gather, whose split over the grid is left in p; negative: more than a launch has
+// Blocks of the gather, whose split over the grid is left in p
 static int64_t plan_compact(CompactParams& p) {
   const int per_block = compact_rows(p);
   p.row_blocks = (p.k_total + per_block - 1) / per_block;
@@ -88,12 +88,22 @@ static int64_t plan_compact(CompactParams& p) {
   return (int64_t)p.batch * p.hkv * p.row_blocks;
 }
 
+// A launch has fewer than 2^32 threads.  With few rows per (batch, KV head), a block or a part of one for each, the blocks can be more.
+constexpr int64_t kMostBlocks = UINT32_MAX / kCompactThreads;
+
+static hipError_t launch_blocks(CompactParams& p, int64_t first, int64_t blocks, hipStream_t s) {
+  for (; first < blocks; first += kMostBlocks) {
+    p.first_block = (int)first;
+    const hipError_t e = launch(compact_kernel, dim3((unsigned)(blocks - first < kMostBlocks ? blocks - first : kMostBlocks)), dim3(kCompactThreads), 0, s, p);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 hipError_t launch_compact(const CompactParams& p, hipStream_t s) {
   CompactParams c = p;
   const int64_t blocks = plan_compact(c);
-  if (blocks == 0) return hipSuccess;
-  if (blocks > INT32_MAX) return hipErrorInvalidValue;
-  return launch(compact_kernel, dim3((unsigned)blocks), dim3(kCompactThreads), 0, s, c);
+  return blocks > INT32_MAX ? hipErrorInvalidValue : launch_blocks(c, 0, blocks, s);
 }
 
 hipError_t launch_compact_combine(const CompactParams& p, const AttnParams& a, int dtype, hipStream_t s) {
@@ -103,13 +113,15 @@ hipError_t launch_compact_combine(const CompactParams& p, const AttnParams& a, i
     constexpr int MAX = decltype(max)::value;
     const int64_t n_combine = MAX > 0 ? (int64_t)4 * a.batch * a.hq : combine_blocks(a);
     CompactParams c = p;
-    const int64_t blocks = n_combine + plan_compact(c);
-    if (blocks > INT32_MAX) return hipErrorInvalidValue;
+    const int64_t blocks = plan_compact(c);
+    if (blocks > INT32_MAX || n_combine > kMostBlocks) return hipErrorInvalidValue;
+    const int64_t beside = blocks < kMostBlocks - n_combine ? blocks : kMostBlocks - n_combine;   // of the gather in the merge's launch
     const auto kernel = [&] {
       if constexpr (MAX > 0) return compact_combine_kernel<__bf16, 1, MAX>;
       else return dtype != 0 ? compact_combine_kernel<float, 1, 0> : four ? compact_combine_kernel<__bf16, 4, 0> : compact_combine_kernel<__bf16, 1, 0>;
     }();
-    return launch(kernel, dim3((unsigned)blocks), dim3(kCompactThreads), 0, s, c, a, Divisor(a.hq), (int)n_combine);
+    const hipError_t e = launch(kernel, dim3((unsigned)(n_combine + beside)), dim3(kCompactThreads), 0, s, c, a, Divisor(a.hq), (int)n_combine);
+    return e == hipSuccess ? launch_blocks(c, beside, blocks, s) : e;
   });
 }
 

@@ -186,7 +186,7 @@ struct CompactParams {
   int32_t batch, hkv, k_total, seq_len;
   int32_t row_bytes;
   Divisor by_hkv, by_row_blocks;   // set by the launcher: KV heads, blocks per row of the index set
-  int32_t row_blocks;
+  int32_t row_blocks, first_block;
 };
 
 // Full-sequence bidirectional attention: L query rows per head over all L keys.

@@ -29,3 +29,19 @@ def test_gather(dtype, d, batch, heads, kept):
     for src, dst in ((k, kc), (v, vc)):
         assert torch.equal(dst[:, :, :kept], src.gather(2, rows))
         assert dst[:, :, kept:].isnan().all()                  # nothing behind the retained rows
+
+
+def test_more_blocks_than_a_launch_has():
+    # one row of each of 16 793 600 heads, a block each: 16 385 more than have fewer than 2^32 threads
+    print("[case] compact, 16.8 million heads of one row", flush=True)
+    batch, heads, d = 65600, 256, 64
+    k, v = (torch.randint(-30000, 30000, (batch, heads, 2, d), device=DEV, dtype=torch.int16) for _ in range(2))
+    kc, vc = (torch.zeros(batch, heads, 1, d, device=DEV, dtype=torch.int16) for _ in range(2))
+    shape = B.make_shape(batch=batch, n_q_heads=heads, n_kv_heads=heads, head_dim=d, seq_len=2, block_off=0, block_len=1, dtype=B.SDLLM_BF16,
+                         retention=1.0, cache_rows=1, kv_stride=B.strides_of(k))
+    assert B.sdllm_retained_count(shape)[0] == 1
+    idx = torch.randint(0, 2, (batch, heads, 1), device=DEV, dtype=torch.int32)
+    B.sdllm_compact_kv(shape, k, v, idx, kc, vc)
+    torch.cuda.synchronize()
+    for src, dst in ((k, kc), (v, vc)):
+        assert torch.equal(dst[:, :, 0], torch.where(idx == 0, src[:, :, 0], src[:, :, 1]))
