@@ -14,7 +14,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB_PATH = os.path.join(HERE, "libsdllm.so")
-PYCALL_PATH = os.path.join(HERE, "_pycall.so")   # tensors to entry points without ctypes (binding.py)
+# tensors to entry points without ctypes (binding.py); named for the interpreter that it is built for, as others cannot load it
+PYCALL_PATH = os.path.join(HERE, "_pycall" + sysconfig.get_config_var("EXT_SUFFIX"))
 BUILD_DIR = os.path.join(HERE, "_build")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -41,11 +42,15 @@ def _compile(src: str) -> str:
 
 def _build_pycall() -> None:
     """Host code for the running interpreter.  Without its headers there is none, and the binding goes through ctypes."""
+    for old in (PYCALL_PATH, os.path.join(os.path.dirname(PYCALL_PATH), "_pycall.so")):   # the second: any interpreter would load it
+        if os.path.exists(old):
+            os.remove(old)
     include = sysconfig.get_paths()["include"]
     if not os.path.exists(os.path.join(include, "Python.h")):
         return
     tmp = PYCALL_PATH + ".tmp"
-    cmd = [os.environ.get("CXX", "g++"), "-O2", "-shared", "-fPIC", "-std=c++17", "-I", INCLUDE, "-I", include,
+    # by the compiler that the library is built with; it calls nothing of the HIP runtime and is not linked to it
+    cmd = [HIPCC, "-no-hip-rt", "-x", "c++", "-O2", "-shared", "-fPIC", "-std=c++17", "-I", INCLUDE, "-I", include,
            os.path.join(CSRC, "pycall.cpp"), "-o", tmp]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:

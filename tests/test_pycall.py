@@ -1,10 +1,14 @@
 """The entry points called without ctypes: every argument arrives where the C prototype has it, errors come back as they do through
 ctypes, and nothing is called with arguments that could not be had."""
 import ctypes
+import importlib.util
+import os
+import sysconfig
 
 import pytest
 
 from paper_2508_02558_amd import binding as B
+from paper_2508_02558_amd import build
 
 pytestmark = pytest.mark.skipif(B._pycall is None, reason="built without the interpreter's headers")
 vp, i32, sz = ctypes.c_void_p, ctypes.c_int32, ctypes.c_size_t
@@ -96,3 +100,18 @@ def test_refusals_are_the_same_with_and_without(monkeypatch):
     with_it = refusals()
     monkeypatch.setattr(B, "_pycall", None)
     assert refusals() == with_it
+
+
+def test_built_by_the_librarys_compiler_for_this_interpreter(monkeypatch, tmp_path):
+    suffix = sysconfig.get_config_var("EXT_SUFFIX")
+    assert B._pycall.__file__.endswith("_pycall" + suffix)
+    stale = tmp_path / "_pycall.so"
+    stale.write_bytes(b"")
+    monkeypatch.setattr(build, "PYCALL_PATH", str(tmp_path / ("_pycall" + suffix)))
+    monkeypatch.setenv("CXX", str(tmp_path / "no-compiler"))
+    if os.path.isabs(build.HIPCC):
+        monkeypatch.setenv("PATH", str(tmp_path))                  # no other compiler either
+    build._build_pycall()
+    assert not stale.exists()                                      # one that every interpreter would load
+    spec = importlib.util.spec_from_file_location("_pycall", build.PYCALL_PATH)
+    assert importlib.util.module_from_spec(spec).block_step
