@@ -4,6 +4,8 @@
 #include <math.h>
 #include <stdlib.h>
 
+#include <algorithm>
+
 #include "sdllm.h"
 #include "sdllm_bench.h"
 #include "sdllm_internal.h"
@@ -360,8 +362,8 @@ int burst_splits(int heads, int tiles, int group, int most) {
 }
 
 // Whether that kernel takes a call without by-products (pl is the plan then), given `scratch` bytes of workspace aligned to 16.  It
-// makes do with fewer splits where those of the rule do not fit: sdllm_block_step asks for no more workspace for its sake, but nearly
-// always has it, for scores and for the partials of the longer dense rows.
+// makes do with fewer splits where those of the rule do not fit, and leaves the call to the kernels above where even those are too
+// many: sdllm_workspace_bytes asks for the room (4.3 MB at most), but calls that bring no more than the kernels above need are taken too.
 constexpr size_t kBurstPartialBytes = 32 * (128 + 2) * sizeof(float);
 bool plan_burst(AttnPlan& pl, const sdllm_shape_t& s, int32_t n0, int64_t sr0, int32_t n1, int64_t sr1, size_t scratch) {
   if (!takes_mfma(s, n0, sr0, n1, sr1)) return false;
@@ -378,6 +380,12 @@ bool plan_burst(AttnPlan& pl, const sdllm_shape_t& s, int32_t n0, int64_t sr0, i
   pl.waves = pl.tiles_per_split > kMaxWavesPerWg ? pl.tiles_per_split : kMaxWavesPerWg;
   size_partials(pl, s);
   return pl.ws_bytes() <= scratch;   // two buffers, each a multiple of 256 bytes
+}
+
+// Workspace with which a call without by-products runs that kernel with the splits of its rule, 0 if it does not run it
+size_t burst_bytes(const sdllm_shape_t& s, int32_t n0, int64_t sr0, int32_t n1, int64_t sr1) {
+  AttnPlan pl;
+  return plan_burst(pl, s, n0, sr0, n1, sr1, SIZE_MAX) ? pl.ws_bytes() : 0;
 }
 
 // Whether the dense launch of a cache-update step can also leave the saliency scores: multi-head attention
@@ -760,11 +768,13 @@ int32_t sdllm_workspace_bytes(const sdllm_shape_t* shape, int32_t op, int32_t n_
     case SDLLM_OP_COMPACT_KV: need = 0; break;
     case SDLLM_OP_SPARSE_ATTN:
       if (n_cached < 0) return SDLLM_ERR_INVALID_ARG;
-      need = plan_streams(s, n_cached, s.cache_stride[2], s.block_len, s.blk_stride[2]).ws_bytes();
-      if (AttnPlan b; plan_burst(b, s, n_cached, s.cache_stride[2], s.block_len, s.blk_stride[2], SIZE_MAX) && b.ws_bytes() > need)
-        need = b.ws_bytes();
+      need = std::max(plan_streams(s, n_cached, s.cache_stride[2], s.block_len, s.blk_stride[2]).ws_bytes(),
+                      burst_bytes(s, n_cached, s.cache_stride[2], s.block_len, s.blk_stride[2]));
       break;
-    case SDLLM_OP_BLOCK_STEP: need = plan_block_step(s).bytes(); break;
+    case SDLLM_OP_BLOCK_STEP:   // sdllm_block_step refuses less than the first only
+      need = std::max({plan_block_step(s).bytes(), burst_bytes(s, counts_of(s).k_total, s.cache_stride[2], s.block_len, s.blk_stride[2]),
+                       burst_bytes(s, s.seq_len, s.kv_stride[2], 0, 0)});
+      break;
     default: return SDLLM_ERR_INVALID_ARG;
   }
   *bytes = need > 0 ? need : kAlign;   // never zero, so callers can always allocate
@@ -836,7 +846,7 @@ int32_t sdllm_block_step(const sdllm_shape_t* shape, int32_t step_in_block, int3
   if ((st = sdllm_cache_state(step_in_block, delay, &state)) != SDLLM_OK) return st;
   BlockStepWs w = plan_block_step(s);
   if (ws_bytes < w.bytes()) w = plan_block_step(s, false);
-  const size_t need = w.bytes() > 0 ? w.bytes() : kAlign;   // as sdllm_workspace_bytes says
+  const size_t need = w.bytes() > 0 ? w.bytes() : kAlign;
   if (!ws || ws_bytes < need || (reinterpret_cast<uintptr_t>(ws) % kAlign) != 0) return SDLLM_ERR_WORKSPACE;
   if ((st = check_q(s, q_blk)) != SDLLM_OK) return st;
   if (!k_in || !v_in || !out || !aligned16(k_in) || !aligned16(v_in) || !aligned16(out) ||

@@ -220,11 +220,26 @@ def test_block_step_takes_a_workspace_without_room_for_partials_and_scores_side_
     step = lambda n: lib.sdllm_block_step(ctypes.byref(s), 1, 1, z, fake, fake, fake, fake, fake, fake, fake, n, z, None)
     assert step(full) == step(less) == B.SDLLM_ERR_INVALID_ARG
     assert step(less - 1) == B.SDLLM_ERR_WORKSPACE
-    # the 32-row kernels need it all
-    m = B.make_shape(batch=1, n_q_heads=8, n_kv_heads=8, head_dim=128, seq_len=1500, block_off=500, block_len=32, dtype=B.SDLLM_BF16)
+    # the 32-row kernels need it all, where it is no more than they need (with 8 heads the kernel for small calls would use more)
+    m = B.make_shape(batch=1, n_q_heads=32, n_kv_heads=32, head_dim=128, seq_len=1500, block_off=500, block_len=32, dtype=B.SDLLM_BF16)
     assert B.sdllm_launch_plan(m, B.SDLLM_CALL_UPDATE).key_splits > 1
     need = B.sdllm_workspace_bytes(m, B.SDLLM_OP_BLOCK_STEP)
     assert lib.sdllm_block_step(ctypes.byref(m), 1, 1, z, fake, fake, fake, fake, fake, fake, fake, need - 1, z, None) == B.SDLLM_ERR_WORKSPACE
+
+
+# Heads and cached keys of which a block step used to ask for less than its sparse step had a use for.  least: what it did ask for.
+@pytest.mark.parametrize("heads,kv_heads,seq_len,least", [(16, 2, 700, 828672), (14, 2, 1500, 1452544), (8, 8, 300, 14848), (8, 8, 4500, 1261312),
+                                                          (1, 1, 2500, 147712), (28, 4, 2500, 3896064), (32, 32, 4500, 4962816)])
+def test_block_step_asks_for_room_for_every_split_of_a_small_call_and_takes_less(lib, heads, kv_heads, seq_len, least):
+    s = B.make_shape(batch=1, n_q_heads=heads, n_kv_heads=kv_heads, head_dim=128, seq_len=seq_len, block_off=200, block_len=32, dtype=B.SDLLM_BF16)
+    kept, need = B.sdllm_retained_count(s)[0], B.sdllm_workspace_bytes(s, B.SDLLM_OP_BLOCK_STEP)
+    splits = [B.sdllm_burst_splits(s, call, kept) for call in (B.SDLLM_CALL_SPARSE, B.SDLLM_CALL_FULL)]
+    assert need >= max(n if n > 1 else 0 for n in splits) * heads * 32 * (128 + 2) * 4
+    assert need >= B.sdllm_workspace_bytes(s, B.SDLLM_OP_SPARSE_ATTN, kept)
+    fake, z = ctypes.c_void_p(0x1000), ctypes.c_void_p(None)
+    step = lambda n: lib.sdllm_block_step(ctypes.byref(s), 1, 1, z, fake, fake, fake, fake, fake, fake, fake, n, z, None)
+    assert step(need) == step(least) == B.SDLLM_ERR_INVALID_ARG       # past the size check the missing queries are the error
+    assert step(least - 1) == B.SDLLM_ERR_WORKSPACE
 
 
 def test_current_stream_with_and_without_torchs_private_function(monkeypatch):

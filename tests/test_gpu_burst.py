@@ -57,11 +57,31 @@ def test_dense_rows(batch, q_heads, kv_heads, seq_len, splits):
                          dtype=B.SDLLM_BF16)
     assert B.sdllm_burst_splits(shape, B.SDLLM_CALL_FULL) == splits
     out = torch.full_like(q, float("nan"))
-    # room for every split, which a block step's workspace may not have
-    ws = torch.empty(max(B.sdllm_workspace_bytes(shape, B.SDLLM_OP_BLOCK_STEP), batch * q_heads * splits * 16640 + 512), dtype=torch.uint8, device=DEV)
+    ws = torch.empty(B.sdllm_workspace_bytes(shape, B.SDLLM_OP_BLOCK_STEP), dtype=torch.uint8, device=DEV)
     B.sdllm_block_step(shape, 0, 1, q, k, v, None, None, None, out, ws)
     torch.cuda.synchronize()
     U.assert_close(out, U.oracle_attention_batch(q, k, v), "bf16", f"L={seq_len}")
+
+
+# A sparse step is the same call as sdllm_block_step and as sdllm_sparse_attn, with the workspace that each asks for.  Few heads: the other states of
+# the step need less than the sparse one's splits.
+@pytest.mark.parametrize("q_heads,kv_heads,seq_len", [(8, 8, 1300), (14, 2, 2500), (16, 2, 900), (1, 1, 4000)])
+def test_block_step_and_sparse_attention_are_one(q_heads, kv_heads, seq_len):
+    print(f"[case] burst, block step {q_heads}/{kv_heads} L={seq_len}", flush=True)
+    torch.manual_seed(seq_len)
+    shape = B.make_shape(batch=1, n_q_heads=q_heads, n_kv_heads=kv_heads, head_dim=128, seq_len=seq_len, block_off=480, block_len=32, dtype=B.SDLLM_BF16)
+    kept = B.sdllm_retained_count(shape)[0]
+    q = (2.0 * torch.randn(1, q_heads, 32, 128, device=DEV)).bfloat16()
+    kc, vc = (torch.randn(1, kv_heads, seq_len - 32, 128, device=DEV).bfloat16() for _ in range(2))
+    kb, vb = (torch.randn(1, kv_heads, 32, 128, device=DEV).bfloat16() for _ in range(2))
+    outs = [torch.full_like(q, float("nan")) for _ in range(2)]
+    ws = [torch.empty(B.sdllm_workspace_bytes(shape, op, kept), dtype=torch.uint8, device=DEV) for op in (B.SDLLM_OP_SPARSE_ATTN, B.SDLLM_OP_BLOCK_STEP)]
+    B.sdllm_sparse_attn(shape, q, kc, vc, kept, kb, vb, outs[0], ws[0])
+    assert B.sdllm_block_step(shape, 2, 1, q, kb, vb, None, kc, vc, outs[1], ws[1]) == B.SDLLM_STATE_REUSE
+    torch.cuda.synchronize()
+    U.assert_close(outs[0], U.oracle_attention_batch(q, torch.cat([kc[:, :, :kept], kb], 2), torch.cat([vc[:, :, :kept], vb], 2)), "bf16",
+                   f"{q_heads}/{kv_heads} L={seq_len}")
+    assert torch.equal(*outs)
 
 
 @pytest.mark.parametrize("n_cached", [128, 200, 600])
