@@ -342,7 +342,8 @@ AttnPlan plan_streams(const sdllm_shape_t& s, int32_t n0, int64_t sr0, int32_t n
 // More than one round of workgroups, whose second round waits for the first, is a quarter to a half slower (28 x 90 11.1 / 13.8).
 // The splits are those of least modelled time: a tile in a workgroup 0.22 us, the ninth 0.08 more (a third wave on one SIMD), four
 // splits to fold 0.16, and 0.94 for 16 KB of partials on each of 100 workgroups, fitted to 460 calls of 2 to 96 heads x 10 to 280
-// tiles (rms 0.2 us; half a per cent lost to the best count on average, 5 % at 2 of 130 sizes).
+// tiles (rms 0.2 us; half a per cent lost to the best count on average, 5 % at 2 of 130 sizes).  The merge folds as many as it is
+// instantiated for: 1 head x 40 tiles in 20 splits (as 24) 6.96 us, in 14 (as 16) 6.48.
 // most: no more of them.
 int burst_splits(int heads, int tiles, int group, int most) {
   static constexpr int kMostMultiHead[kBurstMaxTiles + 1] = {kNumCUs, kNumCUs, kNumCUs, kNumCUs, 216, 240, kNumCUs, 216, 176, 136};   // by tiles
@@ -355,7 +356,8 @@ int burst_splits(int heads, int tiles, int group, int most) {
   int best = 0, least = INT32_MAX;
   for (int n = (tiles + kBurstMaxTiles - 1) / kBurstMaxTiles; n <= most && n * heads <= kNumCUs; ++n) {
     const int mine = (tiles + n - 1) / n;
-    const int cost = 22 * mine + (mine > kMaxWavesPerWg ? 8 : 0) + 16 * ((n + 3) / 4) + 15 * heads * n / 16;   // 0.01 us
+    const int fours = n <= 16 ? (n + 3) / 4 : n <= 24 ? 6 : 8;   // with_combine32
+    const int cost = 22 * mine + (mine > kMaxWavesPerWg ? 8 : 0) + 16 * fours + 15 * heads * n / 16;   // 0.01 us
     if (cost < least) { least = cost; best = n; }
   }
   return best;

@@ -168,6 +168,7 @@ def test_launches_of_the_general_kernel_stay_below_two_to_the_32_threads():
     (2, 32, 32, 15, 0), (2, 32, 32, 16, 2), (1, 72, 72, 20, 0), (1, 72, 72, 21, 3), (5, 16, 16, 21, 0), (5, 16, 16, 22, 3), (3, 32, 32, 28, 0),
     (1, 40, 8, 14, 0), (1, 40, 8, 15, 3), (2, 28, 4, 17, 0), (2, 28, 4, 18, 3), (3, 16, 2, 16, 0), (3, 16, 2, 17, 3), (2, 32, 8, 23, 0), (2, 32, 8, 24, 3), (5, 16, 2, 24, 0),
     (1, 28, 4, 69, 8), (1, 28, 4, 81, 9), (1, 28, 4, 82, 0), (1, 32, 8, 72, 8), (1, 32, 8, 73, 0), (1, 2, 2, 288, 32), (1, 2, 2, 289, 0),
+    (1, 1, 1, 40, 14), (1, 1, 1, 56, 14), (1, 1, 1, 140, 24),      # as many as the merge folds at once
 ])
 def test_small_calls_whose_tiles_are_fetched_at_once(batch, q_heads, kv_heads, tiles, splits):
     shape = dict(batch=batch, n_q_heads=q_heads, n_kv_heads=kv_heads, head_dim=128, seq_len=32 * tiles, block_off=0, block_len=32, dtype=B.SDLLM_BF16)
