@@ -60,6 +60,14 @@ int32_t sdllm_burst_splits(const sdllm_shape_t* shape, int32_t call, int32_t n_c
  * call (or a shape) without such a launch.  Host only. */
 int32_t sdllm_dense_tail_groups(const sdllm_shape_t* shape, int32_t* groups);
 
+/* Which kernels reduce the columns of the scoring: those for blocks of 32 query rows, the same with the blocks of 32 rows of a head (rows that
+ * are not there among them) as heads, or the general one.  The dense launch of a cache-update step of SDLLM_COLUMNS_32 may leave the
+ * scores by itself.  Host only. */
+#define SDLLM_COLUMNS_GENERAL 0
+#define SDLLM_COLUMNS_32 1
+#define SDLLM_COLUMNS_BLOCKS 2
+int32_t sdllm_column_kernel(const sdllm_shape_t* shape, int32_t* kernel);
+
 #ifdef __cplusplus
 }
 #endif

@@ -30,11 +30,13 @@ SDLLM_OP_SCORE_SELECT, SDLLM_OP_COMPACT_KV, SDLLM_OP_SPARSE_ATTN, SDLLM_OP_BLOCK
 EXPORTED = ("sdllm_error_string", "sdllm_version", "sdllm_retained_count", "sdllm_workspace_bytes",
             "sdllm_cache_state", "sdllm_score_select", "sdllm_compact_kv", "sdllm_sparse_attn",
             "sdllm_sparse_attn_noalloc", "sdllm_block_step", "sdllm_dense_attn", "sdllm_stream_read_probe",
-            "sdllm_launch_plan", "sdllm_burst_splits", "sdllm_dense_tail_groups")
+            "sdllm_launch_plan", "sdllm_burst_splits", "sdllm_dense_tail_groups",
+            "sdllm_column_kernel")
 
 # constants of include/sdllm_bench.h
 SDLLM_CALL_SPARSE, SDLLM_CALL_FULL, SDLLM_CALL_UPDATE, SDLLM_CALL_DENSE = 0, 1, 2, 3
 SDLLM_KERNEL_GENERAL, SDLLM_KERNEL_PER_HEAD, SDLLM_KERNEL_SHARED_TILE, SDLLM_KERNEL_STREAM, SDLLM_KERNEL_DENSE = 0, 1, 2, 3, 4
+SDLLM_COLUMNS_GENERAL, SDLLM_COLUMNS_32, SDLLM_COLUMNS_BLOCKS = 0, 1, 2
 
 
 class sdllm_shape_t(ctypes.Structure):
@@ -106,6 +108,8 @@ def load() -> ctypes.CDLL:
     lib.sdllm_burst_splits.argtypes = [shp, i32, i32, i32p]
     lib.sdllm_dense_tail_groups.restype = i32
     lib.sdllm_dense_tail_groups.argtypes = [shp, i32p]
+    lib.sdllm_column_kernel.restype = i32
+    lib.sdllm_column_kernel.argtypes = [shp, i32p]
     _lib = lib
     return lib
 
@@ -302,3 +306,9 @@ def sdllm_dense_tail_groups(shape: sdllm_shape_t) -> int:
     groups = ctypes.c_int32(-1)
     _check(load().sdllm_dense_tail_groups(ctypes.byref(shape), ctypes.byref(groups)), "sdllm_dense_tail_groups")
     return groups.value
+
+
+def sdllm_column_kernel(shape: sdllm_shape_t) -> int:
+    kernel = ctypes.c_int32(-1)
+    _check(load().sdllm_column_kernel(ctypes.byref(shape), ctypes.byref(kernel)), "sdllm_column_kernel")
+    return kernel.value

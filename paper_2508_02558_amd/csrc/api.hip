@@ -494,6 +494,13 @@ void plan_columns(size_t rows, int tiles, int& waves, int& n_part, int& tiles_pe
   n_part = (tiles + tiles_per_part - 1) / tiles_per_part;   // no empty part
 }
 
+// Tiles of the candidates that get a score, per KV head
+int scored_tiles(const sdllm_shape_t& s) {
+  const Counts c = counts_of(s);
+  const int n1 = s.evict_scope == SDLLM_EVICT_PREFIX_ONLY ? 0 : c.n_suf;
+  return (c.n_pre + kTileKeys - 1) / kTileKeys + (n1 + kTileKeys - 1) / kTileKeys;
+}
+
 ScorePlan plan_score(const sdllm_shape_t& s) {
   const Counts c = counts_of(s);
   ScorePlan pl{};
@@ -514,9 +521,7 @@ ScorePlan plan_score(const sdllm_shape_t& s) {
   pl.tiles_per_part = 0;
   pl.waves = 1;
   if (pl.mfma) {
-    const int n0 = pl.n_scored < c.n_pre ? pl.n_scored : c.n_pre;
-    const int n1 = pl.n_scored - n0;
-    plan_columns(rows, (n0 + kTileKeys - 1) / kTileKeys + (n1 + kTileKeys - 1) / kTileKeys, pl.waves, pl.n_part, pl.tiles_per_part);
+    plan_columns(rows, scored_tiles(s), pl.waves, pl.n_part, pl.tiles_per_part);
   } else {
     // row statistics: a statistics-only run of the general attention kernel over the whole sequence
     AttnPlan st{};
@@ -532,7 +537,9 @@ ScorePlan plan_score(const sdllm_shape_t& s) {
 // fetch tiles for all heads at once, where the general kernel reads queries and keys from LDS for each.  Cache-update steps, general / as
 // heads: block of 64, 2 x 32 heads x 1280 positions 38.9 / 37.9 us, 1 x 8 x 1100 26.0 / 23.2, 1 x 8/2 x 600 31.0 / 22.6, 8 x 32/8 x 4000 220 / 173;
 // block of 16, 1 x 14/2 x 600 27.0 / 21.8, 8 x 28/4 x 3000 84 / 68, 4 x 32 x 2000 72.1 / 70.4, but one block per KV head and few of them, where the
-// general kernel's smaller workgroups are more: 16 x 900 23.8 / 24.8.
+// general kernel's smaller workgroups are more: KV heads x positions, each layer with keys of its own, 64 x 200 22.5 / 22.1, x 600 30.3 / 29.8,
+// x 2600 61.6 / 56.6, 128 x 600 36.3 / 35.3, x 1300 60.2 / 55.6, 48 x 600 level, 32 x 600 28.5 / 27.6, x 1800 31.6 / 32.8, x 2600 38.1 / 39.3, 16 x 900
+// 23.8 / 24.8.  (With all keys and values in the memory-side cache 64 x 1300 and 128 x 600 lose 3 to 6 %.)
 bool blocks_as_heads(const sdllm_shape_t& s) {
   const int group = row_blocks(s, s.block_len) * (s.n_q_heads / s.n_kv_heads);
   return s.dtype == SDLLM_BF16 && s.head_dim == 128 && (s.block_len % 32 == 0 || s.score_mode == SDLLM_SOFTMAX_MEAN) &&
@@ -622,9 +629,7 @@ int32_t score_select_impl(const sdllm_shape_t& s, const void* q_blk, const void*
       sp.q_shift = row_blocks(s, s.block_len) - 1;
       sp.hq <<= sp.q_shift; sp.group <<= sp.q_shift;
       sp.skip_stats = 1;
-      const int n0 = sp.n_cand < s.block_off ? sp.n_cand : s.block_off, n1 = sp.n_cand - n0;
-      plan_columns((size_t)s.batch * s.n_kv_heads, (n0 + kTileKeys - 1) / kTileKeys + (n1 + kTileKeys - 1) / kTileKeys, sp.waves, sp.n_part,
-                   sp.tiles_per_part);
+      plan_columns((size_t)s.batch * s.n_kv_heads, scored_tiles(s), sp.waves, sp.n_part, sp.tiles_per_part);
       e = launch_score_mfma_bf16(sp, hs);
     } else if (e == hipSuccess) {
       e = launch_score_cols_general(sp, s.dtype, hs);
@@ -969,6 +974,14 @@ int32_t sdllm_burst_splits(const sdllm_shape_t* shape, int32_t call, int32_t n_c
   const bool taken = call == SDLLM_CALL_SPARSE ? plan_burst(pl, s, n_cached, s.cache_stride[2], s.block_len, s.blk_stride[2], SIZE_MAX)
                                                : call == SDLLM_CALL_FULL && plan_burst(pl, s, s.seq_len, s.kv_stride[2], 0, 0, SIZE_MAX);
   *splits = taken ? pl.n_split : 0;
+  return SDLLM_OK;
+}
+
+int32_t sdllm_column_kernel(const sdllm_shape_t* shape, int32_t* kernel) {
+  const int32_t st = check_shape(shape);
+  if (st != SDLLM_OK) return st;
+  if (!kernel) return SDLLM_ERR_INVALID_ARG;
+  *kernel = plan_score(*shape).mfma ? SDLLM_COLUMNS_32 : blocks_as_heads(*shape) ? SDLLM_COLUMNS_BLOCKS : SDLLM_COLUMNS_GENERAL;
   return SDLLM_OK;
 }
 

@@ -180,3 +180,18 @@ def test_small_calls_whose_tiles_are_fetched_at_once(batch, q_heads, kv_heads, t
         assert B.sdllm_burst_splits(B.make_shape(**{**shape, **more}), SPARSE, 32 * (tiles - 1)) == 0
     if splits > 1:   # never more partials than the static scratch holds
         assert batch * q_heads * splits * 16640 <= B.SDLLM_STATIC_SCRATCH_BYTES
+
+
+# Column pass of other block lengths: blocks as heads of the kernels for 32 rows, with one block per KV head from 64 of them on
+@pytest.mark.parametrize("batch,heads,kv_heads,L,more,kernel", [
+    (1, 8, 8, 600, dict(block_len=32), B.SDLLM_COLUMNS_32), (1, 14, 2, 600, dict(block_len=16), B.SDLLM_COLUMNS_BLOCKS),
+    (2, 32, 32, 1280, dict(block_len=64), B.SDLLM_COLUMNS_BLOCKS), (1, 5, 1, 300, dict(block_len=64), B.SDLLM_COLUMNS_GENERAL),
+    (1, 8, 8, 600, dict(block_len=64, score_mode=B.SDLLM_LOGIT_MEAN), B.SDLLM_COLUMNS_BLOCKS),
+    (1, 8, 8, 600, dict(block_len=48, score_mode=B.SDLLM_LOGIT_MEAN), B.SDLLM_COLUMNS_GENERAL),
+    (1, 8, 8, 600, dict(block_len=64, head_dim=64), B.SDLLM_COLUMNS_GENERAL), (1, 8, 8, 600, dict(block_len=64, dtype=B.SDLLM_F32), B.SDLLM_COLUMNS_GENERAL),
+    (7, 8, 8, 600, dict(block_len=16), B.SDLLM_COLUMNS_GENERAL), (8, 8, 8, 100, dict(block_len=16), B.SDLLM_COLUMNS_BLOCKS),
+    (7, 8, 8, 600, dict(block_len=33), B.SDLLM_COLUMNS_BLOCKS),
+])
+def test_column_pass_of_other_block_lengths(batch, heads, kv_heads, L, more, kernel):
+    shape = dict(batch=batch, n_q_heads=heads, n_kv_heads=kv_heads, head_dim=128, seq_len=L, block_off=L // 2, dtype=B.SDLLM_BF16)
+    assert B.sdllm_column_kernel(B.make_shape(**{**shape, **more})) == kernel
