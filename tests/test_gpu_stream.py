@@ -1,6 +1,7 @@
 """The attention kernel that fetches tiles straight into LDS, at the sizes where its pipeline and its launch rule can go
-wrong: waves with no, one, two and many tiles, a ragged last tile of either key segment, key splits, more heads than CUs,
-and the scoring statistics when the block's own keys share tiles with candidates.  Tolerances: tests/parity_util.py."""
+wrong: waves with two or three tiles and with many, a ragged last tile of either key segment, key splits, more heads than CUs,
+and the scoring statistics when the block's own keys share tiles with candidates.  Sparse steps of fewer than ten tiles run another kernel
+(tests/test_gpu_burst.py), as do some of ten and more that bring a workspace.  Tolerances: tests/parity_util.py."""
 import pytest
 import torch
 
@@ -14,10 +15,17 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda"
 
 
+def _workspace(shape, n_cached):
+    """What the call asks for, or none where the kernel for small calls would then take it."""
+    splits = B.sdllm_burst_splits(shape, B.SDLLM_CALL_SPARSE, n_cached)
+    assert splits != 1                                      # a call that it takes without a workspace
+    return None if splits else torch.empty(B.sdllm_workspace_bytes(shape, B.SDLLM_OP_SPARSE_ATTN, n_cached), dtype=torch.uint8, device=DEV)
+
+
 @pytest.mark.parametrize("batch,q_heads,kv_heads,n_cached,waves,touches", [
-    (1, 7, 1, 0, 1, 0), (1, 7, 1, 1, 2, 0), (1, 7, 1, 96, 4, 0), (1, 7, 1, 97, 4, 0), (2, 8, 2, 255, 4, 0), (1, 14, 2, 512, 6, 0),
-    (3, 6, 2, 671, 6, 0),
-    (1, 32, 32, 77, 4, 0), (4, 8, 8, 400, 5, 0),            # multi-head calls small enough to go unsplit
+    (1, 28, 4, 257, 5, 0), (1, 28, 4, 288, 5, 0), (2, 28, 4, 300, 5, 0), (2, 28, 4, 500, 6, 0), (3, 16, 2, 479, 5, 0), (9, 16, 2, 1500, 6, 0),
+    (1, 7, 1, 289, 5, 0), (1, 14, 2, 512, 6, 0), (3, 6, 2, 671, 6, 0),                              # without a workspace
+    (1, 32, 32, 270, 5, 0), (3, 8, 8, 281, 5, 0), (4, 8, 8, 400, 5, 0),                             # multi-head calls small enough to go unsplit
     (8, 28, 4, 1633, 8, 0), (5, 28, 4, 2111, 8, 0),         # one workgroup per head, eight waves
     (10, 28, 4, 1185, 4, 0),                                # more heads than CUs: four waves
     # heads bring tiles into L2 for each other; ragged last tiles in both segments, waves with a tile less than others
@@ -35,8 +43,7 @@ def test_stream_sparse_attn(batch, q_heads, kv_heads, n_cached, waves, touches):
     kc, vc = (torch.randn(batch, kv_heads, rows, d, device=DEV).bfloat16() for _ in range(2))
     kb, vb = (torch.randn(batch, kv_heads, b, d, device=DEV).bfloat16() for _ in range(2))
     out = torch.full_like(q, float("nan"))
-    ws = torch.empty(B.sdllm_workspace_bytes(shape, B.SDLLM_OP_SPARSE_ATTN, n_cached), dtype=torch.uint8, device=DEV)
-    B.sdllm_sparse_attn(shape, q, kc, vc, n_cached, kb, vb, out, ws)
+    B.sdllm_sparse_attn(shape, q, kc, vc, n_cached, kb, vb, out, _workspace(shape, n_cached))
     torch.cuda.synchronize()
     k_all = torch.cat([kc[:, :, :n_cached], kb], 2)
     v_all = torch.cat([vc[:, :, :n_cached], vb], 2)
@@ -59,19 +66,18 @@ def test_stream_statistics_at_the_cache_update_step(q_heads, kv_heads, batch, pr
     _run_block(w, block_index=2, n_steps=3, **modes)
 
 
-@pytest.mark.parametrize("n_cached", [128, 600])
-def test_tiles_of_infinitely_low_keys(n_cached):
+@pytest.mark.parametrize("batch,q_heads,kv_heads,n_cached", [(1, 7, 1, 300), (1, 7, 1, 600), (2, 28, 4, 290), (1, 32, 32, 270), (10, 28, 4, 1200)])
+def test_tiles_of_infinitely_low_keys(batch, q_heads, kv_heads, n_cached):
     # whole tiles without weight, among them the first of a wave
-    print(f"[case] stream, -inf tiles n_cached={n_cached}", flush=True)
+    print(f"[case] stream, -inf tiles B={batch} {q_heads}/{kv_heads} n_cached={n_cached}", flush=True)
     torch.manual_seed(n_cached)
-    q = torch.randn(1, 7, 32, 128, device=DEV).bfloat16()
-    kc, vc, kb, vb = (torch.randn(1, 1, n, 128, device=DEV).bfloat16() for n in (n_cached, n_cached, 32, 32))
+    q = torch.randn(batch, q_heads, 32, 128, device=DEV).bfloat16()
+    kc, vc, kb, vb = (torch.randn(batch, kv_heads, n, 128, device=DEV).bfloat16() for n in (n_cached, n_cached, 32, 32))
     kept = _hide(kc, q, [*range(32, 64), *range(96, 128)])
-    shape = B.make_shape(batch=1, n_q_heads=7, n_kv_heads=1, head_dim=128, seq_len=4096, block_off=2048, block_len=32,
+    shape = B.make_shape(batch=batch, n_q_heads=q_heads, n_kv_heads=kv_heads, head_dim=128, seq_len=4096, block_off=2048, block_len=32,
                          dtype=B.SDLLM_BF16, cache_rows=n_cached)
     assert B.sdllm_launch_plan(shape, B.SDLLM_CALL_SPARSE, n_cached).kernel == B.SDLLM_KERNEL_STREAM
     out = torch.zeros_like(q)
-    ws = torch.empty(B.sdllm_workspace_bytes(shape, B.SDLLM_OP_SPARSE_ATTN, n_cached), dtype=torch.uint8, device=DEV)
-    B.sdllm_sparse_attn(shape, q, kc, vc, n_cached, kb, vb, out, ws)
+    B.sdllm_sparse_attn(shape, q, kc, vc, n_cached, kb, vb, out, _workspace(shape, n_cached))
     torch.cuda.synchronize()
     U.assert_close(out, U.oracle_attention_batch(q, torch.cat([kc[:, :, kept], kb], 2), torch.cat([vc[:, :, kept], vb], 2)), "bf16", "kept keys")
