@@ -633,12 +633,12 @@ def test_block_step_on_sequence_major_views():
     U.assert_close(out, ref, "bf16", "sparse, strided")
 
 
-@pytest.mark.parametrize("Bt,Hq,Hkv,n_cached", [(1, 4, 4, 700), (2, 14, 2, 333), (160, 28, 4, 300)])
+@pytest.mark.parametrize("Bt,Hq,Hkv,n_cached", [(1, 4, 4, 700), (2, 14, 2, 333), (2, 28, 4, 500), (2, 28, 4, 1300), (160, 28, 4, 300)])
 def test_attention_with_peaked_softmax_and_late_maxima(Bt, Hq, Hkv, n_cached):
     # logits with a spread of several dozen (softmax close to one-hot) and, per row, a dominant key
     # planted in a late tile: the running softmax reference has to jump by far more than its slack
-    # after many tiles have been accumulated, in the per-head, the key-split and (last case) the
-    # shared-tile grouped-query kernel
+    # after many tiles have been accumulated, in the kernel for small calls, the one that streams tiles into LDS (500 keys), the
+    # per-head one with key splits (1300) and (last case) the shared-tile grouped-query kernel
     _note(f"[case] peaked softmax B={Bt} Hq={Hq} Hkv={Hkv} n_cached={n_cached}")
     torch.manual_seed(77 + n_cached)
     b, d = 32, 128
