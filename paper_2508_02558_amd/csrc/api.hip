@@ -332,19 +332,21 @@ AttnPlan plan_streams(const sdllm_shape_t& s, int32_t n0, int64_t sr0, int32_t n
 // Key splits with which the kernel that fetches all of a workgroup's tiles at once (attn_burst_mfma.hip) takes a call ahead of the
 // kernels above, 0 if it does not.  It wins as long as its workgroups fit one to a CU, except (other kernel / this one, us, calls one after
 // the other on 32 layers' keys and values, which come from memory where they are more than the memory-side cache holds)
-// * unsplit multi-head heads, whose keys are all different, from some 20 MB on, where streams of a wave's tiles keep memory busier than
-//   one burst: 136 heads x 9 tiles 8.35 / 8.29, 144 x 9 8.41 / 8.50, 224 x 9 9.26 / 10.3; 176 x 8 8.46 / 8.39, 192 x 8 8.53 / 8.76; 216 x 7 8.57 /
-//   8.53, 232 x 7 8.72 / 8.90; 240 x 5 7.61 / 7.62, 256 x 5 7.73 / 7.88; 216 x 4 6.82 / 6.79, 256 x 4 7.03 / 7.21; 256 x 6 8.63 / 8.67, x 3 6.6 / 6.24;
-// * where the others go unsplit and it would have to split: multi-head 20 heads x 10 6.72 / 6.51, 28 x 12 7.24 / 6.94, but x 13 7.25 / 7.52, 32 x 13 7.57 /
-//   7.80, x 15 8.40 / 7.94, 34 x 13 7.55 / 7.91, 40 x 11 7.42 / 7.59, x 12 7.99 / 7.81, 48 x 14 9.09 / 9.32, x 15 9.63 / 9.14, 64 x 15 9.98 / 10.2, x 16 10.4 /
-//   10.25, 72 x 20 11.6 / 11.8, x 21 12.05 / 11.95; grouped-query 28 x 11 7.18 / 6.64, 40 x 13 7.36 / 7.58, x 15 7.63 / 7.49, 48 x 17 7.93 / 7.90 (two heads
-//   to a group 7.94 / 8.23), 56 x 17 7.94 / 8.08, x 18 8.19 / 8.20, 64 x 24 9.5 / 8.9, and not at all with more than 64 heads (80 x 10 6.3 / 7.5, x 27 9.5 /
-//   9.8);
-// * split multi-head heads with more than 18 of them, from 1400 tiles (23 MB) or from where the others take another split on (33 and 44 tiles): all tiles
-//   come at once, but the arithmetic waits for the last of them, where streams compute meanwhile.  24 x 59 11.20 / 11.18, x 68 11.68 / 12.16, 28 x
-//   50 11.18 / 11.27, x 68 12.16 / 13.05, 32 x 41 11.31 / 10.81, x 44 11.22 / 11.52, x 68 12.79 / 13.82, 40 x 41 12.82 / 12.00, x 44 12.13 / 12.61, 48 x 32
-//   13.16 / 11.47, x 35 12.09 / 12.24, 64 x 32 13.58 / 13.13, x 35 13.42 / 14.07, 72 x 23 12.12 / 12.11, x 26 12.40 / 13.09, 80 x 23 12.38 / 12.82.  (With three layers' keys in the memory-side cache it is
-//   8 to 12 % the faster one at these.)
+// * unsplit multi-head heads, whose keys are all different, from some 20 MB on, where streams of a wave's tiles keep memory busier than one
+//   burst: 136 heads x 9 tiles 8.35 / 8.29, 144 x 9 8.41 / 8.50, 224 x 9 9.26 / 10.3; 176 x 8 8.46 / 8.39, 192 x 8 8.53 / 8.76; 216 x 7 8.57 /
+//   8.53 (dense rows 8.74 / 8.92), 232 x 7 8.72 / 8.90; 240 x 5 7.61 / 7.62, 256 x 5 7.73 / 7.88; 216 x 4 6.82 / 6.79, 256 x 4 7.03 / 7.21; 256 x
+//   6 8.63 / 8.67, x 3 6.6 / 6.24;
+// * where the others go unsplit and it would have to split: multi-head 20 heads x 10 6.72 / 6.51, 28 x 12 7.24 / 6.94, but x 13 7.25 / 7.52, 32 x
+//   13 7.57 / 7.80, x 15 8.40 / 7.94, 34 x 13 7.55 / 7.91, 40 x 11 7.42 / 7.59, x 12 7.99 / 7.81, 48 x 14 9.09 / 9.32, x 15 9.63 / 9.14, 64 x 15
+//   9.98 / 10.2, x 16 10.4 / 10.25, 72 x 20 11.6 / 11.8, x 21 12.05 / 11.95, x 23 12.1 / 12.1 (dense rows 11.6 / 12.3); grouped-query 28 x 11
+//   7.18 / 6.64, 40 x 13 7.36 / 7.58, x 15 7.63 / 7.49, 48 x 17 7.93 / 7.90 (two heads to a group 7.94 / 8.23), 56 x 17 7.94 / 8.08, x 18 8.19 /
+//   8.20, 64 x 24 9.5 / 8.9, 80 x 10 6.3 / 7.5, x 27 9.5 / 9.8; so not with more than 64 heads;
+// * split multi-head heads with more than 18 of them, from 1280 tiles (21 MB) or from where the others take another split on (33 and 44 tiles):
+//   all tiles come at once, but the arithmetic waits for the last of them, where streams compute meanwhile.  20 x 71 11.34 / 11.33 (dense rows x
+//   65 10.88 / 11.17), 24 x 59 11.20 / 11.18, x 68 11.68 / 12.16, 28 x 47 10.95 / 10.88 (dense rows x 50 11.31 / 11.52), x 50 11.18 / 11.27, x 68
+//   12.16 / 13.05, 32 x 41 11.31 / 10.81 (dense rows 10.91 / 11.13), x 44 11.22 / 11.52, x 68 12.79 / 13.82, 40 x 41 12.82 / 12.00, x 44 12.13 /
+//   12.61, 48 x 32 13.16 / 11.47, x 35 12.09 / 12.24, 64 x 32 13.58 / 13.13, x 35 13.42 / 14.07.  (With three layers' keys in the memory-side
+//   cache it is 8 to 12 % the faster one at these.)
 // More than one round of workgroups, whose second round waits for the first, is a quarter to a half slower (28 x 90 11.1 / 13.8).
 // The splits are those of least modelled time: a tile in a workgroup 0.22 us, the ninth 0.08 more (a third wave on one SIMD), four
 // splits to fold 0.16, and 0.94 for 16 KB of partials on each of 100 workgroups, fitted to 460 calls of 2 to 96 heads x 10 to 280
@@ -352,15 +354,15 @@ AttnPlan plan_streams(const sdllm_shape_t& s, int32_t n0, int64_t sr0, int32_t n
 // instantiated for: 1 head x 40 tiles in 20 splits (as 24) 6.96 us, in 14 (as 16) 6.48.
 // most: no more of them.
 int burst_splits(int heads, int tiles, int group, int most) {
-  static constexpr int kMostMultiHead[kBurstMaxTiles + 1] = {kNumCUs, kNumCUs, kNumCUs, kNumCUs, 216, 240, kNumCUs, 216, 176, 136};   // by tiles
+  static constexpr int kMostMultiHead[kBurstMaxTiles + 1] = {kNumCUs, kNumCUs, kNumCUs, kNumCUs, 216, 240, kNumCUs, 200, 176, 136};   // by tiles
   if (tiles <= kBurstMaxTiles) return heads <= (group > 1 ? kNumCUs : kMostMultiHead[tiles]) ? 1 : 0;
-  if (heads > (group > 1 ? 64 : 72)) return 0;
+  if (heads > 64) return 0;
   const int from = heads <= 20 ? 10 : heads <= 30 || (group > 1 && heads <= 36) ? 11
                    : group > 1 ? (heads <= 40 ? 15 : heads <= 48 ? (group == 2 ? 18 : 17) : heads <= 56 ? 18 : 24)
-                               : (heads <= 38 ? 15 : heads <= 44 ? 12 : heads <= 56 ? 15 : heads <= 64 ? 16 : 21);
+                               : (heads <= 38 ? 15 : heads <= 44 ? 12 : heads <= 56 ? 15 : 16);
   if (tiles < from) return 0;
   if (group == 1 && heads > 25 && (tiles == 13 || tiles == 14) && heads <= 38) return 0;
-  if (group == 1 && heads > 18 && tiles > (heads <= 32 ? 1400 / heads : heads <= 42 ? 43 : heads <= 64 ? 32 : 23)) return 0;
+  if (group == 1 && heads > 18 && tiles > (heads <= 32 ? 1280 / heads : heads <= 42 ? 43 : 32)) return 0;
   int best = 0, least = INT32_MAX;
   for (int n = (tiles + kBurstMaxTiles - 1) / kBurstMaxTiles; n <= most && n * heads <= kNumCUs; ++n) {
     const int mine = (tiles + n - 1) / n;

@@ -162,14 +162,14 @@ def test_launches_of_the_general_kernel_stay_below_two_to_the_32_threads():
 # Small calls that go to the kernel that fetches all tiles of a workgroup at once, ahead of the routes above, with how many splits.
 @pytest.mark.parametrize("batch,q_heads,kv_heads,tiles,splits", [
     (1, 1, 1, 1, 1), (8, 28, 4, 9, 1), (8, 32, 8, 9, 1), (9, 32, 8, 2, 0), (8, 32, 32, 6, 1), (8, 32, 32, 7, 0), (7, 32, 32, 9, 0),
-    (1, 136, 136, 9, 1), (1, 137, 137, 9, 0), (1, 176, 176, 8, 1), (1, 177, 177, 8, 0), (1, 216, 216, 7, 1), (1, 217, 217, 7, 0), (1, 240, 240, 5, 1),
+    (1, 136, 136, 9, 1), (1, 137, 137, 9, 0), (1, 176, 176, 8, 1), (1, 177, 177, 8, 0), (1, 200, 200, 7, 1), (1, 201, 201, 7, 0), (1, 240, 240, 5, 1),
     (8, 32, 32, 5, 0), (1, 216, 216, 4, 1), (8, 32, 32, 4, 0), (8, 32, 32, 3, 1), (8, 32, 32, 1, 1), (8, 32, 16, 9, 1),
     (1, 16, 2, 10, 4), (1, 28, 4, 10, 0), (1, 28, 4, 11, 3), (1, 32, 32, 10, 0), (1, 32, 32, 11, 0), (1, 40, 40, 11, 0), (1, 44, 44, 12, 3), (1, 56, 56, 14, 0), (1, 56, 56, 15, 3),
-    (2, 32, 32, 15, 0), (2, 32, 32, 16, 2), (1, 72, 72, 20, 0), (1, 72, 72, 21, 3), (5, 16, 16, 21, 0), (5, 16, 16, 22, 0), (3, 32, 32, 28, 0),
+    (2, 32, 32, 15, 0), (2, 32, 32, 16, 2), (1, 72, 72, 21, 0), (5, 16, 16, 21, 0), (5, 16, 16, 22, 0), (3, 32, 32, 28, 0),
     (1, 28, 28, 12, 3), (1, 28, 28, 13, 0), (1, 28, 28, 15, 3), (1, 32, 32, 14, 0), (1, 32, 32, 15, 3), (1, 38, 38, 14, 0), (1, 40, 40, 12, 3),
     # multi-head with many bytes
-    (1, 18, 18, 100, 12), (1, 20, 20, 70, 8), (1, 20, 20, 71, 0), (1, 28, 28, 50, 7), (1, 28, 28, 51, 0), (1, 32, 32, 43, 5), (1, 32, 32, 44, 0), (1, 42, 42, 43, 5), (1, 42, 42, 44, 0),
-    (2, 32, 32, 32, 4), (2, 32, 32, 33, 0), (1, 72, 72, 23, 3), (1, 72, 72, 24, 0), (1, 48, 24, 17, 0), (1, 48, 24, 18, 3),
+    (1, 18, 18, 100, 12), (1, 20, 20, 64, 8), (1, 20, 20, 65, 0), (1, 28, 28, 45, 6), (1, 28, 28, 46, 0), (1, 32, 32, 40, 5), (1, 32, 32, 41, 0), (1, 42, 42, 43, 5), (1, 42, 42, 44, 0),
+    (2, 32, 32, 32, 4), (2, 32, 32, 33, 0), (1, 48, 24, 17, 0), (1, 48, 24, 18, 3),
     (1, 40, 8, 14, 0), (1, 40, 8, 15, 3), (2, 28, 4, 17, 0), (2, 28, 4, 18, 3), (3, 16, 2, 16, 0), (3, 16, 2, 17, 3), (2, 32, 8, 23, 0), (2, 32, 8, 24, 3), (5, 16, 2, 24, 0),
     (1, 28, 4, 69, 8), (1, 28, 4, 81, 9), (1, 28, 4, 82, 0), (1, 32, 8, 72, 8), (1, 32, 8, 73, 0), (1, 2, 2, 288, 32), (1, 2, 2, 289, 0),
     (1, 1, 1, 40, 14), (1, 1, 1, 56, 14), (1, 1, 1, 140, 24),      # as many as the merge folds at once
