@@ -34,7 +34,7 @@ extern "C" {
 #define SDLLM_OK 0
 #define SDLLM_ERR_INVALID_ARG (-1) /* null pointer, bad size, r outside [0,1], even pool kernel, misalignment */
 #define SDLLM_ERR_UNSUPPORTED (-2) /* a legal request this build has no kernel for */
-#define SDLLM_ERR_WORKSPACE (-3)   /* workspace pointer null or smaller than sdllm_workspace_bytes() */
+#define SDLLM_ERR_WORKSPACE (-3)   /* workspace missing or too small (sdllm_workspace_bytes is always enough) */
 #define SDLLM_ERR_HIP (-4)         /* a HIP launch reported an error */
 #define SDLLM_ERR_STATIC_LIMIT (-5) /* sdllm_sparse_attn_noalloc: the request needs more than SDLLM_STATIC_SCRATCH_BYTES */
 
@@ -122,6 +122,12 @@ int32_t sdllm_retained_count(const sdllm_shape_t* shape, int32_t* k_total, int32
  * Bytes of device workspace `op` needs for this shape (host call).  n_cached is the number of
  * cache rows sdllm_sparse_attn will be given (ignored by the other ops; SDLLM_OP_BLOCK_STEP
  * covers every state of the step, including dense attention over all L keys).
+ *
+ * With that much, aligned to 256 bytes, a call runs the kernel and the key splits that its sizes choose.  Attention calls also
+ * take less, down to an amount that depends on their sizes only and often is nothing: they then run fewer key splits or another kernel,
+ * as small bf16 calls (head_dim 128, block of 32) of sdllm_sparse_attn do with a workspace that is not aligned to 16 bytes, and
+ * the results differ by rounding.  sdllm_sparse_attn and state 2 of sdllm_block_step give the same bits for the same tensors if each
+ * is given its full size.
  */
 int32_t sdllm_workspace_bytes(const sdllm_shape_t* shape, int32_t op, int32_t n_cached, size_t* bytes);
 
@@ -159,7 +165,7 @@ int32_t sdllm_compact_kv(const sdllm_shape_t* shape, const void* k_full, const v
  * q_blk [B,Hq,b,d] (q_stride); k_cache/v_cache [B,Hkv,n_cached,d] (cache_stride), n_cached >= 0
  * (0: attention over the block only; the cache pointers may then be NULL); k_blk/v_blk
  * [B,Hkv,b,d] (blk_stride); out [B,Hq,b,d] (out_stride).  ws as for sdllm_score_select with
- * SDLLM_OP_SPARSE_ATTN and the same n_cached.
+ * SDLLM_OP_SPARSE_ATTN and the same n_cached; less is taken where sdllm_workspace_bytes says so.
  */
 int32_t sdllm_sparse_attn(const sdllm_shape_t* shape, const void* q_blk, const void* k_cache, const void* v_cache,
                           int32_t n_cached, const void* k_blk, const void* v_blk, void* out, void* ws,
@@ -168,7 +174,7 @@ int32_t sdllm_sparse_attn(const sdllm_shape_t* shape, const void* q_blk, const v
 /*
  * sdllm_sparse_attn for callers that cannot allocate or size a workspace: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same kernels and
- * bit-identical results, but the split-KV partials live in an array of SDLLM_STATIC_SCRATCH_BYTES
+ * results bit-identical to those with a full-sized workspace, but the split-KV partials live in an array of SDLLM_STATIC_SCRATCH_BYTES
  * that is part of the library's device image (every GPU the library runs on holds one copy until the
  * process ends).  The call allocates nothing and frees nothing.  A shape whose launch plan needs
  * more scratch than that returns SDLLM_ERR_STATIC_LIMIT and enqueues nothing (use sdllm_sparse_attn
@@ -195,7 +201,8 @@ int32_t sdllm_sparse_attn_noalloc(const sdllm_shape_t* shape, const void* q_blk,
  * idx [B,Hkv,k_total] int32; ws sized by SDLLM_OP_BLOCK_STEP.  `state_out` (host, may be NULL)
  * receives the state that was executed.  For fp32 tensors, head_dim 64, block lengths other than 32 and other shapes of
  * the general kernels that size lets state 1 keep its key-split partials until the compaction; a workspace
- * that holds the partials and the scoring buffers one after the other is accepted too (same results, one more launch).
+ * that holds the partials and the scoring buffers one after the other is accepted too (same results, one more launch).  For small
+ * bf16 calls it holds all key splits that states 0 and 2 have a use for; less is accepted, with fewer of them (sdllm_workspace_bytes).
  */
 int32_t sdllm_block_step(const sdllm_shape_t* shape, int32_t step_in_block, int32_t delay, const void* q_blk,
                          const void* k_in, const void* v_in, int32_t* idx, void* k_cache, void* v_cache, void* out,

@@ -10,12 +10,14 @@
 //   * then the waves share out the output instead of the keys: wave w multiplies 32 columns of V with the numerators of 16 query
 //     rows over all tiles and weighs the tiles' products as their maxima say, so that there is nothing to merge; its V operands
 //     come from LDS under the exponentials.
-// 28 heads x 69 tiles in 8 splits: 1.7 us for the launch, 1.1 until all has landed, 0.5 logits, 0.6 numerators, 0.6 products, 0.9 until the
-// partials are out, and 3.3 for the merge.  Calls, before and after (replayed graphs): 28 heads x 69 tiles 10.1 -> 9.1 us, x 40 8.8 -> 7.7,
-// x 7 5.55 -> 4.5, x 2 4.6 -> 3.65; 32 x 21 8.9 -> 7.8; 4 x 72 8.9 -> 7.1; 224 x 6 6.0 -> 4.8; 128 x 7 (multi-head) 7.4 -> 6.3; geometric mean
-// over 130 sizes 1.18.  Where the line to the other kernels lies: burst_splits in api.hip.
+// 28 heads x 69 tiles in 8 splits, by time stamps when the tiles still shared one reference per row: 1.7 us for the launch, 1.1 until all has
+// landed, 0.5 logits, 0.6 numerators, 0.6 products, 0.9 until the partials are out, and 3.3 for the merge.  Calls, before and after (replayed
+// graphs, each layer with keys of its own): 28 heads x 69 tiles 10.45 -> 9.35 us, x 40 9.34 -> 7.85, x 7 5.95 -> 4.99, x 2 4.56 -> 3.53; 32 x 21 9.64 ->
+// 9.23; 4 x 72 10.45 -> 7.34; 224 x 6 6.17 -> 5.24; 128 x 7 (multi-head) 7.77 -> 7.09; geometric mean over 313 sizes 1.23, none slower
+// (profiles/small_calls_sweep.txt).  Where the line to the other kernels lies: burst_splits in api.hip.
 // Tried, not kept: the same in chunks of eight tiles, K of the next requested behind the operand reads of the last (2.2 us a chunk against 1.3 of
-// the streaming kernels: what stands between two barriers of everybody adds up); V operands read behind the barrier of the numerators
+// the streaming kernels: what stands between two barriers of everybody adds up); non-temporal fetches for multi-head calls (level, also where the
+// keys come from memory); V operands read behind the barrier of the numerators
 // (+0.15 us); all kernel arguments loaded first (level).  Indexes divided by the compiler instead of by Divisor cost 0.15 to 0.3 us.
 #include <type_traits>
 
